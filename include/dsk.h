@@ -328,8 +328,7 @@ DSK_API int dsk_moe_route(int dtype, const void* x, const void* wr, int n, int d
 
 /* ---- hooks for tests and benchmarks (process-wide, not thread-safe; no production caller needs them) ----
  * Unknown names and out-of-range values return DSK_EINVAL.
- *   "force_generic": 1 = bf16 work runs on the plain-ALU kernels that serve fp32 models (about a hundred times
- *                slower).  Without it a bf16 shape the tensor-core kernels do not handle is an error (DSK_ESHAPE
+ *   "force_generic": 1 = all work runs on the plain-ALU kernels (bf16 about a hundred times slower).  Without it a bf16 shape the tensor-core kernels do not handle is an error (DSK_ESHAPE
  *                from dsk_model_create, dsk_linear, dsk_attention), never a silent switch of kernels.
  *   "gemm_tiling": force one of the two prefill tilings of the bf16 GEMM on any M > 64 (default 0 = picked by
  *                size): 1 = 256x256 tiles on the 16x16x32 MFMA, 2 = 128x128 tiles on the 32x32x16 MFMA
@@ -346,7 +345,7 @@ DSK_API int dsk_set_option(const char* name, int value);
 
 /* Counters since the last reset: "e_cache_chunks" (row chunks of host-resident E caches that a first recomputed
  * layer followed as they arrived), "gemm_mfma_launches", "gemm_generic_launches", "attn_mfma_launches",
- * "attn_generic_launches", "attn_key_split_launches" (tensor-core attention launches that split the keys over
+ * "attn_generic_launches" (the two "generic" ones count fp32 work, on whichever kernel), "attn_key_split_launches" (tensor-core attention launches that split the keys over
  * workgroups) and, of those, "attn_packed_head_launches" (four q heads of a kv group per workgroup); and for the
  * launches bracketed under "time_gemm": "timed_gemm_launches", "timed_gemm_ms" (sum of their durations; waits for
  * them to finish), "timed_gemm_flops" (sum of 2*M*N*K), and the same three as "timed_attn_..." for the attention

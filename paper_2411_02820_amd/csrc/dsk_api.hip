@@ -196,6 +196,9 @@ hipError_t gemm_any(int dtype, const void* A, int64_t lda, const void* W, int64_
     return e;
   }
   ++g_stats.gemm_generic;
+  // the residual and the result of an fp32 problem are fp32 whatever the epilogue flags say
+  if (dtype == DSK_F32 && !g_force_generic && gemm_fp32_supported(A, lda, W, ldw, C, ldc, R, ldr, M, N, K))
+    return launch_gemm_fp32(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, s);
   return launch_gemm_generic(dtype, A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, s);
 }
 
@@ -232,6 +235,7 @@ hipError_t attention_any(int dtype, const AttnArgs& a, hipStream_t s) {
     return e;
   }
   ++g_stats.attn_generic;
+  if (dtype == DSK_F32 && !g_force_generic && attn_fp32_supported(a)) return launch_attn_fp32(a, s);
   return launch_attn_generic(dtype, a, s);
 }
 
@@ -330,13 +334,21 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
                           gemm_small_m_prescale_supported(n, d, nq, nq, nq, m->gemm_ws_bytes) &&
                           gemm_small_m_prescale_supported(n, d, F, F, F, m->gemm_ws_bytes) &&
                           gemm_small_m_fused_supported(n, 2 * F, d, d, d, m->gemm_ws_bytes);
+  // fp32: the norms in front of QKV and gate/up, RoPE + KV write and SwiGLU ride on the projections
+  const bool fp32_fused = all_f32 && !g_force_generic;
+  const bool fp32_rope = fp32_fused && c.head_dim % 32 == 0 && gemm_fp32_supported(h_in, d, w.wqkv, d, m->qkv, m->n_qkv, nullptr, 0, n, m->n_qkv, d);
+  const bool fp32_swiglu = fp32_fused && c.n_experts == 0 && m->gu_block >= 16 && gemm_fp32_supported(h_mid, d, w.wgu, d, m->act, F, nullptr, 0, n, 2 * F, d);
   if (xn_prescaled && !split_norm) return DSK_EINVAL;  // the caller decides both from the same conditions
-  if (!xn_prescaled) HIP_TRY(launch_rmsnorm(c.dtype, h_in, h_in_f32 || all_f32, w.g1, m->xn, n, d, (float)c.rms_eps, s));
+  if (!xn_prescaled && !fp32_rope) HIP_TRY(launch_rmsnorm(c.dtype, h_in, h_in_f32 || all_f32, w.g1, m->xn, n, d, (float)c.rms_eps, s));
   if (few_rows && gemm_small_m_rope_supported(n, d, c.n_q_heads, c.n_kv_heads, c.head_dim, d, d, m->n_qkv, m->gemm_ws_bytes)) {
     HIP_TRY(launch_gemm_small_m_rope(m->xn, d, w.wqkv, d, m->qkv, m->n_qkv, cs, k_own, v_own, n, d, c.n_q_heads,
                                      c.n_kv_heads, c.head_dim, m->gemm_ws, m->gemm_ws_bytes,
                                      xn_prescaled ? m->ssq : nullptr, (float)c.rms_eps, s));
     ++g_stats.gemm_mfma;
+  } else if (fp32_rope) {
+    HIP_TRY(launch_gemm_fp32_norm_rope((const float*)h_in, w.g1, (float)c.rms_eps, w.wqkv, m->qkv, cs, k_own, v_own, n, d,
+                                       c.n_q_heads, c.n_kv_heads, c.head_dim, s));
+    ++g_stats.gemm_generic;
   } else {
     if (xn_prescaled) return DSK_EINVAL;
     HIP_TRY(gemm(m, m->xn, d, w.wqkv, d, m->qkv, m->n_qkv, nullptr, 0, n, m->n_qkv, d, EPI_STORE, s));
@@ -377,11 +389,14 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
   } else {
     HIP_TRY(gemm(m, m->attn, nq, w.wo, nq, h_mid, d, h_in, d, n, d, nq,
                  EPI_RESIDUAL | EPI_C_F32 | ((h_in_f32 || all_f32) ? EPI_R_F32 : 0), s));
-    HIP_TRY(launch_rmsnorm(c.dtype, h_mid, 1, w.g2, m->xn, n, d, (float)c.rms_eps, s));
+    if (!fp32_swiglu) HIP_TRY(launch_rmsnorm(c.dtype, h_mid, 1, w.g2, m->xn, n, d, (float)c.rms_eps, s));
   }
   if (c.n_experts > 0) return run_moe_mlp(m, w, n, h_mid, h_out, h_out_f32 || all_f32, s);
   if (c.dtype == DSK_BF16 && !g_force_generic && m->gu_block == 32 && gemm_mfma_swiglu_supported(n, 2 * F, d, m->gemm_ws ? m->gemm_ws_bytes : 0)) {
     HIP_TRY(gemm(m, m->xn, d, w.wgu, d, m->act, F, nullptr, 0, n, 2 * F, d, EPI_SWIGLU, s));  // SwiGLU in the epilogue
+  } else if (fp32_swiglu) {
+    HIP_TRY(launch_gemm_fp32_norm_swiglu(h_mid, w.g2, (float)c.rms_eps, w.wgu, m->act, n, d, F, m->gu_block, s));
+    ++g_stats.gemm_generic;
   } else {
     HIP_TRY(gemm(m, m->xn, d, w.wgu, d, m->gu, 2 * (int64_t)F, nullptr, 0, n, 2 * F, d, EPI_STORE, s));
     HIP_TRY(launch_swiglu(c.dtype, m->gu, m->act, n, F, m->gu_block, s));
@@ -977,7 +992,10 @@ int dsk_linear_static(int dtype, const void* x, const void* w, void* y, const vo
     HIP_TRY(launch_gemm_mfma_bf16(x, K, w, K, y, N, r, N, M, N, K, epi, ptr, DSK_STATIC_SCRATCH_BYTES, s));
     ++g_stats.gemm_mfma;
   } else {
-    HIP_TRY(launch_gemm_generic(dtype, x, K, w, K, y, N, r, N, M, N, K, epi, s));
+    if (dtype == DSK_F32 && !g_force_generic && gemm_fp32_supported(x, K, w, K, y, N, r, N, M, N, K))
+      HIP_TRY(launch_gemm_fp32(x, K, w, K, y, N, r, N, M, N, K, s));
+    else
+      HIP_TRY(launch_gemm_generic(dtype, x, K, w, K, y, N, r, N, M, N, K, epi, s));
     ++g_stats.gemm_generic;
   }
   return DSK_OK;

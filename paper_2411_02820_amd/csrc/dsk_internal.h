@@ -92,6 +92,17 @@ enum { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_R_F32 = 2, EPI_C_F32 = 4, EPI_SWIGLU
 // C[M,N] = A[M,K] * W[N,K]^T (+ R[M,N] when epi has EPI_RESIDUAL); row strides in elements.
 hipError_t launch_gemm_generic(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc,
                                const void* R, int64_t ldr, int M, int N, int K, int epi, hipStream_t s);
+// fp32 on the matrix instruction (fp32_mfma.hip).  The first asks whether rows are whole 16-byte pieces; the plain-ALU
+// kernel takes the others.  The fused two: C = epilogue(rmsnorm(h) W^T) with RoPE + KV write (head_dim a multiple of 32)
+// or SwiGLU (gate and up interleaved in blocks of 16 or 32) behind the projection.
+bool gemm_fp32_supported(const void* A, int64_t lda, const void* W, int64_t ldw, const void* C, int64_t ldc, const void* R,
+                         int64_t ldr, int M, int N, int K);
+hipError_t launch_gemm_fp32(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R,
+                            int64_t ldr, int M, int N, int K, hipStream_t s);
+hipError_t launch_gemm_fp32_norm_rope(const float* h, const void* gain, float eps, const void* wqkv, void* qkv, const float2* cs,
+                                      void* k_rows, void* v_rows, int M, int d, int Hq, int Hkv, int dh, hipStream_t s);
+hipError_t launch_gemm_fp32_norm_swiglu(const float* h, const void* gain, float eps, const void* wgu, void* act, int M, int d,
+                                        int F, int gu_block, hipStream_t s);
 // bf16 MFMA GEMM; returns hipErrorNotSupported when the shape is outside what it handles.
 // ws: optional fp32 scratch for the K-split partial tiles of the small-M path (see gemm_mfma_workspace_bytes).
 hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc,
@@ -162,6 +173,8 @@ struct AttnArgs {
   const void* vt; int64_t ldvt;  // transposed V (see launch_transpose_v); NULL: not available
   void* ws; int64_t ws_bytes;    // fp32 scratch for key-split partial results (attn_mfma_workspace_bytes); optional
 };
+bool attn_fp32_supported(const AttnArgs& a);
+hipError_t launch_attn_fp32(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_generic(int dtype, const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s);
 int64_t attn_mfma_workspace_bytes(int Hq, int dh);

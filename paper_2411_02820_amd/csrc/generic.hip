@@ -1,6 +1,7 @@
 // Plain-ALU kernels for any shape and both dtypes: an LDS-tiled GEMM and a one-wave-per-query
-// attention.  They carry the fp32 model (where bf16 MFMA does not apply) and shapes the MFMA
-// kernels do not take; arithmetic is fp32 with fp32 accumulation.
+// attention.  They carry fp32 shapes whose rows are no whole 16-byte pieces or whose head_dim the fp32 matrix kernels
+// (fp32_mfma.hip) do not take, bf16 attention without a scratch buffer, and the "force_generic" hook; arithmetic is fp32
+// with fp32 accumulation.
 #include "dsk_internal.h"
 
 namespace {
