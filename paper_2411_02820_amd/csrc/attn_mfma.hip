@@ -37,7 +37,7 @@ constexpr int BKV = 64;  // keys per tile
 struct AttnParams {
   const bf16_t* q; int64_t ldq;
   const bf16_t* k; const bf16_t* vt; int64_t ldvt;
-  bf16_t* out;
+  bf16_t* out; int out_blocks;  // rows of Hq*dh, or blocks (block_at)
   float* part_o; float* part_ml;  // split mode: [n_q][Hq][splits][dh] and [n_q][Hq][splits][2]
   const int32_t* q_cu; const int32_t* p_cu;
   int n_seqs; int own_row0; int Hq, Hkv; int total_tiles; int splits;
@@ -439,16 +439,22 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
           bf16x4 v;
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = (bf16_t)(o[dt][4 * g + e] * inv);
-          *(bf16x4*)(op + 32 * dt + 8 * g + 4 * hh) = v;
+          const int at = 32 * dt + 8 * g + 4 * hh;
+          if (p.out_blocks) *(bf16x4*)(p.out + block_at(qrow, h * DH + at, p.Hq * DH)) = v;
+          else *(bf16x4*)(op + at) = v;
         }
     }
   }
 }
 
+__device__ __forceinline__ int64_t out_at(int q, int k, int width, int out_blocks) {
+  return out_blocks ? block_at(q, k, width) : (int64_t)q * width + k;
+}
+
 // out[q][h][:] = sum_s o_s * 2^((m_s - M) c) / sum_s l_s * 2^((m_s - M) c), M = max_s m_s; one wave per (q, h).
 template <int DH>
 __global__ void __launch_bounds__(64) attn_combine_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                          bf16_t* __restrict__ out, int Hq, int splits, float c) {
+                                                          bf16_t* __restrict__ out, int out_blocks, int Hq, int splits, float c) {
   const int64_t qh = (int64_t)blockIdx.x * Hq + blockIdx.y;
   const float* ml = part_ml + qh * splits * 2;
   float M = -INFINITY;
@@ -464,7 +470,7 @@ __global__ void __launch_bounds__(64) attn_combine_kernel(const float* __restric
   }
   const float inv = 1.0f / den;
 #pragma unroll
-  for (int a = 0; a < DH / 64; ++a) out[qh * DH + threadIdx.x + 64 * a] = (bf16_t)(acc[a] * inv);
+  for (int a = 0; a < DH / 64; ++a) out[out_at(blockIdx.x, blockIdx.y * DH + threadIdx.x + 64 * a, Hq * DH, out_blocks)] = (bf16_t)(acc[a] * inv);
 }
 
 // The same for at most MAXS splits, with every partial result requested before the first is used: the merge is a
@@ -473,7 +479,7 @@ __global__ void __launch_bounds__(64) attn_combine_kernel(const float* __restric
 template <int DH, int MAXS>
 __global__ void __launch_bounds__(64) attn_combine_batched_kernel(const float* __restrict__ part_o,
                                                                   const float* __restrict__ part_ml, bf16_t* __restrict__ out,
-                                                                  int Hq, int splits, float c) {
+                                                                  int out_blocks, int Hq, int splits, float c) {
   const int64_t qh = (int64_t)blockIdx.x * Hq + blockIdx.y;
   const float* ml = part_ml + qh * splits * 2;
   float ms[MAXS], ls[MAXS], po[MAXS][DH / 64];
@@ -499,7 +505,7 @@ __global__ void __launch_bounds__(64) attn_combine_batched_kernel(const float* _
   }
   const float inv = 1.0f / den;
 #pragma unroll
-  for (int a = 0; a < DH / 64; ++a) out[qh * DH + threadIdx.x + 64 * a] = (bf16_t)(acc[a] * inv);
+  for (int a = 0; a < DH / 64; ++a) out[out_at(blockIdx.x, blockIdx.y * DH + threadIdx.x + 64 * a, Hq * DH, out_blocks)] = (bf16_t)(acc[a] * inv);
 }
 
 // Vt[(kvh*dh + d)*ldvt + row] = V[row][kvh*dh + d] for the valid rows, 0 for the others, over whole
@@ -587,7 +593,7 @@ hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s) {
     return hipErrorNotSupported;
   AttnParams p;
   p.q = (const bf16_t*)a.q; p.ldq = a.ldq; p.k = (const bf16_t*)a.k_rows; p.vt = (const bf16_t*)a.vt; p.ldvt = a.ldvt;
-  p.out = (bf16_t*)a.out; p.q_cu = a.q_cu; p.p_cu = a.p_cu; p.n_seqs = a.n_seqs; p.own_row0 = (int)a.own_row0;
+  p.out = (bf16_t*)a.out; p.out_blocks = a.out_blocks; p.q_cu = a.q_cu; p.p_cu = a.p_cu; p.n_seqs = a.n_seqs; p.own_row0 = (int)a.own_row0;
   p.Hq = a.Hq; p.Hkv = a.Hkv;
   // 4-wave workgroups (128 queries).  8-wave workgroups halve the tile loads a wave issues per key tile and are
   // faster when the kernel is timed alone (+14 % at 8k tokens) but slower inside the layer, behind the projections
@@ -648,15 +654,15 @@ hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s) {
     if (e != hipSuccess) return e;
     dim3 cgrid(a.n_q, a.Hq);
     if (a.dh == 128 && splits <= 16)
-      hipLaunchKernelGGL((attn_combine_batched_kernel<128, 16>), cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.Hq, splits, p.c);
+      hipLaunchKernelGGL((attn_combine_batched_kernel<128, 16>), cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.out_blocks, a.Hq, splits, p.c);
     else if (a.dh == 128 && splits <= 32)
-      hipLaunchKernelGGL((attn_combine_batched_kernel<128, 32>), cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.Hq, splits, p.c);
+      hipLaunchKernelGGL((attn_combine_batched_kernel<128, 32>), cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.out_blocks, a.Hq, splits, p.c);
     else if (a.dh == 128)
-      hipLaunchKernelGGL(attn_combine_kernel<128>, cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.Hq, splits, p.c);
+      hipLaunchKernelGGL(attn_combine_kernel<128>, cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.out_blocks, a.Hq, splits, p.c);
     else if (splits <= 32)
-      hipLaunchKernelGGL((attn_combine_batched_kernel<64, 32>), cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.Hq, splits, p.c);
+      hipLaunchKernelGGL((attn_combine_batched_kernel<64, 32>), cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.out_blocks, a.Hq, splits, p.c);
     else
-      hipLaunchKernelGGL(attn_combine_kernel<64>, cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.Hq, splits, p.c);
+      hipLaunchKernelGGL(attn_combine_kernel<64>, cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.out_blocks, a.Hq, splits, p.c);
     return hipGetLastError();
   }
   dim3 grid((unsigned)total * a.Hq);

@@ -174,7 +174,7 @@ struct Stats {
   TimedList gemm, attn;
 } g_stats;
 
-hipError_t gemm_any(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc,
+hipError_t gemm_any(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc,
                     const void* R, int64_t ldr, int M, int N, int K, int epi, void* ws, int64_t ws_bytes, hipStream_t s) {
   if (dtype == DSK_BF16 && !g_force_generic) {
     std::unique_lock<std::mutex> timed_lock(g_stats.timed_mu, std::defer_lock);
@@ -186,7 +186,7 @@ hipError_t gemm_any(int dtype, const void* A, int64_t lda, const void* W, int64_
     }
     // a shape the tensor-core kernels refuse comes back as hipErrorNotSupported (the caller's DSK_ESHAPE): a bf16
     // problem never drops to the plain-ALU kernel behind the caller's back, that kernel is a hundred times slower
-    hipError_t e = launch_gemm_mfma_bf16(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, ws, ws_bytes, s);
+    hipError_t e = launch_gemm_mfma_bf16(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, ws, ws_bytes, s);
     if (e == hipSuccess) {
       ++g_stats.gemm_mfma;
       if (timed) e = g_stats.gemm.end(s, 2.0 * M * N * K);
@@ -199,12 +199,12 @@ hipError_t gemm_any(int dtype, const void* A, int64_t lda, const void* W, int64_
   // the residual and the result of an fp32 problem are fp32 whatever the epilogue flags say
   if (dtype == DSK_F32 && !g_force_generic && gemm_fp32_supported(A, lda, W, ldw, C, ldc, R, ldr, M, N, K))
     return launch_gemm_fp32(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, s);
-  return launch_gemm_generic(dtype, A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, s);
+  return launch_gemm_generic(dtype, A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, s);
 }
 
 hipError_t gemm(const dsk_model* m, const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc,
                 const void* R, int64_t ldr, int M, int N, int K, int epi, hipStream_t s) {
-  return gemm_any(m->cfg.dtype, A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, m->gemm_ws, m->gemm_ws_bytes, s);
+  return gemm_any(m->cfg.dtype, A, lda, W, ldw, m->w_blocks, C, ldc, R, ldr, M, N, K, epi, m->gemm_ws, m->gemm_ws_bytes, s);
 }
 
 hipError_t attention_any(int dtype, const AttnArgs& a, hipStream_t s) {
@@ -267,7 +267,7 @@ int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, 
         timed_lock.lock();
         HIP_TRY(g_stats.gemm.begin(s, &timed));
       }
-      const hipError_t e = launch_gemm_mfma_grouped(A, lda, (int64_t)n * k, W, ldw, w_stride, C, ldc, N, K, epi, m->moe_tab,
+      const hipError_t e = launch_gemm_mfma_grouped(A, lda, (int64_t)n * k, W, ldw, m->w_blocks, w_stride, C, ldc, N, K, epi, m->moe_tab,
                                                     tile_rows, s);
       if (e != hipSuccess && timed) g_stats.gemm.abandon();
       HIP_TRY(e);
@@ -301,6 +301,62 @@ int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, 
   return DSK_OK;
 }
 
+// Attention of the n query rows in m->qkv, result in m->attn (rows, or blocks for the few-row projections).
+int layer_attention(dsk_model* m, char* k_layer, char* v_layer, int64_t own_row0, const int32_t* q_cu, const int32_t* q_cu_host,
+                    const int32_t* p_cu, const int32_t* p_cu_host, int64_t n_pre_rows, int n_seqs, int n, int64_t vt_first_row,
+                    int out_blocks, hipStream_t s) {
+  const dsk_config_t& c = m->cfg;
+  AttnArgs a;
+  a.q = m->qkv; a.ldq = m->n_qkv; a.k_rows = k_layer; a.v_rows = v_layer; a.out = m->attn; a.out_blocks = out_blocks;
+  a.q_cu = q_cu; a.p_cu = p_cu; a.q_cu_host = q_cu_host; a.p_cu_host = p_cu_host; a.n_seqs = n_seqs;
+  a.own_row0 = own_row0; a.n_q = n; a.ws = m->attn_ws; a.ws_bytes = m->attn_ws_bytes;
+  a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.dh = c.head_dim;
+  a.vt = nullptr; a.ldvt = 0;
+  if (m->vt && !g_force_generic) {
+    HIP_TRY(launch_transpose_v(v_layer, m->vt, m->ldvt, c.n_kv_heads * c.head_dim, n_pre_rows, own_row0, n, vt_first_row, s));
+    a.vt = m->vt; a.ldvt = m->ldvt;
+  }
+  HIP_TRY(attention(m, a, s));
+  return DSK_OK;
+}
+
+// Whether a pass over n token rows takes the few-row kernels (few_rows.hip).
+bool takes_few_rows(const dsk_model* m, int n) {
+  const dsk_config_t& c = m->cfg;
+  return m->w_blocks && !g_force_generic && m->vt && m->gu_block == 32 && few_rows_supported(n, c.hidden, c.ffn, c.n_q_heads, c.n_kv_heads, c.head_dim);
+}
+
+// run_layer for few rows.  ready: m->xn and m->ssq already hold this layer's normalisation input (left by the layer in
+// front); g_next: gain of the next layer's input norm, whose input this layer then leaves (*left).
+int run_layer_few(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, int h_out_f32, char* k_layer, char* v_layer,
+                  int64_t own_row0, const int32_t* q_cu, const int32_t* q_cu_host, const int32_t* p_cu, const int32_t* p_cu_host,
+                  int64_t n_pre_rows, int n_seqs, int n, hipStream_t s, bool ready, const void* g_next, bool* left) {
+  const dsk_config_t& c = m->cfg;
+  const LayerWeights& w = m->layers[l];
+  const int d = c.hidden, F = c.ffn, nq = c.n_q_heads * c.head_dim;
+  const int64_t own = own_row0 * c.n_kv_heads * c.head_dim * m->elem;
+  const float eps = (float)c.rms_eps;
+  *left = false;
+  if (!ready) HIP_TRY(launch_few_norm(h_in, h_in_f32, w.g1, m->xn, m->ssq, n, d, s));
+  HIP_TRY(launch_few_qkv(m->xn, m->ssq, eps, w.wqkv, m->qkv, m->n_qkv, m->rope_cs, k_layer + own, v_layer + own, n, d, c.n_q_heads,
+                         c.n_kv_heads, c.head_dim, s));
+  int rc = layer_attention(m, k_layer, v_layer, own_row0, q_cu, q_cu_host, p_cu, p_cu_host, n_pre_rows, n_seqs, n, 0, 1, s);
+  if (rc) return rc;
+  g_stats.gemm_mfma += 2;
+  if (c.n_experts > 0) {  // the router reads normalised rows
+    HIP_TRY(launch_few_residual(m->attn, w.wo, h_in, h_in_f32, m->h, 1, nullptr, nullptr, nullptr, n, d, nq, m->gemm_ws,
+                                m->gemm_ws_bytes, s));
+    HIP_TRY(launch_rmsnorm(c.dtype, m->h, 1, w.g2, m->xn, n, d, eps, s));
+    return run_moe_mlp(m, w, n, m->h, h_out, h_out_f32, s);
+  }
+  HIP_TRY(launch_few_residual(m->attn, w.wo, h_in, h_in_f32, m->h, 1, w.g2, m->xn, m->ssq, n, d, nq, m->gemm_ws, m->gemm_ws_bytes, s));
+  HIP_TRY(launch_few_swiglu(m->xn, m->ssq, eps, w.wgu, m->act, n, 2 * F, d, s));
+  HIP_TRY(launch_few_residual(m->act, w.wd, m->h, 1, h_out, h_out_f32, g_next, m->xn, m->ssq, n, d, F, m->gemm_ws, m->gemm_ws_bytes, s));
+  g_stats.gemm_mfma += 2;
+  *left = g_next != nullptr;
+  return DSK_OK;
+}
+
 // One decoder layer over n token rows.  h_in: residual stream entering the layer; h_out: where the
 // state leaving the layer is written (may equal h_in).  K/V of the tokens go to rows own_row0.. of the
 // cache layer (k_rows, v_rows); attention additionally sees the prefix rows delimited by p_cu.
@@ -311,11 +367,9 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
               char* v_layer, int64_t own_row0,
               const int32_t* q_cu, const int32_t* q_cu_host, const int32_t* p_cu, const int32_t* p_cu_host,
               int64_t n_pre_rows, int n_seqs, int n, hipStream_t s, float* h_mid = nullptr, const float2* cs = nullptr,
-              int64_t vt_first_row = 0, bool xn_prescaled = false, const void* g_next = nullptr,
-              bool* next_prescaled = nullptr) {
+              int64_t vt_first_row = 0) {
   if (!h_mid) h_mid = m->h;
   if (!cs) cs = m->rope_cs;
-  if (next_prescaled) *next_prescaled = false;
   const dsk_config_t& c = m->cfg;
   const LayerWeights& w = m->layers[l];
   const int d = c.hidden, F = c.ffn, nq = c.n_q_heads * c.head_dim;
@@ -323,74 +377,25 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
   char* k_own = k_layer + own_row0 * row_bytes;
   char* v_own = v_layer + own_row0 * row_bytes;
   const int all_f32 = c.dtype == DSK_F32;  // an fp32 model: every buffer is fp32 anyway
-  // few token rows (the suffix pass) on the tensor-core path: RoPE + KV write, and below the post-attention
-  // RMSNorm, are done by the split-K reduction of the projection in front of them
-  const bool few_rows = c.dtype == DSK_BF16 && !g_force_generic && n <= 64 && m->gemm_ws;
-  // ... and with a hidden width in whole 1024-column blocks each RMSNorm is split in two: the reduction in front of it
-  // leaves h * g and the row's sums of squares, the reduction behind the next projection applies the row factor
-  // (xn_prescaled: the layer before has done so for this layer's input norm).  Dense MLP only: the router of an
-  // expert layer reads the normalised rows themselves.
-  const bool split_norm = few_rows && c.n_experts == 0 && m->ssq && m->gu_block == 32 &&
-                          gemm_small_m_prescale_supported(n, d, nq, nq, nq, m->gemm_ws_bytes) &&
-                          gemm_small_m_prescale_supported(n, d, F, F, F, m->gemm_ws_bytes) &&
-                          gemm_small_m_fused_supported(n, 2 * F, d, d, d, m->gemm_ws_bytes);
   // fp32: the norms in front of QKV and gate/up, RoPE + KV write and SwiGLU ride on the projections
   const bool fp32_fused = all_f32 && !g_force_generic;
   const bool fp32_rope = fp32_fused && c.head_dim % 32 == 0 && gemm_fp32_supported(h_in, d, w.wqkv, d, m->qkv, m->n_qkv, nullptr, 0, n, m->n_qkv, d);
   const bool fp32_swiglu = fp32_fused && c.n_experts == 0 && m->gu_block >= 16 && gemm_fp32_supported(h_mid, d, w.wgu, d, m->act, F, nullptr, 0, n, 2 * F, d);
-  if (xn_prescaled && !split_norm) return DSK_EINVAL;  // the caller decides both from the same conditions
-  if (!xn_prescaled && !fp32_rope) HIP_TRY(launch_rmsnorm(c.dtype, h_in, h_in_f32 || all_f32, w.g1, m->xn, n, d, (float)c.rms_eps, s));
-  if (few_rows && gemm_small_m_rope_supported(n, d, c.n_q_heads, c.n_kv_heads, c.head_dim, d, d, m->n_qkv, m->gemm_ws_bytes)) {
-    HIP_TRY(launch_gemm_small_m_rope(m->xn, d, w.wqkv, d, m->qkv, m->n_qkv, cs, k_own, v_own, n, d, c.n_q_heads,
-                                     c.n_kv_heads, c.head_dim, m->gemm_ws, m->gemm_ws_bytes,
-                                     xn_prescaled ? m->ssq : nullptr, (float)c.rms_eps, s));
-    ++g_stats.gemm_mfma;
-  } else if (fp32_rope) {
+  if (!fp32_rope) HIP_TRY(launch_rmsnorm(c.dtype, h_in, h_in_f32 || all_f32, w.g1, m->xn, n, d, (float)c.rms_eps, s));
+  if (fp32_rope) {
     HIP_TRY(launch_gemm_fp32_norm_rope((const float*)h_in, w.g1, (float)c.rms_eps, w.wqkv, m->qkv, cs, k_own, v_own, n, d,
                                        c.n_q_heads, c.n_kv_heads, c.head_dim, s));
     ++g_stats.gemm_generic;
   } else {
-    if (xn_prescaled) return DSK_EINVAL;
     HIP_TRY(gemm(m, m->xn, d, w.wqkv, d, m->qkv, m->n_qkv, nullptr, 0, n, m->n_qkv, d, EPI_STORE, s));
     HIP_TRY(launch_rope_kv_write(c.dtype, m->qkv, cs, k_own, v_own, n, c.n_q_heads, c.n_kv_heads, c.head_dim, s));
   }
-  AttnArgs a;
-  a.q = m->qkv; a.ldq = m->n_qkv; a.k_rows = k_layer; a.v_rows = v_layer; a.out = m->attn;
-  a.q_cu = q_cu; a.p_cu = p_cu; a.q_cu_host = q_cu_host; a.p_cu_host = p_cu_host; a.n_seqs = n_seqs;
-  a.own_row0 = own_row0; a.n_q = n; a.ws = m->attn_ws; a.ws_bytes = m->attn_ws_bytes;
-  a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.dh = c.head_dim;
-  a.vt = nullptr; a.ldvt = 0;
-  if (m->vt && !g_force_generic) {
-    HIP_TRY(launch_transpose_v(v_layer, m->vt, m->ldvt, c.n_kv_heads * c.head_dim, n_pre_rows, own_row0, n, vt_first_row, s));
-    a.vt = m->vt; a.ldvt = m->ldvt;
-  }
-  HIP_TRY(attention(m, a, s));
-  if (split_norm) {
-    HIP_TRY(launch_gemm_small_m_prescale(m->attn, nq, w.wo, nq, h_mid, h_in, h_in_f32 ? 1 : 0, w.g2, m->xn, m->ssq, n, d, nq,
-                                         m->gemm_ws, m->gemm_ws_bytes, s));
-    HIP_TRY(launch_gemm_small_m_swiglu_scaled(m->xn, d, w.wgu, d, m->act, F, n, 2 * F, d, m->gemm_ws, m->gemm_ws_bytes, m->ssq,
-                                              (float)c.rms_eps, s));
-    g_stats.gemm_mfma += 2;
-    if (g_next && h_out_f32) {
-      // the down projection prepares the next layer's input norm the same way
-      HIP_TRY(launch_gemm_small_m_prescale(m->act, F, w.wd, F, (float*)h_out, h_mid, 1, g_next, m->xn, m->ssq, n, d, F,
-                                           m->gemm_ws, m->gemm_ws_bytes, s));
-      ++g_stats.gemm_mfma;
-      if (next_prescaled) *next_prescaled = true;
-      return DSK_OK;
-    }
-    HIP_TRY(gemm(m, m->act, F, w.wd, F, h_out, d, h_mid, d, n, d, F, EPI_RESIDUAL | EPI_R_F32 | (h_out_f32 ? EPI_C_F32 : 0), s));
-    return DSK_OK;
-  }
-  if (few_rows && gemm_small_m_rmsnorm_supported(n, d, nq, nq, nq, m->gemm_ws_bytes)) {
-    HIP_TRY(launch_gemm_small_m_rmsnorm(m->attn, nq, w.wo, nq, h_mid, h_in, h_in_f32 ? 1 : 0, w.g2, m->xn, (float)c.rms_eps, n,
-                                        d, nq, m->gemm_ws, m->gemm_ws_bytes, s));
-    ++g_stats.gemm_mfma;
-  } else {
-    HIP_TRY(gemm(m, m->attn, nq, w.wo, nq, h_mid, d, h_in, d, n, d, nq,
-                 EPI_RESIDUAL | EPI_C_F32 | ((h_in_f32 || all_f32) ? EPI_R_F32 : 0), s));
-    if (!fp32_swiglu) HIP_TRY(launch_rmsnorm(c.dtype, h_mid, 1, w.g2, m->xn, n, d, (float)c.rms_eps, s));
-  }
+  const int rc = layer_attention(m, k_layer, v_layer, own_row0, q_cu, q_cu_host, p_cu, p_cu_host, n_pre_rows, n_seqs, n,
+                                 vt_first_row, 0, s);
+  if (rc) return rc;
+  HIP_TRY(gemm(m, m->attn, nq, w.wo, nq, h_mid, d, h_in, d, n, d, nq,
+               EPI_RESIDUAL | EPI_C_F32 | ((h_in_f32 || all_f32) ? EPI_R_F32 : 0), s));
+  if (!fp32_swiglu) HIP_TRY(launch_rmsnorm(c.dtype, h_mid, 1, w.g2, m->xn, n, d, (float)c.rms_eps, s));
   if (c.n_experts > 0) return run_moe_mlp(m, w, n, h_mid, h_out, h_out_f32 || all_f32, s);
   if (c.dtype == DSK_BF16 && !g_force_generic && m->gu_block == 32 && gemm_mfma_swiglu_supported(n, 2 * F, d, m->gemm_ws ? m->gemm_ws_bytes : 0)) {
     HIP_TRY(gemm(m, m->xn, d, w.wgu, d, m->act, F, nullptr, 0, n, 2 * F, d, EPI_SWIGLU, s));  // SwiGLU in the epilogue
@@ -435,7 +440,7 @@ int plan_e_chunks(const dsk_model* m, int T, int n_seqs, int* bounds) {
   return n;
 }
 
-struct TensorPlace { void* base; int64_t rows, cols; int map; int64_t row_off; };
+struct TensorPlace { void* base; int64_t rows, cols; int map; int64_t row_off; int blocks; };
 
 int place_tensor(const dsk_model* m, int layer, int tensor, TensorPlace* p) {
   if (layer < 0 || layer >= m->cfg.n_layers) return DSK_EINVAL;
@@ -445,16 +450,16 @@ int place_tensor(const dsk_model* m, int layer, int tensor, TensorPlace* p) {
   if (c.n_experts > 0) {
     // a mixture-of-experts layer: router, and WG/WU/WD per expert under DSK_EXPERT(e, t)
     if (tensor == DSK_WG || tensor == DSK_WU || tensor == DSK_WD) return DSK_EINVAL;
-    if (tensor == DSK_WR) { *p = {w.wr, c.n_experts, d, 0, 0}; return DSK_OK; }
+    if (tensor == DSK_WR) { *p = {w.wr, c.n_experts, d, 0, 0, 0}; return DSK_OK; }
     if (tensor >= 16) {
       const int e = (tensor - 16) / 16, t = (tensor - 16) % 16;
       if (e >= c.n_experts) return DSK_EINVAL;
       char* gu = (char*)w.wgu + (int64_t)e * 2 * F * d * m->elem;
       char* dn = (char*)w.wd + (int64_t)e * d * F * m->elem;
       switch (t) {
-        case DSK_WG: *p = {gu, F, d, 1, 0}; return DSK_OK;
-        case DSK_WU: *p = {gu, F, d, 2, 0}; return DSK_OK;
-        case DSK_WD: *p = {dn, d, F, 0, 0}; return DSK_OK;
+        case DSK_WG: *p = {gu, F, d, 1, 0, m->w_blocks}; return DSK_OK;
+        case DSK_WU: *p = {gu, F, d, 2, 0, m->w_blocks}; return DSK_OK;
+        case DSK_WD: *p = {dn, d, F, 0, 0, m->w_blocks}; return DSK_OK;
         default: return DSK_EINVAL;
       }
     }
@@ -462,15 +467,15 @@ int place_tensor(const dsk_model* m, int layer, int tensor, TensorPlace* p) {
     return DSK_EINVAL;
   }
   switch (tensor) {
-    case DSK_G1: *p = {w.g1, 1, d, 0, 0}; break;
-    case DSK_G2: *p = {w.g2, 1, d, 0, 0}; break;
-    case DSK_WQ: *p = {w.wqkv, nq, d, 0, 0}; break;
-    case DSK_WK: *p = {w.wqkv, nkv, d, 0, nq}; break;
-    case DSK_WV: *p = {w.wqkv, nkv, d, 0, nq + nkv}; break;
-    case DSK_WO: *p = {w.wo, d, nq, 0, 0}; break;
-    case DSK_WG: *p = {w.wgu, F, d, 1, 0}; break;
-    case DSK_WU: *p = {w.wgu, F, d, 2, 0}; break;
-    case DSK_WD: *p = {w.wd, d, F, 0, 0}; break;
+    case DSK_G1: *p = {w.g1, 1, d, 0, 0, 0}; break;
+    case DSK_G2: *p = {w.g2, 1, d, 0, 0, 0}; break;
+    case DSK_WQ: *p = {w.wqkv, nq, d, 0, 0, m->w_blocks}; break;
+    case DSK_WK: *p = {w.wqkv, nkv, d, 0, nq, m->w_blocks}; break;
+    case DSK_WV: *p = {w.wqkv, nkv, d, 0, nq + nkv, m->w_blocks}; break;
+    case DSK_WO: *p = {w.wo, d, nq, 0, 0, m->w_blocks}; break;
+    case DSK_WG: *p = {w.wgu, F, d, 1, 0, m->w_blocks}; break;
+    case DSK_WU: *p = {w.wgu, F, d, 2, 0, m->w_blocks}; break;
+    case DSK_WD: *p = {w.wd, d, F, 0, 0, m->w_blocks}; break;
     default: return DSK_EINVAL;
   }
   return DSK_OK;
@@ -524,6 +529,7 @@ int dsk_model_create(const dsk_config_t* cfg, int64_t max_tokens, int64_t max_kv
     if (cfg->ffn % g == 0) { m->gu_block = g; break; }
   const int L = cfg->n_layers;
   const int64_t d = cfg->hidden, nq = (int64_t)cfg->n_q_heads * cfg->head_dim, F = cfg->ffn;
+  m->w_blocks = cfg->dtype == DSK_BF16 && d % 32 == 0 && nq % 32 == 0 && F % 32 == 0 && m->n_qkv % 16 == 0;
   int rc = DSK_OK;
   m->layers = (LayerWeights*)calloc(L, sizeof(LayerWeights));
   m->ev_kv = (hipEvent_t*)calloc(L, sizeof(hipEvent_t));
@@ -540,7 +546,7 @@ int dsk_model_create(const dsk_config_t* cfg, int64_t max_tokens, int64_t max_kv
     if ((rc = alloc_dev(&w.wd, n_mlp * d * F * elem, &m->weight_bytes))) break;
     if (E > 0 && (rc = alloc_dev(&w.wr, (int64_t)E * d * elem, &m->weight_bytes))) break;
   }
-  const int64_t T = max_tokens;
+  const int64_t T = (max_tokens + 15) / 16 * 16;  // the few-row kernels keep activations in blocks of 16 rows
   const int half = cfg->head_dim / 2;
   if (rc == DSK_OK) rc = alloc_dev(&m->xn, T * d * elem, &m->workspace_bytes);
   if (rc == DSK_OK) rc = alloc_dev(&m->qkv, T * m->n_qkv * elem, &m->workspace_bytes);
@@ -577,8 +583,10 @@ int dsk_model_create(const dsk_config_t* cfg, int64_t max_tokens, int64_t max_kv
     int max_n = m->n_qkv > 2 * cfg->ffn ? m->n_qkv : 2 * cfg->ffn;
     if (cfg->hidden > max_n) max_n = cfg->hidden;
     m->gemm_ws_bytes = gemm_mfma_workspace_bytes(max_n);
+    const int64_t few = few_rows_workspace_bytes((int)d, (int)(nq > F ? nq : F));
+    if (few > m->gemm_ws_bytes) m->gemm_ws_bytes = few;
     rc = alloc_dev(&m->gemm_ws, m->gemm_ws_bytes, &m->workspace_bytes);
-    if (rc == DSK_OK) rc = alloc_dev((void**)&m->ssq, 64 * DSK_MAX_SSQ_PARTS * (int64_t)sizeof(float), &m->workspace_bytes);
+    if (rc == DSK_OK) rc = alloc_dev((void**)&m->ssq, 64 * ((d + 15) / 16) * (int64_t)sizeof(float), &m->workspace_bytes);
   }
   if (rc == DSK_OK) {
     double* th = (double*)malloc(half * sizeof(double));
@@ -627,7 +635,7 @@ int dsk_model_set_tensor(dsk_model_t* model, int layer, int tensor, const void* 
   hipStream_t s = (hipStream_t)stream;
   const int64_t bytes = p.rows * p.cols * model->elem;
   if (src_mem == DSK_MEM_DEVICE) {
-    HIP_TRY(launch_pack_rows(model->cfg.dtype, p.base, src, p.rows, p.cols, p.map, model->gu_block, p.row_off, 1, s));
+    HIP_TRY(launch_pack_rows(model->cfg.dtype, p.base, src, p.rows, p.cols, p.map, model->gu_block, p.row_off, p.blocks, 1, s));
     return DSK_OK;
   }
   // host source: staged through a temporary device buffer; this path waits for the copy to finish
@@ -635,7 +643,7 @@ int dsk_model_set_tensor(dsk_model_t* model, int layer, int tensor, const void* 
   HIP_TRY(hipMalloc(&staging, (size_t)bytes));
   hipError_t e = hipMemcpy(staging, src, (size_t)bytes, hipMemcpyHostToDevice);
   if (e == hipSuccess)
-    e = launch_pack_rows(model->cfg.dtype, p.base, staging, p.rows, p.cols, p.map, model->gu_block, p.row_off, 1, s);
+    e = launch_pack_rows(model->cfg.dtype, p.base, staging, p.rows, p.cols, p.map, model->gu_block, p.row_off, p.blocks, 1, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   (void)hipFree(staging);
   HIP_TRY(e);
@@ -647,7 +655,7 @@ int dsk_model_get_tensor(const dsk_model_t* model, int layer, int tensor, void* 
   TensorPlace p;
   int rc = place_tensor(model, layer, tensor, &p);
   if (rc) return rc;
-  HIP_TRY(launch_pack_rows(model->cfg.dtype, p.base, dst_device, p.rows, p.cols, p.map, model->gu_block, p.row_off, 0,
+  HIP_TRY(launch_pack_rows(model->cfg.dtype, p.base, dst_device, p.rows, p.cols, p.map, model->gu_block, p.row_off, p.blocks, 0,
                            (hipStream_t)stream));
   return DSK_OK;
 }
@@ -660,7 +668,7 @@ int dsk_model_init_random(dsk_model_t* model, uint64_t seed, float std, void* st
     int rc = place_tensor(model, l, tensor, &p);
     if (rc) return rc;
     const float offset = (tensor == DSK_G1 || tensor == DSK_G2) ? 1.0f : 0.0f;
-    HIP_TRY(launch_fill_weight(model->cfg.dtype, p.base, p.rows, p.cols, p.map, model->gu_block, p.row_off, seed, stream_id,
+    HIP_TRY(launch_fill_weight(model->cfg.dtype, p.base, p.rows, p.cols, p.map, model->gu_block, p.row_off, p.blocks, seed, stream_id,
                                std, offset, (hipStream_t)stream));
     return (int)DSK_OK;
   };
@@ -828,6 +836,8 @@ int dsk_partial_prefill_groups(dsk_model_t* model, const dsk_group_t* groups, in
         HIP_TRY(launch_rope_table(batch->positions_dev, m->theta, m->rope_cs, T, c.head_dim / 2, s));
         table_done = true;
       }
+      const bool few = takes_few_rows(m, T);
+      bool ready = false;  // few rows: the layer in front has left this layer's norm input
       for (int l = G.lo; l < G.hi; ++l) {
         const bool last = l == G.hi - 1 && G.hidden_out;
         void* h_next = last ? G.hidden_out : (void*)m->h;
@@ -853,8 +863,13 @@ int dsk_partial_prefill_groups(dsk_model_t* model, const dsk_group_t* groups, in
           if (next_host && (rc = hand_over_stage())) return rc;
           continue;
         }
-        rc = run_layer(m, l, h_cur, l > G.lo, h_next, !last, kv_k(kv_out, l), kv_v(kv_out, l), 0, batch->cu_seqlens_dev,
-                       batch->cu_seqlens_host, nullptr, nullptr, 0, batch->n_seqs, T, s);
+        if (few)
+          rc = run_layer_few(m, l, h_cur, l > G.lo, h_next, !last, kv_k(kv_out, l), kv_v(kv_out, l), 0, batch->cu_seqlens_dev,
+                             batch->cu_seqlens_host, nullptr, nullptr, 0, batch->n_seqs, T, s, ready,
+                             l + 1 < G.hi ? m->layers[l + 1].g1 : nullptr, &ready);
+        else
+          rc = run_layer(m, l, h_cur, l > G.lo, h_next, !last, kv_k(kv_out, l), kv_v(kv_out, l), 0, batch->cu_seqlens_dev,
+                         batch->cu_seqlens_host, nullptr, nullptr, 0, batch->n_seqs, T, s);
         if (rc) return rc;
         h_cur = h_next;
         if (l == G.lo && next_host && (rc = hand_over_stage())) return rc;
@@ -902,7 +917,8 @@ int dsk_suffix_prefill(dsk_model_t* model, const void* suffix_hidden_in, const d
   hipStream_t s = (hipStream_t)stream;
   HIP_TRY(launch_rope_table(suffix->positions_dev, m->theta, m->rope_cs, S, c.head_dim / 2, s));
   const void* h_cur = suffix_hidden_in;
-  bool prescaled = false;  // whether the layer before has prepared this layer's input norm (few rows, see run_layer)
+  const bool few = takes_few_rows(m, S);
+  bool ready = false;  // few rows: the layer in front has left this layer's norm input
   for (int l = 0; l < c.n_layers; ++l) {
     if (m->pending[l]) {
       HIP_TRY(hipStreamWaitEvent(s, m->ev_kv[l], 0));
@@ -910,12 +926,15 @@ int dsk_suffix_prefill(dsk_model_t* model, const void* suffix_hidden_in, const d
     }
     const bool last = l == c.n_layers - 1;
     void* h_next = last ? hidden_out : (void*)m->h;
-    bool next_prescaled = false;
-    rc = run_layer(m, l, h_cur, l > 0, h_next, !last, kv_k(kv, l), kv_v(kv, l), suffix_row0, suffix->cu_seqlens_dev,
-                   suffix->cu_seqlens_host, prefix->cu_seqlens_dev, prefix->cu_seqlens_host, prefix->n_tokens,
-                   suffix->n_seqs, S, s, nullptr, nullptr, 0, prescaled, last ? nullptr : m->layers[l + 1].g1, &next_prescaled);
+    if (few)
+      rc = run_layer_few(m, l, h_cur, l > 0, h_next, !last, kv_k(kv, l), kv_v(kv, l), suffix_row0, suffix->cu_seqlens_dev,
+                         suffix->cu_seqlens_host, prefix->cu_seqlens_dev, prefix->cu_seqlens_host, prefix->n_tokens,
+                         suffix->n_seqs, S, s, ready, last ? nullptr : m->layers[l + 1].g1, &ready);
+    else
+      rc = run_layer(m, l, h_cur, l > 0, h_next, !last, kv_k(kv, l), kv_v(kv, l), suffix_row0, suffix->cu_seqlens_dev,
+                     suffix->cu_seqlens_host, prefix->cu_seqlens_dev, prefix->cu_seqlens_host, prefix->n_tokens,
+                     suffix->n_seqs, S, s);
     if (rc) return rc;
-    prescaled = next_prescaled;
     h_cur = h_next;
   }
   m->any_pending = 0;
@@ -962,7 +981,7 @@ int dsk_linear(int dtype, const void* x, const void* w, void* y, const void* r, 
     HIP_TRY(hipMalloc(&ws, (size_t)gemm_mfma_workspace_bytes(N)));
     ws_bytes = gemm_mfma_workspace_bytes(N);
   }
-  HIP_TRY(gemm_any(dtype, x, K, w, K, y, N, r, N, M, N, K, epi, may_split ? ws : nullptr, may_split ? ws_bytes : 0,
+  HIP_TRY(gemm_any(dtype, x, K, w, K, 0, y, N, r, N, M, N, K, epi, may_split ? ws : nullptr, may_split ? ws_bytes : 0,
                    (hipStream_t)stream));
   return DSK_OK;
 }
@@ -989,13 +1008,13 @@ int dsk_linear_static(int dtype, const void* x, const void* w, void* y, const vo
   hipStream_t s = (hipStream_t)stream;
   // no launch timing here (its event pool is allocated on first use); the kernels are those of dsk_linear
   if (dtype == DSK_BF16 && !g_force_generic) {
-    HIP_TRY(launch_gemm_mfma_bf16(x, K, w, K, y, N, r, N, M, N, K, epi, ptr, DSK_STATIC_SCRATCH_BYTES, s));
+    HIP_TRY(launch_gemm_mfma_bf16(x, K, w, K, 0, y, N, r, N, M, N, K, epi, ptr, DSK_STATIC_SCRATCH_BYTES, s));
     ++g_stats.gemm_mfma;
   } else {
     if (dtype == DSK_F32 && !g_force_generic && gemm_fp32_supported(x, K, w, K, y, N, r, N, M, N, K))
       HIP_TRY(launch_gemm_fp32(x, K, w, K, y, N, r, N, M, N, K, s));
     else
-      HIP_TRY(launch_gemm_generic(dtype, x, K, w, K, y, N, r, N, M, N, K, epi, s));
+      HIP_TRY(launch_gemm_generic(dtype, x, K, w, K, 0, y, N, r, N, M, N, K, epi, s));
     ++g_stats.gemm_generic;
   }
   return DSK_OK;

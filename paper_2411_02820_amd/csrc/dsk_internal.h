@@ -20,6 +20,12 @@ template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float x) { return
 // packed rows [2*gu_block*j, 2*gu_block*j+gu_block) hold gate rows [gu_block*j, ..+gu_block),
 // the next gu_block packed rows hold the same up rows, so that a GEMM tile owns gate and up of
 // the same FFN index.
+// The projections of a bf16 model are kept in blocks of 16 rows x 32 columns (dsk_model::w_blocks), each in the lane order of
+// an MFMA operand: what the few-row kernels stream (few_rows.hip), and as good as rows for the tiled GEMMs.  Matrices
+// whose widths are no whole blocks (fp32 models, test shapes) stay row-major.
+__host__ __device__ inline int64_t block_at(int64_t r, int64_t k, int64_t K) {  // element offset of (r, k), K columns
+  return ((r >> 4) * (K >> 5) + (k >> 5)) * 512 + (((k & 31) >> 3) * 16 + (r & 15)) * 8 + (k & 7);
+}
 struct LayerWeights {
   void* g1;
   void* wqkv;  // [(Hq+2Hkv)*dh, d]
@@ -40,6 +46,7 @@ struct dsk_model {
   int gu_block;
   int n_qkv;        // (Hq+2Hkv)*dh
   LayerWeights* layers;
+  int w_blocks;     // projections are in blocks (see above)
   int64_t weight_bytes;
   // workspace
   void* xn;         // [maxT, d]      normalised activations
@@ -53,7 +60,7 @@ struct dsk_model {
   double* theta;    // [dh/2]         rope_base^(-2i/dh)
   void* vt;         // [Hkv*dh, ldvt] transposed V of the layer in flight (bf16 MFMA attention)
   int64_t ldvt;     // max_kv_rows rounded up to 64
-  float* ssq;       // [64, DSK_MAX_SSQ_PARTS] partial sums of squares of the few-row pass (RMSNorm split in two)
+  float* ssq;       // [d/16, 64] sums of squares of the few-row pass (RMSNorm split in two)
   void* gemm_ws;    // fp32 partial tiles of the K-split small-M GEMM
   int64_t gemm_ws_bytes;
   void* attn_ws;    // fp32 partial outputs of the key-split attention
@@ -89,9 +96,9 @@ struct dsk_model {
 enum { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_R_F32 = 2, EPI_C_F32 = 4, EPI_SWIGLU = 8 };
 
 // ---- launchers (each validates nothing: the C-ABI layer has checked shapes) ----
-// C[M,N] = A[M,K] * W[N,K]^T (+ R[M,N] when epi has EPI_RESIDUAL); row strides in elements.
-hipError_t launch_gemm_generic(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc,
-                               const void* R, int64_t ldr, int M, int N, int K, int epi, hipStream_t s);
+// C[M,N] = A[M,K] * W[N,K]^T (+ R[M,N] when epi has EPI_RESIDUAL); row strides in elements.  w_blocks: W is in blocks.
+hipError_t launch_gemm_generic(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C,
+                               int64_t ldc, const void* R, int64_t ldr, int M, int N, int K, int epi, hipStream_t s);
 // fp32 on the matrix instruction (fp32_mfma.hip).  The first asks whether rows are whole 16-byte pieces; the plain-ALU
 // kernel takes the others.  The fused two: C = epilogue(rmsnorm(h) W^T) with RoPE + KV write (head_dim a multiple of 32)
 // or SwiGLU (gate and up interleaved in blocks of 16 or 32) behind the projection.
@@ -105,34 +112,24 @@ hipError_t launch_gemm_fp32_norm_swiglu(const float* h, const void* gain, float 
                                         int F, int gu_block, hipStream_t s);
 // bf16 MFMA GEMM; returns hipErrorNotSupported when the shape is outside what it handles.
 // ws: optional fp32 scratch for the K-split partial tiles of the small-M path (see gemm_mfma_workspace_bytes).
-hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc,
+hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc,
                                  const void* R, int64_t ldr, int M, int N, int K, int epi, void* ws, int64_t ws_bytes,
                                  hipStream_t s);
 int64_t gemm_mfma_workspace_bytes(int max_n);
 bool gemm_mfma_swiglu_supported(int M, int N, int K, int64_t ws_bytes);
-// Few token rows (M <= 64, bf16): the projection and the step that follows it in one pass of the split-K reduction.
-bool gemm_small_m_fused_supported(int M, int N, int K, int64_t lda, int64_t ldw, int64_t ws_bytes);
-bool gemm_small_m_rope_supported(int M, int K, int Hq, int Hkv, int dh, int64_t lda, int64_t ldw, int64_t ldq,
-                                 int64_t ws_bytes);
-bool gemm_small_m_rmsnorm_supported(int M, int d, int K, int64_t lda, int64_t ldw, int64_t ws_bytes);
-// ssq (optional, with eps): the input rows lack the RMSNorm row factor, which is applied to the sums (see prescale)
-hipError_t launch_gemm_small_m_rope(const void* A, int64_t lda, const void* W, int64_t ldw, void* qkv, int64_t ldq,
-                                    const float2* cs, void* k_rows, void* v_rows, int M, int K, int Hq, int Hkv, int dh,
-                                    void* ws, int64_t ws_bytes, const float* ssq, float eps, hipStream_t s);
-// Few rows, RMSNorm split in two: a projection with residual writes h, a = bf16(h * g) and per-row partial sums of
-// h^2 (ssq [M, d/1024]); the projection that reads a multiplies its sums by rsqrt(mean(h^2) + eps).  One launch less
-// per norm than normalising in between, and the reduction stays spread over all compute units.
-constexpr int DSK_MAX_SSQ_PARTS = 16;
-bool gemm_small_m_prescale_supported(int M, int d, int K, int64_t lda, int64_t ldw, int64_t ws_bytes);
-hipError_t launch_gemm_small_m_prescale(const void* A, int64_t lda, const void* W, int64_t ldw, float* h, const void* R,
-                                        int r_f32, const void* g, void* a, float* ssq, int M, int d, int K, void* ws,
-                                        int64_t ws_bytes, hipStream_t s);
-hipError_t launch_gemm_small_m_swiglu_scaled(const void* A, int64_t lda, const void* W, int64_t ldw, void* act, int64_t ldc,
-                                             int M, int N, int K, void* ws, int64_t ws_bytes, const float* ssq, float eps,
-                                             hipStream_t s);
-hipError_t launch_gemm_small_m_rmsnorm(const void* A, int64_t lda, const void* W, int64_t ldw, float* h, const void* R,
-                                       int r_f32, const void* g, void* xn, float eps, int M, int d, int K, void* ws,
-                                       int64_t ws_bytes, hipStream_t s);
+// Few token rows (M <= 64, bf16, few_rows.hip): weights and activations in blocks, the step that follows a projection (and
+// the RMSNorm in front of it) done by the projection.  a = bf16(h * gain) in blocks, ssq [d/16][64] its sums of squares.
+bool few_rows_supported(int M, int d, int F, int Hq, int Hkv, int dh);
+int64_t few_rows_workspace_bytes(int d, int K_max);
+hipError_t launch_few_norm(const void* h, int h_f32, const void* gain, void* a, float* ssq, int M, int d, hipStream_t s);
+hipError_t launch_few_qkv(const void* a, const float* ssq, float eps, const void* W, void* qkv, int64_t ldq, const float2* cs,
+                          void* k_rows, void* v_rows, int M, int d, int Hq, int Hkv, int dh, hipStream_t s);
+// act (blocks, [M, N/2]) = silu(gate) * up
+hipError_t launch_few_swiglu(const void* a, const float* ssq, float eps, const void* W, void* act, int M, int N, int K,
+                             hipStream_t s);
+// C (row-major) = x W^T + R; with gain: a and ssq for the next projection
+hipError_t launch_few_residual(const void* x, const void* W, const void* R, int r_f32, void* C, int c_f32, const void* gain,
+                               void* a, float* ssq, int M, int N, int K, void* ws, int64_t ws_bytes, hipStream_t s);
 
 // x is fp32 when x_f32 is set, else the model dtype; g and y are the model dtype
 hipError_t launch_rmsnorm(int dtype, const void* x, int x_f32, const void* g, void* y, int T, int d, float eps, hipStream_t s);
@@ -171,6 +168,7 @@ struct AttnArgs {
   const int32_t* q_cu; const int32_t* p_cu; const int32_t* q_cu_host; const int32_t* p_cu_host; int n_seqs;
   int64_t own_row0; int n_q; int Hq, Hkv, dh;
   const void* vt; int64_t ldvt;  // transposed V (see launch_transpose_v); NULL: not available
+  int out_blocks = 0;            // out in blocks (block_at, Hq*dh columns) instead of rows
   void* ws; int64_t ws_bytes;    // fp32 scratch for key-split partial results (attn_mfma_workspace_bytes); optional
 };
 bool attn_fp32_supported(const AttnArgs& a);
@@ -190,8 +188,8 @@ hipError_t launch_fill_normal(void* dst, int64_t n, uint64_t seed, uint64_t stre
                               int64_t idx0, int dtype, hipStream_t s);
 // weight (re)packing: logical tensor rows <-> packed rows.  map: 0 identity + row_off, 1 gate rows, 2 up rows.
 hipError_t launch_pack_rows(int dtype, void* packed, const void* logical, int64_t rows, int64_t cols, int map,
-                            int gu_block, int64_t row_off, int to_packed, hipStream_t s);
-hipError_t launch_fill_weight(int dtype, void* packed, int64_t rows, int64_t cols, int map, int gu_block, int64_t row_off,
+                            int gu_block, int64_t row_off, int blocks, int to_packed, hipStream_t s);
+hipError_t launch_fill_weight(int dtype, void* packed, int64_t rows, int64_t cols, int map, int gu_block, int64_t row_off, int blocks,
                               uint64_t seed, uint64_t stream_id, float std, float offset, hipStream_t s);
 
 // mixture-of-experts MLP: router, grouping by expert, grouped projections, gate-weighted sum (moe.hip, gemm_mfma.hip)
@@ -207,7 +205,7 @@ hipError_t launch_moe_gather(int dtype, const void* xn, const int32_t* src_token
 hipError_t launch_moe_combine(const float* y, const float* h_mid, const float* gates, const int32_t* experts,
                               const int32_t* slot_of, void* out, int out_f32, int n, int d, int top_k, int64_t y_rows,
                               hipStream_t s);
-hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const void* W, int64_t ldw,
+hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const void* W, int64_t ldw, int w_blocks,
                                     int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
                                     const void* tile_tab, int tile_rows, hipStream_t s);
 

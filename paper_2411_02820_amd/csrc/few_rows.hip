@@ -1,0 +1,352 @@
+// Projections of few token rows (M <= 64, bf16): the suffix pass, where a layer is one pass over its weights.
+//
+// Bound: HBM (weight bytes) and, from about 32 rows on, the rate at which L2 feeds a compute unit with activations.
+// A load instruction costs by the cache lines it touches: one that takes 16 bytes from each of 16 rows runs at a fifth
+// of the rate of one that takes 1 KB in one piece (measured: gate/up of the 8B shape at 64 rows 126 us against
+// 77 us with only the operands' layout changed).  So both operands are kept in blocks of 16 rows x 32 columns, each
+// block the 1 KB that a wave loads for one MFMA operand in lane order: block (r/16, k/32) of a matrix with K columns is at
+// ((r/16) * K/32 + k/32) * 512 elements, element ((k%32)/8 * 16 + r%16) * 8 + k%8 inside it.  Weights are packed that way
+// when they are set; activations are written that way by the step in front (they live in the workspace only).
+//
+// No LDS ring: a wave streams both operands straight to registers, PF steps ahead; the waves of a workgroup split
+// the contraction (neighbouring chunks, so that a workgroup reads 512 contiguous bytes and more per row block) and
+// add up through LDS in wave order.  A workgroup that has whole sums applies the step that follows (RoPE + KV write,
+// residual + what the next RMSNorm needs, SwiGLU) itself: no partial sums in memory, no reduction launch.
+// RMSNorm is split: the producer of the residual stream h also writes a = bf16(h * gain) and, per 16 columns,
+// the row's sum of squares; the projection that reads a scales its sums by rsqrt(mean(h^2) + eps).
+#include "dsk_internal.h"
+
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+enum { EP_ROPE = 0, EP_SWIGLU = 1, EP_RES = 2, EP_PART = 3 };
+
+struct StreamArgs {
+  const bf16_t* X;  // blocks, rows up to a multiple of 16
+  const bf16_t* W;  // blocks
+  int M, N, K;
+  const float* ssq; float eps;  // EP_ROPE, EP_SWIGLU: row factor of the RMSNorm in front, from [K/16][64] sums of squares
+  bf16_t* out;                  // EP_ROPE: q rows, stride ldq; EP_SWIGLU: blocks [M, N/2]; EP_RES: blocks a = h * gain
+  int64_t ldq;
+  const float2* cs; bf16_t* k_rows; bf16_t* v_rows; int Hq, Hkv, dh;
+  const void* R; int r_f32; void* C; int c_f32;         // EP_RES: C = sum + R, row-major
+  const bf16_t* gain; float* ssq_out;                   // EP_RES: both null when nothing follows
+  float* P;                                             // EP_PART: [splits][M][N]
+};
+
+__device__ __forceinline__ bf16x4 to_bf16x4(f32x4 v) {
+  bf16x4 o;
+  o[0] = (bf16_t)v[0]; o[1] = (bf16_t)v[1]; o[2] = (bf16_t)v[2]; o[3] = (bf16_t)v[3];
+  return o;
+}
+
+// v[n..n+3] of row m: + R, C, and the next norm's share; the four lanes of a 16-column group are at lane ^ X1, lane ^ X2
+template <int X1, int X2>
+__device__ __forceinline__ void residual_quad(f32x4 v, int m, int n, int N, bool in, const void* R, int r_f32, void* C,
+                                              int c_f32, const bf16_t* gain, bf16_t* a, float* ssq_out) {
+  const int64_t at = (int64_t)m * N + n;
+  if (in) {
+    if (r_f32) {
+      v += *(const f32x4*)((const float*)R + at);
+    } else {
+      const bf16x4 r = *(const bf16x4*)((const bf16_t*)R + at);
+      v[0] += (float)r[0]; v[1] += (float)r[1]; v[2] += (float)r[2]; v[3] += (float)r[3];
+    }
+    if (C) {
+      if (c_f32) *(f32x4*)((float*)C + at) = v;
+      else *(bf16x4*)((bf16_t*)C + at) = to_bf16x4(v);
+    }
+  }
+  if (!gain) return;
+  float ss = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+  ss += __shfl_xor(ss, X1, 64);
+  ss += __shfl_xor(ss, X2, 64);
+  if (in) {
+    const bf16x4 g = *(const bf16x4*)(gain + n);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] *= (float)g[e];
+    *(bf16x4*)(a + block_at(m, n, N)) = to_bf16x4(v);
+    if (n % 16 == 0) ssq_out[(n / 16) * 64 + m] = ss;
+  }
+}
+
+// Wave tile: MT blocks of 16 rows x NT blocks of 16 columns, KS x 32 of the contraction per step.  EP_ROPE and EP_SWIGLU
+// take their column blocks in pairs that a lane combines: the halves (i, i + dh/2) of a head, or gate and up (packed in
+// blocks of 32 rows each).
+template <int MT, int NT, int KW, int PF, int KS, int EP>
+__global__ void __launch_bounds__(64 * KW) stream_kernel(StreamArgs p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  f32x4* red = (f32x4*)smem_raw;                          // [KW][MT * NT][64]
+  f32x4* red_ss = red + KW * MT * NT * 64;                // [KW][16]: sums of squares of rows 4 * i ..
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+  const int kw = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr bool PAIRS = EP == EP_ROPE || EP == EP_SWIGLU;
+  const int unit0 = blockIdx.x * (NT / 2);
+  const int half = p.dh >> 1, per_head = half >> 4, n_rot = (p.Hq + p.Hkv) * per_head;
+  auto col0 = [&](int j) {
+    if (EP == EP_ROPE) {
+      const int u = unit0 + j / 2;
+      return u < n_rot ? u / per_head * p.dh + u % per_head * 16 + (j & 1) * half : (p.Hq + p.Hkv) * p.dh + 32 * (u - n_rot) + (j & 1) * 16;
+    }
+    if (EP == EP_SWIGLU) {
+      const int u = unit0 + j / 2;
+      return (u >> 1) * 64 + (u & 1) * 16 + (j & 1) * 32;
+    }
+    return (int)blockIdx.x * 16 * NT + 16 * j;
+  };
+  const int kb = p.K >> 5;  // k blocks
+  uint32_t wo[NT], xo[MT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) wo[j] = ((uint32_t)(col0(j) >> 4) * kb * 64 + lane) * 16;
+#pragma unroll
+  for (int i = 0; i < MT; ++i) xo[i] = ((uint32_t)i * kb * 64 + lane) * 16;
+  f32x4 acc[NT][MT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int i = 0; i < MT; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // steps of this workgroup's share of the contraction (blockIdx.y of gridDim.y shares); K is a multiple of 64
+  const int n_steps_all = kb / KS;
+  const int begin = (int)((int64_t)n_steps_all * blockIdx.y / gridDim.y), end = (int)((int64_t)n_steps_all * (blockIdx.y + 1) / gridDim.y);
+  bf16x8 fw[PF][KS][NT], fx[PF][KS][MT];
+  auto load = [&](int s, int c) {
+    if (c >= end) return;  // uniform over the wave
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+      const int b = c * KS + q;
+      const char* wb = (const char*)p.W + (int64_t)b * 1024;
+      const char* xb = (const char*)p.X + (int64_t)b * 1024;
+#pragma unroll
+      for (int j = 0; j < NT; ++j) fw[s][q][j] = __builtin_nontemporal_load((const bf16x8*)(wb + wo[j]));
+#pragma unroll
+      for (int i = 0; i < MT; ++i) fx[s][q][i] = *(const bf16x8*)(xb + xo[i]);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < PF; ++s) load(s, begin + kw + s * KW);
+  if (PAIRS) {
+    // Sums of squares: four rows a lane, eight loads in flight.  One load at a time took longer than the matrix (25 us instead
+    // of 18.6 us for QKV over 64 rows, 58 us instead of 43.7 us for gate/up); requested in front of the operands: 49 us.
+    const float* src = p.ssq + 4 * r16;
+    const int parts = p.K >> 4;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    if (4 * r16 < 16 * MT) {
+      for (int q = tid >> 4; q < parts; q += 8 * 4 * KW) {
+        f32x4 b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) b[u] = q + u * 4 * KW < parts ? *(const f32x4*)(src + (q + u * 4 * KW) * 64) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += b[u];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s[e] += __shfl_xor(s[e], 16, 64);
+      s[e] += __shfl_xor(s[e], 32, 64);
+    }
+    if (lane < 16) red_ss[kw * 16 + lane] = s;
+  }
+  for (int c = begin + kw; c < end; c += PF * KW) {
+#pragma unroll
+    for (int s = 0; s < PF; ++s) {
+      if (c + s * KW < end) {
+#pragma unroll
+        for (int q = 0; q < KS; ++q)
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+              acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[s][q][j], fx[s][q][i], acc[j][i], 0, 0, 0);
+        load(s, c + (s + PF) * KW);
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int i = 0; i < MT; ++i) red[(kw * MT * NT + j * MT + i) * 64 + lane] = acc[j][i];
+  __syncthreads();
+  auto total = [&](int j, int i) {
+    f32x4 v = red[(j * MT + i) * 64 + lane];
+#pragma unroll
+    for (int k = 1; k < KW; ++k) v += red[(k * MT * NT + j * MT + i) * 64 + lane];
+    return v;
+  };
+  for (int it = kw; it < MT * (PAIRS ? NT / 2 : NT); it += KW) {
+    const int i = it % MT, jj = it / MT, m = 16 * i + r16;
+    const bool in = m < p.M;
+    if (!PAIRS) {
+      const int n = col0(jj) + 4 * g;
+      const f32x4 v = total(jj, i);
+      if (EP == EP_PART) {
+        if (in) *(f32x4*)(p.P + ((int64_t)blockIdx.y * p.M + m) * p.N + n) = v;
+      } else {
+        residual_quad<16, 32>(v, m, n, p.N, in, p.R, p.r_f32, p.C, p.c_f32, p.gain, p.out, p.ssq_out);
+      }
+      continue;
+    }
+    f32x4 x0 = total(2 * jj, i), x1 = total(2 * jj + 1, i);
+    if (!in) continue;
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < KW; ++k) s += ((const float*)red_ss)[k * 64 + m];
+    const float rs = rsqrtf(s / (float)p.K + p.eps);
+    x0 *= rs;
+    x1 *= rs;
+    if (EP == EP_SWIGLU) {
+      f32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x0[e]));
+        o[e] = x0[e] * sig * x1[e];
+      }
+      *(bf16x4*)(p.out + block_at(m, 16 * (unit0 + jj) + 4 * g, p.N >> 1)) = to_bf16x4(o);
+    } else {
+      const int c0 = col0(2 * jj), rot_cols = (p.Hq + p.Hkv) * p.dh, kvw = p.Hkv * p.dh;
+      if (c0 < rot_cols) {
+        const int head = c0 / p.dh, i0 = c0 % p.dh + 4 * g;
+        f32x4 y0, y1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float2 c = p.cs[(int64_t)m * half + i0 + e];
+          y0[e] = x0[e] * c.x - x1[e] * c.y;
+          y1[e] = x1[e] * c.x + x0[e] * c.y;
+        }
+        bf16_t* dst = head < p.Hq ? p.out + (int64_t)m * p.ldq + head * p.dh + i0
+                                  : p.k_rows + (int64_t)m * kvw + (head - p.Hq) * p.dh + i0;
+        *(bf16x4*)dst = to_bf16x4(y0);
+        *(bf16x4*)(dst + half) = to_bf16x4(y1);
+      } else {
+        bf16_t* dst = p.v_rows + (int64_t)m * kvw + (c0 - rot_cols) + 4 * g;
+        *(bf16x4*)dst = to_bf16x4(x0);
+        *(bf16x4*)(dst + 16) = to_bf16x4(x1);
+      }
+    }
+  }
+}
+
+// What stream_kernel's EP_RES does, for a contraction split over workgroups (partial sums P, added in split order), or with
+// no projection in front (splits = 0: the input norm of the first layer).  One thread per 4 columns of a row.
+__global__ void __launch_bounds__(256) few_residual_kernel(const float* __restrict__ P, int splits, const void* R, int r_f32,
+                                                           void* C, int c_f32, const bf16_t* __restrict__ gain,
+                                                           bf16_t* __restrict__ a, float* __restrict__ ssq_out, int M, int N) {
+  const int i = blockIdx.x * 256 + threadIdx.x, quads = N / 4;
+  const bool in = i < M * quads;
+  const int m = in ? i / quads : 0, n = in ? (i - m * quads) * 4 : 0;
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (in && splits > 0) {
+    f32x4 b[4];
+    const int64_t stride = (int64_t)M * N;
+    const float* src = P + (int64_t)m * N + n;
+    for (int k = 0; k < splits; k += 4) {  // four at a time in flight
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (k + u < splits) b[u] = *(const f32x4*)(src + (k + u) * stride);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (k + u < splits) v += b[u];
+    }
+  }
+  residual_quad<1, 2>(v, m, n, N, in, R, r_f32, C, c_f32, gain, a, ssq_out);
+}
+
+template <int MT, int NT, int KW, int PF, int KS, int EP>
+hipError_t launch_stream(const StreamArgs& p, int tiles, int splits, hipStream_t s) {
+  auto kern = stream_kernel<MT, NT, KW, PF, KS, EP>;
+  constexpr int lds = KW * MT * NT * 1024 + KW * 256;
+  if constexpr (lds > 64 << 10) {
+    static bool configured = false;
+    if (!configured) {
+      hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if (e != hipSuccess) return e;
+      configured = true;
+    }
+  }
+  hipLaunchKernelGGL(kern, dim3(tiles, splits), dim3(64 * KW), lds, s, p);
+  return hipGetLastError();
+}
+
+// A projection with residual runs unsplit on 16-column tiles (every compute unit gets one at the 8B width) as long as
+// that many tiles re-reading the activations stay cheap; beyond 256 MB of such reads the contraction is split over about 256
+// workgroups of 64 columns, and a reduction launch adds up.  64 rows, 8B shape: O (134 MB of reads) 13.6 us against
+// 10.6 us + 4.9 us split; down (470 MB) 40 us against 24.6 us + 4.9 us.
+int residual_splits(int M, int N, int K) {
+  const int rows = (M + 15) / 16 * 16;
+  if (rows <= 32 || (int64_t)(N / 16) * rows * K * 2 <= (int64_t)256 << 20) return 0;
+  const int tiles = N / 64, splits = (256 + tiles - 1) / tiles;
+  return splits > K / 512 ? (K / 512 > 0 ? K / 512 : 1) : splits;
+}
+
+}  // namespace
+
+// Widths in whole blocks, heads in whole pairs of blocks.
+bool few_rows_supported(int M, int d, int F, int Hq, int Hkv, int dh) {
+  return M >= 1 && M <= 64 && d % 64 == 0 && F % 64 == 0 && dh % 32 == 0 && Hq * dh % 64 == 0;
+}
+
+int64_t few_rows_workspace_bytes(int d, int K_max) {
+  const int s = residual_splits(64, d, K_max);
+  return (int64_t)(s > 0 ? s : 1) * 64 * d * 4;
+}
+
+hipError_t launch_few_norm(const void* h, int h_f32, const void* gain, void* a, float* ssq, int M, int d, hipStream_t s) {
+  hipLaunchKernelGGL(few_residual_kernel, dim3((M * (d / 4) + 255) / 256), dim3(256), 0, s, (const float*)nullptr, 0, h, h_f32,
+                     (void*)nullptr, 0, (const bf16_t*)gain, (bf16_t*)a, ssq, M, d);
+  return hipGetLastError();
+}
+
+hipError_t launch_few_qkv(const void* a, const float* ssq, float eps, const void* W, void* qkv, int64_t ldq, const float2* cs,
+                          void* k_rows, void* v_rows, int M, int d, int Hq, int Hkv, int dh, hipStream_t s) {
+  StreamArgs p = {};
+  p.X = (const bf16_t*)a; p.W = (const bf16_t*)W; p.M = M; p.N = (Hq + 2 * Hkv) * dh; p.K = d; p.ssq = ssq; p.eps = eps;
+  p.out = (bf16_t*)qkv; p.ldq = ldq; p.cs = cs; p.k_rows = (bf16_t*)k_rows; p.v_rows = (bf16_t*)v_rows;
+  p.Hq = Hq; p.Hkv = Hkv; p.dh = dh;
+  const int tiles = p.N / 32;
+  switch ((M + 15) / 16) {
+    case 1: return launch_stream<1, 2, 8, 2, 2, EP_ROPE>(p, tiles, 1, s);
+    case 2: return launch_stream<2, 2, 8, 2, 2, EP_ROPE>(p, tiles, 1, s);
+    case 3: return launch_stream<3, 2, 8, 2, 2, EP_ROPE>(p, tiles, 1, s);
+    default: return launch_stream<4, 2, 8, 2, 2, EP_ROPE>(p, tiles, 1, s);
+  }
+}
+
+// 32 rows and fewer: 32-column tiles; more: 128-column tiles (224 workgroups at the 8B width), which read the activations
+// a quarter as often (64 rows, 8B shape: 42.6 us against 57 us)
+hipError_t launch_few_swiglu(const void* a, const float* ssq, float eps, const void* W, void* act, int M, int N, int K,
+                             hipStream_t s) {
+  StreamArgs p = {};
+  p.X = (const bf16_t*)a; p.W = (const bf16_t*)W; p.M = M; p.N = N; p.K = K; p.ssq = ssq; p.eps = eps; p.out = (bf16_t*)act;
+  switch ((M + 15) / 16) {
+    case 1: return launch_stream<1, 2, 8, 2, 2, EP_SWIGLU>(p, N / 32, 1, s);
+    case 2: return launch_stream<2, 2, 8, 2, 2, EP_SWIGLU>(p, N / 32, 1, s);
+    case 3: return launch_stream<3, 8, 4, 1, 1, EP_SWIGLU>(p, N / 128, 1, s);
+    default: return launch_stream<4, 8, 4, 1, 1, EP_SWIGLU>(p, N / 128, 1, s);
+  }
+}
+
+hipError_t launch_few_residual(const void* x, const void* W, const void* R, int r_f32, void* C, int c_f32, const void* gain,
+                               void* a, float* ssq, int M, int N, int K, void* ws, int64_t ws_bytes, hipStream_t s) {
+  StreamArgs p = {};
+  p.X = (const bf16_t*)x; p.W = (const bf16_t*)W; p.M = M; p.N = N; p.K = K;
+  p.R = R; p.r_f32 = r_f32; p.C = C; p.c_f32 = c_f32; p.gain = (const bf16_t*)gain; p.out = (bf16_t*)a; p.ssq_out = ssq;
+  p.P = (float*)ws;
+  const int mt = (M + 15) / 16, splits = residual_splits(M, N, K);
+  if (splits > 0) {
+    if (!ws || (int64_t)splits * M * N * 4 > ws_bytes) return hipErrorNotSupported;
+    hipError_t e = mt == 3 ? launch_stream<3, 4, 8, 2, 1, EP_PART>(p, N / 64, splits, s)
+                           : launch_stream<4, 4, 8, 2, 1, EP_PART>(p, N / 64, splits, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(few_residual_kernel, dim3((M * (N / 4) + 255) / 256), dim3(256), 0, s, (const float*)ws, splits, R, r_f32,
+                       C, c_f32, (const bf16_t*)gain, (bf16_t*)a, ssq, M, N);
+    return hipGetLastError();
+  }
+  switch (mt) {
+    case 1: return launch_stream<1, 1, 8, 2, 2, EP_RES>(p, N / 16, 1, s);
+    case 2: return launch_stream<2, 1, 8, 2, 2, EP_RES>(p, N / 16, 1, s);
+    case 3: return launch_stream<3, 1, 8, 2, 2, EP_RES>(p, N / 16, 1, s);
+    default: return launch_stream<4, 1, 8, 2, 2, EP_RES>(p, N / 16, 1, s);
+  }
+}

@@ -44,6 +44,13 @@ constexpr int GROUP_M = 4;    // M-tiles per scheduling group
 
 __device__ __forceinline__ int slot(int row, int chunk) { return (row * CH + (chunk ^ ((row >> 1) & (CH - 1)))) * 8; }
 
+// W in blocks (WB; block_at in dsk_internal.h): a k-tile of 64 columns is two 1 KB blocks per 16 rows.  Each goes to LDS as
+// it is, in one wave load of 1 KB in a row, and a fragment is read back in lane order: no swizzle, no conflicts.  The
+// other way round, fetching blocks piecewise into the row layout, lets a load touch 64 bytes of a line at a time and
+// costs the large GEMMs 10 % (8192 x 28672 x 4096).
+constexpr int BLK = 512;  // elements of a block
+template <bool WB> __device__ __forceinline__ int w_step() { return WB ? 32 : 2; }  // bytes of W per k of a tile's origin
+
 // C[m][n..n+3] = v (+ R[m][n..n+3]); R and C are bf16 or fp32 as the epilogue flags say.
 __device__ __forceinline__ void store_quad(void* C, int64_t ldc, const void* R, int64_t ldr, int m, int n, f32x4 v, int epi) {
   if (epi & EPI_RESIDUAL) {
@@ -70,7 +77,7 @@ __device__ __forceinline__ void store_quad(void* C, int64_t ldc, const void* R, 
 // rows), so MFMA tiles j (even) and j+1 of a wave are gate and up of the same 32 FFN indices at the same
 // lane/register; the epilogue writes silu(gate)*up to C[M, N/2].
 // SCHED: software-pipeline schedule of the k loop, see the top of the file.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool PARTIAL, int SCHED = 0>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool PARTIAL, int SCHED, bool WB>
 __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     gemm_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W, int64_t ldw,
                      void* __restrict__ C, int64_t ldc, const void* __restrict__ R, int64_t ldr,
@@ -119,8 +126,9 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   }
 #pragma unroll
   for (int i = 0; i < W_INST; ++i) {
-    int row = RPI * (wave * W_INST + i) + lr;
-    w_off[i] = (uint32_t)(((int64_t)min(n0 + row, N - 1) * ldw + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
+    const int row = RPI * (wave * W_INST + i) + lr, blk = wave * W_INST + i;  // WB: block blk % 2 of rows 16 * (blk / 2) ..
+    w_off[i] = WB ? (uint32_t)(min(n0 / 16 + blk / 2, N / 16 - 1) * (int)(ldw / 32) + blk % 2) * (BLK * 2u) + lane * 16u
+                  : (uint32_t)(((int64_t)min(n0 + row, N - 1) * ldw + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
   }
   typedef __attribute__((address_space(3))) void lds_void;
   typedef const __attribute__((address_space(1))) void glb_void;
@@ -131,7 +139,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   auto issue_load = [&](int stage, int k0, int idx) {
     const bool is_a = idx < A_INST;
     const int li = is_a ? idx : idx - A_INST;
-    const char* base = (is_a ? (const char*)A : (const char*)W) + (int64_t)k0 * 2;
+    const char* base = is_a ? (const char*)A + (int64_t)k0 * 2 : (const char*)W + (int64_t)k0 * w_step<WB>();
     const uint32_t voff = is_a ? a_off[li] : w_off[li];
     const uint32_t dst = is_a ? sA_lds + (uint32_t)(stage * BM * BK + RPI * (wave * A_INST + li) * BK) * 2
                               : sW_lds + (uint32_t)(stage * BN * BK + RPI * (wave * W_INST + li) * BK) * 2;
@@ -159,7 +167,10 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 #pragma unroll
     for (int i = 0; i < TM; ++i) xf[i] = *(const bf16x8*)(a_s + slot(wm * WTM + i * 32 + frag_row, ch));
 #pragma unroll
-    for (int j = 0; j < TN; ++j) wf[j] = *(const bf16x8*)(w_s + slot(wn * WTN + j * 32 + frag_row, ch));
+    for (int j = 0; j < TN; ++j) {
+      const int r = wn * WTN + j * 32 + frag_row;
+      wf[j] = *(const bf16x8*)(w_s + (WB ? ((r >> 4) * 2 + (ch >> 2)) * BLK + ((ch & 3) * 16 + (r & 15)) * 8 : slot(r, ch)));
+    }
   };
 
   // ---- K range of this workgroup ----
@@ -441,7 +452,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 // tm of the grid is described by tile_tab[tm] = {expert, first row, end of the expert's rows, -} (built on the
 // device; tile_tab[tiles_m].x = number of tiles that exist; expert < 0: no such tile, the workgroup leaves); the
 // expert's matrix is W + expert * w_group_stride.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool GROUPED = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false>
 __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     gemm16_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W_all, int64_t ldw,
                        void* __restrict__ C, int64_t ldc, const void* __restrict__ R, int64_t ldr, int M_all, int N, int K,
@@ -500,14 +511,15 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   }
 #pragma unroll
   for (int i = 0; i < W_INST; ++i) {
-    int row = RPI * (wave * W_INST + i) + lr;
-    w_off[i] = (uint32_t)(((int64_t)min(n0 + row, N - 1) * ldw + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
+    const int row = RPI * (wave * W_INST + i) + lr, blk = wave * W_INST + i;  // WB: block blk % 2 of rows 16 * (blk / 2) ..
+    w_off[i] = WB ? (uint32_t)(min(n0 / 16 + blk / 2, N / 16 - 1) * (int)(ldw / 32) + blk % 2) * (BLK * 2u) + lane * 16u
+                  : (uint32_t)(((int64_t)min(n0 + row, N - 1) * ldw + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
   }
   const uint32_t sA_lds = (uint32_t)(uintptr_t)sA, sW_lds = (uint32_t)(uintptr_t)sW;
   auto issue_load = [&](int stage, int k0, int idx) {
     const bool is_a = idx < A_INST;
     const int li = is_a ? idx : idx - A_INST;
-    const char* base = (is_a ? (const char*)A : (const char*)W) + (int64_t)k0 * 2;
+    const char* base = is_a ? (const char*)A + (int64_t)k0 * 2 : (const char*)W + (int64_t)k0 * w_step<WB>();
     const uint32_t voff = is_a ? a_off[li] : w_off[li];
     const uint32_t dst = is_a ? sA_lds + (uint32_t)(stage * BM * BK + RPI * (wave * A_INST + li) * BK) * 2
                               : sW_lds + (uint32_t)(stage * BN * BK + RPI * (wave * W_INST + li) * BK) * 2;
@@ -530,9 +542,9 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   bf16x8 xs[2][TM], ws[2][TN];
   auto read_frag = [&](const bf16_t* a_s, const bf16_t* w_s, int ks, int f) {
     const int ch = ks * 4 + fq;
-    if (f == 0) ws[ks][0] = *(const bf16x8*)(w_s + slot(wn * WTN + frow, ch));
-    else if (f <= TM) xs[ks][f - 1] = *(const bf16x8*)(a_s + slot(wm * WTM + (f - 1) * 16 + frow, ch));
-    else ws[ks][f - TM] = *(const bf16x8*)(w_s + slot(wn * WTN + (f - TM) * 16 + frow, ch));
+    const int j = f == 0 ? 0 : f - TM;
+    if (f >= 1 && f <= TM) xs[ks][f - 1] = *(const bf16x8*)(a_s + slot(wm * WTM + (f - 1) * 16 + frow, ch));
+    else ws[ks][j] = *(const bf16x8*)(w_s + (WB ? ((wn * WTN / 16 + j) * 2 + ks) * BLK + lane * 8 : slot(wn * WTN + j * 16 + frow, ch)));
   };
 
   const int n_kt = K / BK;
@@ -758,18 +770,8 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const float* __restr
 // The same for the gate/up projection, with SwiGLU applied to the sums: act[m][f] = silu(gate) * up, where gate
 // column f sits at packed column (f/32)*64 + f%32 of P and its up column 32 further (rows of W interleaved in
 // blocks of 32).  N = 2F columns in P, F columns in act.
-// ssq != nullptr: the projection's input rows were x*g without the RMSNorm factor; the sums of row m are multiplied
-// by rsqrt(mean(x^2) + eps) here, from the row's n_parts partial sums of squares (row_scale below).
-__device__ __forceinline__ float row_scale(const float* __restrict__ ssq, int m, int n_parts, float inv_d, float eps) {
-  float ss = 0.f;
-  for (int c = 0; c < n_parts; ++c) ss += ssq[m * n_parts + c];
-  return rsqrtf(ss * inv_d + eps);
-}
-
 __global__ void __launch_bounds__(256) splitk_reduce_swiglu_kernel(const float* __restrict__ P, bf16_t* __restrict__ act,
-                                                                   int64_t ldc, int M, int N, int splits,
-                                                                   const float* __restrict__ ssq, int n_parts, float inv_d,
-                                                                   float eps) {
+                                                                   int64_t ldc, int M, int N, int splits) {
   const int F = N / 2;
   const int64_t quads = (int64_t)M * (F / 4);
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -778,11 +780,6 @@ __global__ void __launch_bounds__(256) splitk_reduce_swiglu_kernel(const float* 
   const int pg = (f / 32) * 64 + f % 32;
   f32x4 g, u;
   sum_splits2(P + (int64_t)m * N + pg, P + (int64_t)m * N + pg + 32, (int64_t)M * N, splits, &g, &u);
-  if (ssq) {
-    const float rs = row_scale(ssq, m, n_parts, inv_d, eps);
-    g *= rs;
-    u *= rs;
-  }
   bf16x4 o;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -792,166 +789,10 @@ __global__ void __launch_bounds__(256) splitk_reduce_swiglu_kernel(const float* 
   *(bf16x4*)(act + (int64_t)m * ldc + f) = o;
 }
 
-// The same for the fused QKV projection of few token rows, followed by what rope_kv_write_kernel does: q and k
-// heads rotated with the (cos, sin) table of the tokens (pairs (i, i + dh/2)), q written to the qkv buffer, rotated
-// k and v written to the rows of the cache.  One thread per 4 rotary pairs, or per 4 values of v.
-__global__ void __launch_bounds__(256) splitk_reduce_rope_kernel(const float* __restrict__ P, bf16_t* __restrict__ qkv,
-                                                                 int64_t ldq, const float2* __restrict__ cs,
-                                                                 bf16_t* __restrict__ k_rows, bf16_t* __restrict__ v_rows,
-                                                                 int M, int N, int splits, int Hq, int Hkv, int dh,
-                                                                 const float* __restrict__ ssq, int n_parts, float inv_d,
-                                                                 float eps) {
-  const int half = dh / 2;
-  const int rot_units = (Hq + Hkv) * (half / 4), v_units = Hkv * dh / 4;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)M * (rot_units + v_units)) return;
-  const int m = (int)(i / (rot_units + v_units)), u = (int)(i - (int64_t)m * (rot_units + v_units));
-  const int kvw = Hkv * dh;
-  const float rs = ssq ? row_scale(ssq, m, n_parts, inv_d, eps) : 1.0f;
-  const float* row = P + (int64_t)m * N;
-  const int64_t stride = (int64_t)M * N;
-  auto to_bf16 = [](f32x4 v) {
-    bf16x4 o;
-    o[0] = (bf16_t)v[0]; o[1] = (bf16_t)v[1]; o[2] = (bf16_t)v[2]; o[3] = (bf16_t)v[3];
-    return o;
-  };
-  if (u < rot_units) {
-    const int head = u / (half / 4), i0 = (u % (half / 4)) * 4;
-    f32x4 x1, x2;
-    sum_splits2(row + head * dh + i0, row + head * dh + i0 + half, stride, splits, &x1, &x2);
-    x1 *= rs;  // 1 when the input rows carried their RMSNorm factor already
-    x2 *= rs;
-    f32x4 y1, y2;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float2 c = cs[(int64_t)m * half + i0 + e];
-      y1[e] = x1[e] * c.x - x2[e] * c.y;
-      y2[e] = x2[e] * c.x + x1[e] * c.y;
-    }
-    bf16_t* dst = head < Hq ? qkv + (int64_t)m * ldq + head * dh + i0 : k_rows + (int64_t)m * kvw + (head - Hq) * dh + i0;
-    *(bf16x4*)dst = to_bf16(y1);
-    *(bf16x4*)(dst + half) = to_bf16(y2);
-  } else {
-    const int j = (u - rot_units) * 4;
-    *(bf16x4*)(v_rows + (int64_t)m * kvw + j) = to_bf16(sum_splits(row + (Hq + Hkv) * dh + j, stride, splits) * rs);
-  }
-}
-
-// The same for a projection with residual whose result feeds an RMSNorm (the O projection before the MLP): one
-// workgroup per token row adds the partial sums and the residual, writes the fp32 residual stream h and the
-// normalised row xn = h * rsqrt(mean(h^2) + eps) * g in bf16.  d <= 1024 * NCH.
-template <int NCH>
-__global__ void __launch_bounds__(256) splitk_reduce_rmsnorm_kernel(const float* __restrict__ P, float* __restrict__ h,
-                                                                    const void* __restrict__ R, int r_f32,
-                                                                    const bf16_t* __restrict__ g, bf16_t* __restrict__ xn,
-                                                                    int M, int d, int splits, float eps) {
-  __shared__ float part[4];
-  const int m = blockIdx.x;
-  f32x4 v[NCH];
-  float ss = 0.f;
-  // partial sums in split order; the loads of four splits are issued together (one workgroup per row: it is
-  // the loads in flight per lane that decide how fast the row arrives)
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int n = (threadIdx.x + c * 256) * 4;
-    if (n < d) v[c] = *(const f32x4*)(P + (int64_t)m * d + n);
-  }
-  int k = 1;
-  for (; k + 3 < splits; k += 4) {
-    f32x4 b[4][NCH];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int n = (threadIdx.x + c * 256) * 4;
-        if (n < d) b[u][c] = *(const f32x4*)(P + ((int64_t)(k + u) * M + m) * d + n);
-      }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int n = (threadIdx.x + c * 256) * 4;
-        if (n < d) v[c] += b[u][c];
-      }
-  }
-  for (; k < splits; ++k) {
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int n = (threadIdx.x + c * 256) * 4;
-      if (n < d) v[c] += *(const f32x4*)(P + ((int64_t)k * M + m) * d + n);
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int n = (threadIdx.x + c * 256) * 4;
-    if (n < d) {
-      f32x4 a = v[c];
-      if (r_f32) {
-        a += *(const f32x4*)((const float*)R + (int64_t)m * d + n);
-      } else {
-        const bf16x4 r = *(const bf16x4*)((const bf16_t*)R + (int64_t)m * d + n);
-        a[0] += (float)r[0]; a[1] += (float)r[1]; a[2] += (float)r[2]; a[3] += (float)r[3];
-      }
-      *(f32x4*)(h + (int64_t)m * d + n) = a;
-      v[c] = a;
-      ss += a[0] * a[0] + a[1] * a[1] + a[2] * a[2] + a[3] * a[3];
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  const float r = 1.0f / sqrtf((part[0] + part[1] + part[2] + part[3]) / (float)d + eps);
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int n = (threadIdx.x + c * 256) * 4;
-    if (n < d) {
-      const bf16x4 gg = *(const bf16x4*)(g + n);
-      bf16x4 o;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = (bf16_t)(v[c][e] * r * (float)gg[e]);
-      *(bf16x4*)(xn + (int64_t)m * d + n) = o;
-    }
-  }
-}
-
-// A projection with residual whose result feeds an RMSNorm, with the norm's row factor left to the next projection's
-// reduction: h = sum of the partials + R (fp32 residual stream), a = bf16(h * g) (what that projection reads), and
-// ssq[m][c] = sum of h^2 over columns 1024c .. 1024c+1023 (one workgroup per row and 1024 columns; the partial sums
-// of a row are added in index order by row_scale).  N a multiple of 1024.
-__global__ void __launch_bounds__(256) splitk_reduce_prescale_kernel(const float* __restrict__ P, float* __restrict__ h,
-                                                                     const void* __restrict__ R, int r_f32,
-                                                                     const bf16_t* __restrict__ g, bf16_t* __restrict__ a,
-                                                                     float* __restrict__ ssq, int M, int N, int splits) {
-  __shared__ float part[4];
-  const int n_parts = N / 1024;
-  const int m = blockIdx.x / n_parts, c = blockIdx.x % n_parts;
-  const int n = c * 1024 + threadIdx.x * 4;
-  f32x4 v = sum_splits(P + (int64_t)m * N + n, (int64_t)M * N, splits);
-  if (r_f32) {
-    v += *(const f32x4*)((const float*)R + (int64_t)m * N + n);
-  } else {
-    const bf16x4 rb = *(const bf16x4*)((const bf16_t*)R + (int64_t)m * N + n);
-    v[0] += (float)rb[0]; v[1] += (float)rb[1]; v[2] += (float)rb[2]; v[3] += (float)rb[3];
-  }
-  *(f32x4*)(h + (int64_t)m * N + n) = v;
-  const bf16x4 gg = *(const bf16x4*)(g + n);
-  bf16x4 o;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) o[e] = (bf16_t)(v[e] * (float)gg[e]);
-  *(bf16x4*)(a + (int64_t)m * N + n) = o;
-  float ss = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  if (threadIdx.x == 0) ssq[m * n_parts + c] = (part[0] + part[1]) + (part[2] + part[3]);
-}
-
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool PARTIAL, int SCHED = 0>
-hipError_t launch(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R, int64_t ldr,
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool PARTIAL, int SCHED, bool WB>
+hipError_t launch_form(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R, int64_t ldr,
                   float* P, int M, int N, int K, int epi, int splits, int kt_per_split, hipStream_t s) {
-  auto kern = gemm_bf16_kernel<BM, BN, WAVES_M, WAVES_N, PARTIAL, SCHED>;
+  auto kern = gemm_bf16_kernel<BM, BN, WAVES_M, WAVES_N, PARTIAL, SCHED, WB>;
   constexpr int lds = NSTAGE * (BM + BN) * BK * 2;
   static bool configured = false;
   if (!configured) {
@@ -965,10 +806,18 @@ hipError_t launch(const void* A, int64_t lda, const void* W, int64_t ldw, void* 
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N>
-hipError_t launch16(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R, int64_t ldr,
+// W in rows or in blocks, as the caller has it
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool PARTIAL, int SCHED = 0>
+hipError_t launch(const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc, const void* R, int64_t ldr,
+                  float* P, int M, int N, int K, int epi, int splits, int kt_per_split, hipStream_t s) {
+  return w_blocks ? launch_form<BM, BN, WAVES_M, WAVES_N, PARTIAL, SCHED, true>(A, lda, W, ldw, C, ldc, R, ldr, P, M, N, K, epi, splits, kt_per_split, s)
+                  : launch_form<BM, BN, WAVES_M, WAVES_N, PARTIAL, SCHED, false>(A, lda, W, ldw, C, ldc, R, ldr, P, M, N, K, epi, splits, kt_per_split, s);
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB>
+hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R, int64_t ldr,
                     int M, int N, int K, int epi, hipStream_t s) {
-  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N>;
+  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, WB>;
   constexpr int lds = NSTAGE * (BM + BN) * BK * 2;
   static bool configured = false;
   if (!configured) {
@@ -983,9 +832,16 @@ hipError_t launch16(const void* A, int64_t lda, const void* W, int64_t ldw, void
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N>
+hipError_t launch16(const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc, const void* R, int64_t ldr,
+                    int M, int N, int K, int epi, hipStream_t s) {
+  return w_blocks ? launch16_form<BM, BN, WAVES_M, WAVES_N, true>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, s)
+                  : launch16_form<BM, BN, WAVES_M, WAVES_N, false>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, s);
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N>
 hipError_t launch16_grouped(const void* A, int64_t lda, const void* W, int64_t ldw, int64_t w_group_stride, void* C,
                             int64_t ldc, int N, int K, int epi, const int4* tile_tab, int tile_rows, hipStream_t s) {
-  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, true>;
+  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, true, true>;
   constexpr int lds = NSTAGE * (BM + BN) * BK * 2;
   static bool configured = false;
   if (!configured) {
@@ -1040,7 +896,7 @@ bool gemm_mfma_uses_prefill_tile(int M, int N) {
   return M > 64 && (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 192;
 }
 
-hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc,
+hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc,
                                  const void* R, int64_t ldr, int M, int N, int K, int epi, void* ws, int64_t ws_bytes,
                                  hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
@@ -1056,17 +912,17 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
       bool wide;
       int splits, per;
       small_m_plan(M, N, K, ws_bytes, &wide, &splits, &per);
-      hipError_t e = wide ? launch<64, 128, 1, 4, true>(A, lda, W, ldw, C, ldc, R, ldr, (float*)ws, M, N, K, 0, splits, per, s)
-                          : launch<64, 64, 1, 2, true>(A, lda, W, ldw, C, ldc, R, ldr, (float*)ws, M, N, K, 0, splits, per, s);
+      hipError_t e = wide ? launch<64, 128, 1, 4, true>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, (float*)ws, M, N, K, 0, splits, per, s)
+                          : launch<64, 64, 1, 2, true>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, (float*)ws, M, N, K, 0, splits, per, s);
       if (e != hipSuccess) return e;
       const int64_t quads = (int64_t)M * (N / 8);
       hipLaunchKernelGGL(splitk_reduce_swiglu_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s,
-                         (const float*)ws, (bf16_t*)C, ldc, M, N, splits, (const float*)nullptr, 0, 0.f, 0.f);
+                         (const float*)ws, (bf16_t*)C, ldc, M, N, splits);
       return hipGetLastError();
     }
     if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 192 || variant == 1)
-      return launch16<256, 256, 2, 4>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, s);
-    return launch<128, 128, 2, 2, false, 1>(A, lda, W, ldw, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
+      return launch16<256, 256, 2, 4>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, s);
+    return launch<128, 128, 2, 2, false, 1>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
   }
   // A few hundred token rows: too few 128 x 128 tiles to fill the chip, so K is split over workgroups as on the
   // few-row path (fp32 partial planes, fixed-order reduce); every split gets at least two k-tiles.
@@ -1079,7 +935,7 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
       const int per = (KT + sp - 1) / sp;
       const int splits = (KT + per - 1) / per;
       if (splits > 1) {
-        hipError_t e = launch<128, 128, 2, 2, true, 1>(A, lda, W, ldw, C, ldc, R, ldr, (float*)ws, M, N, K, epi, splits, per, s);
+        hipError_t e = launch<128, 128, 2, 2, true, 1>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, (float*)ws, M, N, K, epi, splits, per, s);
         if (e != hipSuccess) return e;
         const int64_t quads = (int64_t)M * (N / 4);
         hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, (const float*)ws,
@@ -1098,132 +954,34 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
       bool wide;
       int splits, per;
       if (ws && small_m_plan(M, N, K, ws_bytes, &wide, &splits, &per)) {
-        hipError_t e = wide ? launch<64, 128, 1, 4, true>(A, lda, W, ldw, C, ldc, R, ldr, (float*)ws, M, N, K, epi, splits, per, s)
-                            : launch<64, 64, 1, 2, true>(A, lda, W, ldw, C, ldc, R, ldr, (float*)ws, M, N, K, epi, splits, per, s);
+        hipError_t e = wide ? launch<64, 128, 1, 4, true>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, (float*)ws, M, N, K, epi, splits, per, s)
+                            : launch<64, 64, 1, 2, true>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, (float*)ws, M, N, K, epi, splits, per, s);
         if (e != hipSuccess) return e;
         const int64_t quads = (int64_t)M * (N / 4);
         hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, (const float*)ws,
                            C, ldc, R, ldr, M, N, splits, epi);
         return hipGetLastError();
       }
-      return launch<64, 64, 1, 2, false>(A, lda, W, ldw, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
+      return launch<64, 64, 1, 2, false>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
     }
     // the two prefill tilings: the 256x256 tile on the 16x16x32 MFMA (1; large problems are power-limited, and that
     // instruction is the thriftier one) and the 128x128 tile on the 32x32x16 MFMA (2; medium sizes are issue- and
     // latency-bound, where it is 15-30 % faster)
-    case 2: return launch<128, 128, 2, 2, false, 1>(A, lda, W, ldw, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
-    default: return launch16<256, 256, 2, 4>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, s);
+    case 2: return launch<128, 128, 2, 2, false, 1>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
+    default: return launch16<256, 256, 2, 4>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, s);
   }
 }
 
 // Projections of a mixture-of-experts layer over token rows sorted by expert: one launch over all experts, on the
 // 256-row prefill tiling.  tile_tab[0..tile_rows) describes the row tiles and tile_tab[tile_rows] holds their number
 // (see the kernel); rows of A and C are the sorted slots.  epi: EPI_SWIGLU (C bf16 [slots, N/2]) or EPI_C_F32 / EPI_STORE (C [slots, N]); no residual.
-hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const void* W, int64_t ldw,
+hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const void* W, int64_t ldw, int w_blocks,
                                     int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
                                     const void* tile_tab, int tile_rows, hipStream_t s) {
   if (tile_rows <= 0) return hipSuccess;
-  if (K < BK || K % BK || N % 64 || (lda & 7) || (ldw & 7) || (ldc & 3) || (epi & EPI_RESIDUAL)) return hipErrorNotSupported;
+  // (a model the tensor-core path takes has its weights in blocks)
+  if (!w_blocks || K < BK || K % BK || N % 64 || (lda & 7) || (ldw & 7) || (ldc & 3) || (epi & EPI_RESIDUAL)) return hipErrorNotSupported;
   if (a_rows * lda * 2 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 2 >= ((int64_t)1 << 32)) return hipErrorNotSupported;
   return launch16_grouped<256, 256, 2, 4>(A, lda, W, ldw, w_group_stride, C, ldc, N, K, epi, (const int4*)tile_tab,
                                           tile_rows, s);
-}
-
-// ---- few token rows (M <= 64): projection + the step that follows it, in the split-K reduction ----
-
-bool gemm_small_m_fused_supported(int M, int N, int K, int64_t lda, int64_t ldw, int64_t ws_bytes) {
-  if (M < 1 || M > 64 || K < BK || K % BK || N % 4 || (lda & 7) || (ldw & 7)) return false;
-  if ((int64_t)M * lda * 2 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 2 >= ((int64_t)1 << 32)) return false;
-  bool wide;
-  int splits, per;
-  return small_m_plan(M, N, K, ws_bytes, &wide, &splits, &per);
-}
-
-static hipError_t small_m_partials(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, void* ws,
-                                   int64_t ws_bytes, int* splits, hipStream_t s) {
-  if (!ws || !gemm_small_m_fused_supported(M, N, K, lda, ldw, ws_bytes)) return hipErrorNotSupported;
-  bool wide;
-  int per;
-  small_m_plan(M, N, K, ws_bytes, &wide, splits, &per);
-  return wide ? launch<64, 128, 1, 4, true>(A, lda, W, ldw, nullptr, N, nullptr, 0, (float*)ws, M, N, K, 0, *splits, per, s)
-              : launch<64, 64, 1, 2, true>(A, lda, W, ldw, nullptr, N, nullptr, 0, (float*)ws, M, N, K, 0, *splits, per, s);
-}
-
-// The two fused launchers below refuse exactly what these predicates refuse; the layer asks them first and takes
-// the unfused steps (projection, then RoPE / RMSNorm kernel) otherwise.
-bool gemm_small_m_rope_supported(int M, int K, int Hq, int Hkv, int dh, int64_t lda, int64_t ldw, int64_t ldq,
-                                 int64_t ws_bytes) {
-  return dh % 8 == 0 && (ldq & 3) == 0 && gemm_small_m_fused_supported(M, (Hq + 2 * Hkv) * dh, K, lda, ldw, ws_bytes);
-}
-
-bool gemm_small_m_rmsnorm_supported(int M, int d, int K, int64_t lda, int64_t ldw, int64_t ws_bytes) {
-  return d % 4 == 0 && d <= 8192 && gemm_small_m_fused_supported(M, d, K, lda, ldw, ws_bytes);
-}
-
-// qkv projection + RoPE + KV-cache write: N = (Hq + 2 Hkv) dh
-// ssq (optional): the rows of A are x*g of an RMSNorm over K columns without its row factor, ssq [M, K/1024] holds
-// the partial sums of x^2 (splitk_reduce_prescale_kernel), and the factor is applied to the sums here
-hipError_t launch_gemm_small_m_rope(const void* A, int64_t lda, const void* W, int64_t ldw, void* qkv, int64_t ldq,
-                                    const float2* cs, void* k_rows, void* v_rows, int M, int K, int Hq, int Hkv, int dh,
-                                    void* ws, int64_t ws_bytes, const float* ssq, float eps, hipStream_t s) {
-  const int N = (Hq + 2 * Hkv) * dh;
-  if (!ws || !gemm_small_m_rope_supported(M, K, Hq, Hkv, dh, lda, ldw, ldq, ws_bytes)) return hipErrorNotSupported;
-  if (ssq && K % 1024) return hipErrorNotSupported;
-  int splits = 0;
-  hipError_t e = small_m_partials(A, lda, W, ldw, M, N, K, ws, ws_bytes, &splits, s);
-  if (e != hipSuccess) return e;
-  const int64_t units = (int64_t)M * ((Hq + Hkv) * (dh / 8) + Hkv * dh / 4);
-  hipLaunchKernelGGL(splitk_reduce_rope_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s, (const float*)ws,
-                     (bf16_t*)qkv, ldq, cs, (bf16_t*)k_rows, (bf16_t*)v_rows, M, N, splits, Hq, Hkv, dh, ssq, K / 1024,
-                     1.0f / (float)K, eps);
-  return hipGetLastError();
-}
-
-// gate/up projection + SwiGLU over few rows whose input lacks the RMSNorm row factor (see above): act [M, N/2]
-hipError_t launch_gemm_small_m_swiglu_scaled(const void* A, int64_t lda, const void* W, int64_t ldw, void* act, int64_t ldc,
-                                             int M, int N, int K, void* ws, int64_t ws_bytes, const float* ssq, float eps,
-                                             hipStream_t s) {
-  if (!ws || !ssq || K % 1024 || N % 64 || !gemm_small_m_fused_supported(M, N, K, lda, ldw, ws_bytes)) return hipErrorNotSupported;
-  int splits = 0;
-  hipError_t e = small_m_partials(A, lda, W, ldw, M, N, K, ws, ws_bytes, &splits, s);
-  if (e != hipSuccess) return e;
-  const int64_t quads = (int64_t)M * (N / 8);
-  hipLaunchKernelGGL(splitk_reduce_swiglu_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, (const float*)ws,
-                     (bf16_t*)act, ldc, M, N, splits, ssq, K / 1024, 1.0f / (float)K, eps);
-  return hipGetLastError();
-}
-
-// projection + residual, result prepared for an RMSNorm whose row factor the next projection applies:
-// h [M, d] fp32 = x W^T + R, a [M, d] bf16 = h * g, ssq [M, d/1024] partial sums of h^2; d a multiple of 1024
-bool gemm_small_m_prescale_supported(int M, int d, int K, int64_t lda, int64_t ldw, int64_t ws_bytes) {
-  return d % 1024 == 0 && d / 1024 <= DSK_MAX_SSQ_PARTS && gemm_small_m_fused_supported(M, d, K, lda, ldw, ws_bytes);
-}
-
-hipError_t launch_gemm_small_m_prescale(const void* A, int64_t lda, const void* W, int64_t ldw, float* h, const void* R,
-                                        int r_f32, const void* g, void* a, float* ssq, int M, int d, int K, void* ws,
-                                        int64_t ws_bytes, hipStream_t s) {
-  if (!ws || !gemm_small_m_prescale_supported(M, d, K, lda, ldw, ws_bytes)) return hipErrorNotSupported;
-  int splits = 0;
-  hipError_t e = small_m_partials(A, lda, W, ldw, M, d, K, ws, ws_bytes, &splits, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(splitk_reduce_prescale_kernel, dim3((unsigned)(M * (d / 1024))), dim3(256), 0, s, (const float*)ws, h, R,
-                     r_f32, (const bf16_t*)g, (bf16_t*)a, ssq, M, d, splits);
-  return hipGetLastError();
-}
-
-// projection + residual + RMSNorm: h[M, d] (fp32) = x W^T + R, xn[M, d] (bf16) = rmsnorm(h) * g; dense rows
-hipError_t launch_gemm_small_m_rmsnorm(const void* A, int64_t lda, const void* W, int64_t ldw, float* h, const void* R,
-                                       int r_f32, const void* g, void* xn, float eps, int M, int d, int K, void* ws,
-                                       int64_t ws_bytes, hipStream_t s) {
-  if (!ws || !gemm_small_m_rmsnorm_supported(M, d, K, lda, ldw, ws_bytes)) return hipErrorNotSupported;
-  int splits = 0;
-  hipError_t e = small_m_partials(A, lda, W, ldw, M, d, K, ws, ws_bytes, &splits, s);
-  if (e != hipSuccess) return e;
-  if (d <= 4096)
-    hipLaunchKernelGGL(splitk_reduce_rmsnorm_kernel<4>, dim3(M), dim3(256), 0, s, (const float*)ws, h, R, r_f32,
-                       (const bf16_t*)g, (bf16_t*)xn, M, d, splits, eps);
-  else
-    hipLaunchKernelGGL(splitk_reduce_rmsnorm_kernel<8>, dim3(M), dim3(256), 0, s, (const float*)ws, h, R, r_f32,
-                       (const bf16_t*)g, (bf16_t*)xn, M, d, splits, eps);
-  return hipGetLastError();
 }

@@ -11,7 +11,7 @@ constexpr int TM = 64, TN = 64, TK = 16;
 // C[M,N] = A[M,K] * W[N,K]^T (+R).  256 threads, each a 4x4 micro-tile; tiles are zero-padded at the edges.
 template <typename T>
 __global__ void __launch_bounds__(256) gemm_generic_kernel(const T* __restrict__ A, int64_t lda, const T* __restrict__ W,
-                                                           int64_t ldw, void* __restrict__ Cv, int64_t ldc,
+                                                           int64_t ldw, int w_blocks, void* __restrict__ Cv, int64_t ldc,
                                                            const void* __restrict__ Rv, int64_t ldr, int M, int N, int K,
                                                            int epi) {
   __shared__ float sa[TK][TM + 4];
@@ -26,7 +26,7 @@ __global__ void __launch_bounds__(256) gemm_generic_kernel(const T* __restrict__
       int k = k0 + lk + j;
       int m = m0 + lr, n = n0 + lr;
       sa[lk + j][lr] = (m < M && k < K) ? to_f32(A[(int64_t)m * lda + k]) : 0.f;
-      sw[lk + j][lr] = (n < N && k < K) ? to_f32(W[(int64_t)n * ldw + k]) : 0.f;
+      sw[lk + j][lr] = (n < N && k < K) ? to_f32(W[w_blocks ? block_at(n, k, K) : (int64_t)n * ldw + k]) : 0.f;
     }
     __syncthreads();
 #pragma unroll
@@ -130,16 +130,16 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(const T* __restrict__ 
 
 }  // namespace
 
-hipError_t launch_gemm_generic(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc,
-                               const void* R, int64_t ldr, int M, int N, int K, int epi, hipStream_t s) {
+hipError_t launch_gemm_generic(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C,
+                               int64_t ldc, const void* R, int64_t ldr, int M, int N, int K, int epi, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
   dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM);
   if (dtype == DSK_F32)
-    hipLaunchKernelGGL(gemm_generic_kernel<float>, grid, dim3(256), 0, s, (const float*)A, lda, (const float*)W, ldw, C,
+    hipLaunchKernelGGL(gemm_generic_kernel<float>, grid, dim3(256), 0, s, (const float*)A, lda, (const float*)W, ldw, w_blocks, C,
                        ldc, R, ldr, M, N, K, epi);
   else
     hipLaunchKernelGGL(gemm_generic_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)A, lda, (const bf16_t*)W, ldw,
-                       C, ldc, R, ldr, M, N, K, epi);
+                       w_blocks, C, ldc, R, ldr, M, N, K, epi);
   return hipGetLastError();
 }
 

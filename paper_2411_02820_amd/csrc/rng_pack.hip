@@ -55,27 +55,33 @@ __global__ void fill_normal_kernel(T* dst, int64_t n, uint64_t key, float scale,
   for (; i < n; i += stride) dst[i] = from_f32<T>(ih8(key, (uint64_t)(idx0 + i), scale, offset));
 }
 
+__device__ __forceinline__ int64_t packed_at(int map, int gu_block, int64_t row_off, int blocks, int64_t r, int64_t c, int64_t cols) {
+  const int64_t pr = packed_row(map, gu_block, row_off, r);
+  return blocks ? block_at(pr, c, cols) : pr * cols + c;
+}
+
 template <typename T>
-__global__ void fill_weight_kernel(T* packed, int64_t rows, int64_t cols, int map, int gu_block, int64_t row_off,
+__global__ void fill_weight_kernel(T* packed, int64_t rows, int64_t cols, int map, int gu_block, int64_t row_off, int blocks,
                                    uint64_t key, float scale, float offset) {
   int64_t n = rows * cols;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (; i < n; i += stride) {
     int64_t r = i / cols, c = i - r * cols;
-    packed[packed_row(map, gu_block, row_off, r) * cols + c] = from_f32<T>(ih8(key, (uint64_t)i, scale, offset));
+    packed[packed_at(map, gu_block, row_off, blocks, r, c, cols)] = from_f32<T>(ih8(key, (uint64_t)i, scale, offset));
   }
 }
 
-template <typename T>
-__global__ void pack_rows_kernel(T* packed, T* logical, int64_t rows, int64_t cols, int map, int gu_block,
-                                 int64_t row_off, int to_packed) {
-  int64_t n = rows * cols;
+// U: what one thread moves, an element or (rows in whole 16-byte pieces on both sides) eight bf16 at once
+template <typename U, int PER>
+__global__ void pack_rows_kernel(U* packed, U* logical, int64_t rows, int64_t cols, int map, int gu_block,
+                                 int64_t row_off, int blocks, int to_packed) {
+  int64_t n = rows * cols / PER;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (; i < n; i += stride) {
-    int64_t r = i / cols, c = i - r * cols;
-    int64_t p = packed_row(map, gu_block, row_off, r) * cols + c;
+    int64_t r = i * PER / cols, c = i * PER - r * cols;
+    int64_t p = packed_at(map, gu_block, row_off, blocks, r, c, cols) / PER;
     if (to_packed) packed[p] = logical[i];
     else logical[i] = packed[p];
   }
@@ -103,29 +109,32 @@ hipError_t launch_fill_normal(void* dst, int64_t n, uint64_t seed, uint64_t stre
 }
 
 hipError_t launch_fill_weight(int dtype, void* packed, int64_t rows, int64_t cols, int map, int gu_block, int64_t row_off,
-                              uint64_t seed, uint64_t stream_id, float std, float offset, hipStream_t s) {
+                              int blocks, uint64_t seed, uint64_t stream_id, float std, float offset, hipStream_t s) {
   int64_t n = rows * cols;
   if (n <= 0) return hipSuccess;
   uint64_t key = stream_key(seed, stream_id);
   float scale = scale_for_std(std);
   if (dtype == DSK_F32)
     hipLaunchKernelGGL(fill_weight_kernel<float>, dim3(grid_for(n)), dim3(256), 0, s, (float*)packed, rows, cols, map,
-                       gu_block, row_off, key, scale, offset);
+                       gu_block, row_off, blocks, key, scale, offset);
   else
     hipLaunchKernelGGL(fill_weight_kernel<bf16_t>, dim3(grid_for(n)), dim3(256), 0, s, (bf16_t*)packed, rows, cols, map,
-                       gu_block, row_off, key, scale, offset);
+                       gu_block, row_off, blocks, key, scale, offset);
   return hipGetLastError();
 }
 
 hipError_t launch_pack_rows(int dtype, void* packed, const void* logical, int64_t rows, int64_t cols, int map,
-                            int gu_block, int64_t row_off, int to_packed, hipStream_t s) {
+                            int gu_block, int64_t row_off, int blocks, int to_packed, hipStream_t s) {
   int64_t n = rows * cols;
   if (n <= 0) return hipSuccess;
   if (dtype == DSK_F32)
-    hipLaunchKernelGGL(pack_rows_kernel<float>, dim3(grid_for(n)), dim3(256), 0, s, (float*)packed, (float*)logical, rows,
-                       cols, map, gu_block, row_off, to_packed);
+    hipLaunchKernelGGL((pack_rows_kernel<float, 1>), dim3(grid_for(n)), dim3(256), 0, s, (float*)packed, (float*)logical, rows,
+                       cols, map, gu_block, row_off, blocks, to_packed);
+  else if (cols % 8 == 0 && ((uintptr_t)logical & 15) == 0)  // the library's own side is aligned
+    hipLaunchKernelGGL((pack_rows_kernel<int4, 8>), dim3(grid_for(n / 8)), dim3(256), 0, s, (int4*)packed, (int4*)logical, rows,
+                       cols, map, gu_block, row_off, blocks, to_packed);
   else
-    hipLaunchKernelGGL(pack_rows_kernel<bf16_t>, dim3(grid_for(n)), dim3(256), 0, s, (bf16_t*)packed, (bf16_t*)logical,
-                       rows, cols, map, gu_block, row_off, to_packed);
+    hipLaunchKernelGGL((pack_rows_kernel<bf16_t, 1>), dim3(grid_for(n)), dim3(256), 0, s, (bf16_t*)packed, (bf16_t*)logical,
+                       rows, cols, map, gu_block, row_off, blocks, to_packed);
   return hipGetLastError();
 }

@@ -1,0 +1,58 @@
+"""The few-row projections (activations and weights in blocks) at the edges of their tilings: row counts around multiples of
+16, every row tiling, narrow and odd widths, a contraction split over workgroups, against the plain kernels and the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dsk_oracle as O
+from paper_2411_02820_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2411_02820_amd import binding
+    return binding
+
+
+# d = 64 (four sums of squares a row), widths that are odd multiples of 64, dh 64 and 128
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 33, 48, 49, 64])
+@pytest.mark.parametrize("d,Hq,Hkv,dh,F", [(64, 1, 1, 64, 64), (448, 7, 1, 64, 832), (512, 6, 2, 128, 320)])
+def test_layers_over_few_rows_match_the_oracle(B, rows, d, Hq, Hkv, dh, F):
+    from tests import gpu_util as G
+    from tests.helpers import kv_list, oracle_config, weights_fn
+    shape = synth.ModelShape(2, d, Hq, Hkv, dh, F, 10000.0, 1e-5, "bf16")
+    lens = [rows] if rows < 3 else [rows - 2, 2]
+    x = synth.hidden_states(shape, rows)
+    with G.GpuModel(shape, rows) as m:   # the workspace is sized for exactly these rows
+        m.load_from_generator(3)
+        B.dsk_set_option("reset_stats", 0)
+        kv, h = m.partial(G.to_dev(x, shape), 0, 2, None, lens)
+        torch.cuda.synchronize()
+        assert B.dsk_get_stat("gemm_mfma_launches") == 8 and B.dsk_get_stat("gemm_generic_launches") == 0
+        w = m.get_tensor(1, synth.WU)    # blocks and back
+        assert np.array_equal(G.to_np(w), synth.layer_tensor(shape, 3, 1, synth.WU))
+    kv_ref, h_ref = O.partial_prefill(oracle_config(shape), weights_fn(shape, 3), x.astype(np.float64), 0, 2,
+                                      [(None, None)] * 2, synth.packed_positions(lens), synth.cu_seqlens(lens))
+    # the bound of the bf16 path at this weight scale
+    assert O.max_rel_err(G.to_np(h), h_ref) <= 2e-2
+    for l in range(2):
+        assert O.max_rel_err(G.to_np(kv[l, 0]), kv_ref[l][0]) <= 2e-2 and O.max_rel_err(G.to_np(kv[l, 1]), kv_ref[l][1]) <= 2e-2
+
+
+@pytest.mark.parametrize("rows", [40, 64])
+def test_split_contraction_matches_the_unsplit_one(B, rows):
+    # the down projection's 256 column tiles would read 48 or 64 rows of 28672 each, more than 256 MB, so it is split over
+    # workgroups; the same rows one at a time take the unsplit kernel.  The order of fp32 sums differs, and with it now and
+    # then a bf16 rounding (2^-9) of an intermediate: a few of those on the way to a result.
+    from tests import gpu_util as G
+    shape = synth.ModelShape(1, 4096, 32, 8, 128, 28672, 500000.0, 1e-5, "bf16")
+    x = G.to_dev(synth.hidden_states(shape, rows), shape)
+    with G.GpuModel(shape, rows) as m:
+        m.init_random(0)
+        _, h = m.partial(x, 0, 1, None, [1] * rows)
+        singles = [m.partial(x[i:i + 1].contiguous(), 0, 1, None, [1], positions=np.zeros(1, np.int32))[1].clone() for i in (0, 17, rows - 1)]
+        torch.cuda.synchronize()
+    for i, one in zip((0, 17, rows - 1), singles):
+        assert O.max_rel_err(G.to_np(h[i:i + 1]), G.to_np(one).astype(np.float64)) <= 2 ** -6
