@@ -72,19 +72,56 @@ __global__ void fill_weight_kernel(T* packed, int64_t rows, int64_t cols, int ma
   }
 }
 
-// U: what one thread moves, an element or (rows in whole 16-byte pieces on both sides) eight bf16 at once
-template <typename U, int PER>
-__global__ void pack_rows_kernel(U* packed, U* logical, int64_t rows, int64_t cols, int map, int gu_block,
+template <typename T>
+__global__ void pack_rows_kernel(T* packed, T* logical, int64_t rows, int64_t cols, int map, int gu_block,
                                  int64_t row_off, int blocks, int to_packed) {
-  int64_t n = rows * cols / PER;
+  int64_t n = rows * cols;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (; i < n; i += stride) {
-    int64_t r = i * PER / cols, c = i * PER - r * cols;
-    int64_t p = packed_at(map, gu_block, row_off, blocks, r, c, cols) / PER;
+    int64_t r = i / cols, c = i - r * cols;
+    int64_t p = packed_at(map, gu_block, row_off, blocks, r, c, cols);
     if (to_packed) packed[p] = logical[i];
     else logical[i] = packed[p];
   }
+}
+
+// Whole blocks of 16 rows x 32 columns, a wave per block and 16 bytes per lane in the block's order, so that the packed side is
+// one piece of 1 KB and the logical side 16 of 64 bytes.
+__device__ __forceinline__ void block_item(int64_t i, int64_t cols, int64_t* r, int64_t* c) {
+  const int64_t blk = i >> 6, per_row = cols >> 5;
+  *r = blk / per_row * 16 + (i & 15);
+  *c = blk % per_row * 32 + ((i >> 4) & 3) * 8;
+}
+__global__ void pack_blocks_kernel(bf16_t* packed, bf16_t* logical, int64_t rows, int64_t cols, int map, int gu_block, int64_t row_off,
+                                   int to_packed) {
+  const int64_t n = rows * cols / 8, stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    int64_t r, c;
+    block_item(i, cols, &r, &c);
+    int4* p = (int4*)(packed + packed_at(map, gu_block, row_off, 1, r, c, cols));
+    int4* l = (int4*)(logical + r * cols + c);
+    if (to_packed) *p = *l;
+    else *l = *p;
+  }
+}
+__global__ void fill_blocks_kernel(bf16_t* packed, int64_t rows, int64_t cols, int map, int gu_block, int64_t row_off, uint64_t key,
+                                   float scale, float offset) {
+  const int64_t n = rows * cols / 8, stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    int64_t r, c;
+    block_item(i, cols, &r, &c);
+    typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+    bf16x8 v;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (bf16_t)ih8(key, (uint64_t)(r * cols + c + e), scale, offset);
+    *(bf16x8*)(packed + packed_at(map, gu_block, row_off, 1, r, c, cols)) = v;
+  }
+}
+
+// tensors that are whole blocks on the packed side (gate and up rows are interleaved in blocks of gu_block)
+inline bool whole_blocks(int dtype, int blocks, int64_t rows, int64_t row_off, int map, int gu_block) {
+  return dtype == DSK_BF16 && blocks && rows % 16 == 0 && row_off % 16 == 0 && (map == 0 || gu_block % 16 == 0);
 }
 
 inline int grid_for(int64_t n) {
@@ -114,7 +151,10 @@ hipError_t launch_fill_weight(int dtype, void* packed, int64_t rows, int64_t col
   if (n <= 0) return hipSuccess;
   uint64_t key = stream_key(seed, stream_id);
   float scale = scale_for_std(std);
-  if (dtype == DSK_F32)
+  if (whole_blocks(dtype, blocks, rows, row_off, map, gu_block))
+    hipLaunchKernelGGL(fill_blocks_kernel, dim3(grid_for(n / 8)), dim3(256), 0, s, (bf16_t*)packed, rows, cols, map, gu_block, row_off,
+                       key, scale, offset);
+  else if (dtype == DSK_F32)
     hipLaunchKernelGGL(fill_weight_kernel<float>, dim3(grid_for(n)), dim3(256), 0, s, (float*)packed, rows, cols, map,
                        gu_block, row_off, blocks, key, scale, offset);
   else
@@ -127,14 +167,14 @@ hipError_t launch_pack_rows(int dtype, void* packed, const void* logical, int64_
                             int gu_block, int64_t row_off, int blocks, int to_packed, hipStream_t s) {
   int64_t n = rows * cols;
   if (n <= 0) return hipSuccess;
-  if (dtype == DSK_F32)
-    hipLaunchKernelGGL((pack_rows_kernel<float, 1>), dim3(grid_for(n)), dim3(256), 0, s, (float*)packed, (float*)logical, rows,
-                       cols, map, gu_block, row_off, blocks, to_packed);
-  else if (cols % 8 == 0 && ((uintptr_t)logical & 15) == 0)  // the library's own side is aligned
-    hipLaunchKernelGGL((pack_rows_kernel<int4, 8>), dim3(grid_for(n / 8)), dim3(256), 0, s, (int4*)packed, (int4*)logical, rows,
+  if (whole_blocks(dtype, blocks, rows, row_off, map, gu_block) && ((uintptr_t)logical & 15) == 0)
+    hipLaunchKernelGGL(pack_blocks_kernel, dim3(grid_for(n / 8)), dim3(256), 0, s, (bf16_t*)packed, (bf16_t*)logical, rows, cols,
+                       map, gu_block, row_off, to_packed);
+  else if (dtype == DSK_F32)
+    hipLaunchKernelGGL(pack_rows_kernel<float>, dim3(grid_for(n)), dim3(256), 0, s, (float*)packed, (float*)logical, rows,
                        cols, map, gu_block, row_off, blocks, to_packed);
   else
-    hipLaunchKernelGGL((pack_rows_kernel<bf16_t, 1>), dim3(grid_for(n)), dim3(256), 0, s, (bf16_t*)packed, (bf16_t*)logical,
+    hipLaunchKernelGGL(pack_rows_kernel<bf16_t>, dim3(grid_for(n)), dim3(256), 0, s, (bf16_t*)packed, (bf16_t*)logical,
                        rows, cols, map, gu_block, row_off, blocks, to_packed);
   return hipGetLastError();
 }
