@@ -244,8 +244,8 @@ hipError_t attention(const dsk_model* m, const AttnArgs& a, hipStream_t s) { ret
 // The MLP of a mixture-of-experts layer (Sec. 5.4; routing as in Mixtral) over the n normalised rows in m->xn:
 // h_out = h_mid + sum over the token's top_k experts of gate * SwiGLU-MLP_e(xn).  On the tensor-core path with more
 // than 64 rows the (token, expert) pairs are grouped by expert and the two projections run once over all experts;
-// otherwise (few rows: every expert's weights are streamed anyway; fp32 models) every expert runs over all rows and
-// the sum picks the chosen ones.
+// otherwise (fp32 models, "force_generic"; few bf16 rows do not come here) every expert runs over all rows and the sum
+// picks the chosen ones.
 int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, void* h_out, int out_f32, hipStream_t s) {
   const dsk_config_t& c = m->cfg;
   const int d = c.hidden, F = c.ffn, E = c.n_experts, k = c.top_k;
@@ -283,17 +283,11 @@ int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, 
     return DSK_OK;
   }
   if ((int64_t)E * n > m->moe_y_rows) return DSK_EINVAL;
-  const bool fused_swiglu = tensor_cores && m->gu_block == 32 &&
-                            gemm_mfma_swiglu_supported(n, 2 * F, d, m->gemm_ws ? m->gemm_ws_bytes : 0);
   for (int e = 0; e < E; ++e) {
     const char* wgu = (const char*)w.wgu + e * wgu_stride * m->elem;
     const char* wd = (const char*)w.wd + e * wd_stride * m->elem;
-    if (fused_swiglu) {
-      HIP_TRY(gemm(m, m->xn, d, wgu, d, m->act, F, nullptr, 0, n, 2 * F, d, EPI_SWIGLU, s));
-    } else {
-      HIP_TRY(gemm(m, m->xn, d, wgu, d, m->gu, 2 * (int64_t)F, nullptr, 0, n, 2 * F, d, EPI_STORE, s));
-      HIP_TRY(launch_swiglu(c.dtype, m->gu, m->act, n, F, m->gu_block, s));
-    }
+    HIP_TRY(gemm(m, m->xn, d, wgu, d, m->gu, 2 * (int64_t)F, nullptr, 0, n, 2 * F, d, EPI_STORE, s));
+    HIP_TRY(launch_swiglu(c.dtype, m->gu, m->act, n, F, m->gu_block, s));
     HIP_TRY(gemm(m, m->act, F, wd, F, m->moe_y + (int64_t)e * n * d, d, nullptr, 0, n, d, F, EPI_C_F32, s));
   }
   HIP_TRY(launch_moe_combine(m->moe_y, h_mid, m->moe_gates, m->moe_experts, nullptr, h_out, out_f32, n, d, k,
@@ -343,15 +337,16 @@ int run_layer_few(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_o
   int rc = layer_attention(m, k_layer, v_layer, own_row0, q_cu, q_cu_host, p_cu, p_cu_host, n_pre_rows, n_seqs, n, 0, 1, s);
   if (rc) return rc;
   g_stats.gemm_mfma += 2;
-  if (c.n_experts > 0) {  // the router reads normalised rows
-    HIP_TRY(launch_few_residual(m->attn, w.wo, h_in, h_in_f32, m->h, 1, nullptr, nullptr, nullptr, n, d, nq, m->gemm_ws,
-                                m->gemm_ws_bytes, s));
-    HIP_TRY(launch_rmsnorm(c.dtype, m->h, 1, w.g2, m->xn, n, d, eps, s));
-    return run_moe_mlp(m, w, n, m->h, h_out, h_out_f32, s);
-  }
   HIP_TRY(launch_few_residual(m->attn, w.wo, h_in, h_in_f32, m->h, 1, w.g2, m->xn, m->ssq, n, d, nq, m->gemm_ws, m->gemm_ws_bytes, s));
-  HIP_TRY(launch_few_swiglu(m->xn, m->ssq, eps, w.wgu, m->act, n, 2 * F, d, s));
-  HIP_TRY(launch_few_residual(m->act, w.wd, m->h, 1, h_out, h_out_f32, g_next, m->xn, m->ssq, n, d, F, m->gemm_ws, m->gemm_ws_bytes, s));
+  if (c.n_experts > 0) {
+    HIP_TRY(launch_few_route(m->xn, m->ssq, eps, w.wr, m->moe_experts, m->moe_gates, n, d, c.n_experts, c.top_k, s));
+    HIP_TRY(launch_few_experts(m->xn, m->ssq, eps, w.wgu, w.wd, m->act, m->moe_y, m->moe_experts, n, d, F, c.n_experts, c.top_k, s));
+    HIP_TRY(launch_few_combine(m->moe_y, m->moe_experts, m->moe_gates, c.top_k, c.n_experts, m->h, h_out, h_out_f32, g_next, m->xn,
+                               m->ssq, n, d, s));
+  } else {
+    HIP_TRY(launch_few_swiglu(m->xn, m->ssq, eps, w.wgu, m->act, n, 2 * F, d, s));
+    HIP_TRY(launch_few_residual(m->act, w.wd, m->h, 1, h_out, h_out_f32, g_next, m->xn, m->ssq, n, d, F, m->gemm_ws, m->gemm_ws_bytes, s));
+  }
   g_stats.gemm_mfma += 2;
   *left = g_next != nullptr;
   return DSK_OK;
@@ -397,7 +392,7 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
                EPI_RESIDUAL | EPI_C_F32 | ((h_in_f32 || all_f32) ? EPI_R_F32 : 0), s));
   if (!fp32_swiglu) HIP_TRY(launch_rmsnorm(c.dtype, h_mid, 1, w.g2, m->xn, n, d, (float)c.rms_eps, s));
   if (c.n_experts > 0) return run_moe_mlp(m, w, n, h_mid, h_out, h_out_f32 || all_f32, s);
-  if (c.dtype == DSK_BF16 && !g_force_generic && m->gu_block == 32 && gemm_mfma_swiglu_supported(n, 2 * F, d, m->gemm_ws ? m->gemm_ws_bytes : 0)) {
+  if (c.dtype == DSK_BF16 && !g_force_generic && m->gu_block == 32 && gemm_mfma_swiglu_supported(n, 2 * F, d)) {
     HIP_TRY(gemm(m, m->xn, d, w.wgu, d, m->act, F, nullptr, 0, n, 2 * F, d, EPI_SWIGLU, s));  // SwiGLU in the epilogue
   } else if (fp32_swiglu) {
     HIP_TRY(launch_gemm_fp32_norm_swiglu(h_mid, w.g2, (float)c.rms_eps, w.wgu, m->act, n, d, F, m->gu_block, s));
@@ -554,7 +549,9 @@ int dsk_model_create(const dsk_config_t* cfg, int64_t max_tokens, int64_t max_kv
   if (rc == DSK_OK) rc = alloc_dev(&m->gu, T * 2 * F * elem, &m->workspace_bytes);
   // with experts on the tensor-core path the MLP works on top_k rows per token, grouped by expert
   const bool moe_grouped = E > 0 && cfg->dtype == DSK_BF16;
-  if (rc == DSK_OK) rc = alloc_dev(&m->act, T * (moe_grouped ? top_k : 1) * F * elem, &m->workspace_bytes);
+  int64_t act_rows = T * (moe_grouped ? top_k : 1);
+  if (moe_grouped && act_rows < E * (T < 64 ? T : 64)) act_rows = E * (T < 64 ? T : 64);  // few rows: every expert over all of them
+  if (rc == DSK_OK) rc = alloc_dev(&m->act, act_rows * F * elem, &m->workspace_bytes);
   if (rc == DSK_OK && E > 0) {
     m->moe_y_rows = (int64_t)E * T;  // every expert over all rows (few rows, fp32, "force_generic"); grouped: T * top_k
     m->moe_tile_rows = moe_tile_table_rows(T * top_k, E);

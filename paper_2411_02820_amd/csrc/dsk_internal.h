@@ -116,7 +116,7 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
                                  const void* R, int64_t ldr, int M, int N, int K, int epi, void* ws, int64_t ws_bytes,
                                  hipStream_t s);
 int64_t gemm_mfma_workspace_bytes(int max_n);
-bool gemm_mfma_swiglu_supported(int M, int N, int K, int64_t ws_bytes);
+bool gemm_mfma_swiglu_supported(int M, int N, int K);
 // Few token rows (M <= 64, bf16, few_rows.hip): weights and activations in blocks, the step that follows a projection (and
 // the RMSNorm in front of it) done by the projection.  a = bf16(h * gain) in blocks, ssq [d/16][64] its sums of squares.
 bool few_rows_supported(int M, int d, int F, int Hq, int Hkv, int dh);
@@ -130,6 +130,14 @@ hipError_t launch_few_swiglu(const void* a, const float* ssq, float eps, const v
 // C (row-major) = x W^T + R; with gain: a and ssq for the next projection
 hipError_t launch_few_residual(const void* x, const void* W, const void* R, int r_f32, void* C, int c_f32, const void* gain,
                                void* a, float* ssq, int M, int N, int K, void* ws, int64_t ws_bytes, hipStream_t s);
+// expert layers: router on prepared rows, the chosen experts' MLPs (act [E][M up to 16][F] in blocks, y [E][M][d] fp32), their
+// gate-weighted sum on the residual stream
+hipError_t launch_few_route(const void* a, const float* ssq, float eps, const void* wr, int32_t* experts, float* gates, int n,
+                            int d, int E, int top_k, hipStream_t s);
+hipError_t launch_few_experts(const void* a, const float* ssq, float eps, const void* wgu, const void* wd, void* act, float* y,
+                              const int32_t* experts, int M, int d, int F, int E, int top_k, hipStream_t s);
+hipError_t launch_few_combine(const float* y, const int32_t* experts, const float* gates, int top_k, int E, const float* h, void* C,
+                              int c_f32, const void* gain, void* a, float* ssq, int M, int d, hipStream_t s);
 
 // x is fp32 when x_f32 is set, else the model dtype; g and y are the model dtype
 hipError_t launch_rmsnorm(int dtype, const void* x, int x_f32, const void* g, void* y, int T, int d, float eps, hipStream_t s);

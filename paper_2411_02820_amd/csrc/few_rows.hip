@@ -34,7 +34,10 @@ struct StreamArgs {
   const float2* cs; bf16_t* k_rows; bf16_t* v_rows; int Hq, Hkv, dh;
   const void* R; int r_f32; void* C; int c_f32;         // EP_RES: C = sum + R, row-major
   const bf16_t* gain; float* ssq_out;                   // EP_RES: both null when nothing follows
-  float* P;                                             // EP_PART: [splits][M][N]
+  float* P;                                             // EP_PART: [splits][M][N]; experts: [E][M][N]
+  // Expert layers: blockIdx.z is the expert; it is left out when no token has chosen it.  Strides in elements.
+  const int32_t* experts; int n_entries;
+  int64_t x_expert, w_expert, out_expert;
 };
 
 __device__ __forceinline__ bf16x4 to_bf16x4(f32x4 v) {
@@ -84,6 +87,15 @@ __global__ void __launch_bounds__(64 * KW) stream_kernel(StreamArgs p) {
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
   const int kw = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr bool PAIRS = EP == EP_ROPE || EP == EP_SWIGLU;
+  if (p.experts) {
+    bool chosen = false;
+    for (int i = tid; i < p.n_entries; i += 64 * KW) chosen |= p.experts[i] == (int)blockIdx.z;
+    if (!__syncthreads_or(chosen)) return;
+    p.X += blockIdx.z * p.x_expert;
+    p.W += blockIdx.z * p.w_expert;
+    if (EP == EP_PART) p.P += blockIdx.z * p.out_expert;
+    else p.out += blockIdx.z * p.out_expert;
+  }
   const int unit0 = blockIdx.x * (NT / 2);
   const int half = p.dh >> 1, per_head = half >> 4, n_rot = (p.Hq + p.Hkv) * per_head;
   auto col0 = [&](int j) {
@@ -253,8 +265,79 @@ __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restri
   residual_quad<1, 2>(v, m, n, N, in, R, r_f32, C, c_f32, gain, a, ssq_out);
 }
 
+// Router of an expert layer on the prepared rows a (blocks; the RMSNorm factor is applied to the logits), one workgroup per
+// token: eight experts at a time, every thread eight columns of each, sums over the workgroup in a fixed order.  Same
+// rules as the router over rows (moe.hip): fp32 logits, equal ones to the lower expert, NaN last.
+__global__ void __launch_bounds__(256) few_route_kernel(const bf16_t* __restrict__ a, const float* __restrict__ ssq, float eps,
+                                                        const bf16_t* __restrict__ wr, int32_t* __restrict__ experts,
+                                                        float* __restrict__ gates, int d, int E, int top_k) {
+  __shared__ float part[4][9];
+  __shared__ float logit[DSK_MOE_MAX_EXPERTS];
+  const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float ss = 0.f;
+  for (int q = tid; q < d / 16; q += 256) ss += ssq[q * 64 + t];
+  for (int e0 = 0; e0 < E; e0 += 8) {
+    float acc[9] = {};
+    for (int c = tid; c < d / 8; c += 256) {
+      const bf16x8 x = *(const bf16x8*)(a + block_at(t, 8 * c, d));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const bf16x8 w = *(const bf16x8*)(wr + (int64_t)min(e0 + e, E - 1) * d + 8 * c);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc[e] = fmaf((float)x[u], (float)w[u], acc[e]);
+      }
+    }
+    acc[8] = ss;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) acc[e] += __shfl_xor(acc[e], o, 64);
+      if (lane == 0) part[wave][e] = acc[e];
+    }
+    __syncthreads();
+    if (tid < 8 && e0 + tid < E) {
+      const float rs = rsqrtf((part[0][8] + part[1][8] + part[2][8] + part[3][8]) / (float)d + eps);
+      const float v = (part[0][tid] + part[1][tid] + part[2][tid] + part[3][tid]) * rs;
+      logit[e0 + tid] = v == v ? v : -3.0e38f;
+    }
+    __syncthreads();
+  }
+  if (tid != 0) return;
+  float best[DSK_MOE_MAX_TOP_K];
+  float sum = 0.f;
+  for (int j = 0; j < top_k; ++j) {
+    int at = 0;
+    for (int e = 1; e < E; ++e)
+      if (logit[e] > logit[at]) at = e;  // strictly greater: the lower index keeps a tie
+    best[j] = logit[at];
+    logit[at] = -INFINITY;               // below every real entry (a NaN logit counts as -3e38)
+    experts[t * top_k + j] = at;
+    sum += expf(best[j] - best[0]);
+  }
+  const float inv = 1.0f / sum;
+  for (int j = 0; j < top_k; ++j) gates[t * top_k + j] = expf(best[j] - best[0]) * inv;
+}
+
+// C = h + sum_j gates[t][j] * y[experts[t][j]][t], and the next norm's share, as few_residual_kernel
+__global__ void __launch_bounds__(256) few_combine_kernel(const float* __restrict__ y, const int32_t* __restrict__ experts,
+                                                          const float* __restrict__ gates, int top_k, int E, const void* R, void* C,
+                                                          int c_f32, const bf16_t* __restrict__ gain, bf16_t* __restrict__ a,
+                                                          float* __restrict__ ssq_out, int M, int N) {
+  const int i = blockIdx.x * 256 + threadIdx.x, quads = N / 4;
+  const bool in = i < M * quads;
+  const int m = in ? i / quads : 0, n = in ? (i - m * quads) * 4 : 0;
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (in) {
+    for (int j = 0; j < top_k; ++j) {
+      const int e = min(max(experts[m * top_k + j], 0), E - 1);  // always inside y, whatever the table holds
+      v += *(const f32x4*)(y + ((int64_t)e * M + m) * N + n) * gates[m * top_k + j];
+    }
+  }
+  residual_quad<1, 2>(v, m, n, N, in, R, 1, C, c_f32, gain, a, ssq_out);
+}
+
 template <int MT, int NT, int KW, int PF, int KS, int EP>
-hipError_t launch_stream(const StreamArgs& p, int tiles, int splits, hipStream_t s) {
+hipError_t launch_stream(const StreamArgs& p, int tiles, int splits, hipStream_t s, int n_experts = 1) {
   auto kern = stream_kernel<MT, NT, KW, PF, KS, EP>;
   constexpr int lds = KW * MT * NT * 1024 + KW * 256;
   if constexpr (lds > 64 << 10) {
@@ -265,7 +348,7 @@ hipError_t launch_stream(const StreamArgs& p, int tiles, int splits, hipStream_t
       configured = true;
     }
   }
-  hipLaunchKernelGGL(kern, dim3(tiles, splits), dim3(64 * KW), lds, s, p);
+  hipLaunchKernelGGL(kern, dim3(tiles, splits, n_experts), dim3(64 * KW), lds, s, p);
   return hipGetLastError();
 }
 
@@ -349,4 +432,48 @@ hipError_t launch_few_residual(const void* x, const void* W, const void* R, int 
     case 3: return launch_stream<3, 1, 8, 2, 2, EP_RES>(p, N / 16, 1, s);
     default: return launch_stream<4, 1, 8, 2, 2, EP_RES>(p, N / 16, 1, s);
   }
+}
+
+hipError_t launch_few_route(const void* a, const float* ssq, float eps, const void* wr, int32_t* experts, float* gates, int n,
+                            int d, int E, int top_k, hipStream_t s) {
+  if (E < 1 || E > DSK_MOE_MAX_EXPERTS || top_k < 1 || top_k > DSK_MOE_MAX_TOP_K || top_k > E) return hipErrorNotSupported;
+  hipLaunchKernelGGL(few_route_kernel, dim3(n), dim3(256), 0, s, (const bf16_t*)a, ssq, eps, (const bf16_t*)wr, experts, gates, d,
+                     E, top_k);
+  return hipGetLastError();
+}
+
+// The expert MLPs over all rows (a few rows hit most experts, and what it costs is the weights): one launch per projection
+// over every expert that some token has chosen (Mixtral width, 64 rows: 407 + 176 us for 2.8 GB; expert by expert with a
+// reduction behind each, 32 launches, 730 us; one row streams two experts of the eight).  act: [E][rows up to 16][F] in
+// blocks; y: [E][M][d].
+hipError_t launch_few_experts(const void* a, const float* ssq, float eps, const void* wgu, const void* wd, void* act, float* y,
+                              const int32_t* experts, int M, int d, int F, int E, int top_k, hipStream_t s) {
+  StreamArgs p = {};
+  p.X = (const bf16_t*)a; p.W = (const bf16_t*)wgu; p.M = M; p.N = 2 * F; p.K = d; p.ssq = ssq; p.eps = eps; p.out = (bf16_t*)act;
+  p.experts = experts; p.n_entries = M * top_k;
+  p.w_expert = 2 * (int64_t)F * d; p.out_expert = (int64_t)(M + 15) / 16 * 16 * F;
+  hipError_t e;
+  switch ((M + 15) / 16) {
+    case 1: e = launch_stream<1, 2, 8, 2, 2, EP_SWIGLU>(p, p.N / 32, 1, s, E); break;
+    case 2: e = launch_stream<2, 2, 8, 2, 2, EP_SWIGLU>(p, p.N / 32, 1, s, E); break;
+    case 3: e = launch_stream<3, 8, 4, 1, 1, EP_SWIGLU>(p, p.N / 128, 1, s, E); break;
+    default: e = launch_stream<4, 8, 4, 1, 1, EP_SWIGLU>(p, p.N / 128, 1, s, E); break;
+  }
+  if (e != hipSuccess) return e;
+  p.X = (const bf16_t*)act; p.x_expert = p.out_expert;
+  p.W = (const bf16_t*)wd; p.w_expert = (int64_t)d * F;
+  p.N = d; p.K = F; p.P = y; p.out_expert = (int64_t)M * d;
+  switch ((M + 15) / 16) {
+    case 1: return launch_stream<1, 1, 8, 2, 2, EP_PART>(p, d / 16, 1, s, E);
+    case 2: return launch_stream<2, 2, 8, 2, 2, EP_PART>(p, d / 32, 1, s, E);
+    case 3: return launch_stream<3, 4, 8, 2, 1, EP_PART>(p, d / 64, 1, s, E);
+    default: return launch_stream<4, 4, 8, 2, 1, EP_PART>(p, d / 64, 1, s, E);
+  }
+}
+
+hipError_t launch_few_combine(const float* y, const int32_t* experts, const float* gates, int top_k, int E, const float* h, void* C,
+                              int c_f32, const void* gain, void* a, float* ssq, int M, int d, hipStream_t s) {
+  hipLaunchKernelGGL(few_combine_kernel, dim3((M * (d / 4) + 255) / 256), dim3(256), 0, s, y, experts, gates, top_k, E,
+                     (const void*)h, C, c_f32, (const bf16_t*)gain, (bf16_t*)a, ssq, M, d);
+  return hipGetLastError();
 }

@@ -697,7 +697,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 
 // Sum over the K splits of the quads at P + k * stride, k = 0 .. splits-1, added in split order.  The reductions are
 // short chains of dependent steps on little data: what they take is round trips to memory, so the loads of four
-// splits (of two columns at once in the second form) are requested together.
+// splits are requested together.
 __device__ __forceinline__ f32x4 sum_splits(const float* __restrict__ p, int64_t stride, int splits) {
   f32x4 a = *(const f32x4*)p;
   int k = 1;
@@ -719,42 +719,6 @@ __device__ __forceinline__ f32x4 sum_splits(const float* __restrict__ p, int64_t
   }
   return a;
 }
-__device__ __forceinline__ void sum_splits2(const float* __restrict__ p, const float* __restrict__ q, int64_t stride,
-                                            int splits, f32x4* a_out, f32x4* c_out) {
-  f32x4 a = *(const f32x4*)p, c = *(const f32x4*)q;
-  int k = 1;
-  for (; k + 3 < splits; k += 4) {
-    f32x4 b[4], d[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      b[u] = *(const f32x4*)(p + (k + u) * stride);
-      d[u] = *(const f32x4*)(q + (k + u) * stride);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      a += b[u];
-      c += d[u];
-    }
-  }
-  {
-    f32x4 b[3], d[3];
-#pragma unroll
-    for (int u = 0; u < 3; ++u)
-      if (k + u < splits) {
-        b[u] = *(const f32x4*)(p + (k + u) * stride);
-        d[u] = *(const f32x4*)(q + (k + u) * stride);
-      }
-#pragma unroll
-    for (int u = 0; u < 3; ++u)
-      if (k + u < splits) {
-        a += b[u];
-        c += d[u];
-      }
-  }
-  *a_out = a;
-  *c_out = c;
-}
-
 // C[m][n] = bf16( sum_s P[s][m][n] (+ R[m][n]) ), the partials added in split order.
 __global__ void __launch_bounds__(256) splitk_reduce_kernel(const float* __restrict__ P, void* __restrict__ C, int64_t ldc,
                                                             const void* __restrict__ R, int64_t ldr, int M, int N,
@@ -765,28 +729,6 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const float* __restr
   const int m = (int)(i / (N / 4)), n = (int)(i - (int64_t)m * (N / 4)) * 4;
   const f32x4 s = sum_splits(P + (int64_t)m * N + n, (int64_t)M * N, splits);
   store_quad(C, ldc, R, ldr, m, n, s, epi);
-}
-
-// The same for the gate/up projection, with SwiGLU applied to the sums: act[m][f] = silu(gate) * up, where gate
-// column f sits at packed column (f/32)*64 + f%32 of P and its up column 32 further (rows of W interleaved in
-// blocks of 32).  N = 2F columns in P, F columns in act.
-__global__ void __launch_bounds__(256) splitk_reduce_swiglu_kernel(const float* __restrict__ P, bf16_t* __restrict__ act,
-                                                                   int64_t ldc, int M, int N, int splits) {
-  const int F = N / 2;
-  const int64_t quads = (int64_t)M * (F / 4);
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= quads) return;
-  const int m = (int)(i / (F / 4)), f = (int)(i - (int64_t)m * (F / 4)) * 4;
-  const int pg = (f / 32) * 64 + f % 32;
-  f32x4 g, u;
-  sum_splits2(P + (int64_t)m * N + pg, P + (int64_t)m * N + pg + 32, (int64_t)M * N, splits, &g, &u);
-  bf16x4 o;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g[e]));
-    o[e] = (bf16_t)(g[e] * sig * u[e]);
-  }
-  *(bf16x4*)(act + (int64_t)m * ldc + f) = o;
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool PARTIAL, int SCHED, bool WB>
@@ -877,15 +819,8 @@ static bool small_m_plan(int M, int N, int K, int64_t ws_bytes, bool* wide, int*
   return *splits > 1 && (int64_t)*splits * M * N * 4 <= ws_bytes;
 }
 
-// The fused gate/up epilogue needs whole 64-column gate/up blocks; over few token rows it is applied by the
-// split-K reduction, so there it needs the K-split path.
-bool gemm_mfma_swiglu_supported(int M, int N, int K, int64_t ws_bytes) {
-  if (N % 64 != 0 || K < BK || K % BK != 0) return false;
-  if (M > 64) return true;
-  bool wide;
-  int splits, per;
-  return small_m_plan(M, N, K, ws_bytes, &wide, &splits, &per);
-}
+// The fused gate/up epilogue needs whole 64-column gate/up blocks (few rows have kernels of their own, few_rows.hip).
+bool gemm_mfma_swiglu_supported(int M, int N, int K) { return M > 64 && N % 64 == 0 && K >= BK && K % BK == 0; }
 
 // 64 token rows x (splits x N) floats: about 768 tiles of 64 columns (+ one more split's worth) for the 64x64
 // tiling, up to 4 splits of a wide N for the 64x128 tiling
@@ -907,19 +842,7 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
   const int KT = K / BK;
   int variant = g_variant;
   if (epi & EPI_SWIGLU) {
-    if (!gemm_mfma_swiglu_supported(M, N, K, ws ? ws_bytes : 0)) return hipErrorNotSupported;
-    if (M <= 64) {
-      bool wide;
-      int splits, per;
-      small_m_plan(M, N, K, ws_bytes, &wide, &splits, &per);
-      hipError_t e = wide ? launch<64, 128, 1, 4, true>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, (float*)ws, M, N, K, 0, splits, per, s)
-                          : launch<64, 64, 1, 2, true>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, (float*)ws, M, N, K, 0, splits, per, s);
-      if (e != hipSuccess) return e;
-      const int64_t quads = (int64_t)M * (N / 8);
-      hipLaunchKernelGGL(splitk_reduce_swiglu_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s,
-                         (const float*)ws, (bf16_t*)C, ldc, M, N, splits);
-      return hipGetLastError();
-    }
+    if (!gemm_mfma_swiglu_supported(M, N, K)) return hipErrorNotSupported;
     if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 192 || variant == 1)
       return launch16<256, 256, 2, 4>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, s);
     return launch<128, 128, 2, 2, false, 1>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);

@@ -56,3 +56,29 @@ def test_split_contraction_matches_the_unsplit_one(B, rows):
         torch.cuda.synchronize()
     for i, one in zip((0, 17, rows - 1), singles):
         assert O.max_rel_err(G.to_np(h[i:i + 1]), G.to_np(one).astype(np.float64)) <= 2 ** -6
+
+
+# experts without a token (9 choices over 64 experts, a single token), one choice, several tokens, row tilings 1 to 4; an
+# expert count that is no multiple of the router's eight
+@pytest.mark.parametrize("rows,E,k", [(1, 8, 2), (3, 64, 3), (17, 5, 1), (40, 9, 4), (64, 8, 2)])
+def test_expert_layers_over_few_rows_match_the_plain_kernels(B, rows, E, k):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(1, 320, 5, 1, 64, 192, 10000.0, 1e-5, "bf16", E, k)
+    with G.GpuModel(shape, rows) as m:
+        m.init_random(5, std=0.05)
+        # a part along one router row per token, so that the choice of experts does not hang on rounding
+        wr = G.to_np(m.get_tensor(0, synth.WR))
+        x = synth.hidden_states(shape, rows)
+        for j in range(k):
+            x += (9.0 - 1.5 * j) * wr[(np.arange(rows) * 3 + 5 * j) % E] / np.linalg.norm(wr, axis=1).mean()
+        x = G.to_dev(x, shape)
+        kv, h = m.partial(x, 0, 1, None, [rows])
+        B.dsk_set_option("force_generic", 1)
+        try:
+            kv_ref, h_ref = m.partial(x, 0, 1, None, [rows])
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("force_generic", 0)
+    # two bf16 evaluations of one layer: each within 1e-2 of the exact one at this weight scale
+    assert O.max_rel_err(G.to_np(h), G.to_np(h_ref).astype(np.float64)) <= 2e-2
+    assert O.max_rel_err(G.to_np(kv[0]), G.to_np(kv_ref[0]).astype(np.float64)) <= 2e-2
