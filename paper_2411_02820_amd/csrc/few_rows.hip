@@ -80,7 +80,7 @@ __device__ __forceinline__ void residual_quad(f32x4 v, int m, int n, int N, bool
 // take their column blocks in pairs that a lane combines: the halves (i, i + dh/2) of a head, or gate and up (packed in
 // blocks of 32 rows each).
 template <int MT, int NT, int KW, int PF, int KS, int EP>
-__global__ void __launch_bounds__(64 * KW) stream_kernel(StreamArgs p) {
+__global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   f32x4* red = (f32x4*)smem_raw;                          // [KW][MT * NT][64]
   f32x4* red_ss = red + KW * MT * NT * 64;                // [KW][16]: sums of squares of rows 4 * i ..
@@ -397,7 +397,7 @@ hipError_t launch_few_qkv(const void* a, const float* ssq, float eps, const void
 }
 
 // 32 rows and fewer: 32-column tiles; more: 128-column tiles (224 workgroups at the 8B width), which read the activations
-// a quarter as often (64 rows, 8B shape: 42.6 us against 57 us)
+// a quarter as often (64 rows, 8B shape: 45 us against 57 us; with one step in flight instead of two 50 us)
 hipError_t launch_few_swiglu(const void* a, const float* ssq, float eps, const void* W, void* act, int M, int N, int K,
                              hipStream_t s) {
   StreamArgs p = {};
@@ -405,8 +405,8 @@ hipError_t launch_few_swiglu(const void* a, const float* ssq, float eps, const v
   switch ((M + 15) / 16) {
     case 1: return launch_stream<1, 2, 8, 2, 2, EP_SWIGLU>(p, N / 32, 1, s);
     case 2: return launch_stream<2, 2, 8, 2, 2, EP_SWIGLU>(p, N / 32, 1, s);
-    case 3: return launch_stream<3, 8, 4, 1, 1, EP_SWIGLU>(p, N / 128, 1, s);
-    default: return launch_stream<4, 8, 4, 1, 1, EP_SWIGLU>(p, N / 128, 1, s);
+    case 3: return launch_stream<3, 8, 4, 2, 1, EP_SWIGLU>(p, N / 128, 1, s);
+    default: return launch_stream<4, 8, 4, 2, 1, EP_SWIGLU>(p, N / 128, 1, s);
   }
 }
 
@@ -456,8 +456,8 @@ hipError_t launch_few_experts(const void* a, const float* ssq, float eps, const 
   switch ((M + 15) / 16) {
     case 1: e = launch_stream<1, 2, 8, 2, 2, EP_SWIGLU>(p, p.N / 32, 1, s, E); break;
     case 2: e = launch_stream<2, 2, 8, 2, 2, EP_SWIGLU>(p, p.N / 32, 1, s, E); break;
-    case 3: e = launch_stream<3, 8, 4, 1, 1, EP_SWIGLU>(p, p.N / 128, 1, s, E); break;
-    default: e = launch_stream<4, 8, 4, 1, 1, EP_SWIGLU>(p, p.N / 128, 1, s, E); break;
+    case 3: e = launch_stream<3, 8, 4, 2, 1, EP_SWIGLU>(p, p.N / 128, 1, s, E); break;
+    default: e = launch_stream<4, 8, 4, 2, 1, EP_SWIGLU>(p, p.N / 128, 1, s, E); break;
   }
   if (e != hipSuccess) return e;
   p.X = (const bf16_t*)act; p.x_expert = p.out_expert;
