@@ -48,12 +48,9 @@ struct AttnParams {
 // MFMA row of key offset u inside a 64-key tile: bits 2 and 3 swapped (an involution)
 __device__ __forceinline__ int perm_key(int u) { return (u & ~0xC) | ((u & 4) << 1) | ((u & 8) >> 1); }
 
-// PACK (few queries per sequence, several q heads per kv head): the NW waves of a workgroup take the same 32
-// query rows of NW different q heads of one kv group instead of 32*NW rows of one head, so that no wave idles on
-// rows past the end of a short sequence and the K / Vt tiles of the group are loaded once for NW heads.
-template <int DH, bool SPLIT, int NW, bool PACK = false>
+template <int DH, bool SPLIT, int NW>
 __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p) {
-  constexpr int BQ = PACK ? 32 : 32 * NW;  // query rows per workgroup: 32 per wave
+  constexpr int BQ = 32 * NW;  // query rows per workgroup: 32 per wave
   constexpr int KCH = DH / 8;             // 16-byte slots per K row
   constexpr int K_RPI = 64 / KCH;         // K rows per wave load instruction
   constexpr int K_INST = BKV / K_RPI / NW; // per wave
@@ -72,12 +69,7 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
   //      that is a multiple of 8 each XCD serves a fixed eighth of the heads, so the q heads of one kv group
   //      read their K and Vt through the same L2. ----
   int h, rank;
-  if (PACK) {
-    const int quads = p.Hq / NW;  // groups of NW q heads, all within one kv group (the host checks (Hq/Hkv) % NW == 0)
-    const int L = blockIdx.x;
-    h = (L % quads) * NW + wave;
-    rank = L / quads;
-  } else {
+  {
     const int L = blockIdx.x;
     if ((p.Hq & 7) == 0) {
       const int hpx = p.Hq >> 3, j = L >> 3;
@@ -103,7 +95,7 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
   }
   const int q0 = seq_begin + tile * BQ;  // first query row (packed index) of this workgroup
   if (q0 >= seq_end) return;              // cannot happen for a well-formed grid
-  const int qw0 = PACK ? q0 : q0 + 32 * wave;  // first query row of this wave
+  const int qw0 = q0 + 32 * wave;  // first query row of this wave
   const bool wave_active = qw0 < seq_end;
   const int qi = min(qw0 + lq, seq_end - 1);  // this lane's query (clamped for the padding rows)
 
@@ -360,8 +352,6 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
 #pragma unroll
     for (int r = 0; r < 16; ++r) s_a[kt][r] = s_b[kt][r] = 0.f;
   if (it_begin < it_end) {
-    // (A four-stage ring for the packed few-query launch, where a workgroup has a compute unit to itself and next to
-    // no arithmetic per tile, was measured: 23.8 us per launch against 21.2 us with two stages; not kept.)
     // the first two K tiles and the first Vt tile are requested together, behind the Q fragments, and waited for
     // once: one round trip to memory at the start of a workgroup instead of two (the wait is for everything: the
     // compiler's own count for the Q fragments cannot see the direct-to-LDS loads, so a partial wait would be turned
@@ -570,9 +560,9 @@ hipError_t launch_transpose_v(const void* v_rows, void* vt, int64_t ldvt, int wi
   return hipGetLastError();
 }
 
-template <int DH, bool SPLIT, int NW, bool PACK = false>
+template <int DH, bool SPLIT, int NW>
 hipError_t launch_attn(const AttnParams& p, dim3 grid, hipStream_t s) {
-  auto kern = attn_bf16_kernel<DH, SPLIT, NW, PACK>;
+  auto kern = attn_bf16_kernel<DH, SPLIT, NW>;
   constexpr int lds = (2 * BKV * DH + 2 * DH * BKV) * 2;
   static bool configured = false;
   if (!configured) {
@@ -584,8 +574,34 @@ hipError_t launch_attn(const AttnParams& p, dim3 grid, hipStream_t s) {
   return hipGetLastError();
 }
 
+hipError_t launch_attn_combine(const float* part_o, const float* part_ml, void* out, int out_blocks, int n_q, int Hq, int dh,
+                               int splits, float c, hipStream_t s) {
+  const dim3 grid(n_q, Hq);
+  bf16_t* o = (bf16_t*)out;
+  if (dh == 128 && splits <= 16)
+    hipLaunchKernelGGL((attn_combine_batched_kernel<128, 16>), grid, dim3(64), 0, s, part_o, part_ml, o, out_blocks, Hq, splits, c);
+  else if (dh == 128 && splits <= 32)
+    hipLaunchKernelGGL((attn_combine_batched_kernel<128, 32>), grid, dim3(64), 0, s, part_o, part_ml, o, out_blocks, Hq, splits, c);
+  else if (dh == 128)
+    hipLaunchKernelGGL(attn_combine_kernel<128>, grid, dim3(64), 0, s, part_o, part_ml, o, out_blocks, Hq, splits, c);
+  else if (splits <= 32)
+    hipLaunchKernelGGL((attn_combine_batched_kernel<64, 32>), grid, dim3(64), 0, s, part_o, part_ml, o, out_blocks, Hq, splits, c);
+  else
+    hipLaunchKernelGGL(attn_combine_kernel<64>, grid, dim3(64), 0, s, part_o, part_ml, o, out_blocks, Hq, splits, c);
+  return hipGetLastError();
+}
+
 hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s) {
   if (a.n_q <= 0) return hipSuccess;
+  if (attn_few_supported(a)) {
+    int splits = 1;
+    hipError_t e = launch_attn_few(a, &splits, s);
+    if (e == hipSuccess && splits > 1) {
+      ++g_split_launches;
+      ++g_packed_launches;
+    }
+    return e;
+  }
   if ((a.dh != 128 && a.dh != 64) || !a.vt || (a.ldq & 7) || a.own_row0 + a.n_q >= ((int64_t)1 << 31))
     return hipErrorNotSupported;
   // per-lane tile offsets are 32-bit byte offsets
@@ -605,39 +621,26 @@ hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s) {
   };
   constexpr int nw = 4;
   int64_t max_keys = 0;
-  int max_len = 0;
   for (int b = 0; b < a.n_seqs; ++b) {
     const int len = a.q_cu_host[b + 1] - a.q_cu_host[b];
     int64_t keys = len + (a.p_cu_host ? a.p_cu_host[b + 1] - a.p_cu_host[b] : 0);
     if (keys > max_keys) max_keys = keys;
-    if (len > max_len) max_len = len;
   }
-  // sequences of at most 64 queries would leave half of a 128-row workgroup idle: there the four waves take four
-  // q heads of a kv group and 32 rows each (the key-split path only; needs four heads per kv group)
-  // (Eight waves per packed workgroup, two 32-row tiles of the four heads sharing the K / Vt tiles, with twice the
-  // splits to keep 256 workgroups: 5.53 against 5.33 ms for the 8B suffix pass of 64 tokens; not kept.)
-  bool pack = a.ws && a.dh == 128 && max_len <= 64 && (a.Hq / a.Hkv) % nw == 0;
   p.c = (float)(1.4426950408889634 / sqrt((double)a.dh));
   p.k_row_max = (int)(a.own_row0 + a.n_q - 1);
   const int key_tiles = (int)((max_keys + BKV - 1) / BKV) + 1;
-  int total = 0, splits = 1;
-  int64_t blocks = 0;
-  for (;;) {
-    total = (int)count_tiles(pack ? 32 : 32 * nw);
-    blocks = pack ? (int64_t)total * (a.Hq / nw) : (int64_t)total * a.Hq;
-    // split the key tiles when the grid alone cannot fill the chip
-    splits = 1;
-    if (a.ws && blocks < 512 && key_tiles >= 8) {
-      // about two workgroups per CU; measured on 64 queries against 8k and 16k keys: 16 splits beat 8 and 32
-      // (more splits pay more for partial outputs and the per-workgroup start-up than they gain in parallelism)
-      splits = (int)(((pack ? 256 : 512) + blocks - 1) / blocks);
-      if (splits > key_tiles / 4) splits = key_tiles / 4;
-      while (splits > 1 && ((int64_t)a.n_q * splits > kMaxSplitRows ||
-                            (int64_t)a.n_q * splits * a.Hq * (a.dh + 2) * 4 > a.ws_bytes))
-        --splits;
-    }
-    if (pack && splits <= 1) { pack = false; continue; }  // the packed mapping exists for the key-split kernel only
-    break;
+  const int total = (int)count_tiles(32 * nw);
+  const int64_t blocks = (int64_t)total * a.Hq;
+  // split the key tiles when the grid alone cannot fill the chip
+  int splits = 1;
+  if (a.ws && blocks < 512 && key_tiles >= 8) {
+    // about two workgroups per CU; measured on 64 queries against 8k and 16k keys: 16 splits beat 8 and 32
+    // (more splits pay more for partial outputs and the per-workgroup start-up than they gain in parallelism)
+    splits = (int)((512 + blocks - 1) / blocks);
+    if (splits > key_tiles / 4) splits = key_tiles / 4;
+    while (splits > 1 && ((int64_t)a.n_q * splits > kMaxSplitRows ||
+                          (int64_t)a.n_q * splits * a.Hq * (a.dh + 2) * 4 > a.ws_bytes))
+      --splits;
   }
   p.total_tiles = total;
   p.splits = splits;
@@ -648,22 +651,9 @@ hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s) {
     p.part_ml = p.part_o + (int64_t)a.n_q * a.Hq * splits * a.dh;
     dim3 grid((unsigned)blocks, 1, splits);
     ++g_split_launches;
-    if (pack) ++g_packed_launches;
-    hipError_t e = pack ? launch_attn<128, true, 4, true>(p, grid, s)
-                        : a.dh == 128 ? launch_attn<128, true, 4>(p, grid, s) : launch_attn<64, true, 4>(p, grid, s);
+    hipError_t e = a.dh == 128 ? launch_attn<128, true, 4>(p, grid, s) : launch_attn<64, true, 4>(p, grid, s);
     if (e != hipSuccess) return e;
-    dim3 cgrid(a.n_q, a.Hq);
-    if (a.dh == 128 && splits <= 16)
-      hipLaunchKernelGGL((attn_combine_batched_kernel<128, 16>), cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.out_blocks, a.Hq, splits, p.c);
-    else if (a.dh == 128 && splits <= 32)
-      hipLaunchKernelGGL((attn_combine_batched_kernel<128, 32>), cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.out_blocks, a.Hq, splits, p.c);
-    else if (a.dh == 128)
-      hipLaunchKernelGGL(attn_combine_kernel<128>, cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.out_blocks, a.Hq, splits, p.c);
-    else if (splits <= 32)
-      hipLaunchKernelGGL((attn_combine_batched_kernel<64, 32>), cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.out_blocks, a.Hq, splits, p.c);
-    else
-      hipLaunchKernelGGL(attn_combine_kernel<64>, cgrid, dim3(64), 0, s, p.part_o, p.part_ml, p.out, a.out_blocks, a.Hq, splits, p.c);
-    return hipGetLastError();
+    return launch_attn_combine(p.part_o, p.part_ml, p.out, a.out_blocks, a.n_q, a.Hq, a.dh, splits, p.c, s);
   }
   dim3 grid((unsigned)total * a.Hq);
   return a.dh == 128 ? launch_attn<128, false, 4>(p, grid, s) : launch_attn<64, false, 4>(p, grid, s);

@@ -307,7 +307,8 @@ int layer_attention(dsk_model* m, char* k_layer, char* v_layer, int64_t own_row0
   a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.dh = c.head_dim;
   a.vt = nullptr; a.ldvt = 0;
   if (m->vt && !g_force_generic) {
-    HIP_TRY(launch_transpose_v(v_layer, m->vt, m->ldvt, c.n_kv_heads * c.head_dim, n_pre_rows, own_row0, n, vt_first_row, s));
+    if (!attn_few_supported(a))
+      HIP_TRY(launch_transpose_v(v_layer, m->vt, m->ldvt, c.n_kv_heads * c.head_dim, n_pre_rows, own_row0, n, vt_first_row, s));
     a.vt = m->vt; a.ldvt = m->ldvt;
   }
   HIP_TRY(attention(m, a, s));
@@ -1046,8 +1047,9 @@ int dsk_attention(int dtype, const void* q, const void* k_rows, const void* v_ro
   if (dtype == DSK_BF16 && !g_force_generic && scratch) {
     // the caller asked for the tensor-core kernel: a shape it does not handle is an error, not a slower kernel
     if (kvw % 64 || (head_dim != 64 && head_dim != 128) || scratch_bytes < kvw * rows64 * 2) return DSK_ESHAPE;
-    HIP_TRY(launch_transpose_v(v_rows, scratch, rows64, (int)kvw, prefix ? prefix->n_tokens : 0, own_row0,
-                               queries->n_tokens, 0, (hipStream_t)stream));
+    if (!attn_few_supported(a))
+      HIP_TRY(launch_transpose_v(v_rows, scratch, rows64, (int)kvw, prefix ? prefix->n_tokens : 0, own_row0,
+                                 queries->n_tokens, 0, (hipStream_t)stream));
     a.vt = scratch; a.ldvt = rows64;
   }
   HIP_TRY(attention_any(dtype, a, (hipStream_t)stream));

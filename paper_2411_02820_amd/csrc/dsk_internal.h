@@ -175,7 +175,7 @@ struct AttnArgs {
   void* out;
   const int32_t* q_cu; const int32_t* p_cu; const int32_t* q_cu_host; const int32_t* p_cu_host; int n_seqs;
   int64_t own_row0; int n_q; int Hq, Hkv, dh;
-  const void* vt; int64_t ldvt;  // transposed V (see launch_transpose_v); NULL: not available
+  const void* vt; int64_t ldvt;  // transposed V (see launch_transpose_v; not read where attn_few_supported); NULL: not available
   int out_blocks = 0;            // out in blocks (block_at, Hq*dh columns) instead of rows
   void* ws; int64_t ws_bytes;    // fp32 scratch for key-split partial results (attn_mfma_workspace_bytes); optional
 };
@@ -183,6 +183,12 @@ bool attn_fp32_supported(const AttnArgs& a);
 hipError_t launch_attn_fp32(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_generic(int dtype, const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s);
+// Few queries per sequence (attn_few.hip; launch_attn_mfma_bf16 hands such calls over): no transposed V needed.
+bool attn_few_supported(const AttnArgs& a);
+hipError_t launch_attn_few(const AttnArgs& a, int* splits, hipStream_t s);
+// merges key-split partial results [n_q][Hq][splits][dh] / [..][2]
+hipError_t launch_attn_combine(const float* part_o, const float* part_ml, void* out, int out_blocks, int n_q, int Hq, int dh,
+                               int splits, float c, hipStream_t s);
 int64_t attn_mfma_workspace_bytes(int Hq, int dh);
 // vt[(c)*ldvt + row] = v_rows[row][c] for valid rows (row < n_pre or own_row0 <= row < own_row0+n_own), 0 otherwise,
 // over the whole 64-row tiles from the one that holds first_row up to own_row0+n_own (earlier tiles of vt are left as

@@ -1,0 +1,64 @@
+"""Attention of few queries against a long cache at the edges of its tilings, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dsk_oracle as O
+from paper_2411_02820_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2411_02820_amd import binding
+    return binding
+
+
+# columns (queries x heads of a group) on both sides of 16, 64 and 128; one, three (no power of two) and eight heads per
+# group; keys on both sides of a 32-key step and of a stage, key ranges cut through prefix and own rows; ragged
+# sequences; through a model, so that the key split has its workspace and the result goes out in blocks or rows
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(4, 1), (2, 2), (6, 2), (16, 2)])
+@pytest.mark.parametrize("lens,plens", [([1], [31]), ([4], [4000]), ([5], [700]), ([16], [95]), ([17, 1], [300, 1500]),
+                                        ([33], [1000]), ([64, 64], [129, 640])])
+def test_attention_few_queries(B, Hq, Hkv, dh, lens, plens):
+    from tests import gpu_util as G
+    from tests.helpers import kv_list, oracle_config, weights_fn
+    shape = synth.ModelShape(1, 128, Hq, Hkv, dh, 128, 10000.0, 1e-5, "bf16")
+    T, S = sum(plens), sum(lens)
+    kv = synth.kv_cache(shape, T)
+    xs = synth.hidden_states(shape, S, seed=synth.SEED_SUFFIX)
+    cache = torch.full((1, 2, T + 2 + S, Hkv, dh), float("nan"), dtype=torch.bfloat16, device="cuda")
+    cache[:, :, :T] = G.to_dev(kv, shape)   # two rows between the prefix and the own rows stay NaN
+    with G.GpuModel(shape, S, T + 2 + S) as m:
+        m.load_from_generator(0, scale=8.0)
+        B.dsk_set_option("reset_stats", 0)
+        h = m.suffix(G.to_dev(xs, shape), cache, plens, lens, suffix_row0=T + 2)
+        torch.cuda.synchronize()
+        assert B.dsk_get_stat("attn_mfma_launches") == 1
+    base = weights_fn(shape, 0)
+    scaled = lambda l: {k: (v if k in ("g1", "g2") else (v.astype(np.float32) * np.float32(8.0)).astype(np.float64))
+                        for k, v in base(l).items()}
+    _, ref = O.suffix_prefill(oracle_config(shape), scaled, xs.astype(np.float64), kv_list(kv),
+                              synth.packed_positions(lens, start=plens), synth.cu_seqlens(plens), synth.cu_seqlens(lens))
+    # one layer, attention output a fair part of it at this weight scale; the bound of the bf16 path
+    assert O.max_rel_err(G.to_np(h), ref) <= 2e-2
+
+
+def test_attention_few_queries_component_call(B):
+    # rows out, no workspace (one key range per workgroup), peaked scores
+    Hq, Hkv, dh, n, pre = 8, 2, 128, 40, 500
+    bf = lambda a: synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(a))
+    q = bf(synth.normal(n * Hq * dh, 41, 0, 3.0).reshape(n, Hq, dh))
+    k = bf(synth.normal((pre + n) * Hkv * dh, 41, 1, 2.0).reshape(-1, Hkv, dh))
+    v = bf(synth.normal((pre + n) * Hkv * dh, 41, 2, 1.0).reshape(-1, Hkv, dh))
+    ref = np.stack([O.attend_row(*(t.astype(np.float64) for t in (q[i], k[:pre + i + 1], v[:pre + i + 1]))) for i in range(n)])
+    dev = lambda a: torch.from_numpy(a).to(torch.bfloat16).cuda()
+    out = torch.empty((n, Hq * dh), dtype=torch.bfloat16, device="cuda")
+    scratch = torch.empty(Hkv * dh * ((pre + n + 63) // 64 * 64), dtype=torch.bfloat16, device="cuda")
+    qb, pb = B.Batch(synth.cu_seqlens([n])), B.Batch(synth.cu_seqlens([pre]))
+    B.dsk_attention(B.DSK_BF16, dev(q), dev(k), dev(v), out, qb.desc, pb.desc, pre, Hq, Hkv, dh, scratch)
+    torch.cuda.synchronize()
+    # rounding of the probabilities and of the result: 2^-9 each
+    assert O.max_rel_err(out.float().cpu().numpy().reshape(n, Hq, dh), ref) <= 1e-2
