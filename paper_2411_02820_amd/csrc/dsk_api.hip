@@ -204,7 +204,8 @@ hipError_t gemm_any(int dtype, const void* A, int64_t lda, const void* W, int64_
 
 hipError_t gemm(const dsk_model* m, const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc,
                 const void* R, int64_t ldr, int M, int N, int K, int epi, hipStream_t s) {
-  return gemm_any(m->cfg.dtype, A, lda, W, ldw, m->w_blocks, C, ldc, R, ldr, M, N, K, epi, m->gemm_ws, m->gemm_ws_bytes, s);
+  return gemm_any(m->cfg.dtype, A, lda, W, ldw, m->w_blocks, C, ldc, R, ldr, M, N, K, epi, M > 64 ? m->split_ws : m->gemm_ws,
+                  M > 64 ? m->split_ws_bytes : m->gemm_ws_bytes, s);
 }
 
 hipError_t attention_any(int dtype, const AttnArgs& a, hipStream_t s) {
@@ -359,11 +360,14 @@ int run_layer_few(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_o
 // h_in is the model dtype unless h_in_f32; h_out likewise unless h_out_f32 (the workspace stream m->h is fp32).
 // h_mid: fp32 rows that receive the state after the attention block (h_out may be the same rows); cs: rotary table
 // of the n tokens.  vt_first_row: rows of the layer's V before it are already in the transposed copy m->vt.
+// ready: m->xn already holds this layer's normalised input; g_next: gain of the next layer's input norm, whose output this
+// layer may leave there (*left).
 int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, int h_out_f32, char* k_layer,
               char* v_layer, int64_t own_row0,
               const int32_t* q_cu, const int32_t* q_cu_host, const int32_t* p_cu, const int32_t* p_cu_host,
               int64_t n_pre_rows, int n_seqs, int n, hipStream_t s, float* h_mid = nullptr, const float2* cs = nullptr,
-              int64_t vt_first_row = 0) {
+              int64_t vt_first_row = 0, bool ready = false, const void* g_next = nullptr, bool* left = nullptr) {
+  if (left) *left = false;
   if (!h_mid) h_mid = m->h;
   if (!cs) cs = m->rope_cs;
   const dsk_config_t& c = m->cfg;
@@ -377,11 +381,18 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
   const bool fp32_fused = all_f32 && !g_force_generic;
   const bool fp32_rope = fp32_fused && c.head_dim % 32 == 0 && gemm_fp32_supported(h_in, d, w.wqkv, d, m->qkv, m->n_qkv, nullptr, 0, n, m->n_qkv, d);
   const bool fp32_swiglu = fp32_fused && c.n_experts == 0 && m->gu_block >= 16 && gemm_fp32_supported(h_mid, d, w.wgu, d, m->act, F, nullptr, 0, n, 2 * F, d);
-  if (!fp32_rope) HIP_TRY(launch_rmsnorm(c.dtype, h_in, h_in_f32 || all_f32, w.g1, m->xn, n, d, (float)c.rms_eps, s));
+  // bf16, rows that leave the chip unfilled: projections whose contraction is split do the step behind them in the reduction
+  const bool can_split = c.dtype == DSK_BF16 && !g_force_generic && m->split_ws;
+  auto splits = [&](int N, int K) { return can_split && gemm_mfma_splits(n, N, K, m->split_ws_bytes); };
+  if (!fp32_rope && !ready) HIP_TRY(launch_rmsnorm(c.dtype, h_in, h_in_f32 || all_f32, w.g1, m->xn, n, d, (float)c.rms_eps, s));
   if (fp32_rope) {
     HIP_TRY(launch_gemm_fp32_norm_rope((const float*)h_in, w.g1, (float)c.rms_eps, w.wqkv, m->qkv, cs, k_own, v_own, n, d,
                                        c.n_q_heads, c.n_kv_heads, c.head_dim, s));
     ++g_stats.gemm_generic;
+  } else if (splits(m->n_qkv, d)) {
+    HIP_TRY(launch_gemm_split_rope(m->xn, w.wqkv, m->w_blocks, m->qkv, cs, k_own, v_own, n, d, c.n_q_heads, c.n_kv_heads, c.head_dim,
+                                   m->split_ws, m->split_ws_bytes, s));
+    ++g_stats.gemm_mfma;
   } else {
     HIP_TRY(gemm(m, m->xn, d, w.wqkv, d, m->qkv, m->n_qkv, nullptr, 0, n, m->n_qkv, d, EPI_STORE, s));
     HIP_TRY(launch_rope_kv_write(c.dtype, m->qkv, cs, k_own, v_own, n, c.n_q_heads, c.n_kv_heads, c.head_dim, s));
@@ -389,9 +400,15 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
   const int rc = layer_attention(m, k_layer, v_layer, own_row0, q_cu, q_cu_host, p_cu, p_cu_host, n_pre_rows, n_seqs, n,
                                  vt_first_row, 0, s);
   if (rc) return rc;
-  HIP_TRY(gemm(m, m->attn, nq, w.wo, nq, h_mid, d, h_in, d, n, d, nq,
-               EPI_RESIDUAL | EPI_C_F32 | ((h_in_f32 || all_f32) ? EPI_R_F32 : 0), s));
-  if (!fp32_swiglu) HIP_TRY(launch_rmsnorm(c.dtype, h_mid, 1, w.g2, m->xn, n, d, (float)c.rms_eps, s));
+  if (d <= 8192 && splits(d, nq)) {
+    HIP_TRY(launch_gemm_split_norm(m->attn, w.wo, m->w_blocks, h_mid, h_in, h_in_f32, w.g2, m->xn, (float)c.rms_eps, n, d, nq,
+                                   m->split_ws, m->split_ws_bytes, s));
+    ++g_stats.gemm_mfma;
+  } else {
+    HIP_TRY(gemm(m, m->attn, nq, w.wo, nq, h_mid, d, h_in, d, n, d, nq,
+                 EPI_RESIDUAL | EPI_C_F32 | ((h_in_f32 || all_f32) ? EPI_R_F32 : 0), s));
+    if (!fp32_swiglu) HIP_TRY(launch_rmsnorm(c.dtype, h_mid, 1, w.g2, m->xn, n, d, (float)c.rms_eps, s));
+  }
   if (c.n_experts > 0) return run_moe_mlp(m, w, n, h_mid, h_out, h_out_f32 || all_f32, s);
   if (c.dtype == DSK_BF16 && !g_force_generic && m->gu_block == 32 && gemm_mfma_swiglu_supported(n, 2 * F, d)) {
     HIP_TRY(gemm(m, m->xn, d, w.wgu, d, m->act, F, nullptr, 0, n, 2 * F, d, EPI_SWIGLU, s));  // SwiGLU in the epilogue
@@ -401,6 +418,13 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
   } else {
     HIP_TRY(gemm(m, m->xn, d, w.wgu, d, m->gu, 2 * (int64_t)F, nullptr, 0, n, 2 * F, d, EPI_STORE, s));
     HIP_TRY(launch_swiglu(c.dtype, m->gu, m->act, n, F, m->gu_block, s));
+  }
+  if (g_next && h_out_f32 && d <= 8192 && splits(d, F)) {  // ... and the next layer's input norm
+    HIP_TRY(launch_gemm_split_norm(m->act, w.wd, m->w_blocks, (float*)h_out, h_mid, 1, g_next, m->xn, (float)c.rms_eps, n, d, F,
+                                   m->split_ws, m->split_ws_bytes, s));
+    ++g_stats.gemm_mfma;
+    *left = true;
+    return DSK_OK;
   }
   HIP_TRY(gemm(m, m->act, F, w.wd, F, h_out, d, h_mid, d, n, d, F,
                EPI_RESIDUAL | EPI_R_F32 | ((h_out_f32 || all_f32) ? EPI_C_F32 : 0), s));
@@ -584,6 +608,12 @@ int dsk_model_create(const dsk_config_t* cfg, int64_t max_tokens, int64_t max_kv
     const int64_t few = few_rows_workspace_bytes((int)d, (int)(nq > F ? nq : F));
     if (few > m->gemm_ws_bytes) m->gemm_ws_bytes = few;
     rc = alloc_dev(&m->gemm_ws, m->gemm_ws_bytes, &m->workspace_bytes);
+    m->split_ws = m->gemm_ws;
+    m->split_ws_bytes = m->gemm_ws_bytes;
+    if (d % 64 == 0 && F % 64 == 0 && T * 2 * F * elem > m->split_ws_bytes) {  // SwiGLU never leaves the projection there
+      m->split_ws = m->gu;
+      m->split_ws_bytes = T * 2 * F * elem;
+    }
     if (rc == DSK_OK) rc = alloc_dev((void**)&m->ssq, 64 * ((d + 15) / 16) * (int64_t)sizeof(float), &m->workspace_bytes);
   }
   if (rc == DSK_OK) {
@@ -835,7 +865,7 @@ int dsk_partial_prefill_groups(dsk_model_t* model, const dsk_group_t* groups, in
         table_done = true;
       }
       const bool few = takes_few_rows(m, T);
-      bool ready = false;  // few rows: the layer in front has left this layer's norm input
+      bool ready = false;  // the layer in front has left this layer's norm input in the workspace
       for (int l = G.lo; l < G.hi; ++l) {
         const bool last = l == G.hi - 1 && G.hidden_out;
         void* h_next = last ? G.hidden_out : (void*)m->h;
@@ -867,7 +897,8 @@ int dsk_partial_prefill_groups(dsk_model_t* model, const dsk_group_t* groups, in
                              l + 1 < G.hi ? m->layers[l + 1].g1 : nullptr, &ready);
         else
           rc = run_layer(m, l, h_cur, l > G.lo, h_next, !last, kv_k(kv_out, l), kv_v(kv_out, l), 0, batch->cu_seqlens_dev,
-                         batch->cu_seqlens_host, nullptr, nullptr, 0, batch->n_seqs, T, s);
+                         batch->cu_seqlens_host, nullptr, nullptr, 0, batch->n_seqs, T, s, nullptr, nullptr, 0, ready,
+                         l + 1 < G.hi ? m->layers[l + 1].g1 : nullptr, &ready);
         if (rc) return rc;
         h_cur = h_next;
         if (l == G.lo && next_host && (rc = hand_over_stage())) return rc;
@@ -916,7 +947,7 @@ int dsk_suffix_prefill(dsk_model_t* model, const void* suffix_hidden_in, const d
   HIP_TRY(launch_rope_table(suffix->positions_dev, m->theta, m->rope_cs, S, c.head_dim / 2, s));
   const void* h_cur = suffix_hidden_in;
   const bool few = takes_few_rows(m, S);
-  bool ready = false;  // few rows: the layer in front has left this layer's norm input
+  bool ready = false;  // the layer in front has left this layer's norm input in the workspace
   for (int l = 0; l < c.n_layers; ++l) {
     if (m->pending[l]) {
       HIP_TRY(hipStreamWaitEvent(s, m->ev_kv[l], 0));
@@ -931,7 +962,7 @@ int dsk_suffix_prefill(dsk_model_t* model, const void* suffix_hidden_in, const d
     else
       rc = run_layer(m, l, h_cur, l > 0, h_next, !last, kv_k(kv, l), kv_v(kv, l), suffix_row0, suffix->cu_seqlens_dev,
                      suffix->cu_seqlens_host, prefix->cu_seqlens_dev, prefix->cu_seqlens_host, prefix->n_tokens,
-                     suffix->n_seqs, S, s);
+                     suffix->n_seqs, S, s, nullptr, nullptr, 0, ready, last ? nullptr : m->layers[l + 1].g1, &ready);
     if (rc) return rc;
     h_cur = h_next;
   }

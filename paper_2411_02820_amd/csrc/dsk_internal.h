@@ -63,6 +63,8 @@ struct dsk_model {
   float* ssq;       // [d/16, 64] sums of squares of the few-row pass (RMSNorm split in two)
   void* gemm_ws;    // fp32 partial tiles of the K-split small-M GEMM
   int64_t gemm_ws_bytes;
+  void* split_ws;   // the same for more than 64 rows: gemm_ws, or gu where that is larger (nothing else uses gu there)
+  int64_t split_ws_bytes;
   void* attn_ws;    // fp32 partial outputs of the key-split attention
   int64_t attn_ws_bytes;
   // mixture-of-experts layers (cfg.n_experts > 0)
@@ -117,6 +119,13 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
                                  hipStream_t s);
 int64_t gemm_mfma_workspace_bytes(int max_n);
 bool gemm_mfma_swiglu_supported(int M, int N, int K);
+// More than 64 rows with the contraction split over workgroups: the reduction does the step that follows, RoPE + KV write, or
+// the RMSNorm of h = x W^T + R (d <= 8192).
+bool gemm_mfma_splits(int M, int N, int K, int64_t ws_bytes);
+hipError_t launch_gemm_split_rope(const void* A, const void* W, int w_blocks, void* qkv, const float2* cs, void* k_rows, void* v_rows,
+                                  int M, int K, int Hq, int Hkv, int dh, void* ws, int64_t ws_bytes, hipStream_t s);
+hipError_t launch_gemm_split_norm(const void* A, const void* W, int w_blocks, float* h, const void* R, int r_f32, const void* g, void* xn,
+                                  float eps, int M, int d, int K, void* ws, int64_t ws_bytes, hipStream_t s);
 // Few token rows (M <= 64, bf16, few_rows.hip): weights and activations in blocks, the step that follows a projection (and
 // the RMSNorm in front of it) done by the projection.  a = bf16(h * gain) in blocks, ssq [d/16][64] its sums of squares.
 bool few_rows_supported(int M, int d, int F, int Hq, int Hkv, int dh);

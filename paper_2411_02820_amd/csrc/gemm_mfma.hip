@@ -1,15 +1,17 @@
 // bf16 MFMA GEMM for gfx950:  C[M,N] = A[M,K] * W[N,K]^T  (+ R), fp32 accumulation, bf16 output.
 //
-// Both operands are K-contiguous, so both feed the MFMA with 16-byte vectors and no transposition.  Two
-// kernels: gemm16_bf16_kernel on v_mfma_f32_16x16x32_bf16 for the large prefill problems (256 x 256 tile; the chip
-// is power-limited there and that instruction takes less energy per flop), gemm_bf16_kernel on
-// v_mfma_f32_32x32x16_bf16 for everything else (128 x 128 tile, K-split tiles for few rows).  A workgroup owns a BM x BN tile of C and walks K in steps of 64 through a two-stage
+// Both operands are K-contiguous, so both feed the MFMA with 16-byte vectors and no transposition.  Two kernels:
+// gemm16_bf16_kernel on v_mfma_f32_16x16x32_bf16 for more than 64 rows (tiles of 128, 192 or 256 rows x 256 columns, the
+// contraction split over workgroups where the tiles do not fill the chip: gemm_plan), gemm_bf16_kernel on
+// v_mfma_f32_32x32x16_bf16 for 64 rows and fewer of row-major weights (K-split tiles) and for gate/up over up to 256 rows.
+// (Few rows of a model's own weights: few_rows.hip.)  A workgroup owns a BM x BN tile of C and walks K in steps of 64
+// through a two-stage
 // LDS ring filled by direct global->LDS loads (global_load_lds_dwordx4: no staging registers, no
 // ds_write).  The loads of k-tile kt+2 go out, between MFMAs, as soon as a barrier shows that every wave
 // has read k-tile kt out of the stage they overwrite; fragments are read from LDS one or two k-steps ahead
-// of the MFMAs that use them.  Two schedules (SCHED): 0 frees the stage before the last k-step (one
-// barrier per k-tile; any tile shape), 1 frees it before k-step 2 of 4 and spreads the loads over two
-// k-steps (two barriers; the 256 x 256 and 128 x 128 tiles, where it is 5-8 % and up to 25 % faster).
+// of the MFMAs that use them.  Two schedules of the 32x32x16 kernel (SCHED): 0 frees the stage before the last k-step
+// (one barrier per k-tile; any tile shape), 1 frees it before k-step 2 of 4 and spreads the loads over two
+// k-steps (two barriers; the 128 x 128 tile, where it is up to 25 % faster).
 //
 // LDS rows hold 64 bf16 = eight 16-byte slots.  A wave load instruction fills 64 consecutive slots
 // (8 rows); the swizzle is applied on the global side: the lane that fills slot p of row r fetches chunk
@@ -21,9 +23,11 @@
 // that stores cover whole rows of the tile).
 // Workgroup ids are remapped so that each XCD (own L2) works on a compact patch of the tile grid.
 //
-// Small M (the suffix pass: tens of rows) is a weight-streaming problem: a 64 x 64 tile, K split over
-// blockIdx.y so that enough workgroups stream W to fill HBM; each split writes an fp32 partial tile and a
-// second kernel adds the partials in a fixed order (deterministic), applies the residual and rounds.
+// 64 rows and fewer are a weight-streaming problem: a 64 x 64 tile, K split over blockIdx.y so that enough workgroups
+// stream W to fill HBM; each split writes an fp32 partial tile and a second kernel adds the partials in a fixed
+// order (deterministic), applies the residual and rounds.
+#include <math.h>
+
 #include <type_traits>
 
 #include "dsk_internal.h"
@@ -455,8 +459,9 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false>
 __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     gemm16_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W_all, int64_t ldw,
-                       void* __restrict__ C, int64_t ldc, const void* __restrict__ R, int64_t ldr, int M_all, int N, int K,
-                       int epi, int tiles_m, int tiles_n, const int4* __restrict__ tile_tab, int64_t w_group_stride) {
+                       void* C, int64_t ldc, const void* __restrict__ R, int64_t ldr, int M_all, int N, int K,
+                       int epi, int tiles_m, int tiles_n, int kt_per_split, const int4* __restrict__ tile_tab,
+                       int64_t w_group_stride) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
   constexpr int TM = WTM / 16, TN = WTN / 16;  // 16x16 MFMA tiles per wave
@@ -464,7 +469,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   constexpr int PER_TILE = A_INST + W_INST;
   constexpr int NM = TM * TN;                  // MFMAs per k-step
   constexpr int NF = TM + TN;                  // fragment reads per k-step
-  static_assert(WTN == 64 && BK == 64 && PER_TILE % 2 == 0 && NM % 4 == 0, "written for 64-column wave tiles, two k-steps");
+  static_assert(WTN == 64 && BK == 64 && TM % 2 == 0 && BM % (RPI * NW) == 0, "written for 64-column wave tiles, two k-steps");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t* sA = (bf16_t*)smem_raw;
   bf16_t* sW = sA + NSTAGE * BM * BK;
@@ -547,12 +552,15 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     else ws[ks][j] = *(const bf16x8*)(w_s + (WB ? ((wn * WTN / 16 + j) * 2 + ks) * BLK + lane * 8 : slot(wn * WTN + j * 16 + frow, ch)));
   };
 
-  const int n_kt = K / BK;
+  // k-tiles of this workgroup: all of them, or share blockIdx.y of a contraction split over workgroups (C then holds
+  // one fp32 plane of M x N partial sums per share)
+  const int kt0 = (int)blockIdx.y * kt_per_split, n_kt = min(K / BK - kt0, kt_per_split);
+  if (!GROUPED) C = (char*)C + (int64_t)blockIdx.y * M_all * ldc * ((epi & EPI_C_F32) ? 4 : 2);
 #pragma unroll
-  for (int i = 0; i < PER_TILE; ++i) issue_load(0, 0, i);
+  for (int i = 0; i < PER_TILE; ++i) issue_load(0, kt0 * BK, i);
   if (n_kt > 1) {
 #pragma unroll
-    for (int i = 0; i < PER_TILE; ++i) issue_load(1, BK, i);
+    for (int i = 0; i < PER_TILE; ++i) issue_load(1, (kt0 + 1) * BK, i);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_TILE) : "memory");
   } else {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -608,7 +616,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
           if (ks == 1 && has_next2) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int q = m * PER_TILE / NM; q < (m + 1) * PER_TILE / NM; ++q) issue_load(stage, (t + 2) * BK, q);
+            for (int q = m * PER_TILE / NM; q < (m + 1) * PER_TILE / NM; ++q) issue_load(stage, (kt0 + t + 2) * BK, q);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -731,6 +739,86 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const float* __restr
   store_quad(C, ldc, R, ldr, m, n, s, epi);
 }
 
+// The QKV projection's partial sums, followed by what rope_kv_write_kernel does: q and k heads rotated with the (cos, sin)
+// table of the tokens (pairs (i, i + dh/2)), q written to the qkv buffer, rotated k and v to the rows of the cache.
+// One thread per 4 rotary pairs, or per 4 values of v.
+__global__ void __launch_bounds__(256) splitk_reduce_rope_kernel(const float* __restrict__ P, bf16_t* __restrict__ qkv, int64_t ldq,
+                                                                 const float2* __restrict__ cs, bf16_t* __restrict__ k_rows,
+                                                                 bf16_t* __restrict__ v_rows, int M, int N, int splits, int Hq,
+                                                                 int Hkv, int dh) {
+  const int half = dh / 2, kvw = Hkv * dh;
+  const int rot_units = (Hq + Hkv) * (half / 4), v_units = kvw / 4;
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (int64_t)M * (rot_units + v_units)) return;
+  const int m = (int)(i / (rot_units + v_units)), u = (int)(i - (int64_t)m * (rot_units + v_units));
+  const float* row = P + (int64_t)m * N;
+  const int64_t stride = (int64_t)M * N;
+  auto store = [](bf16_t* dst, f32x4 v) {
+    bf16x4 o;
+    o[0] = (bf16_t)v[0]; o[1] = (bf16_t)v[1]; o[2] = (bf16_t)v[2]; o[3] = (bf16_t)v[3];
+    *(bf16x4*)dst = o;
+  };
+  if (u < rot_units) {
+    const int head = u / (half / 4), i0 = (u % (half / 4)) * 4;
+    const f32x4 x1 = sum_splits(row + head * dh + i0, stride, splits), x2 = sum_splits(row + head * dh + i0 + half, stride, splits);
+    f32x4 y1, y2;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float2 c = cs[(int64_t)m * half + i0 + e];
+      y1[e] = x1[e] * c.x - x2[e] * c.y;
+      y2[e] = x2[e] * c.x + x1[e] * c.y;
+    }
+    bf16_t* dst = head < Hq ? qkv + (int64_t)m * ldq + head * dh + i0 : k_rows + (int64_t)m * kvw + (head - Hq) * dh + i0;
+    store(dst, y1);
+    store(dst + half, y2);
+  } else {
+    const int j = (u - rot_units) * 4;
+    store(v_rows + (int64_t)m * kvw + j, sum_splits(row + (Hq + Hkv) * dh + j, stride, splits));
+  }
+}
+
+// The partial sums of a projection with residual whose result feeds an RMSNorm, one workgroup per token row: writes the
+// fp32 residual stream h = sums + R and xn = h * rsqrt(mean(h^2) + eps) * g in bf16.  d <= 1024 * NCH, a multiple of 4.
+template <int NCH>
+__global__ void __launch_bounds__(256) splitk_reduce_rmsnorm_kernel(const float* __restrict__ P, float* h, const void* R, int r_f32,
+                                                                    const bf16_t* __restrict__ g, bf16_t* __restrict__ xn, int M,
+                                                                    int d, int splits, float eps) {
+  __shared__ float part[4];
+  const int m = blockIdx.x;
+  f32x4 v[NCH];
+  float ss = 0.f;
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    const int n = (threadIdx.x + c * 256) * 4;
+    if (n >= d) continue;
+    f32x4 a = sum_splits(P + (int64_t)m * d + n, (int64_t)M * d, splits);
+    if (r_f32) {
+      a += *(const f32x4*)((const float*)R + (int64_t)m * d + n);
+    } else {
+      const bf16x4 r = *(const bf16x4*)((const bf16_t*)R + (int64_t)m * d + n);
+      a[0] += (float)r[0]; a[1] += (float)r[1]; a[2] += (float)r[2]; a[3] += (float)r[3];
+    }
+    *(f32x4*)(h + (int64_t)m * d + n) = a;
+    v[c] = a;
+    ss += a[0] * a[0] + a[1] * a[1] + a[2] * a[2] + a[3] * a[3];
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  const float r = 1.0f / sqrtf((part[0] + part[1] + part[2] + part[3]) / (float)d + eps);
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    const int n = (threadIdx.x + c * 256) * 4;
+    if (n >= d) continue;
+    const bf16x4 gg = *(const bf16x4*)(g + n);
+    bf16x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (bf16_t)(v[c][e] * r * (float)gg[e]);
+    *(bf16x4*)(xn + (int64_t)m * d + n) = o;
+  }
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool PARTIAL, int SCHED, bool WB>
 hipError_t launch_form(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R, int64_t ldr,
                   float* P, int M, int N, int K, int epi, int splits, int kt_per_split, hipStream_t s) {
@@ -758,7 +846,7 @@ hipError_t launch(const void* A, int64_t lda, const void* W, int64_t ldw, int w_
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB>
 hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R, int64_t ldr,
-                    int M, int N, int K, int epi, hipStream_t s) {
+                         int M, int N, int K, int epi, int splits, int kt_per_split, hipStream_t s) {
   auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, WB>;
   constexpr int lds = NSTAGE * (BM + BN) * BK * 2;
   static bool configured = false;
@@ -768,16 +856,20 @@ hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw,
     configured = true;
   }
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  DSK_LAUNCH_TIMED(kern, dim3(tiles_m * tiles_n), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
-                   (const bf16_t*)W, ldw, C, ldc, R, ldr, M, N, K, epi, tiles_m, tiles_n, (const int4*)nullptr, (int64_t)0);
+  DSK_LAUNCH_TIMED(kern, dim3(tiles_m * tiles_n, splits), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
+                   (const bf16_t*)W, ldw, C, ldc, R, ldr, M, N, K, epi, tiles_m, tiles_n, kt_per_split, (const int4*)nullptr,
+                   (int64_t)0);
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N>
-hipError_t launch16(const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc, const void* R, int64_t ldr,
-                    int M, int N, int K, int epi, hipStream_t s) {
-  return w_blocks ? launch16_form<BM, BN, WAVES_M, WAVES_N, true>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, s)
-                  : launch16_form<BM, BN, WAVES_M, WAVES_N, false>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, s);
+// bm: rows of the tile (128, 192 or 256; 256 columns).  splits > 1: fp32 partial planes in C, epi = EPI_C_F32.
+hipError_t launch16(int bm, const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc, const void* R,
+                    int64_t ldr, int M, int N, int K, int epi, int splits, int kt_per_split, hipStream_t s) {
+#define DSK_FORM(BM)                                                                                                      \
+  (w_blocks ? launch16_form<BM, 256, 2, 4, true>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, splits, kt_per_split, s)   \
+            : launch16_form<BM, 256, 2, 4, false>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, splits, kt_per_split, s))
+  return bm == 128 ? DSK_FORM(128) : bm == 192 ? DSK_FORM(192) : DSK_FORM(256);
+#undef DSK_FORM
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N>
@@ -794,11 +886,50 @@ hipError_t launch16_grouped(const void* A, int64_t lda, const void* W, int64_t l
   const int tiles_n = (N + BN - 1) / BN;
   DSK_LAUNCH_TIMED(kern, dim3(tile_rows * tiles_n), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
                    (const bf16_t*)W, ldw, C, ldc, (const void*)nullptr, (int64_t)0, 0, N, K, epi, tile_rows, tiles_n,
-                   tile_tab, w_group_stride);
+                   K / BK, tile_tab, w_group_stride);
   return hipGetLastError();
 }
 
 int g_variant = 0;
+
+// How a projection over more than 64 rows runs: tile rows (256 columns) and over how many workgroups its contraction is
+// split.  A tile of 256 x 256 needs the fewest operand bytes per flop and is the best one where it fills the chip; where
+// it does not, a lower tile makes better-filled rounds, and below one round the contraction is split (fp32 partial
+// planes, fixed-order reduction).  The times below, in microseconds, are fits to measurements on the 8B projections over 96
+// to 3000 rows with cold weights (in brackets the 128 x 128 tiles with split contraction this replaces):
+//   QKV 333 rows 32.8 [43.0], 1500 rows 71.7 [91.7], 3000 rows 140 [165];  O 333 rows 27.8 [35.8], 3000 rows 85 [96];
+//   down 333 rows 55 [81], 700 rows 85 [135], 1500 rows 149 [207].
+struct GemmPlan { int bm, splits, per; };
+
+GemmPlan gemm_plan(int M, int N, int K, bool may_split, int64_t ws_bytes) {
+  const int KT = K / BK, bms[3] = {256, 192, 128};
+  const bool fills = (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 192;  // gemm_mfma_uses_prefill_tile
+  GemmPlan best = {256, 1, KT};
+  float best_us = 1e30f;
+  for (int i = 0; i < 3; ++i) {
+    const int bm = bms[i];
+    const int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + 255) / 256);
+    const int max_sp = fills || !may_split || tiles > 128 ? 1 : (int)(256 / tiles);
+    for (int want = 1; want <= max_sp && (want == 1 || KT / want >= 4); ++want) {
+      const int per = (KT + want - 1) / want, sp = (KT + per - 1) / per;
+      if (sp != want || (sp > 1 && (int64_t)sp * M * N * 4 > ws_bytes)) continue;
+      const float rounds = (float)(tiles * sp) / 256.0f, fill = rounds < 1.f ? rounds : 1.f;
+      // microseconds per k-tile of 64: busier chips clock lower and share the L2s
+      const float kt_us = bm == 256 ? 1.08f + 0.42f * fill : bm == 192 ? 0.97f + 0.30f * fill : 0.85f + 0.15f * fill;
+      // a last round that is not full costs most of a full one; less with lower tiles
+      const float whole = floorf(rounds), frac = rounds - whole;
+      const float tail = bm == 256 ? 0.75f + 0.25f * frac : bm == 192 ? 0.53f + 0.2f * frac : 0.45f + 0.4f * frac;
+      const float n_rounds = rounds <= 1.f ? 1.f : whole + (frac > 0.f ? tail : 0.f);
+      float us = n_rounds * (per * kt_us + 4.f);
+      if (sp > 1) us += 4.5f + (float)sp * M * N * 8.f / 5.0e6f;
+      if (us < best_us * 0.99f) {
+        best_us = us;
+        best = {bm, sp, per};
+      }
+    }
+  }
+  return best;
+}
 
 }  // namespace
 
@@ -843,35 +974,24 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
   int variant = g_variant;
   if (epi & EPI_SWIGLU) {
     if (!gemm_mfma_swiglu_supported(M, N, K)) return hipErrorNotSupported;
-    if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 192 || variant == 1)
-      return launch16<256, 256, 2, 4>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, s);
-    return launch<128, 128, 2, 2, false, 1>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
+    // up to 256 rows the 128 x 128 tiles fill the chip twice over (two workgroups per compute unit) and are faster: 61 us
+    // against 74 us for 96 rows, 71 against 76 us for 200, 8B gate/up
+    if (variant == 2 || (variant == 0 && M <= 256))
+      return launch<128, 128, 2, 2, false, 1>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
+    const int bm = variant == 1 ? 256 : gemm_plan(M, N, K, false, 0).bm;
+    return launch16(bm, A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, 1, KT, s);
   }
-  // A few hundred token rows: too few 128 x 128 tiles to fill the chip, so K is split over workgroups as on the
-  // few-row path (fp32 partial planes, fixed-order reduce); every split gets at least two k-tiles.
-  if (variant == 0 && M > 64 && ws) {
-    const int64_t tiles = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
-    if (tiles <= 256) {
-      int sp = (int)((512 + tiles - 1) / tiles);
-      sp = max(1, min(sp, KT / 2));
-      while (sp > 1 && (int64_t)sp * M * N * 4 > ws_bytes) --sp;
-      const int per = (KT + sp - 1) / sp;
-      const int splits = (KT + per - 1) / per;
-      if (splits > 1) {
-        hipError_t e = launch<128, 128, 2, 2, true, 1>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, (float*)ws, M, N, K, epi, splits, per, s);
-        if (e != hipSuccess) return e;
-        const int64_t quads = (int64_t)M * (N / 4);
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, (const float*)ws,
-                           C, ldc, R, ldr, M, N, splits, epi);
-        return hipGetLastError();
-      }
-    }
+  if (variant == 0 && M > 64) {
+    const GemmPlan p = gemm_plan(M, N, K, ws != nullptr, ws_bytes);
+    if (p.splits == 1) return launch16(p.bm, A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, 1, KT, s);
+    hipError_t e = launch16(p.bm, A, lda, W, ldw, w_blocks, ws, N, nullptr, 0, M, N, K, EPI_C_F32, p.splits, p.per, s);
+    if (e != hipSuccess) return e;
+    const int64_t quads = (int64_t)M * (N / 4);
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, (const float*)ws, C, ldc, R, ldr,
+                       M, N, p.splits, epi);
+    return hipGetLastError();
   }
-  if (variant == 0) {
-    if (M <= 64) variant = 3;
-    else if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 192) variant = 1;
-    else variant = 2;
-  }
+  if (variant == 0) variant = 3;
   switch (variant) {
     case 3: {  // weight streaming: K split over workgroups, fp32 partial planes, fixed-order reduce
       bool wide;
@@ -887,11 +1007,9 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
       }
       return launch<64, 64, 1, 2, false>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
     }
-    // the two prefill tilings: the 256x256 tile on the 16x16x32 MFMA (1; large problems are power-limited, and that
-    // instruction is the thriftier one) and the 128x128 tile on the 32x32x16 MFMA (2; medium sizes are issue- and
-    // latency-bound, where it is 15-30 % faster)
+    // the two prefill tilings by request: the 256x256 tile on the 16x16x32 MFMA (1), the 128x128 tile on the 32x32x16 MFMA (2)
     case 2: return launch<128, 128, 2, 2, false, 1>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
-    default: return launch16<256, 256, 2, 4>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, s);
+    default: return launch16(256, A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, 1, KT, s);
   }
 }
 
@@ -907,4 +1025,41 @@ hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, 
   if (a_rows * lda * 2 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 2 >= ((int64_t)1 << 32)) return hipErrorNotSupported;
   return launch16_grouped<256, 256, 2, 4>(A, lda, W, ldw, w_group_stride, C, ldc, N, K, epi, (const int4*)tile_tab,
                                           tile_rows, s);
+}
+
+// More than 64 rows, dense operands: whether the contraction is split, i.e. a reduction runs behind the projection, which
+// can then do the step that follows (the two launchers below).
+bool gemm_mfma_splits(int M, int N, int K, int64_t ws_bytes) {
+  return g_variant == 0 && M > 64 && K >= BK && K % BK == 0 && N % 8 == 0 && (int64_t)M * K * 2 < ((int64_t)1 << 32) &&
+         (int64_t)N * K * 2 < ((int64_t)1 << 32) && gemm_plan(M, N, K, true, ws_bytes).splits > 1;
+}
+
+// QKV + RoPE + KV write: q rows in qkv [M, N], k and v only in the cache
+hipError_t launch_gemm_split_rope(const void* A, const void* W, int w_blocks, void* qkv, const float2* cs, void* k_rows, void* v_rows,
+                                  int M, int K, int Hq, int Hkv, int dh, void* ws, int64_t ws_bytes, hipStream_t s) {
+  const int N = (Hq + 2 * Hkv) * dh;
+  if (!ws || dh % 8 || !gemm_mfma_splits(M, N, K, ws_bytes)) return hipErrorNotSupported;
+  const GemmPlan p = gemm_plan(M, N, K, true, ws_bytes);
+  hipError_t e = launch16(p.bm, A, K, W, K, w_blocks, ws, N, nullptr, 0, M, N, K, EPI_C_F32, p.splits, p.per, s);
+  if (e != hipSuccess) return e;
+  const int64_t units = (int64_t)M * ((Hq + Hkv) * (dh / 8) + Hkv * dh / 4);
+  hipLaunchKernelGGL(splitk_reduce_rope_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s, (const float*)ws,
+                     (bf16_t*)qkv, (int64_t)N, cs, (bf16_t*)k_rows, (bf16_t*)v_rows, M, N, p.splits, Hq, Hkv, dh);
+  return hipGetLastError();
+}
+
+// h [M, d] fp32 = x W^T + R and xn [M, d] = rmsnorm(h) * g; d <= 8192
+hipError_t launch_gemm_split_norm(const void* A, const void* W, int w_blocks, float* h, const void* R, int r_f32, const void* g, void* xn,
+                                  float eps, int M, int d, int K, void* ws, int64_t ws_bytes, hipStream_t s) {
+  if (!ws || d > 8192 || !gemm_mfma_splits(M, d, K, ws_bytes)) return hipErrorNotSupported;
+  const GemmPlan p = gemm_plan(M, d, K, true, ws_bytes);
+  hipError_t e = launch16(p.bm, A, K, W, K, w_blocks, ws, d, nullptr, 0, M, d, K, EPI_C_F32, p.splits, p.per, s);
+  if (e != hipSuccess) return e;
+  if (d <= 4096)
+    hipLaunchKernelGGL(splitk_reduce_rmsnorm_kernel<4>, dim3(M), dim3(256), 0, s, (const float*)ws, h, R, r_f32, (const bf16_t*)g,
+                       (bf16_t*)xn, M, d, p.splits, eps);
+  else
+    hipLaunchKernelGGL(splitk_reduce_rmsnorm_kernel<8>, dim3(M), dim3(256), 0, s, (const float*)ws, h, R, r_f32, (const bf16_t*)g,
+                       (bf16_t*)xn, M, d, p.splits, eps);
+  return hipGetLastError();
 }

@@ -1,0 +1,57 @@
+"""Projections over 65 to a few thousand rows: every tile height, a contraction split over workgroups with RoPE, residual and
+RMSNorm in its reduction, ragged tiles, against float64 and against the kernels that do not split."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dsk_oracle as O
+from paper_2411_02820_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2411_02820_amd import binding
+    return binding
+
+
+# row-major weights through the component call: rows around multiples of 128, 192 and 256, columns that end inside a tile,
+# contractions of a few k-tiles (unsplit) and many (split with an uneven last share), and more than one round of tiles
+@pytest.mark.parametrize("M,N,K,residual", [(65, 64, 64, False), (129, 516, 320, True), (191, 1028, 1984, False),
+                                            (193, 256, 4096, True), (257, 2052, 1024, True), (385, 512, 8192, False),
+                                            (1025, 1024, 2048, True), (2000, 2560, 256, False), (3000, 5000, 192, True)])
+def test_linear_bf16_medium_rows(B, M, N, K, residual):
+    bf = lambda a: synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(a))
+    x = bf(synth.normal(M * K, 51, 0, 1.0).reshape(M, K))
+    w = bf(synth.normal(N * K, 51, 1, 0.05).reshape(N, K))
+    r = bf(synth.normal(M * N, 51, 2, 1.0).reshape(M, N)) if residual else None
+    ref = x.astype(np.float64) @ w.astype(np.float64).T + (0 if r is None else r.astype(np.float64))
+    dev = lambda a: torch.from_numpy(a).to(torch.bfloat16).cuda()
+    y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.dsk_linear(B.DSK_BF16, dev(x), dev(w), y, None if r is None else dev(r), M, N, K)
+    torch.cuda.synchronize()
+    # one bf16 rounding of the result
+    assert O.max_rel_err(y.float().cpu().numpy(), ref) <= 2 ** -8
+
+
+# two layers, so that the split down projection also leaves the next layer's norm input; dh 64 and 128; against the same
+# model with the tiling forced (which neither splits nor fuses)
+@pytest.mark.parametrize("rows", [65, 130, 200, 390])
+@pytest.mark.parametrize("d,Hq,Hkv,dh,F", [(512, 4, 2, 128, 2048), (1088, 17, 1, 64, 1472)])
+def test_layers_with_split_projections(B, rows, d, Hq, Hkv, dh, F):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(2, d, Hq, Hkv, dh, F, 10000.0, 1e-5, "bf16")
+    x = G.to_dev(synth.hidden_states(shape, rows), shape)
+    with G.GpuModel(shape, rows) as m:
+        m.init_random(7)
+        kv, h = m.partial(x, 0, 2, None, [rows - 9, 9])
+        B.dsk_set_option("gemm_tiling", 2)
+        try:
+            kv_ref, h_ref = m.partial(x, 0, 2, None, [rows - 9, 9])
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("gemm_tiling", 0)
+    # both are bf16 evaluations of the same layers, each within 1e-2 of the exact ones at this weight scale
+    for a, b in ((kv, kv_ref), (h, h_ref)):
+        assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2e-2
