@@ -822,19 +822,24 @@ int dsk_partial_prefill_groups(dsk_model_t* model, const dsk_group_t* groups, in
   // reused layers, ascending (the order the suffix prefill consumes them), one event per layer
   memset(m->pending, 0, L);
   m->any_pending = 0;
+  auto loaded = [&](int l) { return kv_reused && !alias && (mode == DSK_LOAD_ALL_FIRST || !recomputed(l)); };
+  const int64_t bytes = (int64_t)T * row_bytes;
   for (int l = 0; l < L; ++l) {
-    if (recomputed(l) && mode != DSK_LOAD_ALL_FIRST) continue;
-    if (!kv_reused || alias) continue;
-    const int64_t bytes = (int64_t)T * row_bytes;
-    const bool one_piece = kv_reused->v_offset == bytes && kv_out->v_offset == bytes;
-    if (one_piece) {
+    if (!loaded(l)) continue;
+    const int first = l;
+    if (kv_kind == hipMemcpyDeviceToDevice && m->throttle_gbps <= 0.0) {
+      // device to device: a run of layers in one launch, waited for at its first layer (layers are consumed in order)
+      while (l + 1 < L && loaded(l + 1)) ++l;
+      HIP_TRY(launch_splice(kv_reused->base, kv_reused->layer_stride, kv_reused->v_offset, kv_out->base, kv_out->layer_stride,
+                            kv_out->v_offset, first, l + 1 - first, bytes, mode == DSK_LOAD_PIPELINED && n_recomputed > 0, ls));
+    } else if (kv_reused->v_offset == bytes && kv_out->v_offset == bytes) {  // one piece
       if ((rc = load_copy(m, kv_k(kv_out, l), kv_k(kv_reused, l), 2 * bytes, kv_kind))) return rc;
     } else {
       if ((rc = load_copy(m, kv_k(kv_out, l), kv_k(kv_reused, l), bytes, kv_kind))) return rc;
       if ((rc = load_copy(m, kv_v(kv_out, l), kv_v(kv_reused, l), bytes, kv_kind))) return rc;
     }
-    HIP_TRY(hipEventRecord(m->ev_kv[l], ls));
-    m->pending[l] = 1;
+    HIP_TRY(hipEventRecord(m->ev_kv[first], ls));
+    m->pending[first] = 1;
     m->any_pending = 1;
   }
   HIP_TRY(hipEventRecord(m->ev_all, ls));

@@ -165,6 +165,9 @@ extern thread_local hipEvent_t g_launch_ev_start, g_launch_ev_stop;
     }                                                                                                                \
   } while (0)
 
+// K and V rows of layers first .. first+n-1 (bytes of each) from one device cache into another, one launch (splice.hip)
+hipError_t launch_splice(const void* src, int64_t src_stride, int64_t src_v, void* dst, int64_t dst_stride, int64_t dst_v, int first,
+                         int n, int64_t bytes, int background, hipStream_t s);
 // pacing of the load stream against the 100 MHz constant-rate clock
 hipError_t launch_pace_start(unsigned long long* t0, hipStream_t s);
 hipError_t launch_pace_wait(const unsigned long long* t0, unsigned long long ticks, hipStream_t s);
