@@ -1,4 +1,4 @@
-// Attention of few queries per sequence (at most 64: the suffix pass, a generation step) against a long cache, bf16.
+// Attention of few queries per sequence (at most 128: the suffix pass, a generation step) against a long cache, bf16.
 //
 // Bound: the rate at which K and V arrive from HBM, and how soon the first of them do; then the softmax arithmetic of the
 // resident wave or two per SIMD.  So: the q heads of a kv group and their queries form one list of columns (query-major)
@@ -14,6 +14,7 @@
 // 4096 keys 7.8 us (17), and the merge of the key ranges 6 us in both.  Of the 22.5 us the loads alone take 10, the partial
 // outputs 4; runs of 64 keys per wave and stage (two independent steps to schedule) instead of 32 took 25 -> 22.5 us, four column
 // tiles per wave with one wave per SIMD take 35.
+// 128 queries for each of eight sequences of 1k to 8k keys: 189 us (transposed copy 35, attention 150, merge 15).
 #include <math.h>
 
 #include <type_traits>
@@ -33,7 +34,7 @@ struct FewParams {
   bf16_t* out; int out_blocks;
   float* part_o; float* part_ml;  // splits > 1: [n_q][Hq][splits][dh], [n_q][Hq][splits][2]
   const int32_t* q_cu; const int32_t* p_cu;
-  int n_seqs; int own_row0; int Hq, Hkv; int splits;
+  int n_seqs; int own_row0; int Hq, Hkv; int splits; int range;  // key ranges: `splits` of `range` stages each
   float c;  // softmax scale * log2(e)
 };
 
@@ -72,7 +73,7 @@ __global__ void __launch_bounds__(64 * QG * KH) attn_few_kernel(FewParams p) {
   const int n_keys = n_pre + min(n_cols - 1, blk * COLS + COLS - 1) / G + 1;  // keys some column of the workgroup sees
   // stages of this key range
   const int n_stages_all = (n_keys + KEYS - 1) / KEYS;
-  const int st0 = (int)((int64_t)n_stages_all * z / p.splits), st1 = (int)((int64_t)n_stages_all * (z + 1) / p.splits);
+  const int st0 = min(z * p.range, n_stages_all), st1 = min(st0 + p.range, n_stages_all);
 
   const int ldkv = p.Hkv * DH;
   const bf16_t* kb = p.k + kvh * DH;
@@ -242,54 +243,54 @@ __global__ void __launch_bounds__(64 * QG * KH) attn_few_kernel(FewParams p) {
     l[t] += __shfl_xor(l[t], 16, 64);
     l[t] += __shfl_xor(l[t], 32, 64);
   }
-  __syncthreads();
-  f32x4* red = (f32x4*)smem_raw;                              // [QG][KH][QT][NDT][64]
-  float2* red_ml = (float2*)(red + NW * QT * NDT * 64);       // [QG][KH][QT][16]
+  f32x4* red = (f32x4*)smem_raw;                    // [QG][KH][NDT][64]
+  float2* red_ml = (float2*)(red + NW * NDT * 64);  // [QG][KH][16]
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
+  for (int t = 0; t < QT; ++t) {  // one column tile at a time
+    __syncthreads();
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) red[(((qg * KH + kh) * QT + t) * NDT + dt) * 64 + lane] = o[t][dt];
-    if (g == 0) red_ml[((qg * KH + kh) * QT + t) * 16 + r16] = make_float2(m[t], l[t]);
-  }
-  __syncthreads();
+    for (int dt = 0; dt < NDT; ++dt) red[((qg * KH + kh) * NDT + dt) * 64 + lane] = o[t][dt];
+    if (g == 0) red_ml[(qg * KH + kh) * 16 + r16] = make_float2(m[t], l[t]);
+    __syncthreads();
+    if (blk * COLS + (qg * QT + t) * 16 + r16 < n_cols) {
+      float M = -INFINITY, den = 0.f, w[KH];
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    if (blk * COLS + (qg * QT + t) * 16 + r16 >= n_cols) continue;
-    float M = -INFINITY, den = 0.f, w[KH];
+      for (int k = 0; k < KH; ++k) M = fmaxf(M, red_ml[(qg * KH + k) * 16 + r16].x);
+      const float m_safe = M == -INFINITY ? 0.f : M;
 #pragma unroll
-    for (int k = 0; k < KH; ++k) M = fmaxf(M, red_ml[((qg * KH + k) * QT + t) * 16 + r16].x);
-    const float m_safe = M == -INFINITY ? 0.f : M;
-#pragma unroll
-    for (int k = 0; k < KH; ++k) {
-      const float2 ml = red_ml[((qg * KH + k) * QT + t) * 16 + r16];
-      w[k] = __builtin_amdgcn_exp2f((ml.x - m_safe) * p.c);
-      den += ml.y * w[k];
-    }
-    const int64_t qh = (int64_t)qrow[t] * p.Hq + head[t];
-    const float inv = 1.0f / den;
-    for (int dt = kh; dt < NDT; dt += KH) {
-      f32x4 x = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int k = 0; k < KH; ++k) x += red[(((qg * KH + k) * QT + t) * NDT + dt) * 64 + lane] * w[k];
-      const int d = 16 * dt + 4 * g;
-      if (p.splits > 1) {
-        *(f32x4*)(p.part_o + (qh * p.splits + z) * DH + d) = x;
-      } else {
-        x *= inv;
-        bf16x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (bf16_t)x[e];
-        *(bf16x4*)(p.out + (p.out_blocks ? block_at(qrow[t], head[t] * DH + d, p.Hq * DH) : qh * DH + d)) = v;
+      for (int k = 0; k < KH; ++k) {
+        const float2 ml = red_ml[(qg * KH + k) * 16 + r16];
+        w[k] = __builtin_amdgcn_exp2f((ml.x - m_safe) * p.c);
+        den += ml.y * w[k];
       }
+      const int64_t qh = (int64_t)qrow[t] * p.Hq + head[t];
+      const float inv = 1.0f / den;
+      if (st0 < st1) {  // a range past this sequence's keys only says so (m = -inf): nothing reads its outputs
+        for (int dt = kh; dt < NDT; dt += KH) {
+          f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int k = 0; k < KH; ++k) x += red[((qg * KH + k) * NDT + dt) * 64 + lane] * w[k];
+          const int d = 16 * dt + 4 * g;
+          if (p.splits > 1) {
+            *(f32x4*)(p.part_o + (qh * p.splits + z) * DH + d) = x;
+          } else {
+            x *= inv;
+            bf16x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (bf16_t)x[e];
+            *(bf16x4*)(p.out + (p.out_blocks ? block_at(qrow[t], head[t] * DH + d, p.Hq * DH) : qh * DH + d)) = v;
+          }
+        }
+      }
+      if (p.splits > 1 && kh == 0 && g == 0) *(float2*)(p.part_ml + (qh * p.splits + z) * 2) = make_float2(M, den);
     }
-    if (p.splits > 1 && kh == 0 && g == 0) *(float2*)(p.part_ml + (qh * p.splits + z) * 2) = make_float2(M, den);
   }
 }
 
 template <int DH, int QT, int QG, int KH, int KS, int NST>
 hipError_t launch_few(const FewParams& p, int64_t blocks, hipStream_t s) {
   auto kern = attn_few_kernel<DH, QT, QG, KH, KS, NST>;
-  constexpr int ring = NST * 32 * KS * KH * DH * 2 * 2, merge = QG * KH * QT * (DH / 16 * 1024 + 128);
+  constexpr int ring = NST * 32 * KS * KH * DH * 2 * 2, merge = QG * KH * (DH / 16 * 1024 + 128);
   constexpr int lds = ring > merge ? ring : merge;
   static bool configured = false;
   if (!configured) {
@@ -303,12 +304,12 @@ hipError_t launch_few(const FewParams& p, int64_t blocks, hipStream_t s) {
 
 }  // namespace
 
-// Sequences of at most 64 queries.  (Longer ones are bound by arithmetic, where the 32-query waves of attn_mfma.hip do more
+// Sequences of at most 128 queries.  (Longer ones are bound by arithmetic, where the 32-query waves of attn_mfma.hip do more
 // per LDS read.)
 bool attn_few_supported(const AttnArgs& a) {
   if ((a.dh != 128 && a.dh != 64) || (a.ldq & 7) || a.own_row0 + a.n_q >= ((int64_t)1 << 31)) return false;
   for (int b = 0; b < a.n_seqs; ++b)
-    if (a.q_cu_host[b + 1] - a.q_cu_host[b] > 64) return false;
+    if (a.q_cu_host[b + 1] - a.q_cu_host[b] > 128) return false;
   return true;
 }
 
@@ -325,21 +326,38 @@ hipError_t launch_attn_few(const AttnArgs& a, int* splits_out, hipStream_t s) {
   }
   // columns per workgroup: 16 (four waves share the keys), 64, or 128 (32 per wave: a fragment feeds two MFMAs)
   const int cols = max_len * G <= 16 ? 16 : max_len * G <= 64 ? 64 : 128;
+  const int max_stages = (int)((max_keys + 127) / 128);  // every form has stages of 128 keys
+  // Key ranges, the same length for all sequences (short ones leave the last ranges empty): the length that by this count
+  // ends first, with one workgroup per compute unit, 4 us for a workgroup's start and end, 3 us per stage (1 us with 16
+  // columns) and the partial outputs written and read at 5 TB/s.
+  int splits = 1, range = max_stages;
   int64_t blocks = 0;
-  for (int b = 0; b < a.n_seqs; ++b) blocks += ((int64_t)(a.q_cu_host[b + 1] - a.q_cu_host[b]) * G + cols - 1) / cols;
-  blocks *= a.Hkv;
-  // one workgroup per compute unit, ranges of at least 128 keys
-  int splits = 1;
-  if (a.ws && blocks < 256) {
-    splits = (int)(256 / blocks);
-    if (splits > max_keys / 128) splits = (int)(max_keys / 128);
-    while (splits > 1 && (int64_t)a.n_q * splits * a.Hq * (a.dh + 2) * 4 > a.ws_bytes) --splits;
-    if (splits < 1) splits = 1;
+  float best_us = 1e30f;
+  for (int want = 1; want <= 32 && want <= max_stages; ++want) {
+    const int len = (max_stages + want - 1) / want, sp = (max_stages + len - 1) / len;
+    if (sp != want) continue;
+    if (sp > 1 && (!a.ws || (int64_t)a.n_q * sp * a.Hq * (a.dh + 2) * 4 > a.ws_bytes)) break;
+    int64_t busy = 0, all = 0;
+    for (int b = 0; b < a.n_seqs; ++b) {
+      const int64_t q_len = a.q_cu_host[b + 1] - a.q_cu_host[b];
+      const int64_t keys = q_len + (a.p_cu_host ? a.p_cu_host[b + 1] - a.p_cu_host[b] : 0);
+      const int64_t col_blocks = (q_len * G + cols - 1) / cols * a.Hkv;
+      busy += col_blocks * (((keys + 127) / 128 + len - 1) / len);
+      all += col_blocks;
+    }
+    float us = (float)((busy + 255) / 256) * (len * (cols == 16 ? 1.f : 3.f) + 4.f);
+    if (sp > 1) us += 5.f + (float)busy * cols * a.dh * 8.f / 5.0e6f;
+    if (us < best_us) {
+      best_us = us;
+      splits = sp;
+      range = len;
+      blocks = all;
+    }
   }
   FewParams p;
   p.q = (const bf16_t*)a.q; p.ldq = a.ldq; p.k = (const bf16_t*)a.k_rows; p.v = (const bf16_t*)a.v_rows;
   p.out = (bf16_t*)a.out; p.out_blocks = a.out_blocks; p.q_cu = a.q_cu; p.p_cu = a.p_cu; p.n_seqs = a.n_seqs;
-  p.own_row0 = (int)a.own_row0; p.Hq = a.Hq; p.Hkv = a.Hkv; p.splits = splits;
+  p.own_row0 = (int)a.own_row0; p.Hq = a.Hq; p.Hkv = a.Hkv; p.splits = splits; p.range = range;
   p.c = (float)(1.4426950408889634 / sqrt((double)a.dh));
   p.part_o = splits > 1 ? (float*)a.ws : nullptr;
   p.part_ml = splits > 1 ? p.part_o + (int64_t)a.n_q * a.Hq * splits * a.dh : nullptr;

@@ -538,7 +538,8 @@ __global__ void __launch_bounds__(256) transpose_v_kernel(const bf16_t* __restri
 
 }  // namespace
 
-// how many launches took the key-split path, and how many of those with four q heads packed per workgroup
+// how many launches took the key-split path, and how many of those with the q heads of a kv group packed per workgroup and at
+// most 64 queries per sequence
 static int64_t g_split_launches = 0, g_packed_launches = 0;
 void attn_mfma_counts(int64_t* split, int64_t* packed, int reset) {
   if (split) *split = g_split_launches;
@@ -598,7 +599,9 @@ hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s) {
     hipError_t e = launch_attn_few(a, &splits, s);
     if (e == hipSuccess && splits > 1) {
       ++g_split_launches;
-      ++g_packed_launches;
+      bool packed = true;  // counted as such: at most 64 queries per sequence
+      for (int b = 0; b < a.n_seqs; ++b) packed &= a.q_cu_host[b + 1] - a.q_cu_host[b] <= 64;
+      if (packed) ++g_packed_launches;
     }
     return e;
   }

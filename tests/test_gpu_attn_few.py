@@ -21,7 +21,7 @@ def B():
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("Hq,Hkv", [(4, 1), (2, 2), (6, 2), (16, 2)])
 @pytest.mark.parametrize("lens,plens", [([1], [31]), ([4], [4000]), ([5], [700]), ([16], [95]), ([17, 1], [300, 1500]),
-                                        ([33], [1000]), ([64, 64], [129, 640])])
+                                        ([33], [1000]), ([64, 64], [129, 640]), ([128, 100, 7], [900, 2300, 130])])
 def test_attention_few_queries(B, Hq, Hkv, dh, lens, plens):
     from tests import gpu_util as G
     from tests.helpers import kv_list, oracle_config, weights_fn
