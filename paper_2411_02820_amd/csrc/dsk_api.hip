@@ -323,17 +323,18 @@ bool takes_few_rows(const dsk_model* m, int n) {
 }
 
 // run_layer for few rows.  ready: m->xn and m->ssq already hold this layer's normalisation input (left by the layer in
-// front); g_next: gain of the next layer's input norm, whose input this layer then leaves (*left).
+// front); g_next: gain of the next layer's input norm, whose input this layer then leaves (*left); rope: the call's first
+// layer fills the rotary table (such a layer is never ready).
 int run_layer_few(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, int h_out_f32, char* k_layer, char* v_layer,
                   int64_t own_row0, const int32_t* q_cu, const int32_t* q_cu_host, const int32_t* p_cu, const int32_t* p_cu_host,
-                  int64_t n_pre_rows, int n_seqs, int n, hipStream_t s, bool ready, const void* g_next, bool* left) {
+                  int64_t n_pre_rows, int n_seqs, int n, hipStream_t s, bool ready, const void* g_next, bool* left, const RopeJob* rope) {
   const dsk_config_t& c = m->cfg;
   const LayerWeights& w = m->layers[l];
   const int d = c.hidden, F = c.ffn, nq = c.n_q_heads * c.head_dim;
   const int64_t own = own_row0 * c.n_kv_heads * c.head_dim * m->elem;
   const float eps = (float)c.rms_eps;
   *left = false;
-  if (!ready) HIP_TRY(launch_few_norm(h_in, h_in_f32, w.g1, m->xn, m->ssq, n, d, s));
+  if (!ready) HIP_TRY(launch_few_norm(h_in, h_in_f32, w.g1, m->xn, m->ssq, n, d, rope, s));
   HIP_TRY(launch_few_qkv(m->xn, m->ssq, eps, w.wqkv, m->qkv, m->n_qkv, m->rope_cs, k_layer + own, v_layer + own, n, d, c.n_q_heads,
                          c.n_kv_heads, c.head_dim, s));
   int rc = layer_attention(m, k_layer, v_layer, own_row0, q_cu, q_cu_host, p_cu, p_cu_host, n_pre_rows, n_seqs, n, 0, 1, s);
@@ -361,12 +362,13 @@ int run_layer_few(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_o
 // h_mid: fp32 rows that receive the state after the attention block (h_out may be the same rows); cs: rotary table
 // of the n tokens.  vt_first_row: rows of the layer's V before it are already in the transposed copy m->vt.
 // ready: m->xn already holds this layer's normalised input; g_next: gain of the next layer's input norm, whose output this
-// layer may leave there (*left).
+// layer may leave there (*left); rope: the rotary table is still to be filled.
 int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, int h_out_f32, char* k_layer,
               char* v_layer, int64_t own_row0,
               const int32_t* q_cu, const int32_t* q_cu_host, const int32_t* p_cu, const int32_t* p_cu_host,
               int64_t n_pre_rows, int n_seqs, int n, hipStream_t s, float* h_mid = nullptr, const float2* cs = nullptr,
-              int64_t vt_first_row = 0, bool ready = false, const void* g_next = nullptr, bool* left = nullptr) {
+              int64_t vt_first_row = 0, bool ready = false, const void* g_next = nullptr, bool* left = nullptr,
+              const RopeJob* rope = nullptr) {
   if (left) *left = false;
   if (!h_mid) h_mid = m->h;
   if (!cs) cs = m->rope_cs;
@@ -384,7 +386,13 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
   // bf16, rows that leave the chip unfilled: projections whose contraction is split do the step behind them in the reduction
   const bool can_split = c.dtype == DSK_BF16 && !g_force_generic && m->split_ws;
   auto splits = [&](int N, int K) { return can_split && gemm_mfma_splits(n, N, K, m->split_ws_bytes); };
-  if (!fp32_rope && !ready) HIP_TRY(launch_rmsnorm(c.dtype, h_in, h_in_f32 || all_f32, w.g1, m->xn, n, d, (float)c.rms_eps, s));
+  const bool norm_here = !fp32_rope && !ready;
+  if (rope && norm_here && !h_in_f32 && norm_takes_rope(c.dtype, n, d)) {
+    HIP_TRY(launch_rmsnorm_rope(h_in, w.g1, m->xn, n, d, (float)c.rms_eps, *rope, s));
+  } else {
+    if (rope) HIP_TRY(launch_rope_table(*rope, s));
+    if (norm_here) HIP_TRY(launch_rmsnorm(c.dtype, h_in, h_in_f32 || all_f32, w.g1, m->xn, n, d, (float)c.rms_eps, s));
+  }
   if (fp32_rope) {
     HIP_TRY(launch_gemm_fp32_norm_rope((const float*)h_in, w.g1, (float)c.rms_eps, w.wqkv, m->qkv, cs, k_own, v_own, n, d,
                                        c.n_q_heads, c.n_kv_heads, c.head_dim, s));
@@ -846,7 +854,8 @@ int dsk_partial_prefill_groups(dsk_model_t* model, const dsk_group_t* groups, in
   if (mode != DSK_LOAD_PIPELINED) HIP_TRY(hipStreamWaitEvent(s, m->ev_all, 0));  // strategies (a), (b): load, then compute
 
   // recompute the groups on the compute stream, each from its own E cache
-  bool table_done = false;
+  const RopeJob rope = {batch->positions_dev, m->theta, m->rope_cs, T, c.head_dim / 2};
+  bool table_done = false;  // the first recomputed layer fills the rotary table
   for (int g = 0; g < n_groups; ++g) {
     const dsk_group_t& G = groups[g];
     const void* h_cur = G.hidden_in;
@@ -865,8 +874,8 @@ int dsk_partial_prefill_groups(dsk_model_t* model, const dsk_group_t* groups, in
       return stage_e(groups[g + 1]);
     };
     if (G.hi > G.lo) {
-      if (!table_done) {
-        HIP_TRY(launch_rope_table(batch->positions_dev, m->theta, m->rope_cs, T, c.head_dim / 2, s));
+      if (!table_done && chunked) {  // (the chunks would each fill their part; one launch here)
+        HIP_TRY(launch_rope_table(rope, s));
         table_done = true;
       }
       const bool few = takes_few_rows(m, T);
@@ -899,12 +908,13 @@ int dsk_partial_prefill_groups(dsk_model_t* model, const dsk_group_t* groups, in
         if (few)
           rc = run_layer_few(m, l, h_cur, l > G.lo, h_next, !last, kv_k(kv_out, l), kv_v(kv_out, l), 0, batch->cu_seqlens_dev,
                              batch->cu_seqlens_host, nullptr, nullptr, 0, batch->n_seqs, T, s, ready,
-                             l + 1 < G.hi ? m->layers[l + 1].g1 : nullptr, &ready);
+                             l + 1 < G.hi ? m->layers[l + 1].g1 : nullptr, &ready, table_done ? nullptr : &rope);
         else
           rc = run_layer(m, l, h_cur, l > G.lo, h_next, !last, kv_k(kv_out, l), kv_v(kv_out, l), 0, batch->cu_seqlens_dev,
                          batch->cu_seqlens_host, nullptr, nullptr, 0, batch->n_seqs, T, s, nullptr, nullptr, 0, ready,
-                         l + 1 < G.hi ? m->layers[l + 1].g1 : nullptr, &ready);
+                         l + 1 < G.hi ? m->layers[l + 1].g1 : nullptr, &ready, table_done ? nullptr : &rope);
         if (rc) return rc;
+        table_done = true;
         h_cur = h_next;
         if (l == G.lo && next_host && (rc = hand_over_stage())) return rc;
       }
@@ -949,7 +959,7 @@ int dsk_suffix_prefill(dsk_model_t* model, const void* suffix_hidden_in, const d
   if ((rc = check_kv(m, kv, suffix_row0 + S, true))) return rc;
 
   hipStream_t s = (hipStream_t)stream;
-  HIP_TRY(launch_rope_table(suffix->positions_dev, m->theta, m->rope_cs, S, c.head_dim / 2, s));
+  const RopeJob rope = {suffix->positions_dev, m->theta, m->rope_cs, S, c.head_dim / 2};
   const void* h_cur = suffix_hidden_in;
   const bool few = takes_few_rows(m, S);
   bool ready = false;  // the layer in front has left this layer's norm input in the workspace
@@ -963,11 +973,12 @@ int dsk_suffix_prefill(dsk_model_t* model, const void* suffix_hidden_in, const d
     if (few)
       rc = run_layer_few(m, l, h_cur, l > 0, h_next, !last, kv_k(kv, l), kv_v(kv, l), suffix_row0, suffix->cu_seqlens_dev,
                          suffix->cu_seqlens_host, prefix->cu_seqlens_dev, prefix->cu_seqlens_host, prefix->n_tokens,
-                         suffix->n_seqs, S, s, ready, last ? nullptr : m->layers[l + 1].g1, &ready);
+                         suffix->n_seqs, S, s, ready, last ? nullptr : m->layers[l + 1].g1, &ready, l == 0 ? &rope : nullptr);
     else
       rc = run_layer(m, l, h_cur, l > 0, h_next, !last, kv_k(kv, l), kv_v(kv, l), suffix_row0, suffix->cu_seqlens_dev,
                      suffix->cu_seqlens_host, prefix->cu_seqlens_dev, prefix->cu_seqlens_host, prefix->n_tokens,
-                     suffix->n_seqs, S, s, nullptr, nullptr, 0, ready, last ? nullptr : m->layers[l + 1].g1, &ready);
+                     suffix->n_seqs, S, s, nullptr, nullptr, 0, ready, last ? nullptr : m->layers[l + 1].g1, &ready,
+                     l == 0 ? &rope : nullptr);
     if (rc) return rc;
     h_cur = h_next;
   }

@@ -38,6 +38,18 @@ struct LayerWeights {
 
 constexpr int DSK_MAX_E_CHUNKS = 16;
 
+// The rotary table of a call: cs[t][j] = (cos, sin) of pos[t] * theta[j], angle and sincos in fp64, stored as fp32.  The
+// first norm of a call over few rows fills it as well (one launch of some 5 us less in front of the first projection).
+struct RopeJob { const int32_t* pos; const double* theta; float2* cs; int T, half; };
+__device__ __forceinline__ void rope_entry(const RopeJob& j, int64_t i) {
+  if (i >= (int64_t)j.T * j.half) return;
+  const int t = (int)(i / j.half), k = (int)(i - (int64_t)t * j.half);
+  double s, c;
+  sincos((double)j.pos[t] * j.theta[k], &s, &c);
+  j.cs[i] = make_float2((float)c, (float)s);
+}
+inline unsigned rope_blocks(const RopeJob& j) { return (unsigned)(((int64_t)j.T * j.half + 255) / 256); }
+
 struct dsk_model {
   dsk_config_t cfg;
   int elem;         // bytes per element
@@ -130,7 +142,9 @@ hipError_t launch_gemm_split_norm(const void* A, const void* W, int w_blocks, fl
 // the RMSNorm in front of it) done by the projection.  a = bf16(h * gain) in blocks, ssq [d/16][64] its sums of squares.
 bool few_rows_supported(int M, int d, int F, int Hq, int Hkv, int dh);
 int64_t few_rows_workspace_bytes(int d, int K_max);
-hipError_t launch_few_norm(const void* h, int h_f32, const void* gain, void* a, float* ssq, int M, int d, hipStream_t s);
+// rope: also fills the rotary table (may be null)
+hipError_t launch_few_norm(const void* h, int h_f32, const void* gain, void* a, float* ssq, int M, int d, const RopeJob* rope,
+                           hipStream_t s);
 hipError_t launch_few_qkv(const void* a, const float* ssq, float eps, const void* W, void* qkv, int64_t ldq, const float2* cs,
                           void* k_rows, void* v_rows, int M, int d, int Hq, int Hkv, int dh, hipStream_t s);
 // act (blocks, [M, N/2]) = silu(gate) * up
@@ -171,7 +185,10 @@ hipError_t launch_splice(const void* src, int64_t src_stride, int64_t src_v, voi
 // pacing of the load stream against the 100 MHz constant-rate clock
 hipError_t launch_pace_start(unsigned long long* t0, hipStream_t s);
 hipError_t launch_pace_wait(const unsigned long long* t0, unsigned long long ticks, hipStream_t s);
-hipError_t launch_rope_table(const int32_t* pos, const double* theta, float2* cs, int T, int half, hipStream_t s);
+hipError_t launch_rope_table(const RopeJob& rope, hipStream_t s);
+// RMSNorm of the first layer and the rotary table in one launch, where norm_takes_rope says so (bf16, up to 512 rows)
+bool norm_takes_rope(int dtype, int T, int d);
+hipError_t launch_rmsnorm_rope(const void* x, const void* g, void* y, int T, int d, float eps, const RopeJob& rope, hipStream_t s);
 // rotates q (in place) and k of qkv [T, n_qkv]; writes rotated k and v to the cache rows row0..row0+T-1
 hipError_t launch_rope_kv_write(int dtype, void* qkv, const float2* cs, void* k_rows, void* v_rows, int T, int Hq,
                                 int Hkv, int dh, hipStream_t s);

@@ -240,8 +240,8 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
   }
 }
 
-// What stream_kernel's EP_RES does, for a contraction split over workgroups (partial sums P, added in split order), or with
-// no projection in front (splits = 0: the input norm of the first layer).  One thread per 4 columns of a row.
+// What stream_kernel's EP_RES does, for a contraction split over workgroups (partial sums P, added in split order).  One
+// thread per 4 columns of a row.
 __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restrict__ P, int splits, const void* R, int r_f32,
                                                            void* C, int c_f32, const bf16_t* __restrict__ gain,
                                                            bf16_t* __restrict__ a, float* __restrict__ ssq_out, int M, int N) {
@@ -249,7 +249,7 @@ __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restri
   const bool in = i < M * quads;
   const int m = in ? i / quads : 0, n = in ? (i - m * quads) * 4 : 0;
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
-  if (in && splits > 0) {
+  if (in) {
     f32x4 b[4];
     const int64_t stride = (int64_t)M * N;
     const float* src = P + (int64_t)m * N + n;
@@ -336,6 +336,20 @@ __global__ void __launch_bounds__(256) few_combine_kernel(const float* __restric
   residual_quad<1, 2>(v, m, n, N, in, R, 1, C, c_f32, gain, a, ssq_out);
 }
 
+// The input norm of a call's first layer and the call's rotary table: workgroups 0 .. n_norm-1, and those behind them.
+__global__ void __launch_bounds__(256) few_norm_rope_kernel(const void* h, int h_f32, const bf16_t* __restrict__ gain,
+                                                            bf16_t* __restrict__ a, float* __restrict__ ssq_out, int M, int N,
+                                                            int n_norm, RopeJob rope) {
+  if ((int)blockIdx.x >= n_norm) {
+    rope_entry(rope, (int64_t)((int)blockIdx.x - n_norm) * 256 + threadIdx.x);
+    return;
+  }
+  const int i = blockIdx.x * 256 + threadIdx.x, quads = N / 4;
+  const bool in = i < M * quads;
+  const int m = in ? i / quads : 0, n = in ? (i - m * quads) * 4 : 0;
+  residual_quad<1, 2>(f32x4{0.f, 0.f, 0.f, 0.f}, m, n, N, in, h, h_f32, nullptr, 0, gain, a, ssq_out);
+}
+
 template <int MT, int NT, int KW, int PF, int KS, int EP>
 hipError_t launch_stream(const StreamArgs& p, int tiles, int splits, hipStream_t s, int n_experts = 1) {
   auto kern = stream_kernel<MT, NT, KW, PF, KS, EP>;
@@ -375,9 +389,12 @@ int64_t few_rows_workspace_bytes(int d, int K_max) {
   return (int64_t)(s > 0 ? s : 1) * 64 * d * 4;
 }
 
-hipError_t launch_few_norm(const void* h, int h_f32, const void* gain, void* a, float* ssq, int M, int d, hipStream_t s) {
-  hipLaunchKernelGGL(few_residual_kernel, dim3((M * (d / 4) + 255) / 256), dim3(256), 0, s, (const float*)nullptr, 0, h, h_f32,
-                     (void*)nullptr, 0, (const bf16_t*)gain, (bf16_t*)a, ssq, M, d);
+hipError_t launch_few_norm(const void* h, int h_f32, const void* gain, void* a, float* ssq, int M, int d, const RopeJob* rope,
+                           hipStream_t s) {
+  const int n_norm = (M * (d / 4) + 255) / 256;
+  const RopeJob job = rope ? *rope : RopeJob{};
+  hipLaunchKernelGGL(few_norm_rope_kernel, dim3(n_norm + rope_blocks(job)), dim3(256), 0, s, h, h_f32, (const bf16_t*)gain, (bf16_t*)a,
+                     ssq, M, d, n_norm, job);
   return hipGetLastError();
 }
 

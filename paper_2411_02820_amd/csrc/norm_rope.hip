@@ -40,11 +40,16 @@ __device__ __forceinline__ f32x4_t load4(const bf16_t* p) {
 }
 
 // Same for bf16 output with d a multiple of 4 and d <= 4*256*NCH: the row is read once (16- or 8-byte
-// vectors), kept in registers across the reduction, and written as 8-byte vectors.
-template <typename TX, int NCH>
+// vectors), kept in registers across the reduction, and written as 8-byte vectors.  ROPE: the workgroups past the T rows
+// fill the rotary table.
+template <typename TX, int NCH, bool ROPE = false>
 __global__ void __launch_bounds__(256) rmsnorm_vec_kernel(const TX* __restrict__ x, const bf16_t* __restrict__ g,
-                                                          bf16_t* __restrict__ y, int d, float eps) {
+                                                          bf16_t* __restrict__ y, int d, float eps, RopeJob rope) {
   __shared__ float part[4];
+  if (ROPE && (int)blockIdx.x >= rope.T) {
+    rope_entry(rope, (int64_t)((int)blockIdx.x - rope.T) * 256 + threadIdx.x);
+    return;
+  }
   const TX* xr = x + (int64_t)blockIdx.x * d;
   bf16_t* yr = y + (int64_t)blockIdx.x * d;
   f32x4_t v[NCH];
@@ -75,16 +80,7 @@ __global__ void __launch_bounds__(256) rmsnorm_vec_kernel(const TX* __restrict__
   }
 }
 
-// cos/sin of position * theta_i, angle and sincos in fp64, stored as fp32.
-__global__ void rope_table_kernel(const int32_t* __restrict__ pos, const double* __restrict__ theta,
-                                  float2* __restrict__ cs, int T, int half) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)T * half) return;
-  int t = (int)(i / half), j = (int)(i - (int64_t)t * half);
-  double s, c;
-  sincos((double)pos[t] * theta[j], &s, &c);
-  cs[i] = make_float2((float)c, (float)s);
-}
+__global__ void __launch_bounds__(256) rope_table_kernel(RopeJob rope) { rope_entry(rope, (int64_t)blockIdx.x * 256 + threadIdx.x); }
 
 // One block per token.  q and k heads: pair (i, i+dh/2) rotated; rotated k and v go to the cache rows.
 template <typename T>
@@ -209,14 +205,14 @@ hipError_t launch_rmsnorm(int dtype, const void* x, int x_f32, const void* g, vo
     hipLaunchKernelGGL((rmsnorm_kernel<float, float>), dim3(T), dim3(256), 0, s, (const float*)x, (const float*)g, (float*)y, d, eps);
   else if (d % 4 == 0 && d <= 4096) {
     if (x_f32)
-      hipLaunchKernelGGL((rmsnorm_vec_kernel<float, 4>), dim3(T), dim3(256), 0, s, (const float*)x, (const bf16_t*)g, (bf16_t*)y, d, eps);
+      hipLaunchKernelGGL((rmsnorm_vec_kernel<float, 4>), dim3(T), dim3(256), 0, s, (const float*)x, (const bf16_t*)g, (bf16_t*)y, d, eps, RopeJob{});
     else
-      hipLaunchKernelGGL((rmsnorm_vec_kernel<bf16_t, 4>), dim3(T), dim3(256), 0, s, (const bf16_t*)x, (const bf16_t*)g, (bf16_t*)y, d, eps);
+      hipLaunchKernelGGL((rmsnorm_vec_kernel<bf16_t, 4>), dim3(T), dim3(256), 0, s, (const bf16_t*)x, (const bf16_t*)g, (bf16_t*)y, d, eps, RopeJob{});
   } else if (d % 4 == 0 && d <= 8192) {
     if (x_f32)
-      hipLaunchKernelGGL((rmsnorm_vec_kernel<float, 8>), dim3(T), dim3(256), 0, s, (const float*)x, (const bf16_t*)g, (bf16_t*)y, d, eps);
+      hipLaunchKernelGGL((rmsnorm_vec_kernel<float, 8>), dim3(T), dim3(256), 0, s, (const float*)x, (const bf16_t*)g, (bf16_t*)y, d, eps, RopeJob{});
     else
-      hipLaunchKernelGGL((rmsnorm_vec_kernel<bf16_t, 8>), dim3(T), dim3(256), 0, s, (const bf16_t*)x, (const bf16_t*)g, (bf16_t*)y, d, eps);
+      hipLaunchKernelGGL((rmsnorm_vec_kernel<bf16_t, 8>), dim3(T), dim3(256), 0, s, (const bf16_t*)x, (const bf16_t*)g, (bf16_t*)y, d, eps, RopeJob{});
   } else if (x_f32)
     hipLaunchKernelGGL((rmsnorm_kernel<float, bf16_t>), dim3(T), dim3(256), 0, s, (const float*)x, (const bf16_t*)g, (bf16_t*)y, d, eps);
   else
@@ -224,10 +220,21 @@ hipError_t launch_rmsnorm(int dtype, const void* x, int x_f32, const void* g, vo
   return hipGetLastError();
 }
 
-hipError_t launch_rope_table(const int32_t* pos, const double* theta, float2* cs, int T, int half, hipStream_t s) {
-  if (T <= 0) return hipSuccess;
-  int64_t n = (int64_t)T * half;
-  hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pos, theta, cs, T, half);
+hipError_t launch_rope_table(const RopeJob& rope, hipStream_t s) {
+  if (rope.T <= 0) return hipSuccess;
+  hipLaunchKernelGGL(rope_table_kernel, dim3(rope_blocks(rope)), dim3(256), 0, s, rope);
+  return hipGetLastError();
+}
+
+// One launch less: 246 -> 241 us for an 8B layer over 333 rows.  But the fp64 sincos takes the norm to where fewer waves fit a
+// compute unit: from about a thousand rows it loses (1145 -> 1152 us, two layers over 1024), where the norm is
+// bound by memory.
+bool norm_takes_rope(int dtype, int T, int d) { return dtype == DSK_BF16 && T <= 512 && d % 4 == 0 && d <= 8192; }
+
+hipError_t launch_rmsnorm_rope(const void* x, const void* g, void* y, int T, int d, float eps, const RopeJob& rope, hipStream_t s) {
+  if (rope.T != T || !norm_takes_rope(DSK_BF16, T, d)) return hipErrorNotSupported;
+  auto kern = d <= 4096 ? rmsnorm_vec_kernel<bf16_t, 4, true> : rmsnorm_vec_kernel<bf16_t, 8, true>;
+  hipLaunchKernelGGL(kern, dim3(T + rope_blocks(rope)), dim3(256), 0, s, (const bf16_t*)x, (const bf16_t*)g, (bf16_t*)y, d, eps, rope);
   return hipGetLastError();
 }
 
