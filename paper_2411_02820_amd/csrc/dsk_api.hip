@@ -69,7 +69,7 @@ void free_model(dsk_model* m) {
     if (m->ev_e_chunk[i]) (void)hipEventDestroy(m->ev_e_chunk[i]);
   (void)hipFree(m->chunk_cu);
   (void)hipFree(m->moe_experts); (void)hipFree(m->moe_gates); (void)hipFree(m->moe_slot); (void)hipFree(m->moe_src);
-  (void)hipFree(m->moe_tab); (void)hipFree(m->moe_xg); (void)hipFree(m->moe_y);
+  (void)hipFree(m->moe_tab); (void)hipFree(m->moe_y);
   if (m->load_stream) (void)hipStreamDestroy(m->load_stream);
   free(m->pending);
   free(m);
@@ -255,12 +255,12 @@ int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, 
   const bool tensor_cores = c.dtype == DSK_BF16 && !g_force_generic;
   if (tensor_cores && n > 64) {
     if (m->gu_block != 32) return DSK_ESHAPE;
-    int tile_rows = moe_tile_table_rows((int64_t)n * k, E);
+    const int tile_m = moe_tile_rows_for((int64_t)n * k, E);
+    int tile_rows = moe_tile_table_rows((int64_t)n * k, E, tile_m);
     if (tile_rows > m->moe_tile_rows) tile_rows = m->moe_tile_rows;
-    HIP_TRY(launch_moe_place(m->moe_experts, m->moe_slot, m->moe_src, m->moe_tab, n, k, E, 256, tile_rows, s));
-    HIP_TRY(launch_moe_gather(c.dtype, m->xn, m->moe_src, m->moe_xg, n * k, n, d, s));
+    HIP_TRY(launch_moe_place(m->moe_experts, m->moe_slot, m->moe_src, m->moe_tab, n, k, E, tile_m, tile_rows, s));
     // under "time_gemm" the two grouped launches are bracketed like the other prefill projections (n*k rows each)
-    auto grouped = [&](const void* A, int64_t lda, const void* W, int64_t ldw, int64_t w_stride, void* C, int64_t ldc, int N,
+    auto grouped = [&](const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw, int64_t w_stride, void* C, int64_t ldc, int N,
                        int K, int epi) -> int {
       std::unique_lock<std::mutex> timed_lock(g_stats.timed_mu, std::defer_lock);
       bool timed = false;
@@ -268,16 +268,17 @@ int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, 
         timed_lock.lock();
         HIP_TRY(g_stats.gemm.begin(s, &timed));
       }
-      const hipError_t e = launch_gemm_mfma_grouped(A, lda, (int64_t)n * k, W, ldw, m->w_blocks, w_stride, C, ldc, N, K, epi, m->moe_tab,
-                                                    tile_rows, s);
+      const hipError_t e = launch_gemm_mfma_grouped(A, lda, a_rows, a_row, W, ldw, m->w_blocks, w_stride, C, ldc, N, K, epi, m->moe_tab,
+                                                    tile_m, tile_rows, s);
       if (e != hipSuccess && timed) g_stats.gemm.abandon();
       HIP_TRY(e);
       ++g_stats.gemm_mfma;
       if (timed) HIP_TRY(g_stats.gemm.end(s, 2.0 * n * k * N * K));
       return DSK_OK;
     };
-    int rc = grouped(m->moe_xg, d, w.wgu, d, wgu_stride, m->act, F, 2 * F, d, EPI_SWIGLU);
-    if (rc == DSK_OK) rc = grouped(m->act, F, w.wd, F, wd_stride, m->moe_y, d, d, F, EPI_C_F32);
+    // gate/up reads the token rows where they are; its result, and what follows, is in sorted order
+    int rc = grouped(m->xn, d, n, m->moe_src, w.wgu, d, wgu_stride, m->act, F, 2 * F, d, EPI_SWIGLU);
+    if (rc == DSK_OK) rc = grouped(m->act, F, (int64_t)n * k, nullptr, w.wd, F, wd_stride, m->moe_y, d, d, F, EPI_C_F32);
     if (rc) return rc;
     HIP_TRY(launch_moe_combine(m->moe_y, h_mid, m->moe_gates, m->moe_experts, m->moe_slot, h_out, out_f32, n, d, k,
                                (int64_t)n * k, s));
@@ -587,13 +588,12 @@ int dsk_model_create(const dsk_config_t* cfg, int64_t max_tokens, int64_t max_kv
   if (rc == DSK_OK) rc = alloc_dev(&m->act, act_rows * F * elem, &m->workspace_bytes);
   if (rc == DSK_OK && E > 0) {
     m->moe_y_rows = (int64_t)E * T;  // every expert over all rows (few rows, fp32, "force_generic"); grouped: T * top_k
-    m->moe_tile_rows = moe_tile_table_rows(T * top_k, E);
+    m->moe_tile_rows = moe_tile_table_rows(T * top_k, E, 128);  // the lowest tile: enough for any
     rc = alloc_dev((void**)&m->moe_experts, T * top_k * 4, &m->workspace_bytes);
     if (rc == DSK_OK) rc = alloc_dev((void**)&m->moe_gates, T * top_k * 4, &m->workspace_bytes);
     if (rc == DSK_OK) rc = alloc_dev((void**)&m->moe_slot, T * top_k * 4, &m->workspace_bytes);
     if (rc == DSK_OK) rc = alloc_dev((void**)&m->moe_src, T * top_k * 4, &m->workspace_bytes);
     if (rc == DSK_OK) rc = alloc_dev(&m->moe_tab, ((int64_t)m->moe_tile_rows + 1) * 16, &m->workspace_bytes);
-    if (rc == DSK_OK && moe_grouped) rc = alloc_dev(&m->moe_xg, T * top_k * d * elem, &m->workspace_bytes);
     if (rc == DSK_OK) rc = alloc_dev((void**)&m->moe_y, m->moe_y_rows * d * 4, &m->workspace_bytes);
   }
   if (rc == DSK_OK) rc = alloc_dev((void**)&m->h, T * d * 4, &m->workspace_bytes);

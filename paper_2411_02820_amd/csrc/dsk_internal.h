@@ -86,7 +86,6 @@ struct dsk_model {
   int32_t* moe_src;      // [maxT*top_k]  token of every grouped row
   void* moe_tab;         // int4 [moe_tile_rows] row tiles of the grouped projections
   int moe_tile_rows;
-  void* moe_xg;          // [maxT*top_k, d] normalised activations, grouped by expert
   float* moe_y;          // expert outputs, fp32: [maxT*top_k, d] grouped, or [E][n][d] when every expert runs over all rows
   int64_t moe_y_rows;
   int64_t workspace_bytes;
@@ -241,16 +240,16 @@ hipError_t launch_moe_route(int dtype, const void* xn, const void* wr, int32_t* 
 // tile_tab: int4 [tile_rows_max + 1] (the last entry receives the number of tiles)
 hipError_t launch_moe_place(const int32_t* experts, int32_t* slot_of, int32_t* src_token, void* tile_tab, int n, int top_k,
                             int E, int tile_m, int tile_rows_max, hipStream_t s);
-// rows of the grouped projections' tile table for n_rows rows over E experts (every expert may end in a partial tile)
-inline int moe_tile_table_rows(int64_t n_rows, int E) { return (int)((n_rows + 255) / 256) + E; }
-hipError_t launch_moe_gather(int dtype, const void* xn, const int32_t* src_token, void* xg, int n_slots, int n_tokens, int d,
-                             hipStream_t s);
+// rows of the grouped projections' tile table for n_rows rows over E experts in tiles of tile_m (every expert may end in a
+// partial tile)
+int moe_tile_rows_for(int64_t n_rows, int E);
+inline int moe_tile_table_rows(int64_t n_rows, int E, int tile_m) { return (int)((n_rows + tile_m - 1) / tile_m) + E; }
 hipError_t launch_moe_combine(const float* y, const float* h_mid, const float* gates, const int32_t* experts,
                               const int32_t* slot_of, void* out, int out_f32, int n, int d, int top_k, int64_t y_rows,
                               hipStream_t s);
-hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const void* W, int64_t ldw, int w_blocks,
-                                    int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
-                                    const void* tile_tab, int tile_rows, hipStream_t s);
+hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw,
+                                    int w_blocks, int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
+                                    const void* tile_tab, int tile_m, int tile_rows, hipStream_t s);
 
 // tuning knobs (dsk_set_option)
 void gemm_mfma_set_variant(int v);

@@ -455,13 +455,14 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 // GROUPED (the expert projections of a mixture-of-experts layer): the token rows are sorted by expert, and row tile
 // tm of the grid is described by tile_tab[tm] = {expert, first row, end of the expert's rows, -} (built on the
 // device; tile_tab[tiles_m].x = number of tiles that exist; expert < 0: no such tile, the workgroup leaves); the
-// expert's matrix is W + expert * w_group_stride.
+// expert's matrix is W + expert * w_group_stride.  a_row (optional): sorted row r is row a_row[r] of A's a_rows rows, so
+// that the rows are read where they are (gathered into a buffer first they cost 38 us more at 8192 tokens).
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false>
 __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     gemm16_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W_all, int64_t ldw,
                        void* C, int64_t ldc, const void* __restrict__ R, int64_t ldr, int M_all, int N, int K,
                        int epi, int tiles_m, int tiles_n, int kt_per_split, const int4* __restrict__ tile_tab,
-                       int64_t w_group_stride) {
+                       int64_t w_group_stride, const int32_t* __restrict__ a_row, int a_rows) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
   constexpr int TM = WTM / 16, TN = WTN / 16;  // 16x16 MFMA tiles per wave
@@ -512,7 +513,9 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 #pragma unroll
   for (int i = 0; i < A_INST; ++i) {
     int row = RPI * (wave * A_INST + i) + lr;
-    a_off[i] = (uint32_t)(((int64_t)min(m0 + row, M - 1) * lda + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
+    int ar = min(m0 + row, M - 1);
+    if (GROUPED && a_row) ar = min(max(a_row[ar], 0), a_rows - 1);  // always inside A, whatever the table holds
+    a_off[i] = (uint32_t)(((int64_t)ar * lda + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
   }
 #pragma unroll
   for (int i = 0; i < W_INST; ++i) {
@@ -858,7 +861,7 @@ hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw,
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   DSK_LAUNCH_TIMED(kern, dim3(tiles_m * tiles_n, splits), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
                    (const bf16_t*)W, ldw, C, ldc, R, ldr, M, N, K, epi, tiles_m, tiles_n, kt_per_split, (const int4*)nullptr,
-                   (int64_t)0);
+                   (int64_t)0, (const int32_t*)nullptr, 0);
   return hipGetLastError();
 }
 
@@ -873,8 +876,9 @@ hipError_t launch16(int bm, const void* A, int64_t lda, const void* W, int64_t l
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N>
-hipError_t launch16_grouped(const void* A, int64_t lda, const void* W, int64_t ldw, int64_t w_group_stride, void* C,
-                            int64_t ldc, int N, int K, int epi, const int4* tile_tab, int tile_rows, hipStream_t s) {
+hipError_t launch16_grouped(const void* A, int64_t lda, const int32_t* a_row, int a_rows, const void* W, int64_t ldw,
+                            int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi, const int4* tile_tab, int tile_rows,
+                            hipStream_t s) {
   auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, true, true>;
   constexpr int lds = NSTAGE * (BM + BN) * BK * 2;
   static bool configured = false;
@@ -886,7 +890,7 @@ hipError_t launch16_grouped(const void* A, int64_t lda, const void* W, int64_t l
   const int tiles_n = (N + BN - 1) / BN;
   DSK_LAUNCH_TIMED(kern, dim3(tile_rows * tiles_n), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
                    (const bf16_t*)W, ldw, C, ldc, (const void*)nullptr, (int64_t)0, 0, N, K, epi, tile_rows, tiles_n,
-                   K / BK, tile_tab, w_group_stride);
+                   K / BK, tile_tab, w_group_stride, a_row, a_rows);
   return hipGetLastError();
 }
 
@@ -1013,18 +1017,26 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
   }
 }
 
-// Projections of a mixture-of-experts layer over token rows sorted by expert: one launch over all experts, on the
-// 256-row prefill tiling.  tile_tab[0..tile_rows) describes the row tiles and tile_tab[tile_rows] holds their number
-// (see the kernel); rows of A and C are the sorted slots.  epi: EPI_SWIGLU (C bf16 [slots, N/2]) or EPI_C_F32 / EPI_STORE (C [slots, N]); no residual.
-hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const void* W, int64_t ldw, int w_blocks,
-                                    int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
-                                    const void* tile_tab, int tile_rows, hipStream_t s) {
+// Row tile of the grouped projections: 256 rows, lower where an expert has fewer (all its rows in one tile, with room for
+// the spread of a balanced router).
+int moe_tile_rows_for(int64_t n_rows, int E) {
+  const int64_t avg = n_rows / E;
+  return avg <= 104 ? 128 : avg <= 168 ? 192 : 256;
+}
+
+// Projections of a mixture-of-experts layer over token rows sorted by expert: one launch over all experts.
+// tile_tab[0..tile_rows) describes the tiles of tile_m rows and tile_tab[tile_rows] holds their number (see the kernel);
+// rows of C are the sorted slots, rows of A too unless a_row says where they are.  sorted_rows: number of slots.
+// epi: EPI_SWIGLU (C bf16 [slots, N/2]) or EPI_C_F32 / EPI_STORE (C [slots, N]); no residual.
+hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw,
+                                    int w_blocks, int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
+                                    const void* tile_tab, int tile_m, int tile_rows, hipStream_t s) {
   if (tile_rows <= 0) return hipSuccess;
   // (a model the tensor-core path takes has its weights in blocks)
   if (!w_blocks || K < BK || K % BK || N % 64 || (lda & 7) || (ldw & 7) || (ldc & 3) || (epi & EPI_RESIDUAL)) return hipErrorNotSupported;
   if (a_rows * lda * 2 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 2 >= ((int64_t)1 << 32)) return hipErrorNotSupported;
-  return launch16_grouped<256, 256, 2, 4>(A, lda, W, ldw, w_group_stride, C, ldc, N, K, epi, (const int4*)tile_tab,
-                                          tile_rows, s);
+  auto f = tile_m == 128 ? launch16_grouped<128, 256, 2, 4> : tile_m == 192 ? launch16_grouped<192, 256, 2, 4> : launch16_grouped<256, 256, 2, 4>;
+  return f(A, lda, a_row, (int)a_rows, W, ldw, w_group_stride, C, ldc, N, K, epi, (const int4*)tile_tab, tile_rows, s);
 }
 
 // More than 64 rows, dense operands: whether the contraction is split, i.e. a reduction runs behind the projection, which

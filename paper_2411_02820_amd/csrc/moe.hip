@@ -98,6 +98,78 @@ __global__ void __launch_bounds__(256) moe_route_kernel(const T* __restrict__ xn
   }
 }
 
+// The same choice on the matrix cores, for bf16 rows of whole 32-element steps and more than a few tokens: one workgroup per
+// 16 tokens, its four waves take every fourth step of the contraction (v_mfma_f32_16x16x32_bf16, fp32 accumulation; experts
+// are the MFMA rows in NT blocks of 16), partial logits meet in LDS in wave order.  Bound by reading the rows once (67 MB at
+// 8192 x 4096); the kernel above re-reads all router weights per token from the L2s: 41 us there, with this one 19 us.
+template <int NT>
+__global__ void __launch_bounds__(256) moe_route_mfma_kernel(const bf16_t* __restrict__ xn, const bf16_t* __restrict__ wr,
+                                                             int32_t* __restrict__ experts, float* __restrict__ gates, int n, int d,
+                                                             int E, int top_k) {
+  typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  constexpr int PF = NT <= 2 ? 8 : 4;  // steps in flight
+  __shared__ float part[4][16][16 * NT + 1];
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4, wave = tid >> 6;
+  const int t0 = blockIdx.x * 16;
+  const bf16_t* x = xn + (int64_t)min(t0 + r16, n - 1) * d + 8 * g;
+  const bf16_t* w[NT];
+  f32x4 acc[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    w[j] = wr + (int64_t)min(16 * j + r16, E - 1) * d + 8 * g;
+    acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const int steps = d / 32;
+  for (int s0 = wave; s0 < steps; s0 += 4 * PF) {
+    bf16x8 fx[PF], fw[PF][NT];
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+      if (s0 + 4 * u < steps) {
+        fx[u] = *(const bf16x8*)(x + (s0 + 4 * u) * 32);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) fw[u][j] = *(const bf16x8*)(w[j] + (s0 + 4 * u) * 32);
+      }
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+      if (s0 + 4 * u < steps)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[u][j], fx[u], acc[j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[wave][r16][16 * j + 4 * g + r] = acc[j][r];
+  __syncthreads();
+  for (int i = tid; i < 16 * E; i += 256) {
+    const int t = i / E, e = i - t * E;
+    const float v = part[0][t][e] + part[1][t][e] + part[2][t][e] + part[3][t][e];
+    part[0][t][e] = v == v ? v : -3.0e38f;  // only this thread reads and writes the entry
+  }
+  __syncthreads();
+  if (tid >= 16 || t0 + tid >= n) return;
+  float* logit = part[0][tid];
+  const int64_t at = (int64_t)(t0 + tid) * top_k;
+  float best[MAX_K], sum = 0.f;
+#pragma unroll
+  for (int j = 0; j < MAX_K; ++j) {
+    if (j >= top_k) break;
+    int b = 0;
+    for (int e = 1; e < E; ++e)
+      if (logit[e] > logit[b]) b = e;  // strictly greater: the lower index keeps a tie
+    best[j] = logit[b];
+    logit[b] = -INFINITY;
+    experts[at + j] = b;
+    sum += expf(best[j] - best[0]);
+  }
+  const float inv = 1.0f / sum;
+#pragma unroll
+  for (int j = 0; j < MAX_K; ++j) {
+    if (j >= top_k) break;
+    gates[at + j] = expf(best[j] - best[0]) * inv;
+  }
+}
+
 // Groups the n*top_k (token, choice) entries by expert, keeping token order inside an expert (so the result does not
 // depend on timing).  One workgroup per expert e: it counts the entries of every expert (LDS histogram), derives the
 // first slot of its own rows and the first row tile of its own tiles, then walks the entries in order and gives the
@@ -105,18 +177,19 @@ __global__ void __launch_bounds__(256) moe_route_kernel(const T* __restrict__ xn
 // tile_rows_max: {expert, first slot of the tile, end of the expert's slots, 0}, the tiles of all experts back to back,
 // expert -1 past the last tile; tile_tab[tile_rows_max].x = number of tiles (the GEMM spreads exactly those over the
 // chip: a grid sized for the worst case would leave the dies that get its empty end idle).
-__global__ void __launch_bounds__(256) moe_place_kernel(const int32_t* __restrict__ experts, int32_t* __restrict__ slot_of,
+constexpr int PLACE_T = 1024;  // threads: the walk is a chain of rounds, wider ones make it shorter (256: 23 us at 8192 tokens)
+__global__ void __launch_bounds__(PLACE_T) moe_place_kernel(const int32_t* __restrict__ experts, int32_t* __restrict__ slot_of,
                                                         int32_t* __restrict__ src_token, int4* __restrict__ tile_tab,
                                                         int n_entries, int top_k, int E, int tile_m, int tile_rows_max) {
   __shared__ int hist[DSK_MOE_MAX_EXPERTS];
-  __shared__ int wave_cnt[2][4][4];
+  __shared__ int wave_cnt[2][4][PLACE_T / 64];
   const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid < DSK_MOE_MAX_EXPERTS) hist[tid] = 0;
   __syncthreads();
-  for (int base = tid; base < n_entries; base += 1024) {
+  for (int base = tid; base < n_entries; base += 4 * PLACE_T) {
     int x[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) x[q] = base + 256 * q < n_entries ? experts[base + 256 * q] : -1;
+    for (int q = 0; q < 4; ++q) x[q] = base + PLACE_T * q < n_entries ? experts[base + PLACE_T * q] : -1;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       if ((unsigned)x[q] < (unsigned)E) atomicAdd(&hist[x[q]], 1);  // the router only writes experts below E
@@ -129,21 +202,21 @@ __global__ void __launch_bounds__(256) moe_place_kernel(const int32_t* __restric
   }
   const int mine = hist[e];
   const int my_tiles = (mine + tile_m - 1) / tile_m;
-  for (int r = tid; r < my_tiles; r += 256)
+  for (int r = tid; r < my_tiles; r += PLACE_T)
     if (first_tile + r < tile_rows_max) tile_tab[first_tile + r] = make_int4(e, first + r * tile_m, first + mine, 0);
   if (e == E - 1) {
-    for (int r = first_tile + my_tiles + tid; r < tile_rows_max; r += 256) tile_tab[r] = make_int4(-1, 0, 0, 0);
+    for (int r = first_tile + my_tiles + tid; r < tile_rows_max; r += PLACE_T) tile_tab[r] = make_int4(-1, 0, 0, 0);
     if (tid == 0) tile_tab[tile_rows_max] = make_int4(min(first_tile + my_tiles, tile_rows_max), 0, 0, 0);
   }
-  // rounds of 1024 entries, four groups of 256 in entry order; a thread's four entries are requested together (the
+  // rounds of 4 * PLACE_T entries, four groups of PLACE_T in entry order; a thread's four entries are requested together (the
   // walk is a chain of short rounds: what it takes is the round trips to memory)
   int running = 0;
   int buf = 0;
-  for (int base = 0; base < n_entries; base += 1024, buf ^= 1) {
+  for (int base = 0; base < n_entries; base += 4 * PLACE_T, buf ^= 1) {
     int ex[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int i = base + 256 * q + tid;
+      const int i = base + PLACE_T * q + tid;
       ex[q] = i < n_entries ? experts[i] : -1;
     }
     unsigned long long mask[4];
@@ -158,13 +231,13 @@ __global__ void __launch_bounds__(256) moe_place_kernel(const int32_t* __restric
       int before = __popcll(mask[q] & ((1ull << lane) - 1ull));
       int total = 0;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
+      for (int w = 0; w < PLACE_T / 64; ++w) {
         const int c = wave_cnt[buf][q][w];
         if (w < wave) before += c;
         total += c;
       }
       if (ex[q] == e) {
-        const int i = base + 256 * q + tid;
+        const int i = base + PLACE_T * q + tid;
         const int slot = first + running + before;
         slot_of[i] = slot;
         src_token[slot] = i / top_k;
@@ -172,19 +245,6 @@ __global__ void __launch_bounds__(256) moe_place_kernel(const int32_t* __restric
       running += total;
     }
   }
-}
-
-// xg[slot][:] = xn[src_token[slot]][:], rows of d elements moved 16 bytes at a time
-template <typename T>
-__global__ void __launch_bounds__(256) moe_gather_kernel(const T* __restrict__ xn, const int32_t* __restrict__ src_token,
-                                                         T* __restrict__ xg, int n_slots, int n_tokens, int d) {
-  const int per_row = d * (int)sizeof(T) / 16;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)n_slots * per_row) return;
-  const int slot = (int)(i / per_row), c = (int)(i - (int64_t)slot * per_row);
-  const int tok = min(max(src_token[slot], 0), n_tokens - 1);  // always inside xn, whatever the table holds
-  const int4* src = (const int4*)(xn + (int64_t)tok * d);
-  ((int4*)(xg + (int64_t)slot * d))[c] = src[c];
 }
 
 // out[t][:] = h_mid[t][:] + sum_j gates[t][j] * y[row(t, j)][:], j in the order of the router's list (highest logit
@@ -222,7 +282,10 @@ hipError_t launch_moe_route(int dtype, const void* xn, const void* wr, int32_t* 
   if (n <= 0) return hipSuccess;
   if (E < 1 || E > DSK_MOE_MAX_EXPERTS || top_k < 1 || top_k > MAX_K || top_k > E || d % 8) return hipErrorNotSupported;
   const dim3 grid((unsigned)((n + 3) / 4));
-  if (dtype == DSK_BF16)
+  if (dtype == DSK_BF16 && d % 32 == 0 && n > 64) {
+    auto kern = E <= 16 ? moe_route_mfma_kernel<1> : E <= 32 ? moe_route_mfma_kernel<2> : moe_route_mfma_kernel<4>;
+    hipLaunchKernelGGL(kern, dim3((n + 15) / 16), dim3(256), 0, s, (const bf16_t*)xn, (const bf16_t*)wr, experts, gates, n, d, E, top_k);
+  } else if (dtype == DSK_BF16)
     hipLaunchKernelGGL(moe_route_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)xn, (const bf16_t*)wr, experts, gates,
                        n, d, E, top_k);
   else
@@ -234,23 +297,8 @@ hipError_t launch_moe_route(int dtype, const void* xn, const void* wr, int32_t* 
 hipError_t launch_moe_place(const int32_t* experts, int32_t* slot_of, int32_t* src_token, void* tile_tab, int n, int top_k,
                             int E, int tile_m, int tile_rows_max, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(moe_place_kernel, dim3(E), dim3(256), 0, s, experts, slot_of, src_token, (int4*)tile_tab, n * top_k,
+  hipLaunchKernelGGL(moe_place_kernel, dim3(E), dim3(PLACE_T), 0, s, experts, slot_of, src_token, (int4*)tile_tab, n * top_k,
                      top_k, E, tile_m, tile_rows_max);
-  return hipGetLastError();
-}
-
-hipError_t launch_moe_gather(int dtype, const void* xn, const int32_t* src_token, void* xg, int n_slots, int n_tokens,
-                             int d, hipStream_t s) {
-  if (n_slots <= 0) return hipSuccess;
-  const int elem = dtype == DSK_BF16 ? 2 : 4;
-  const int64_t units = (int64_t)n_slots * (d * elem / 16);
-  const dim3 grid((unsigned)((units + 255) / 256));
-  if (dtype == DSK_BF16)
-    hipLaunchKernelGGL(moe_gather_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)xn, src_token, (bf16_t*)xg, n_slots,
-                       n_tokens, d);
-  else
-    hipLaunchKernelGGL(moe_gather_kernel<float>, grid, dim3(256), 0, s, (const float*)xn, src_token, (float*)xg, n_slots,
-                       n_tokens, d);
   return hipGetLastError();
 }
 

@@ -59,9 +59,11 @@ def test_split_contraction_matches_the_unsplit_one(B, rows):
 
 
 # experts without a token (9 choices over 64 experts, a single token), one choice, several tokens, row tilings 1 to 4; an
-# expert count that is no multiple of the router's eight
-@pytest.mark.parametrize("rows,E,k", [(1, 8, 2), (3, 64, 3), (17, 5, 1), (40, 9, 4), (64, 8, 2)])
-def test_expert_layers_over_few_rows_match_the_plain_kernels(B, rows, E, k):
+# expert count that is no multiple of the router's eight; and beyond 64 rows the grouped projections on each tile height
+# (about 17, 120, 140 and 300 rows an expert) with the matrix-core router over one, two and four blocks of experts
+@pytest.mark.parametrize("rows,E,k", [(1, 8, 2), (3, 64, 3), (17, 5, 1), (40, 9, 4), (64, 8, 2),
+                                      (70, 17, 4), (300, 5, 2), (350, 5, 2), (600, 4, 2), (900, 40, 3)])
+def test_expert_layers_match_the_plain_kernels(B, rows, E, k):
     from tests import gpu_util as G
     shape = synth.ModelShape(1, 320, 5, 1, 64, 192, 10000.0, 1e-5, "bf16", E, k)
     with G.GpuModel(shape, rows) as m:

@@ -55,3 +55,31 @@ def test_layers_with_split_projections(B, rows, d, Hq, Hkv, dh, F):
     # both are bf16 evaluations of the same layers, each within 1e-2 of the exact ones at this weight scale
     for a, b in ((kv, kv_ref), (h, h_ref)):
         assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2e-2
+
+
+# the router on the matrix cores: token counts around multiples of 16, one to four blocks of experts, contractions shorter
+# and longer than the steps in flight, a row of NaN; the choice must be one of the best by more than fp32 sums can differ
+@pytest.mark.parametrize("n,d,E,k", [(65, 32, 2, 1), (80, 320, 16, 2), (100, 4096, 17, 8), (129, 1056, 33, 3), (70, 2080, 64, 8)])
+def test_router_on_the_matrix_cores(B, n, d, E, k):
+    bf = lambda a: synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(a))
+    x, w = bf(synth.normal(n * d, 61, 0, 1.0).reshape(n, d)), bf(synth.normal(E * d, 61, 1, 0.05).reshape(E, d))
+    x[3] = np.nan
+    w[E - 1] = w[0]   # equal logits: the lower index goes first
+    dev = lambda a: torch.from_numpy(a).to(torch.bfloat16).cuda()
+    experts = torch.full((n, k), -7, dtype=torch.int32, device="cuda")
+    gates = torch.full((n, k), float("nan"), device="cuda")
+    B.dsk_moe_route(B.DSK_BF16, dev(x), dev(w), n, d, E, k, experts, gates)
+    torch.cuda.synchronize()
+    experts, gates = experts.cpu().numpy(), gates.cpu().numpy()
+    logits = x.astype(np.float64) @ w.astype(np.float64).T
+    assert np.all(np.sort(experts, axis=1)[:, 1:] != np.sort(experts, axis=1)[:, :-1]) and experts.min() >= 0 and experts.max() < E
+    for t in range(n):
+        if t == 3:
+            continue
+        got, best = logits[t, experts[t]], np.sort(logits[t])[::-1][:k]
+        # fp32 sums of d products: 2^-24 sqrt(d) of their scale, far below 1e-4
+        assert np.abs(got - best).max() <= 1e-4
+        assert np.abs(gates[t] - np.exp(got - got[0]) / np.exp(got - got[0]).sum()).max() <= 1e-4
+        if 0 in experts[t] and E - 1 in experts[t]:
+            assert list(experts[t]).index(0) < list(experts[t]).index(E - 1)
+        assert not (E - 1 in experts[t] and 0 not in experts[t])
