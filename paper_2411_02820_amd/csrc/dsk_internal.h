@@ -170,7 +170,7 @@ extern thread_local int g_last_hip_error;  // hipError_t of the last failed HIP 
 extern thread_local hipEvent_t g_launch_ev_start, g_launch_ev_stop;
 #define DSK_LAUNCH_TIMED(kern, grid, block, lds, stream, ...)                                                        \
   do {                                                                                                               \
-    if (g_launch_ev_start) {                                                                                         \
+    if (g_launch_ev_start || g_launch_ev_stop) {                                                                     \
       hipExtLaunchKernelGGL(kern, grid, block, lds, stream, g_launch_ev_start, g_launch_ev_stop, 0, __VA_ARGS__);    \
       g_launch_ev_start = g_launch_ev_stop = nullptr;                                                                \
     } else {                                                                                                         \

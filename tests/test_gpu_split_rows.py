@@ -20,7 +20,8 @@ def B():
 # contractions of a few k-tiles (unsplit) and many (split with an uneven last share), and more than one round of tiles
 @pytest.mark.parametrize("M,N,K,residual", [(65, 64, 64, False), (129, 516, 320, True), (191, 1028, 1984, False),
                                             (193, 256, 4096, True), (257, 2052, 1024, True), (385, 512, 8192, False),
-                                            (1025, 1024, 2048, True), (2000, 2560, 256, False), (3000, 5000, 192, True)])
+                                            (1025, 1024, 2048, True), (2000, 2560, 256, False), (3000, 5000, 192, True),
+                                            (4200, 4612, 128, True)])   # whole rounds and a rest, in two launches
 def test_linear_bf16_medium_rows(B, M, N, K, residual):
     bf = lambda a: synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(a))
     x = bf(synth.normal(M * K, 51, 0, 1.0).reshape(M, K))
