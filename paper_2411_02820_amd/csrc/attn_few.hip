@@ -1,4 +1,5 @@
-// Attention of few queries per sequence (at most 128: the suffix pass, a generation step) against a long cache, bf16.
+// Attention of few queries (at most 128 per sequence against a long cache: the suffix pass, a generation step; or the prefill
+// of a short prompt), bf16.
 //
 // Bound: the rate at which K and V arrive from HBM, and how soon the first of them do; then the softmax arithmetic of the
 // resident wave or two per SIMD.  So: the q heads of a kv group and their queries form one list of columns (query-major)
@@ -304,12 +305,19 @@ hipError_t launch_few(const FewParams& p, int64_t blocks, hipStream_t s) {
 
 }  // namespace
 
-// Sequences of at most 128 queries.  (Longer ones are bound by arithmetic, where the 32-query waves of attn_mfma.hip do more
-// per LDS read.)
+// Sequences of at most 128 queries; or a call too small to fill the chip with the 128-query workgroups of attn_mfma.hip (at
+// most 256 of them, up to 1024 queries) over short key ranges: there the transposed copy, a launch of its own, and the
+// latency of few wide workgroups weigh more.  A layer of the 8B shape over one prompt of 333 / 512 / 768 / 1024 tokens:
+// 241 -> 240, 289 -> 278, 399 -> 384, 472 -> 458 us; a 70B layer over 512 tokens 793 -> 776 us.  Past it the 32-query waves of
+// attn_mfma.hip do more per LDS read: 2048 tokens 798 there, 812 here, 8 x 512 tokens 1375 and 1389 us.
+// A chunked layer's later chunks need the transposed rows of this one.
 bool attn_few_supported(const AttnArgs& a) {
-  if ((a.dh != 128 && a.dh != 64) || (a.ldq & 7) || a.own_row0 + a.n_q >= ((int64_t)1 << 31)) return false;
-  for (int b = 0; b < a.n_seqs; ++b)
-    if (a.q_cu_host[b + 1] - a.q_cu_host[b] > 128) return false;
+  if ((a.dh != 128 && a.dh != 64) || (a.ldq & 7) || a.own_row0 + a.n_q >= ((int64_t)1 << 31) || a.keep_vt) return false;
+  const bool small = a.n_q <= 1024 && (int64_t)a.n_q * a.Hq <= 256 * 128;
+  for (int b = 0; b < a.n_seqs; ++b) {
+    const int len = a.q_cu_host[b + 1] - a.q_cu_host[b];
+    if (len > 128 && (!small || len + (a.p_cu_host ? a.p_cu_host[b + 1] - a.p_cu_host[b] : 0) > 1024)) return false;
+  }
   return true;
 }
 

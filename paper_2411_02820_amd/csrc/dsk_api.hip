@@ -307,10 +307,11 @@ int layer_attention(dsk_model* m, char* k_layer, char* v_layer, int64_t own_row0
   a.q_cu = q_cu; a.p_cu = p_cu; a.q_cu_host = q_cu_host; a.p_cu_host = p_cu_host; a.n_seqs = n_seqs;
   a.own_row0 = own_row0; a.n_q = n; a.ws = m->attn_ws; a.ws_bytes = m->attn_ws_bytes;
   a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.dh = c.head_dim;
-  a.vt = nullptr; a.ldvt = 0;
+  a.vt = nullptr; a.ldvt = 0; a.keep_vt = vt_first_row >= 0;
   if (m->vt && !g_force_generic) {
     if (!attn_few_supported(a))
-      HIP_TRY(launch_transpose_v(v_layer, m->vt, m->ldvt, c.n_kv_heads * c.head_dim, n_pre_rows, own_row0, n, vt_first_row, s));
+      HIP_TRY(launch_transpose_v(v_layer, m->vt, m->ldvt, c.n_kv_heads * c.head_dim, n_pre_rows, own_row0, n,
+                                 vt_first_row > 0 ? vt_first_row : 0, s));
     a.vt = m->vt; a.ldvt = m->ldvt;
   }
   HIP_TRY(attention(m, a, s));
@@ -338,7 +339,7 @@ int run_layer_few(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_o
   if (!ready) HIP_TRY(launch_few_norm(h_in, h_in_f32, w.g1, m->xn, m->ssq, n, d, rope, s));
   HIP_TRY(launch_few_qkv(m->xn, m->ssq, eps, w.wqkv, m->qkv, m->n_qkv, m->rope_cs, k_layer + own, v_layer + own, n, d, c.n_q_heads,
                          c.n_kv_heads, c.head_dim, s));
-  int rc = layer_attention(m, k_layer, v_layer, own_row0, q_cu, q_cu_host, p_cu, p_cu_host, n_pre_rows, n_seqs, n, 0, 1, s);
+  int rc = layer_attention(m, k_layer, v_layer, own_row0, q_cu, q_cu_host, p_cu, p_cu_host, n_pre_rows, n_seqs, n, -1, 1, s);
   if (rc) return rc;
   g_stats.gemm_mfma += 2;
   HIP_TRY(launch_few_residual(m->attn, w.wo, h_in, h_in_f32, m->h, 1, w.g2, m->xn, m->ssq, n, d, nq, m->gemm_ws, m->gemm_ws_bytes, s));
@@ -361,14 +362,15 @@ int run_layer_few(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_o
 // cache layer (k_rows, v_rows); attention additionally sees the prefix rows delimited by p_cu.
 // h_in is the model dtype unless h_in_f32; h_out likewise unless h_out_f32 (the workspace stream m->h is fp32).
 // h_mid: fp32 rows that receive the state after the attention block (h_out may be the same rows); cs: rotary table
-// of the n tokens.  vt_first_row: rows of the layer's V before it are already in the transposed copy m->vt.
+// of the n tokens.  vt_first_row >= 0: the layer runs in chunks of rows, and the layer's V rows before it are already in the
+// transposed copy m->vt.
 // ready: m->xn already holds this layer's normalised input; g_next: gain of the next layer's input norm, whose output this
 // layer may leave there (*left); rope: the rotary table is still to be filled.
 int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, int h_out_f32, char* k_layer,
               char* v_layer, int64_t own_row0,
               const int32_t* q_cu, const int32_t* q_cu_host, const int32_t* p_cu, const int32_t* p_cu_host,
               int64_t n_pre_rows, int n_seqs, int n, hipStream_t s, float* h_mid = nullptr, const float2* cs = nullptr,
-              int64_t vt_first_row = 0, bool ready = false, const void* g_next = nullptr, bool* left = nullptr,
+              int64_t vt_first_row = -1, bool ready = false, const void* g_next = nullptr, bool* left = nullptr,
               const RopeJob* rope = nullptr) {
   if (left) *left = false;
   if (!h_mid) h_mid = m->h;
@@ -911,7 +913,7 @@ int dsk_partial_prefill_groups(dsk_model_t* model, const dsk_group_t* groups, in
                              l + 1 < G.hi ? m->layers[l + 1].g1 : nullptr, &ready, table_done ? nullptr : &rope);
         else
           rc = run_layer(m, l, h_cur, l > G.lo, h_next, !last, kv_k(kv_out, l), kv_v(kv_out, l), 0, batch->cu_seqlens_dev,
-                         batch->cu_seqlens_host, nullptr, nullptr, 0, batch->n_seqs, T, s, nullptr, nullptr, 0, ready,
+                         batch->cu_seqlens_host, nullptr, nullptr, 0, batch->n_seqs, T, s, nullptr, nullptr, -1, ready,
                          l + 1 < G.hi ? m->layers[l + 1].g1 : nullptr, &ready, table_done ? nullptr : &rope);
         if (rc) return rc;
         table_done = true;
@@ -977,7 +979,7 @@ int dsk_suffix_prefill(dsk_model_t* model, const void* suffix_hidden_in, const d
     else
       rc = run_layer(m, l, h_cur, l > 0, h_next, !last, kv_k(kv, l), kv_v(kv, l), suffix_row0, suffix->cu_seqlens_dev,
                      suffix->cu_seqlens_host, prefix->cu_seqlens_dev, prefix->cu_seqlens_host, prefix->n_tokens,
-                     suffix->n_seqs, S, s, nullptr, nullptr, 0, ready, last ? nullptr : m->layers[l + 1].g1, &ready,
+                     suffix->n_seqs, S, s, nullptr, nullptr, -1, ready, last ? nullptr : m->layers[l + 1].g1, &ready,
                      l == 0 ? &rope : nullptr);
     if (rc) return rc;
     h_cur = h_next;

@@ -204,6 +204,7 @@ struct AttnArgs {
   const int32_t* q_cu; const int32_t* p_cu; const int32_t* q_cu_host; const int32_t* p_cu_host; int n_seqs;
   int64_t own_row0; int n_q; int Hq, Hkv, dh;
   const void* vt; int64_t ldvt;  // transposed V (see launch_transpose_v; not read where attn_few_supported); NULL: not available
+  int keep_vt = 0;               // later calls rely on the transposed copy of this call's rows
   int out_blocks = 0;            // out in blocks (block_at, Hq*dh columns) instead of rows
   void* ws; int64_t ws_bytes;    // fp32 scratch for key-split partial results (attn_mfma_workspace_bytes); optional
 };

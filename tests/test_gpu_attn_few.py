@@ -62,3 +62,35 @@ def test_attention_few_queries_component_call(B):
     torch.cuda.synchronize()
     # rounding of the probabilities and of the result: 2^-9 each
     assert O.max_rel_err(out.float().cpu().numpy().reshape(n, Hq, dh), ref) <= 1e-2
+
+
+# more than 128 queries over short key ranges: the first and the last sizes of the rule and one past it, without and with
+# keys in front, ragged
+@pytest.mark.parametrize("lens,plens", [([129], None), ([333, 130, 1], None), ([500, 161], [524, 17]), ([1024], None),
+                                        ([1025], None)])
+@pytest.mark.parametrize("Hq,Hkv,dh", [(8, 2, 128), (6, 2, 64)])
+def test_attention_short_prompts(B, Hq, Hkv, dh, lens, plens):
+    n, pre = sum(lens), sum(plens or [0])
+    bf = lambda a: synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(a))
+    q = bf(synth.normal(n * Hq * dh, 43, 0, 3.0).reshape(n, Hq, dh))
+    k = bf(synth.normal((pre + n) * Hkv * dh, 43, 1, 2.0).reshape(-1, Hkv, dh))
+    v = bf(synth.normal((pre + n) * Hkv * dh, 43, 2, 1.0).reshape(-1, Hkv, dh))
+    qc, pc = synth.cu_seqlens(lens), synth.cu_seqlens(plens or [0] * len(lens))
+    ref = np.empty((n, Hq, dh))
+    for b in range(len(lens)):
+        rows = np.r_[pc[b]:pc[b + 1], pre + qc[b]:pre + qc[b + 1]]
+        n_pre = pc[b + 1] - pc[b]
+        for h in range(Hq):
+            kk, vv = (t[rows, h * Hkv // Hq].astype(np.float64) for t in (k, v))
+            s = q[qc[b]:qc[b + 1], h].astype(np.float64) @ kk.T / np.sqrt(dh)
+            s[np.arange(len(rows))[None] > n_pre + np.arange(lens[b])[:, None]] = -np.inf
+            p = np.exp(s - s.max(axis=1, keepdims=True))
+            ref[qc[b]:qc[b + 1], h] = p @ vv / p.sum(axis=1, keepdims=True)
+    dev = lambda a: torch.from_numpy(a).to(torch.bfloat16).cuda()
+    out = torch.empty((n, Hq * dh), dtype=torch.bfloat16, device="cuda")
+    scratch = torch.empty(Hkv * dh * ((pre + n + 63) // 64 * 64), dtype=torch.bfloat16, device="cuda")
+    qb, pb = B.Batch(qc), B.Batch(pc) if plens else None
+    B.dsk_attention(B.DSK_BF16, dev(q), dev(k), dev(v), out, qb.desc, pb.desc if plens else None, pre, Hq, Hkv, dh, scratch)
+    torch.cuda.synchronize()
+    # rounding of the probabilities and of the result: 2^-9 each
+    assert O.max_rel_err(out.float().cpu().numpy().reshape(n, Hq, dh), ref) <= 1e-2
