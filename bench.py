@@ -383,7 +383,7 @@ def main():
     else:
         out["roofline"] = {"bound": "alu", "achieved": round(flops / (t_partial * 1e-3) / 1e12, 3), "peak": 157.3,
                            "unit": "TFLOP/s", "frac": round(flops / (t_partial * 1e-3) / 157.3e12, 5), "traffic": None,
-                           "kernel": "fp32 plain-ALU path (latency bound at this size)"}
+                           "kernel": "fp32 matrix-core path (latency bound at this size)"}
     if shape.dtype == "bf16" and attn_n > 0:
         a_tf = attn_flops / (attn_ms * 1e-3) / 1e12
         out["roofline_attention"] = {"bound": "mfma", "achieved": round(a_tf, 1), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",

@@ -312,7 +312,8 @@ DSK_API int dsk_linear_static(int dtype, const void* x, const void* w, void* y, 
  * (prefix may be NULL) and rows own_row0+queries.cu[b] .. own_row0+i.  out [n_q, Hq*dh].  All device.
  * prefix.n_tokens <= own_row0 (the two row ranges do not overlap), else DSK_EINVAL.
  * scratch: device buffer of scratch_bytes >= Hkv*dh*roundup64(own_row0+n_q)*elem bytes: the bf16 tensor-core
- * kernel keeps a transposed copy of V there.  scratch = NULL selects the plain-ALU kernel (any dtype); a bf16 call
+ * kernel keeps a transposed copy of V there (not written where at most 128 queries per sequence or a short prompt read V
+ * as it lies; the size is required all the same).  scratch = NULL selects the plain-ALU kernel (any dtype); a bf16 call
  * with scratch whose shape the tensor-core kernel does not handle (head_dim other than 64 or 128, Hkv*dh not a
  * multiple of 64, scratch too small) returns DSK_ESHAPE. */
 DSK_API int dsk_attention(int dtype, const void* q, const void* k_rows, const void* v_rows, void* out,
@@ -328,10 +329,12 @@ DSK_API int dsk_moe_route(int dtype, const void* x, const void* wr, int n, int d
 
 /* ---- hooks for tests and benchmarks (process-wide, not thread-safe; no production caller needs them) ----
  * Unknown names and out-of-range values return DSK_EINVAL.
- *   "force_generic": 1 = all work runs on the plain-ALU kernels (bf16 about a hundred times slower).  Without it a bf16 shape the tensor-core kernels do not handle is an error (DSK_ESHAPE
- *                from dsk_model_create, dsk_linear, dsk_attention), never a silent switch of kernels.
+ *   "force_generic": 1 = all work runs on the plain-ALU kernels (bf16 about a hundred times slower).  Without it a bf16
+ *                shape the tensor-core kernels do not handle is an error (DSK_ESHAPE from dsk_model_create, dsk_linear,
+ *                dsk_attention), never a silent switch of kernels.
  *   "gemm_tiling": force one of the two prefill tilings of the bf16 GEMM on any M > 64 (default 0 = picked by
- *                size): 1 = 256x256 tiles on the 16x16x32 MFMA, 2 = 128x128 tiles on the 32x32x16 MFMA
+ *                size, with 128- and 192-row tiles and split contractions among the choices): 1 = 256x256 tiles on the
+ *                16x16x32 MFMA, 2 = 128x128 tiles on the 32x32x16 MFMA
  *   "e_chunk_rows": how a host-resident E cache is cut into row chunks that the first recomputed layer follows as
  *                they arrive: 0 (default) = 4096-row chunks where that keeps every result bit-identical to the
  *                unchunked run (one sequence, bf16, chunks that still fill the chip), -1 = never, n > 0 (a multiple
@@ -339,7 +342,8 @@ DSK_API int dsk_moe_route(int dtype, const void* x, const void* wr, int n, int d
  *   "time_gemm": 1 = bracket every tensor-core GEMM launch that runs on the 256 x 256 prefill tiling (at least
  *                192 such tiles), and every tensor-core attention launch of the prefix pass (at least 1024 query rows, no
  *                earlier rows), by a pair of HIP events attached to the kernel's own dispatch (they receive its start and
- *                stop times, nothing else is put into the stream; read back through dsk_get_stat)
+ *                stop times, nothing else is put into the stream; read back through dsk_get_stat); a projection that runs as
+ *                whole rounds of 256-row tiles and a rest in lower tiles is one such pair over both launches
  *   "reset_stats": any value; clears all counters and recorded timings */
 DSK_API int dsk_set_option(const char* name, int value);
 
