@@ -174,26 +174,34 @@ struct Stats {
   TimedList gemm, attn;
 } g_stats;
 
+// One projection on the tensor-core kernels, under "time_gemm" bracketed by a pair of events if it is a prefill one.
+template <typename F>
+hipError_t timed_gemm(int M, int N, int K, hipStream_t s, F&& launch) {
+  std::unique_lock<std::mutex> timed_lock(g_stats.timed_mu, std::defer_lock);
+  bool timed = false;
+  if (g_time_gemm && gemm_mfma_uses_prefill_tile(M, N)) {
+    timed_lock.lock();
+    hipError_t ee = g_stats.gemm.begin(s, &timed);
+    if (ee != hipSuccess) return ee;
+  }
+  hipError_t e = launch();
+  if (e == hipSuccess) {
+    ++g_stats.gemm_mfma;
+    if (timed) e = g_stats.gemm.end(s, 2.0 * M * N * K);
+  } else if (timed) {
+    g_stats.gemm.abandon();
+  }
+  return e;
+}
+
 hipError_t gemm_any(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc,
                     const void* R, int64_t ldr, int M, int N, int K, int epi, void* ws, int64_t ws_bytes, hipStream_t s) {
   if (dtype == DSK_BF16 && !g_force_generic) {
-    std::unique_lock<std::mutex> timed_lock(g_stats.timed_mu, std::defer_lock);
-    bool timed = false;
-    if (g_time_gemm && gemm_mfma_uses_prefill_tile(M, N)) {
-      timed_lock.lock();
-      hipError_t ee = g_stats.gemm.begin(s, &timed);
-      if (ee != hipSuccess) return ee;
-    }
     // a shape the tensor-core kernels refuse comes back as hipErrorNotSupported (the caller's DSK_ESHAPE): a bf16
     // problem never drops to the plain-ALU kernel behind the caller's back, that kernel is a hundred times slower
-    hipError_t e = launch_gemm_mfma_bf16(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, ws, ws_bytes, s);
-    if (e == hipSuccess) {
-      ++g_stats.gemm_mfma;
-      if (timed) e = g_stats.gemm.end(s, 2.0 * M * N * K);
-    } else if (timed) {
-      g_stats.gemm.abandon();
-    }
-    return e;
+    return timed_gemm(M, N, K, s, [&] {
+      return launch_gemm_mfma_bf16(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, ws, ws_bytes, s);
+    });
   }
   ++g_stats.gemm_generic;
   // the residual and the result of an fp32 problem are fp32 whatever the epilogue flags say
@@ -404,6 +412,10 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
     HIP_TRY(launch_gemm_split_rope(m->xn, w.wqkv, m->w_blocks, m->qkv, cs, k_own, v_own, n, d, c.n_q_heads, c.n_kv_heads, c.head_dim,
                                    m->split_ws, m->split_ws_bytes, s));
     ++g_stats.gemm_mfma;
+  } else if (c.dtype == DSK_BF16 && !g_force_generic && gemm_mfma_rope_supported(n, m->n_qkv, d, m->w_blocks, c.head_dim)) {
+    HIP_TRY(timed_gemm(n, m->n_qkv, d, s, [&] {
+      return launch_gemm_rope(m->xn, w.wqkv, m->qkv, cs, k_own, v_own, n, d, c.n_q_heads, c.n_kv_heads, s);
+    }));
   } else {
     HIP_TRY(gemm(m, m->xn, d, w.wqkv, d, m->qkv, m->n_qkv, nullptr, 0, n, m->n_qkv, d, EPI_STORE, s));
     HIP_TRY(launch_rope_kv_write(c.dtype, m->qkv, cs, k_own, v_own, n, c.n_q_heads, c.n_kv_heads, c.head_dim, s));

@@ -135,6 +135,10 @@ bool gemm_mfma_swiglu_supported(int M, int N, int K);
 bool gemm_mfma_splits(int M, int N, int K, int64_t ws_bytes);
 hipError_t launch_gemm_split_rope(const void* A, const void* W, int w_blocks, void* qkv, const float2* cs, void* k_rows, void* v_rows,
                                   int M, int K, int Hq, int Hkv, int dh, void* ws, int64_t ws_bytes, hipStream_t s);
+// The QKV projection with RoPE + KV write in its epilogue (heads of 128, weights in blocks, contraction not split).
+bool gemm_mfma_rope_supported(int M, int N, int K, int w_blocks, int dh);
+hipError_t launch_gemm_rope(const void* A, const void* W, void* qkv, const float2* cs, void* k_rows, void* v_rows, int M, int K, int Hq,
+                            int Hkv, hipStream_t s);
 hipError_t launch_gemm_split_norm(const void* A, const void* W, int w_blocks, float* h, const void* R, int r_f32, const void* g, void* xn,
                                   float eps, int M, int d, int K, void* ws, int64_t ws_bytes, hipStream_t s);
 // Few token rows (M <= 64, bf16, few_rows.hip): weights and activations in blocks, the step that follows a projection (and

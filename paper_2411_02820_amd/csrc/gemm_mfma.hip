@@ -457,12 +457,23 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 // device; tile_tab[tiles_m].x = number of tiles that exist; expert < 0: no such tile, the workgroup leaves); the
 // expert's matrix is W + expert * w_group_stride.  a_row (optional): sorted row r is row a_row[r] of A's a_rows rows, so
 // that the rows are read where they are (gathered into a buffer first they cost 38 us more at 8192 tokens).
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false>
+// ROPE (the QKV projection, heads of 128, weights in blocks): a wave's 64 columns are 32 rotary pairs of one head (elements
+// p0 .. p0 + 31 and their partners 64 further on: tiles j and j + 2, the same lane and register), so that the epilogue
+// rotates the fp32 sums and writes q to C and k and v straight to their cache rows.  The separate pass read and wrote
+// every row once more (33 us for 8192 rows of the 8B shape); a layer over 4096 rows 1432 -> 1421 us, over eight ragged
+// contexts (39892 rows) 18.60 -> 18.42 ms, a Mixtral layer over 8192 rows 5958 -> 5925 us, a 70B one 10489 -> 10461 us.
+struct RopeOut {
+  const float2* cs;  // [M][64] (cos, sin)
+  bf16_t *k, *v;     // [M][Hkv * 128]
+  int Hq, Hkv;
+};
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false, bool ROPE = false>
 __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     gemm16_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W_all, int64_t ldw,
                        void* C, int64_t ldc, const void* __restrict__ R, int64_t ldr, int M_all, int N, int K,
                        int epi, int tiles_m, int tiles_n, int kt_per_split, const int4* __restrict__ tile_tab,
-                       int64_t w_group_stride, const int32_t* __restrict__ a_row, int a_rows) {
+                       int64_t w_group_stride, const int32_t* __restrict__ a_row, int a_rows, RopeOut ro) {
+  static_assert(!ROPE || (WB && !GROUPED && BN % 128 == 0 && BN / WAVES_N == 64), "two waves a head");
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
   constexpr int TM = WTM / 16, TN = WTN / 16;  // 16x16 MFMA tiles per wave
@@ -552,7 +563,10 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     const int ch = ks * 4 + fq;
     const int j = f == 0 ? 0 : f - TM;
     if (f >= 1 && f <= TM) xs[ks][f - 1] = *(const bf16x8*)(a_s + slot(wm * WTM + (f - 1) * 16 + frow, ch));
-    else ws[ks][j] = *(const bf16x8*)(w_s + (WB ? ((wn * WTN / 16 + j) * 2 + ks) * BLK + lane * 8 : slot(wn * WTN + j * 16 + frow, ch)));
+    else {
+      const int cb = ROPE ? wn / 2 * 8 + wn % 2 * 2 + j / 2 * 4 + j % 2 : wn * WTN / 16 + j;  // 16-column block of the tile
+      ws[ks][j] = *(const bf16x8*)(w_s + (WB ? (cb * 2 + ks) * BLK + lane * 8 : slot(wn * WTN + j * 16 + frow, ch)));
+    }
   };
 
   // k-tiles of this workgroup: all of them, or share blockIdx.y of a contraction split over workgroups (C then holds
@@ -641,6 +655,59 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   const int er = lane_e & 15, eq = lane_e >> 4;
   const int rr = lane_e >> 4, c4 = (lane_e & 15) * 4;
   const int rr_s = lane_e >> 3, c4_s = (lane_e & 7) * 4;
+  if constexpr (ROPE) {
+    const int head = n0 / 128 + wn / 2, p0 = wn % 2 * 32;
+    if (head >= ro.Hq + 2 * ro.Hkv) return;  // uniform over the wave; no barrier follows
+    const bool rotates = head < ro.Hq + ro.Hkv;
+    bf16_t* out = head < ro.Hq ? (bf16_t*)C + head * 128 : rotates ? ro.k + (head - ro.Hq) * 128 : ro.v + (head - ro.Hq - ro.Hkv) * 128;
+    const int64_t ldo = head < ro.Hq ? ldc : ro.Hkv * 128;
+    f32x4 cs[2][2][2][2];  // [ib % 2][h][j][.]: (cos, sin) of the lane's four pairs, requested one block of 32 rows ahead
+    auto request = [&](int ib) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int m = min(m0 + wm * WTM + ib * 32 + 16 * h + er, M - 1);
+          const f32x4* src = (const f32x4*)(ro.cs + (int64_t)m * 64 + p0 + 16 * j + 4 * eq);
+          cs[ib % 2][h][j][0] = src[0];
+          cs[ib % 2][h][j][1] = src[1];
+        }
+    };
+    if (rotates) request(0);
+#pragma unroll
+    for (int ib = 0; ib < TM / 2; ++ib) {
+      if (rotates && ib + 1 < TM / 2) request(ib + 1);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int i = 2 * ib + h;
+        float* rowp = stage_f + (16 * h + er) * ROW_F + 4 * eq;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          f32x4 y1 = acc[j][i], y2 = acc[j + 2][i];
+          if (rotates) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float c = cs[ib % 2][h][j][e / 2][e % 2 * 2], sn = cs[ib % 2][h][j][e / 2][e % 2 * 2 + 1];
+              const float a = y1[e], b = y2[e];
+              y1[e] = a * c - b * sn;
+              y2[e] = b * c + a * sn;
+            }
+          }
+          *(f32x4*)(rowp + 16 * j) = y1;
+          *(f32x4*)(rowp + 16 * (j + 2)) = y2;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int it = 0; it < 8; ++it) {
+        const int r = it * 4 + rr, m = m0 + wm * WTM + ib * 32 + r;
+        const f32x4 v = *(const f32x4*)(stage_f + r * ROW_F + c4);
+        if (m < M) store_quad(out, ldo, nullptr, 0, m, p0 + (c4 & 31) + (c4 & 32) * 2, v, EPI_STORE);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    return;
+  }
 #pragma unroll
   for (int ib = 0; ib < TM / 2; ++ib) {
 #pragma unroll
@@ -861,7 +928,24 @@ hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw,
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   DSK_LAUNCH_TIMED(kern, dim3(tiles_m * tiles_n, splits), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
                    (const bf16_t*)W, ldw, C, ldc, R, ldr, M, N, K, epi, tiles_m, tiles_n, kt_per_split, (const int4*)nullptr,
-                   (int64_t)0, (const int32_t*)nullptr, 0);
+                   (int64_t)0, (const int32_t*)nullptr, 0, RopeOut{});
+  return hipGetLastError();
+}
+
+template <int BM>
+hipError_t launch16_rope(const void* A, const void* W, void* qkv, const RopeOut& ro, int M, int K, hipStream_t s) {
+  auto kern = gemm16_bf16_kernel<BM, 256, 2, 4, true, false, true>;
+  constexpr int lds = NSTAGE * (BM + 256) * BK * 2;
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  const int N = (ro.Hq + 2 * ro.Hkv) * 128, tiles_m = (M + BM - 1) / BM, tiles_n = (N + 255) / 256;
+  DSK_LAUNCH_TIMED(kern, dim3(tiles_m * tiles_n), dim3(512), lds, s, (const bf16_t*)A, (int64_t)K, (const bf16_t*)W, (int64_t)K, qkv,
+                   (int64_t)N, (const void*)nullptr, (int64_t)0, M, N, K, (int)EPI_STORE, tiles_m, tiles_n, K / BK,
+                   (const int4*)nullptr, (int64_t)0, (const int32_t*)nullptr, 0, ro);
   return hipGetLastError();
 }
 
@@ -890,7 +974,7 @@ hipError_t launch16_grouped(const void* A, int64_t lda, const int32_t* a_row, in
   const int tiles_n = (N + BN - 1) / BN;
   DSK_LAUNCH_TIMED(kern, dim3(tile_rows * tiles_n), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
                    (const bf16_t*)W, ldw, C, ldc, (const void*)nullptr, (int64_t)0, 0, N, K, epi, tile_rows, tiles_n,
-                   K / BK, tile_tab, w_group_stride, a_row, a_rows);
+                   K / BK, tile_tab, w_group_stride, a_row, a_rows, RopeOut{});
   return hipGetLastError();
 }
 
@@ -1089,6 +1173,31 @@ hipError_t launch_gemm_split_rope(const void* A, const void* W, int w_blocks, vo
   hipLaunchKernelGGL(splitk_reduce_rope_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s, (const float*)ws,
                      (bf16_t*)qkv, (int64_t)N, cs, (bf16_t*)k_rows, (bf16_t*)v_rows, M, N, p.splits, Hq, Hkv, dh);
   return hipGetLastError();
+}
+
+// The same step where the contraction is not split: in the projection's epilogue.
+bool gemm_mfma_rope_supported(int M, int N, int K, int w_blocks, int dh) {
+  return g_variant == 0 && w_blocks && dh == 128 && M > 64 && K >= BK && K % BK == 0 && (int64_t)M * K * 2 < ((int64_t)1 << 32) &&
+         (int64_t)N * K * 2 < ((int64_t)1 << 32);
+}
+
+hipError_t launch_gemm_rope(const void* A, const void* W, void* qkv, const float2* cs, void* k_rows, void* v_rows, int M, int K, int Hq,
+                            int Hkv, hipStream_t s) {
+  const int N = (Hq + 2 * Hkv) * 128;
+  if (!gemm_mfma_rope_supported(M, N, K, 1, 128)) return hipErrorNotSupported;
+  const GemmPlan p = gemm_plan(M, N, K, false, 0);
+  auto run = [&](int bm, int64_t r0, int64_t rows) {
+    const RopeOut ro = {cs + r0 * 64, (bf16_t*)k_rows + r0 * Hkv * 128, (bf16_t*)v_rows + r0 * Hkv * 128, Hq, Hkv};
+    auto f = bm == 128 ? launch16_rope<128> : bm == 192 ? launch16_rope<192> : launch16_rope<256>;
+    return f((const bf16_t*)A + r0 * K, W, (bf16_t*)qkv + r0 * N, ro, (int)rows, K, s);
+  };
+  if (p.head_rows == 0) return run(p.bm, 0, M);
+  const hipEvent_t stop = g_launch_ev_stop;  // a pair of events taken for this call spans both launches
+  g_launch_ev_stop = nullptr;
+  const hipError_t e = run(256, 0, p.head_rows);
+  if (e != hipSuccess) return e;
+  g_launch_ev_stop = stop;
+  return run(p.rest_bm, p.head_rows, M - p.head_rows);
 }
 
 // h [M, d] fp32 = x W^T + R and xn [M, d] = rmsnorm(h) * g; d <= 8192

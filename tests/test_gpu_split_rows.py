@@ -84,3 +84,25 @@ def test_router_on_the_matrix_cores(B, n, d, E, k):
         if 0 in experts[t] and E - 1 in experts[t]:
             assert list(experts[t]).index(0) < list(experts[t]).index(E - 1)
         assert not (E - 1 in experts[t] and 0 not in experts[t])
+
+
+# RoPE + KV write in the epilogue of an unsplit QKV projection (heads of 128): every tile height, a last column tile that is
+# half full, rows that end inside a tile, whole rounds and a rest in two launches (22000 rows); against the same model with
+# the tiling forced, where the rotation is a pass of its own over the rounded projection
+@pytest.mark.parametrize("lens", [[65], [150, 1], [300], [500, 140], [1000] * 22])
+def test_rope_in_the_projection(B, lens):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(1, 128, 3, 1, 128, 128, 10000.0, 1e-5, "bf16")
+    x = G.to_dev(synth.hidden_states(shape, sum(lens)), shape)
+    with G.GpuModel(shape, sum(lens)) as m:
+        m.init_random(9)
+        kv, h = m.partial(x, 0, 1, None, lens)
+        B.dsk_set_option("gemm_tiling", 2)
+        try:
+            kv_ref, h_ref = m.partial(x, 0, 1, None, lens)
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("gemm_tiling", 0)
+    # k: one rounding here, up to two of each of the pair's elements there (2^-9 each); v and the state: one each
+    for a, b in ((kv, kv_ref), (h, h_ref)):
+        assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2 ** -7
