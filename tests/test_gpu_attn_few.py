@@ -94,3 +94,49 @@ def test_attention_short_prompts(B, Hq, Hkv, dh, lens, plens):
     torch.cuda.synchronize()
     # rounding of the probabilities and of the result: 2^-9 each
     assert O.max_rel_err(out.float().cpu().numpy().reshape(n, Hq, dh), ref) <= 1e-2
+
+
+# V rows that are not finite reach the queries that see them and no others (a probability of 0 does not take them out of a
+# product): every column form, one and four heads per group, the bad row in front of, inside and behind a wave's own columns,
+# in the last key too (its row is repeated up to the end of a stage)
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,n,pre,bad", [(4, 4, 10, 250, 7), (4, 4, 50, 100, 49), (4, 4, 128, 0, 100), (4, 4, 128, 300, 3),
+                                              (8, 2, 4, 127, 3), (8, 2, 16, 130, 9), (8, 2, 100, 64, 70), (4, 1, 300, 0, 120)])
+def test_attention_rows_that_are_not_finite_reach_later_queries_only(B, Hq, Hkv, n, pre, bad, dh):
+    bf = lambda a: torch.from_numpy(a).to(torch.bfloat16).cuda()
+    q = bf(synth.normal(n * Hq * dh, 45, 0, 1.0).reshape(n, Hq, dh))
+    k, v = (bf(synth.normal((pre + n) * Hkv * dh, 45, j, 1.0).reshape(-1, Hkv, dh)) for j in (1, 2))
+    scratch = torch.empty(Hkv * dh * ((pre + n + 63) // 64 * 64), dtype=torch.bfloat16, device="cuda")
+    qb, pb = B.Batch(synth.cu_seqlens([n])), B.Batch(synth.cu_seqlens([pre])) if pre else None
+
+    def run():
+        out = torch.empty((n, Hq, dh), dtype=torch.bfloat16, device="cuda")
+        B.dsk_attention(B.DSK_BF16, q, k, v, out, qb.desc, pb.desc if pre else None, pre, Hq, Hkv, dh, scratch)
+        torch.cuda.synchronize()
+        return out.float().cpu().numpy()
+
+    clean = run()
+    v[pre + bad, :, 0] = float("inf")
+    v[pre + bad, :, 1:dh // 2] = float("nan")
+    got = run()
+    # what does not take part in a sum does not change it
+    assert np.array_equal(got[:bad], clean[:bad]) and np.array_equal(got[bad:, :, dh // 2:], clean[bad:, :, dh // 2:])
+    assert np.isposinf(got[bad:, :, 0]).all() and np.isnan(got[bad:, :, 1:dh // 2]).all()
+
+
+@pytest.mark.parametrize("n,pre,bad", [(40, 4000, 21), (100, 2000, 60)])
+def test_suffix_token_that_is_not_finite_reaches_later_tokens_only(B, n, pre, bad):
+    # through a model: the keys split over workgroups, the partial results merged
+    from tests import gpu_util as G
+    shape = synth.ModelShape(2, 256, 4, 4, 64, 256, 10000.0, 1e-5, "bf16")
+    cache = torch.full((2, 2, pre + n, 4, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+    cache[:, :, :pre] = G.to_dev(synth.kv_cache(shape, pre), shape)
+    xs = G.to_dev(synth.hidden_states(shape, n, seed=synth.SEED_SUFFIX), shape)
+    with G.GpuModel(shape, n, pre + n) as m:
+        m.init_random(11)
+        B.dsk_set_option("reset_stats", 0)
+        clean = G.to_np(m.suffix(xs, cache, [pre], [n]))
+        assert B.dsk_get_stat("attn_key_split_launches") == 2
+        xs[bad] = float("nan")
+        got = G.to_np(m.suffix(xs, cache, [pre], [n]))
+    assert np.array_equal(got[:bad], clean[:bad]) and np.isnan(got[bad:]).all()
