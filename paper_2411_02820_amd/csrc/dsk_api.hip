@@ -594,7 +594,16 @@ int dsk_model_create(const dsk_config_t* cfg, int64_t max_tokens, int64_t max_kv
   if (rc == DSK_OK) rc = alloc_dev(&m->xn, T * d * elem, &m->workspace_bytes);
   if (rc == DSK_OK) rc = alloc_dev(&m->qkv, T * m->n_qkv * elem, &m->workspace_bytes);
   if (rc == DSK_OK) rc = alloc_dev(&m->attn, T * nq * elem, &m->workspace_bytes);
-  if (rc == DSK_OK) rc = alloc_dev(&m->gu, T * 2 * F * elem, &m->workspace_bytes);
+  int64_t split_bytes = 0, gu_bytes = T * 2 * F * elem;
+  if (cfg->dtype == DSK_BF16) {  // QKV, O and down (gate/up is never split)
+    const int64_t need[3] = {gemm_mfma_split_bytes(T, m->n_qkv, (int)d), gemm_mfma_split_bytes(T, (int)d, (int)nq),
+                             E > 0 ? 0 : gemm_mfma_split_bytes(T, (int)d, (int)F)};
+    for (int i = 0; i < 3; ++i)
+      if (need[i] > split_bytes) split_bytes = need[i];
+  }
+  const bool split_in_gu = cfg->dtype == DSK_BF16 && d % 64 == 0 && F % 64 == 0;  // SwiGLU never leaves the projection there
+  if (split_in_gu && split_bytes > gu_bytes) gu_bytes = split_bytes;
+  if (rc == DSK_OK) rc = alloc_dev(&m->gu, gu_bytes, &m->workspace_bytes);
   // with experts on the tensor-core path the MLP works on top_k rows per token, grouped by expert
   const bool moe_grouped = E > 0 && cfg->dtype == DSK_BF16;
   int64_t act_rows = T * (moe_grouped ? top_k : 1);
@@ -629,13 +638,10 @@ int dsk_model_create(const dsk_config_t* cfg, int64_t max_tokens, int64_t max_kv
     m->gemm_ws_bytes = gemm_mfma_workspace_bytes(max_n);
     const int64_t few = few_rows_workspace_bytes((int)d, (int)(nq > F ? nq : F));
     if (few > m->gemm_ws_bytes) m->gemm_ws_bytes = few;
+    if (!split_in_gu && split_bytes > m->gemm_ws_bytes) m->gemm_ws_bytes = split_bytes;
     rc = alloc_dev(&m->gemm_ws, m->gemm_ws_bytes, &m->workspace_bytes);
-    m->split_ws = m->gemm_ws;
-    m->split_ws_bytes = m->gemm_ws_bytes;
-    if (d % 64 == 0 && F % 64 == 0 && T * 2 * F * elem > m->split_ws_bytes) {  // SwiGLU never leaves the projection there
-      m->split_ws = m->gu;
-      m->split_ws_bytes = T * 2 * F * elem;
-    }
+    m->split_ws = split_in_gu ? m->gu : m->gemm_ws;
+    m->split_ws_bytes = split_in_gu ? gu_bytes : m->gemm_ws_bytes;
     if (rc == DSK_OK) rc = alloc_dev((void**)&m->ssq, 64 * ((d + 15) / 16) * (int64_t)sizeof(float), &m->workspace_bytes);
   }
   if (rc == DSK_OK) {

@@ -64,7 +64,7 @@ struct dsk_model {
   void* xn;         // [maxT, d]      normalised activations
   void* qkv;        // [maxT, n_qkv]
   void* attn;       // [maxT, Hq*dh]
-  void* gu;         // [maxT, 2F]
+  void* gu;         // [maxT, 2F], or what split_ws needs
   void* act;        // [maxT, F]
   float* h;         // [maxT, d]      residual stream between the layers of one call, kept in fp32
   void* e_stage;    // [maxT, d]      landing buffer for an E cache that arrives from pinned host memory
@@ -75,7 +75,8 @@ struct dsk_model {
   float* ssq;       // [d/16, 64] sums of squares of the few-row pass (RMSNorm split in two)
   void* gemm_ws;    // fp32 partial tiles of the K-split small-M GEMM
   int64_t gemm_ws_bytes;
-  void* split_ws;   // the same for more than 64 rows: gemm_ws, or gu where that is larger (nothing else uses gu there)
+  void* split_ws;   // the same for more than 64 rows: gu where nothing else uses it there, else gemm_ws; large enough for
+                    // every split, so that how a call is split does not hang on max_tokens
   int64_t split_ws_bytes;
   void* attn_ws;    // fp32 partial outputs of the key-split attention
   int64_t attn_ws_bytes;
@@ -129,6 +130,7 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
                                  const void* R, int64_t ldr, int M, int N, int K, int epi, void* ws, int64_t ws_bytes,
                                  hipStream_t s);
 int64_t gemm_mfma_workspace_bytes(int max_n);
+int64_t gemm_mfma_split_bytes(int64_t max_m, int N, int K);  // scratch with which every split of up to max_m > 64 rows fits
 bool gemm_mfma_swiglu_supported(int M, int N, int K);
 // More than 64 rows with the contraction split over workgroups: the reduction does the step that follows, RoPE + KV write, or
 // the RMSNorm of h = x W^T + R (d <= 8192).

@@ -1066,6 +1066,15 @@ bool gemm_mfma_swiglu_supported(int M, int N, int K) { return M > 64 && N % 64 =
 // tiling, up to 4 splits of a wide N for the 64x128 tiling
 int64_t gemm_mfma_workspace_bytes(int max_n) { return (int64_t)64 * 4 * ((int64_t)768 * 64 + (int64_t)4 * max_n); }
 
+// What the partial planes of a split contraction take at most for up to max_m rows.  plan_one splits tiles so far that 256
+// workgroups run, each with 256 x 256 sums or fewer, and gives every one of them at least four k-tiles.
+int64_t gemm_mfma_split_bytes(int64_t max_m, int N, int K) {
+  if (max_m <= 64) return 0;
+  const int64_t most = (int64_t)256 * 256 * 256 * 4, shares = K / BK / 4 > 1 ? K / BK / 4 : 1;
+  const int64_t bytes = max_m * N * shares * 4;
+  return bytes < most ? bytes : most;
+}
+
 // Whether a projection of this size runs on the 256 x 256 prefill tiling (the kernel the roofline figure is about).
 bool gemm_mfma_uses_prefill_tile(int M, int N) {
   return M > 64 && (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 192;

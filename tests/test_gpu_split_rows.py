@@ -58,6 +58,23 @@ def test_layers_with_split_projections(B, rows, d, Hq, Hkv, dh, F):
         assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2e-2
 
 
+# how a contraction is split, and with it the order of its sums, is a matter of the call's sizes alone: the same rows on a
+# model that takes no more than them and on one that takes more
+@pytest.mark.parametrize("d,F,rows", [(2048, 8192, 500), (4096, 14336, 333), (4096, 14336, 700), (4096, 14336, 1024)])
+def test_split_does_not_depend_on_the_models_capacity(B, d, F, rows):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(1, d, d // 128, d // 512, 128, F, 10000.0, 1e-5, "bf16")
+    x = G.to_dev(synth.hidden_states(shape, rows), shape)
+    got = []
+    for max_tokens in (rows, 4096):
+        with G.GpuModel(shape, max_tokens) as m:
+            m.init_random(13)
+            kv, h = m.partial(x, 0, 1, None, [rows])
+            torch.cuda.synchronize()
+            got.append((kv, h))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 # the router on the matrix cores: token counts around multiples of 16, one to four blocks of experts, contractions shorter
 # and longer than the steps in flight, a row of NaN; the choice must be one of the best by more than fp32 sums can differ
 @pytest.mark.parametrize("n,d,E,k", [(65, 32, 2, 1), (80, 320, 16, 2), (100, 4096, 17, 8), (129, 1056, 33, 3), (70, 2080, 64, 8)])
