@@ -396,7 +396,7 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
   const bool fp32_swiglu = fp32_fused && c.n_experts == 0 && m->gu_block >= 16 && gemm_fp32_supported(h_mid, d, w.wgu, d, m->act, F, nullptr, 0, n, 2 * F, d);
   // bf16, rows that leave the chip unfilled: projections whose contraction is split do the step behind them in the reduction
   const bool can_split = c.dtype == DSK_BF16 && !g_force_generic && m->split_ws;
-  auto splits = [&](int N, int K) { return can_split && gemm_mfma_splits(n, N, K, m->split_ws_bytes); };
+  auto splits = [&](int N, int K) { return can_split && gemm_mfma_splits(n, N, K); };
   const bool norm_here = !fp32_rope && !ready;
   if (rope && norm_here && !h_in_f32 && norm_takes_rope(c.dtype, n, d)) {
     HIP_TRY(launch_rmsnorm_rope(h_in, w.g1, m->xn, n, d, (float)c.rms_eps, *rope, s));
@@ -1033,21 +1033,22 @@ int dsk_linear(int dtype, const void* x, const void* w, void* y, const void* r, 
   if (dtype != DSK_F32 && dtype != DSK_BF16) return DSK_EDTYPE;
   if (!aligned16(x) || !aligned16(w) || !aligned16(y) || !aligned16(r)) return DSK_EINVAL;
   const int epi = r ? EPI_RESIDUAL : EPI_STORE;
-  // split-K partials of the small-M path: one buffer per process, allocated at the first small-M call and kept
-  // (calls that overlap on different streams would share it: this entry point is for tests and micro-benchmarks)
+  // partial sums of split contractions: one buffer per process, allocated at the first such call and kept (calls that
+  // overlap on different streams would share it: this entry point is for tests and micro-benchmarks).  A call is told of
+  // what its own sizes need, not of what earlier ones have left: how it is split must not hang on them.
   static void* ws = nullptr;
   static int64_t ws_bytes = 0;
   static std::mutex ws_mu;
   std::lock_guard<std::mutex> ws_lock(ws_mu);  // host threads take turns; the buffer itself is still one per process
   const bool may_split = M <= 4096;  // the K-split paths are for few and for a few hundred token rows
-  if (dtype == DSK_BF16 && may_split && gemm_mfma_workspace_bytes(N) > ws_bytes) {
+  const int64_t few = gemm_mfma_workspace_bytes(N), most = (int64_t)64 << 20;  // most: gemm_mfma_split_bytes of any call
+  if (dtype == DSK_BF16 && may_split && (few > most ? few : most) > ws_bytes) {
     if (ws) HIP_TRY(hipFree(ws));
     ws = nullptr; ws_bytes = 0;
-    HIP_TRY(hipMalloc(&ws, (size_t)gemm_mfma_workspace_bytes(N)));
-    ws_bytes = gemm_mfma_workspace_bytes(N);
+    HIP_TRY(hipMalloc(&ws, (size_t)(few > most ? few : most)));
+    ws_bytes = few > most ? few : most;
   }
-  HIP_TRY(gemm_any(dtype, x, K, w, K, 0, y, N, r, N, M, N, K, epi, may_split ? ws : nullptr, may_split ? ws_bytes : 0,
-                   (hipStream_t)stream));
+  HIP_TRY(gemm_any(dtype, x, K, w, K, 0, y, N, r, N, M, N, K, epi, may_split ? ws : nullptr, M > 64 ? most : few, (hipStream_t)stream));
   return DSK_OK;
 }
 

@@ -125,7 +125,8 @@ hipError_t launch_gemm_fp32_norm_rope(const float* h, const void* gain, float ep
 hipError_t launch_gemm_fp32_norm_swiglu(const float* h, const void* gain, float eps, const void* wgu, void* act, int M, int d,
                                         int F, int gu_block, hipStream_t s);
 // bf16 MFMA GEMM; returns hipErrorNotSupported when the shape is outside what it handles.
-// ws: optional fp32 scratch for the K-split partial tiles of the small-M path (see gemm_mfma_workspace_bytes).
+// ws: optional fp32 scratch for the partial tiles of a split contraction: gemm_mfma_workspace_bytes up to 64 rows,
+// gemm_mfma_split_bytes beyond.
 hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc,
                                  const void* R, int64_t ldr, int M, int N, int K, int epi, void* ws, int64_t ws_bytes,
                                  hipStream_t s);
@@ -134,7 +135,7 @@ int64_t gemm_mfma_split_bytes(int64_t max_m, int N, int K);  // scratch with whi
 bool gemm_mfma_swiglu_supported(int M, int N, int K);
 // More than 64 rows with the contraction split over workgroups: the reduction does the step that follows, RoPE + KV write, or
 // the RMSNorm of h = x W^T + R (d <= 8192).
-bool gemm_mfma_splits(int M, int N, int K, int64_t ws_bytes);
+bool gemm_mfma_splits(int M, int N, int K);
 hipError_t launch_gemm_split_rope(const void* A, const void* W, int w_blocks, void* qkv, const float2* cs, void* k_rows, void* v_rows,
                                   int M, int K, int Hq, int Hkv, int dh, void* ws, int64_t ws_bytes, hipStream_t s);
 // The QKV projection with RoPE + KV write in its epilogue (heads of 128, weights in blocks, contraction not split).

@@ -989,8 +989,8 @@ int g_variant = 0;
 //   down 333 rows 55 [81], 700 rows 85 [135], 1500 rows 149 [207].
 struct GemmPlan { int bm, splits, per, head_rows, rest_bm; };
 
-// the best single launch and its time
-float plan_one(int M, int N, int K, bool may_split, int64_t ws_bytes, bool full_tile, GemmPlan* plan) {
+// the best single launch and its time (a matter of the sizes alone: the scratch holds every split, gemm_mfma_split_bytes)
+float plan_one(int M, int N, int K, bool may_split, bool full_tile, GemmPlan* plan) {
   const int KT = K / BK, bms[3] = {256, 192, 128};
   const bool fills = (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 192;  // gemm_mfma_uses_prefill_tile
   GemmPlan best = {256, 1, KT, 0, 0};
@@ -1002,7 +1002,7 @@ float plan_one(int M, int N, int K, bool may_split, int64_t ws_bytes, bool full_
     const int max_sp = fills || !may_split || tiles > 128 ? 1 : (int)(256 / tiles);
     for (int want = 1; want <= max_sp && (want == 1 || KT / want >= 4); ++want) {
       const int per = (KT + want - 1) / want, sp = (KT + per - 1) / per;
-      if (sp != want || (sp > 1 && (int64_t)sp * M * N * 4 > ws_bytes)) continue;
+      if (sp != want) continue;
       const float rounds = (float)(tiles * sp) / 256.0f, fill = rounds < 1.f ? rounds : 1.f;
       // microseconds per k-tile of 64: busier chips clock lower and share the L2s
       const float kt_us = bm == 256 ? 1.08f + 0.42f * fill : bm == 192 ? 0.97f + 0.30f * fill : 0.85f + 0.15f * fill;
@@ -1026,15 +1026,15 @@ float plan_one(int M, int N, int K, bool may_split, int64_t ws_bytes, bool full_
 // two launches, the rest in tiles of rest_bm rows.  Neither is split and both are the same kernel, so that a row's sums keep
 // their order whatever the number of rows around it.  QKV over 4096 rows (1.5 rounds) 174 -> 162 us, over 8500 rows 348 -> 325 us;
 // down over 13300 rows (3.25 rounds) 1271 -> 1184 us.
-GemmPlan gemm_plan(int M, int N, int K, bool may_split, int64_t ws_bytes) {
+GemmPlan gemm_plan(int M, int N, int K, bool may_split) {
   GemmPlan best, head, rest;
-  const float us = plan_one(M, N, K, may_split, ws_bytes, false, &best);
+  const float us = plan_one(M, N, K, may_split, false, &best);
   const int tiles_n = (N + 255) / 256;
   const int64_t rounds = (int64_t)((M + 255) / 256) * tiles_n / 256;
   const int64_t head_rows = rounds * 256 / tiles_n * 256;
   if (best.splits == 1 && rounds >= 1 && head_rows >= 256 && M - head_rows > 64) {
-    const float two = plan_one((int)head_rows, N, K, false, 0, true, &head) +
-                      plan_one((int)(M - head_rows), N, K, false, 0, false, &rest) + 2.f;
+    const float two = plan_one((int)head_rows, N, K, false, true, &head) +
+                      plan_one((int)(M - head_rows), N, K, false, false, &rest) + 2.f;
     if (two < us * 0.97f) best = {256, 1, K / BK, (int)head_rows, rest.bm};
   }
   return best;
@@ -1099,7 +1099,7 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
     if (variant == 1) return launch16(256, A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, 1, KT, s);
   }
   if (variant == 0 && M > 64) {
-    const GemmPlan p = gemm_plan(M, N, K, ws != nullptr && !(epi & EPI_SWIGLU), ws_bytes);
+    const GemmPlan p = gemm_plan(M, N, K, ws != nullptr && !(epi & EPI_SWIGLU));
     if (p.head_rows > 0) {
       // a pair of events taken for this call spans both launches
       const hipEvent_t stop = g_launch_ev_stop;
@@ -1112,6 +1112,7 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
                       R ? (const char*)R + r * ldr * (epi & EPI_R_F32 ? 4 : 2) : nullptr, ldr, M - p.head_rows, N, K, epi, 1, KT, s);
     }
     if (p.splits == 1) return launch16(p.bm, A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, 1, KT, s);
+    if (ws_bytes < gemm_mfma_split_bytes(M, N, K)) return hipErrorNotSupported;
     hipError_t e = launch16(p.bm, A, lda, W, ldw, w_blocks, ws, N, nullptr, 0, M, N, K, EPI_C_F32, p.splits, p.per, s);
     if (e != hipSuccess) return e;
     const int64_t quads = (int64_t)M * (N / 4);
@@ -1165,17 +1166,17 @@ hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, 
 
 // More than 64 rows, dense operands: whether the contraction is split, i.e. a reduction runs behind the projection, which
 // can then do the step that follows (the two launchers below).
-bool gemm_mfma_splits(int M, int N, int K, int64_t ws_bytes) {
+bool gemm_mfma_splits(int M, int N, int K) {
   return g_variant == 0 && M > 64 && K >= BK && K % BK == 0 && N % 8 == 0 && (int64_t)M * K * 2 < ((int64_t)1 << 32) &&
-         (int64_t)N * K * 2 < ((int64_t)1 << 32) && gemm_plan(M, N, K, true, ws_bytes).splits > 1;
+         (int64_t)N * K * 2 < ((int64_t)1 << 32) && gemm_plan(M, N, K, true).splits > 1;
 }
 
 // QKV + RoPE + KV write: q rows in qkv [M, N], k and v only in the cache
 hipError_t launch_gemm_split_rope(const void* A, const void* W, int w_blocks, void* qkv, const float2* cs, void* k_rows, void* v_rows,
                                   int M, int K, int Hq, int Hkv, int dh, void* ws, int64_t ws_bytes, hipStream_t s) {
   const int N = (Hq + 2 * Hkv) * dh;
-  if (!ws || dh % 8 || !gemm_mfma_splits(M, N, K, ws_bytes)) return hipErrorNotSupported;
-  const GemmPlan p = gemm_plan(M, N, K, true, ws_bytes);
+  if (!ws || dh % 8 || !gemm_mfma_splits(M, N, K) || ws_bytes < gemm_mfma_split_bytes(M, N, K)) return hipErrorNotSupported;
+  const GemmPlan p = gemm_plan(M, N, K, true);
   hipError_t e = launch16(p.bm, A, K, W, K, w_blocks, ws, N, nullptr, 0, M, N, K, EPI_C_F32, p.splits, p.per, s);
   if (e != hipSuccess) return e;
   const int64_t units = (int64_t)M * ((Hq + Hkv) * (dh / 8) + Hkv * dh / 4);
@@ -1194,7 +1195,7 @@ hipError_t launch_gemm_rope(const void* A, const void* W, void* qkv, const float
                             int Hkv, hipStream_t s) {
   const int N = (Hq + 2 * Hkv) * 128;
   if (!gemm_mfma_rope_supported(M, N, K, 1, 128)) return hipErrorNotSupported;
-  const GemmPlan p = gemm_plan(M, N, K, false, 0);
+  const GemmPlan p = gemm_plan(M, N, K, false);
   auto run = [&](int bm, int64_t r0, int64_t rows) {
     const RopeOut ro = {cs + r0 * 64, (bf16_t*)k_rows + r0 * Hkv * 128, (bf16_t*)v_rows + r0 * Hkv * 128, Hq, Hkv};
     auto f = bm == 128 ? launch16_rope<128> : bm == 192 ? launch16_rope<192> : launch16_rope<256>;
@@ -1212,8 +1213,8 @@ hipError_t launch_gemm_rope(const void* A, const void* W, void* qkv, const float
 // h [M, d] fp32 = x W^T + R and xn [M, d] = rmsnorm(h) * g; d <= 8192
 hipError_t launch_gemm_split_norm(const void* A, const void* W, int w_blocks, float* h, const void* R, int r_f32, const void* g, void* xn,
                                   float eps, int M, int d, int K, void* ws, int64_t ws_bytes, hipStream_t s) {
-  if (!ws || d > 8192 || !gemm_mfma_splits(M, d, K, ws_bytes)) return hipErrorNotSupported;
-  const GemmPlan p = gemm_plan(M, d, K, true, ws_bytes);
+  if (!ws || d > 8192 || !gemm_mfma_splits(M, d, K) || ws_bytes < gemm_mfma_split_bytes(M, d, K)) return hipErrorNotSupported;
+  const GemmPlan p = gemm_plan(M, d, K, true);
   hipError_t e = launch16(p.bm, A, K, W, K, w_blocks, ws, d, nullptr, 0, M, d, K, EPI_C_F32, p.splits, p.per, s);
   if (e != hipSuccess) return e;
   if (d <= 4096)

@@ -75,6 +75,18 @@ def test_split_does_not_depend_on_the_models_capacity(B, d, F, rows):
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
 
 
+def test_linear_does_not_depend_on_earlier_calls(B):
+    # the first wide call of the process makes the shared scratch grow
+    M, N, K = 400, 4096, 14336
+    x, w, wide = (torch.randn(n, k, device="cuda").to(torch.bfloat16) for n, k in ((M, K), (N, K), (60000, 64)))
+    y = [torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    B.dsk_linear(B.DSK_BF16, x, w, y[0], None, M, N, K)
+    B.dsk_linear(B.DSK_BF16, x[:, :64].contiguous(), wide, torch.empty((M, 60000), dtype=torch.bfloat16, device="cuda"), None, M, 60000, 64)
+    B.dsk_linear(B.DSK_BF16, x, w, y[1], None, M, N, K)
+    torch.cuda.synchronize()
+    assert torch.equal(y[0], y[1])
+
+
 # the router on the matrix cores: token counts around multiples of 16, one to four blocks of experts, contractions shorter
 # and longer than the steps in flight, a row of NaN; the choice must be one of the best by more than fp32 sums can differ
 @pytest.mark.parametrize("n,d,E,k", [(65, 32, 2, 1), (80, 320, 16, 2), (100, 4096, 17, 8), (129, 1056, 33, 3), (70, 2080, 64, 8)])
