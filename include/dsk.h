@@ -115,7 +115,8 @@ typedef struct {
 
 /* flags of dsk_partial_prefill */
 #define DSK_DEFER_JOIN 1u /* do not make `stream` wait for the reused-layer loads at the end of the call;
-                             the following dsk_suffix_prefill waits layer by layer, or call dsk_join_loads */
+                             the following dsk_suffix_prefill waits layer by layer (layers that are loaded together at
+                             the first of them), or call dsk_join_loads */
 /* How the reused layers are brought in (the three strategies of Sec. 4.3, Fig. 13). */
 typedef enum {
   DSK_LOAD_PIPELINED = 0,    /* (c) E cache first, reused layers on the side stream under the recompute */
@@ -348,7 +349,8 @@ DSK_API int dsk_moe_route(int dtype, const void* x, const void* wr, int n, int d
 DSK_API int dsk_set_option(const char* name, int value);
 
 /* Counters since the last reset: "e_cache_chunks" (row chunks of host-resident E caches that a first recomputed
- * layer followed as they arrived), "gemm_mfma_launches", "gemm_generic_launches", "attn_mfma_launches",
+ * layer followed as they arrived), "splice_launches" (launches that copied reused layers from a device-resident cache, a run
+ * of layers each), "gemm_mfma_launches", "gemm_generic_launches", "attn_mfma_launches",
  * "attn_generic_launches" (the two "generic" ones count fp32 work, on whichever kernel), "attn_key_split_launches" (tensor-core attention launches that split the keys over
  * workgroups) and, of those, "attn_packed_head_launches" (the q heads of a kv group share a workgroup, at most 64 queries per sequence); and for the
  * launches bracketed under "time_gemm": "timed_gemm_launches", "timed_gemm_ms" (sum of their durations; waits for

@@ -75,3 +75,28 @@ def test_strategies_over_a_slow_link_follow_the_schedule_model():
         torch.cuda.synchronize()
         for name in outs:
             assert torch.equal(outs[name][0], ref_kv) and torch.equal(outs[name][1], ref_h), name
+
+
+# Device-resident layers: one launch per run of layers, but in full reuse with a deferred join, where nothing else covers the
+# loads, the suffix pass follows launches of 1, 2, 4, .. layers; the result is the same either way
+@pytest.mark.parametrize("lo,hi,deferred,launches", [(0, 0, True, 4), (3, 3, True, 4), (0, 0, False, 1), (2, 3, True, 2), (0, 5, True, 1)])
+def test_launches_of_device_resident_layers(lo, hi, deferred, launches):
+    from paper_2411_02820_amd import binding as B
+    from tests import gpu_util as G
+    n, s = 300, 20
+    hidden = G.to_dev(synth.hidden_states(SHAPE, n), SHAPE)
+    xs = G.to_dev(synth.hidden_states(SHAPE, s, seed=synth.SEED_SUFFIX), SHAPE)
+    kv = G.to_dev(synth.kv_cache(SHAPE, n), SHAPE)
+    with G.GpuModel(SHAPE, n, n + s) as m:
+        m.init_random(3)
+        ref_kv, _ = m.partial(hidden, lo, hi, kv, [n], n_rows=n + s)
+        torch.cuda.synchronize()
+        ref = m.suffix(xs, ref_kv, [n], [s])
+        out_kv = m.new_cache(n + s, fill=float("nan"))
+        torch.cuda.synchronize()
+        B.dsk_set_option("reset_stats", 0)
+        m.partial(hidden, lo, hi, kv, [n], kv_out=out_kv, flags=B.DSK_DEFER_JOIN if deferred else 0)
+        out = m.suffix(xs, out_kv, [n], [s])
+        torch.cuda.synchronize()
+        assert B.dsk_get_stat("splice_launches") == launches
+    assert torch.equal(out, ref) and torch.equal(out_kv, ref_kv)
