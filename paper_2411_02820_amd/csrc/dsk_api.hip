@@ -75,6 +75,17 @@ void free_model(dsk_model* m) {
   free(m);
 }
 
+// Memory of the current device.  What the runtime does not know is taken not to be.
+bool on_this_device(const void* p) {
+  hipPointerAttribute_t at;
+  int dev = -1;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == dev;
+}
+
 int check_batch(const dsk_batch_t* b, bool need_positions) {
   if (!b || !b->cu_seqlens_host || !b->cu_seqlens_dev) return DSK_EINVAL;
   if (need_positions && !b->positions_dev) return DSK_EINVAL;
@@ -854,16 +865,19 @@ int dsk_partial_prefill_groups(dsk_model_t* model, const dsk_group_t* groups, in
   auto loaded = [&](int l) { return kv_reused && !alias && (mode == DSK_LOAD_ALL_FIRST || !recomputed(l)); };
   const int64_t bytes = (int64_t)T * row_bytes;
   // Device to device, a run of layers goes in one launch and is waited for at its first layer.  Under a recomputation that
-  // costs nothing; where there is none and the join is deferred, the suffix pass would stand in front of the whole splice:
-  // there the launches take 1, 2, 4, .. layers, each copied while the pass is in the layers of those before it (a layer's
-  // rows take a tenth to a third of the pass's time for it).  32 layers of 8192 8B rows and 64 new tokens: 5053 us in one launch, 4951 us in
-  // six; 16384 rows 5858 and 5713 us.
+  // costs nothing; where there is none and the join is deferred, the suffix pass would stand behind the whole splice: there
+  // the launches take 1, 2, 4, .. layers, each copied while the pass is in the layers of those before it (copying a layer
+  // takes a tenth to a quarter of the pass's time for it).  32 8B layers and 64 new tokens: 8192 rows 5053 us in one
+  // launch, 4951 us in six; 16384 rows 5858 and 5713 us.
   const bool in_steps = n_recomputed == 0 && mode == DSK_LOAD_PIPELINED && (flags & DSK_DEFER_JOIN);
   int step = in_steps ? 1 : L;
+  // a kernel reads what this device can address; a copy also what lies on another one
+  const bool by_kernel = kv_reused && kv_kind == hipMemcpyDeviceToDevice && m->throttle_gbps <= 0.0 &&
+                         on_this_device(kv_reused->base) && on_this_device(kv_out->base);
   for (int l = 0; l < L; ++l) {
     if (!loaded(l)) continue;
     const int first = l;
-    if (kv_kind == hipMemcpyDeviceToDevice && m->throttle_gbps <= 0.0) {
+    if (by_kernel) {
       while (l + 1 < L && l + 1 - first < step && loaded(l + 1)) ++l;
       if (in_steps) step *= 2;
       ++g_stats.splices;

@@ -100,3 +100,23 @@ def test_launches_of_device_resident_layers(lo, hi, deferred, launches):
         torch.cuda.synchronize()
         assert B.dsk_get_stat("splice_launches") == launches
     assert torch.equal(out, ref) and torch.equal(out_kv, ref_kv)
+
+
+def test_cache_that_is_not_this_devices_memory_is_copied():
+    # a peer's cache, which a copy reaches without peer access and a kernel does not; here page-locked host memory stands for
+    # it, which both can address
+    from paper_2411_02820_amd import binding as B
+    from tests import gpu_util as G
+    n = 40
+    kv = G.to_dev(synth.kv_cache(SHAPE, n), SHAPE, pinned=True)
+    desc = B.kv_desc(kv)
+    desc.mem = B.DSK_MEM_DEVICE
+    batch = B.Batch(synth.cu_seqlens([n]), synth.packed_positions([n]))
+    with G.GpuModel(SHAPE, n) as m:
+        out = m.new_cache(n, fill=float("nan"))
+        torch.cuda.synchronize()
+        B.dsk_set_option("reset_stats", 0)
+        B.dsk_partial_prefill_groups(m.handle, [], desc, B.kv_desc(out), batch.desc)
+        torch.cuda.synchronize()
+        assert B.dsk_get_stat("splice_launches") == 0
+    assert torch.equal(out.cpu(), kv)
