@@ -357,7 +357,7 @@ hipError_t launch_few(const FewParams& p, int64_t blocks, hipStream_t s) {
     if (e != hipSuccess) return e;
     configured = true;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * QG * KH), lds, s, p);
+  DSK_LAUNCH_TIMED(kern, dim3((unsigned)blocks), dim3(64 * QG * KH), lds, s, p);
   return hipGetLastError();
 }
 

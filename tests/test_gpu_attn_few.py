@@ -140,3 +140,23 @@ def test_suffix_token_that_is_not_finite_reaches_later_tokens_only(B, n, pre, ba
         xs[bad] = float("nan")
         got = G.to_np(m.suffix(xs, cache, [pre], [n]))
     assert np.array_equal(got[:bad], clean[:bad]) and np.isnan(got[bad:]).all()
+
+
+# the timing hook takes every attention launch of a prefix pass of 1024 rows and more, on whichever kernel
+@pytest.mark.parametrize("lens,timed", [([1024], 2), ([100] * 11, 2), ([1200], 2), ([1023], 0)])
+def test_prefix_attention_is_timed(B, lens, timed):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(2, 256, 4, 2, 64, 256, 10000.0, 1e-5, "bf16")
+    x = G.to_dev(synth.hidden_states(shape, sum(lens)), shape)
+    with G.GpuModel(shape, sum(lens)) as m:
+        m.init_random(1)
+        B.dsk_set_option("reset_stats", 0)
+        B.dsk_set_option("time_gemm", 1)
+        try:
+            m.partial(x, 0, 2, None, lens)
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("time_gemm", 0)
+        assert B.dsk_get_stat("attn_mfma_launches") == 2 and B.dsk_get_stat("timed_attn_launches") == timed
+        assert (B.dsk_get_stat("timed_attn_ms") > 0) == (timed > 0)
+        assert B.dsk_get_stat("timed_attn_flops") == (2 * 4.0 * 4 * 64 * sum(n * (n + 1) / 2 for n in lens) if timed else 0)
