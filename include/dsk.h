@@ -351,8 +351,10 @@ DSK_API int dsk_set_option(const char* name, int value);
 /* Counters since the last reset: "e_cache_chunks" (row chunks of host-resident E caches that a first recomputed
  * layer followed as they arrived), "splice_launches" (launches that copied reused layers from a device-resident cache, a run
  * of layers each), "gemm_mfma_launches", "gemm_generic_launches", "attn_mfma_launches",
- * "attn_generic_launches" (the two "generic" ones count fp32 work, on whichever kernel), "attn_key_split_launches" (tensor-core attention launches that split the keys over
- * workgroups) and, of those, "attn_packed_head_launches" (the q heads of a kv group share a workgroup, at most 64 queries per sequence); and for the
+ * "attn_generic_launches" (the two "generic" ones count fp32 work, on whichever kernel), "attn_few_query_launches"
+ * (tensor-core attention launches on the kernel for few queries, whose workgroups take the q heads of a kv group together),
+ * "attn_key_split_launches" (tensor-core attention launches that split the keys over workgroups) and, of those,
+ * "attn_packed_head_launches" (calls with at most 64 queries per sequence, all on the kernel for few queries); and for the
  * launches bracketed under "time_gemm": "timed_gemm_launches", "timed_gemm_ms" (sum of their durations; waits for
  * them to finish), "timed_gemm_flops" (sum of 2*M*N*K), and the same three as "timed_attn_..." for the attention
  * launches (flops = 4*Hq*dh per (query, visible key) pair, i.e. causal). */

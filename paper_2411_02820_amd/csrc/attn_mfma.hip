@@ -538,13 +538,14 @@ __global__ void __launch_bounds__(256) transpose_v_kernel(const bf16_t* __restri
 
 }  // namespace
 
-// how many launches took the key-split path, and how many of those with the q heads of a kv group packed per workgroup and at
-// most 64 queries per sequence
-static int64_t g_split_launches = 0, g_packed_launches = 0;
-void attn_mfma_counts(int64_t* split, int64_t* packed, int reset) {
+// how many calls split the keys over workgroups, how many of those had at most 64 queries per sequence, and how many calls
+// the kernel for few queries (attn_few.hip) took
+static int64_t g_split_launches = 0, g_split_64_launches = 0, g_few_launches = 0;
+void attn_mfma_counts(int64_t* split, int64_t* split_64, int64_t* few, int reset) {
   if (split) *split = g_split_launches;
-  if (packed) *packed = g_packed_launches;
-  if (reset) g_split_launches = g_packed_launches = 0;
+  if (split_64) *split_64 = g_split_64_launches;
+  if (few) *few = g_few_launches;
+  if (reset) g_split_launches = g_split_64_launches = g_few_launches = 0;
 }
 
 // fp32 scratch for the split mode: n_q * splits <= kMaxSplitRows partial rows of (dh + 2) floats per q head
@@ -597,11 +598,12 @@ hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s) {
   if (attn_few_supported(a)) {
     int splits = 1;
     hipError_t e = launch_attn_few(a, &splits, s);
+    if (e == hipSuccess) ++g_few_launches;
     if (e == hipSuccess && splits > 1) {
       ++g_split_launches;
-      bool packed = true;  // counted as such: at most 64 queries per sequence
-      for (int b = 0; b < a.n_seqs; ++b) packed &= a.q_cu_host[b + 1] - a.q_cu_host[b] <= 64;
-      if (packed) ++g_packed_launches;
+      bool up_to_64 = true;
+      for (int b = 0; b < a.n_seqs; ++b) up_to_64 &= a.q_cu_host[b + 1] - a.q_cu_host[b] <= 64;
+      if (up_to_64) ++g_split_64_launches;
     }
     return e;
   }

@@ -1177,7 +1177,7 @@ int dsk_set_option(const char* name, int value) {
     std::lock_guard<std::mutex> timed_lock(g_stats.timed_mu);
     g_stats.gemm.n = g_stats.attn.n = 0;
     g_stats.gemm.flops = g_stats.attn.flops = 0.0;
-    attn_mfma_counts(nullptr, nullptr, 1);
+    attn_mfma_counts(nullptr, nullptr, nullptr, 1);
   } else return DSK_EINVAL;
   return DSK_OK;
 }
@@ -1190,10 +1190,10 @@ int dsk_get_stat(const char* name, double* value) {
   else if (!strcmp(name, "attn_generic_launches")) *value = (double)g_stats.attn_generic.load();
   else if (!strcmp(name, "e_cache_chunks")) *value = (double)g_stats.e_chunks.load();
   else if (!strcmp(name, "splice_launches")) *value = (double)g_stats.splices.load();
-  else if (!strcmp(name, "attn_key_split_launches") || !strcmp(name, "attn_packed_head_launches")) {
-    int64_t split = 0, packed = 0;
-    attn_mfma_counts(&split, &packed, 0);
-    *value = (double)(name[5] == 'k' ? split : packed);
+  else if (!strcmp(name, "attn_key_split_launches") || !strcmp(name, "attn_packed_head_launches") || !strcmp(name, "attn_few_query_launches")) {
+    int64_t split = 0, split_64 = 0, few = 0;
+    attn_mfma_counts(&split, &split_64, &few, 0);
+    *value = (double)(name[5] == 'k' ? split : name[5] == 'p' ? split_64 : few);
   }
   else if (!strncmp(name, "timed_gemm_", 11) || !strncmp(name, "timed_attn_", 11)) {
     std::lock_guard<std::mutex> timed_lock(g_stats.timed_mu);

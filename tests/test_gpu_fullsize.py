@@ -374,9 +374,9 @@ def test_8b_shape_suffix_ragged_against_oracle(G, B):
 @pytest.mark.parametrize("name,width,S", [("8B", synth.LLAMA_8B, 64), ("8B", synth.LLAMA_8B, 17), ("70B", synth.LLAMA_70B, 64)])
 def test_suffix_pass_at_model_width_against_oracle(G, B, name, width, S):
     # Two layers of the 8B / 70B layer shape, 8192 seeded N(0,1) prefix rows in the cache, S <= 64 new tokens: the
-    # whole suffix pass (Sec. 4.1) against the oracle - few-row projections on the K-split weight-streaming tiles
-    # (64x128 tiles for gate/up), RoPE + cache write, residual + RMSNorm and SwiGLU applied by the split-K
-    # reductions, key-split attention with the q heads of a kv group packed per workgroup, at real widths.
+    # whole suffix pass (Sec. 4.1) against the oracle - few-row projections streaming weights and activations in blocks,
+    # with RoPE + cache write, residual + the next RMSNorm's input and SwiGLU applied by the projections (down at 64 rows:
+    # by the reduction of its split), key-split attention on the kernel for few queries, at real widths.
     shape = synth.ModelShape(2, width.hidden, width.n_q_heads, width.n_kv_heads, width.head_dim, width.ffn,
                              width.rope_base, width.rms_eps, "bf16")
     cfg = oracle_config(shape)
@@ -391,6 +391,7 @@ def test_suffix_pass_at_model_width_against_oracle(G, B, name, width, S):
         hs = m.suffix(G.to_dev(xs_host, shape), kv, [T], [S])
         torch.cuda.synchronize()
         assert B.dsk_get_stat("attn_packed_head_launches") == 2 and B.dsk_get_stat("attn_generic_launches") == 0
+        assert B.dsk_get_stat("attn_few_query_launches") == 2
         assert B.dsk_get_stat("gemm_mfma_launches") == 8 and B.dsk_get_stat("gemm_generic_launches") == 0
         kv_s, hs_ref = O.suffix_prefill(cfg, lambda l: host_layer(shape, synth.SEED_RECEIVER, l), xs_host.astype(np.float64),
                                         [host_kv_rows(shape, l, T) for l in range(2)], spos, cu, cus)
@@ -405,8 +406,8 @@ def test_suffix_pass_at_model_width_against_oracle(G, B, name, width, S):
 
 def test_8b_width_prefix_of_few_tokens(G, B):
     # A prefix of at most 64 tokens at the 8B layer width takes the few-row projections inside the selective prefill as
-    # well (K-split tiles, RoPE / SwiGLU in the reductions, the post-attention RMSNorm split around the gate/up
-    # projection): two layers over 48 tokens of two sequences against the oracle.
+    # well (RoPE and SwiGLU in the projections, the RMSNorms split around them): two layers over 48 tokens of two sequences
+    # against the oracle.
     base = synth.LLAMA_8B
     shape = synth.ModelShape(2, base.hidden, base.n_q_heads, base.n_kv_heads, base.head_dim, base.ffn, base.rope_base,
                              base.rms_eps, "bf16")
@@ -481,11 +482,12 @@ def test_config5_70b_prefix8192_layers_20_36(G, B):
         hs = m.suffix(xs, kv_out, [T], [S])
         torch.cuda.synchronize()
         assert B.dsk_get_stat("attn_packed_head_launches") == shape.n_layers and B.dsk_get_stat("gemm_generic_launches") == 0
+        assert B.dsk_get_stat("attn_few_query_launches") == shape.n_layers
         for l in (0, lo - 1, hi, shape.n_layers - 1):
             assert torch.equal(kv_out[l, :, :T], kv_r[l]), f"splice of layer {l}"
         assert torch.isfinite(h_out.float()).all() and torch.isfinite(hs.float()).all()
-        # the suffix pass at 70B width (8 q heads per kv head packed per workgroup, 64x128 few-row tiles, the
-        # 8192-wide fused reduce + RMSNorm): what it wrote for layers 0 and 1
+        # the suffix pass at 70B width (8 q heads per kv head, 128-column tiles for gate/up, split contractions of the 8192
+        # wide projections): what it wrote for layers 0 and 1
         rows, ref = suffix_kv_of_first_two_layers(oracle_config(shape), shape, synth.hidden_states(shape, S, seed=synth.SEED_SUFFIX),
                                                   synth.packed_positions([S], start=[T]), synth.cu_seqlens([T]),
                                                   synth.cu_seqlens([S]), T, [0])

@@ -146,8 +146,9 @@ def test_small_bf16_dh64_strong_weights(G):
     run_case(G, SMALL_BF16_DH64, [257, 64], 0, 2, [31, 2], 8.0)
 
 
-# suffix attention with the keys split over workgroups (few queries against >= 7 key tiles): four q heads of a kv
-# group packed into one workgroup (sequences of at most 64 queries; 4 and 8 heads per kv group), and unpacked
+# suffix attention with the keys split over workgroups: on the kernel for few queries, which takes the q heads of a kv
+# group together (up to 128 queries per sequence, or a short prompt; 4 and 8 heads per kv group), and on the kernel with
+# one head per workgroup
 def _split_counts(G, fn):
     from paper_2411_02820_amd import binding as B
     B.dsk_set_option("reset_stats", 0)
@@ -155,20 +156,33 @@ def _split_counts(G, fn):
     return B.dsk_get_stat("attn_key_split_launches"), B.dsk_get_stat("attn_packed_head_launches")
 
 
+def _few_launches():
+    from paper_2411_02820_amd import binding as B
+    return B.dsk_get_stat("attn_few_query_launches")
+
+
 def test_small_bf16_key_split_packed_heads(G):
     split, packed = _split_counts(G, lambda: run_case(G, SMALL_BF16, [700], 1, 3, [40], None))
-    # the suffix pass of every layer packs; the prefix pass (700 queries) splits the keys too, unpacked
+    # the suffix pass of every layer, and the prefix pass (700 queries, two layers) splits the keys too
     assert packed == SMALL_BF16.n_layers and split > packed
+    assert _few_launches() == SMALL_BF16.n_layers + 2
 
 
 def test_small_bf16_key_split_packed_heads_group_of_8_ragged(G):
     split, packed = _split_counts(G, lambda: run_case(G, SMALL_BF16_G8, [600, 450], 0, 2, [40, 9], 2.0))
     assert packed == SMALL_BF16_G8.n_layers and split > packed
+    assert _few_launches() == SMALL_BF16_G8.n_layers   # the prefix pass, 1050 queries, is on the other kernel
+
+
+def test_small_bf16_key_split_100_queries(G):
+    split, packed = _split_counts(G, lambda: run_case(G, SMALL_BF16, [700], 1, 3, [100], None))
+    assert split >= SMALL_BF16.n_layers and packed == 0
+    assert _few_launches() == SMALL_BF16.n_layers + 2
 
 
 def test_small_bf16_key_split_unpacked(G):
-    split, packed = _split_counts(G, lambda: run_case(G, SMALL_BF16, [700], 1, 3, [100], None))
-    assert split >= SMALL_BF16.n_layers and packed == 0
+    split, packed = _split_counts(G, lambda: run_case(G, SMALL_BF16, [1030], 1, 3, [130], None))
+    assert split == SMALL_BF16.n_layers + 2 and packed == 0 and _few_launches() == 0
 
 
 def test_pure_splice_and_aliasing(G):
