@@ -348,6 +348,13 @@ DSK_API int dsk_moe_route(int dtype, const void* x, const void* wr, int n, int d
  *   "reset_stats": any value; clears all counters and recorded timings */
 DSK_API int dsk_set_option(const char* name, int value);
 
+/* How the bf16 GEMM runs M > 64 rows x N columns over a contraction of K (a multiple of 64), a matter of these sizes alone (host
+ * code, no device work): plan[0] rows of a tile (of 256 columns), plan[1] workgroups that share a contraction, plan[2] rows
+ * that run first, in whole rounds of 256-row tiles, while the rest follows in a launch of its own (0: one launch), plan[3]
+ * rows of a tile of that rest.  may_split: 0 for gate/up, for QKV as its sums are rotated in place, and for dsk_linear over
+ * more than 4096 rows.  Gate/up over at most 256 rows runs on 128 x 128 tiles whatever the plan. */
+DSK_API int dsk_gemm_plan(int M, int N, int K, int may_split, int32_t* plan);
+
 /* Counters since the last reset: "e_cache_chunks" (row chunks of host-resident E caches that a first recomputed
  * layer followed as they arrived), "splice_launches" (launches that copied reused layers from a device-resident cache, a run
  * of layers each), "gemm_mfma_launches", "gemm_generic_launches", "attn_mfma_launches",

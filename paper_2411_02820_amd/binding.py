@@ -40,7 +40,7 @@ EXPORTS = (
     "dsk_strerror", "dsk_last_hip_error", "dsk_hash_context", "dsk_store_create", "dsk_store_destroy",
     "dsk_store_put_kv", "dsk_store_put_e", "dsk_store_fetch_kv_layer", "dsk_store_fetch_kv", "dsk_store_fetch_e",
     "dsk_store_erase", "dsk_store_usage", "dsk_estimate_prefill_ms", "dsk_select_recompute", "dsk_linear", "dsk_linear_static", "dsk_attention", "dsk_set_option", "dsk_get_stat",
-    "dsk_moe_route",
+    "dsk_moe_route", "dsk_gemm_plan",
 )
 
 
@@ -95,6 +95,7 @@ lib.dsk_attention.argtypes = [C.c_int, _P, _P, _P, _P, C.POINTER(dsk_batch_t), C
                               C.c_int, C.c_int, C.c_int, _P, C.c_int64, _P]
 lib.dsk_moe_route.argtypes = [C.c_int, _P, _P, C.c_int, C.c_int, C.c_int, C.c_int, _P, _P, _P]
 lib.dsk_set_option.argtypes = [C.c_char_p, C.c_int]
+lib.dsk_gemm_plan.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]
 lib.dsk_get_stat.argtypes = [C.c_char_p, C.POINTER(C.c_double)]
 lib.dsk_join_loads.argtypes = [_P, _P]
 lib.dsk_set_load_mode.argtypes = [_P, C.c_int]
@@ -250,6 +251,13 @@ def DSK_EXPERT(e: int, t: int) -> int:
 
 def dsk_set_option(name: str, value: int):
     _check(lib.dsk_set_option(name.encode(), value), "dsk_set_option")
+
+
+def dsk_gemm_plan(M: int, N: int, K: int, may_split: bool = True):
+    """-> (tile rows, splits, rows of the first of two launches or 0, tile rows of the second)"""
+    plan = (C.c_int32 * 4)()
+    _check(lib.dsk_gemm_plan(M, N, K, int(may_split), plan), "dsk_gemm_plan")
+    return tuple(plan)
 
 
 def dsk_get_stat(name: str) -> float:

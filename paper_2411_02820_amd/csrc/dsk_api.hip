@@ -1182,6 +1182,12 @@ int dsk_set_option(const char* name, int value) {
   return DSK_OK;
 }
 
+int dsk_gemm_plan(int M, int N, int K, int may_split, int32_t* plan) {
+  if (!plan || M <= 64 || N < 1 || K < 64 || K % 64) return DSK_EINVAL;
+  gemm_mfma_plan(M, N, K, may_split, plan);
+  return DSK_OK;
+}
+
 int dsk_get_stat(const char* name, double* value) {
   if (!name || !value) return DSK_EINVAL;
   if (!strcmp(name, "gemm_mfma_launches")) *value = (double)g_stats.gemm_mfma.load();

@@ -263,3 +263,4 @@ hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, 
 void gemm_mfma_set_variant(int v);
 void attn_mfma_counts(int64_t* split, int64_t* split_64, int64_t* few, int reset);
 bool gemm_mfma_uses_prefill_tile(int M, int N);
+void gemm_mfma_plan(int M, int N, int K, int may_split, int32_t* plan);  // dsk_gemm_plan

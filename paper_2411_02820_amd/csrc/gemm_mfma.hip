@@ -1075,6 +1075,11 @@ int64_t gemm_mfma_split_bytes(int64_t max_m, int N, int K) {
   return bytes < most ? bytes : most;
 }
 
+void gemm_mfma_plan(int M, int N, int K, int may_split, int32_t* plan) {
+  const GemmPlan p = gemm_plan(M, N, K, may_split);
+  plan[0] = p.bm; plan[1] = p.splits; plan[2] = p.head_rows; plan[3] = p.rest_bm;
+}
+
 // Whether a projection of this size runs on the 256 x 256 prefill tiling (the kernel the roofline figure is about).
 bool gemm_mfma_uses_prefill_tile(int M, int N) {
   return M > 64 && (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 192;

@@ -16,32 +16,57 @@ def B():
     return binding
 
 
-# row-major weights through the component call: rows around multiples of 128, 192 and 256, columns that end inside a tile,
-# contractions of a few k-tiles (unsplit) and many (split with an uneven last share), and more than one round of tiles
-@pytest.mark.parametrize("M,N,K,residual", [(65, 64, 64, False), (129, 516, 320, True), (191, 1028, 1984, False),
-                                            (193, 256, 4096, True), (257, 2052, 1024, True), (385, 512, 8192, False),
-                                            (1025, 1024, 2048, True), (2000, 2560, 256, False), (3000, 5000, 192, True),
-                                            (4200, 4612, 128, True)])   # whole rounds and a rest, in two launches
-def test_linear_bf16_medium_rows(B, M, N, K, residual):
+# row-major weights through the component call: rows around multiples of 128, 192 and 256, columns that end inside a tile; on
+# every form a projection can take: each tile height unsplit and split (an uneven last share), and two launches, whole
+# rounds of 256-row tiles and a rest in either lower height, with the residual's and the result's rows of the second
+@pytest.mark.parametrize("M,N,K,residual,plan", [
+    (65, 64, 64, False, (128, 1, 0, 0)), (129, 516, 320, True, (128, 1, 0, 0)), (2000, 2560, 256, False, (128, 1, 0, 0)),
+    (4200, 4612, 128, True, (192, 1, 0, 0)), (3000, 5000, 192, True, (256, 1, 0, 0)),
+    (191, 1028, 1984, False, (128, 7, 0, 0)), (193, 256, 4096, True, (128, 16, 0, 0)), (257, 2052, 1024, True, (128, 4, 0, 0)),
+    (385, 512, 8192, False, (128, 16, 0, 0)), (1025, 1024, 2048, True, (128, 4, 0, 0)),
+    (129, 4100, 4096, True, (192, 8, 0, 0)), (129, 3076, 8192, False, (192, 13, 0, 0)), (700, 2052, 8192, True, (192, 7, 0, 0)),
+    (385, 4100, 8192, True, (256, 7, 0, 0)), (769, 3076, 4096, False, (256, 4, 0, 0)),
+    (5000, 4612, 4096, True, (256, 1, 3328, 192)), (7700, 4612, 2048, True, (256, 1, 6656, 128))])
+def test_linear_bf16_medium_rows(B, M, N, K, residual, plan):
+    assert B.dsk_gemm_plan(M, N, K, M <= 4096) == plan
     bf = lambda a: synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(a))
     x = bf(synth.normal(M * K, 51, 0, 1.0).reshape(M, K))
     w = bf(synth.normal(N * K, 51, 1, 0.05).reshape(N, K))
     r = bf(synth.normal(M * N, 51, 2, 1.0).reshape(M, N)) if residual else None
     ref = x.astype(np.float64) @ w.astype(np.float64).T + (0 if r is None else r.astype(np.float64))
     dev = lambda a: torch.from_numpy(a).to(torch.bfloat16).cuda()
+    xd, wd, rd = dev(x), dev(w), None if r is None else dev(r)
     y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
-    B.dsk_linear(B.DSK_BF16, dev(x), dev(w), y, None if r is None else dev(r), M, N, K)
+    B.dsk_linear(B.DSK_BF16, xd, wd, y, rd, M, N, K)
     torch.cuda.synchronize()
     # one bf16 rounding of the result
     assert O.max_rel_err(y.float().cpu().numpy(), ref) <= 2 ** -8
+    if plan[1] == 1:   # unsplit, every tile height adds in one order
+        y256 = torch.full_like(y, float("nan"))
+        B.dsk_set_option("gemm_tiling", 1)
+        try:
+            B.dsk_linear(B.DSK_BF16, xd, wd, y256, rd, M, N, K)
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("gemm_tiling", 0)
+        assert torch.equal(y, y256)
 
 
-# two layers, so that the split down projection also leaves the next layer's norm input; dh 64 and 128; against the same
-# model with the tiling forced (which neither splits nor fuses)
-@pytest.mark.parametrize("rows", [65, 130, 200, 390])
-@pytest.mark.parametrize("d,Hq,Hkv,dh,F", [(512, 4, 2, 128, 2048), (1088, 17, 1, 64, 1472)])
-def test_layers_with_split_projections(B, rows, d, Hq, Hkv, dh, F):
+# two layers, so that the split down projection also leaves the next layer's norm input; against the same model with the
+# tiling forced (which neither splits nor fuses).  plans: (tile rows, splits) of QKV, O and down: RoPE + KV write with heads
+# of 64 and 128 and RMSNorm at widths up to 4096 and beyond in the reduction, every tile height, QKV unsplit
+@pytest.mark.parametrize("d,Hq,Hkv,dh,F,rows,plans", [
+    (512, 4, 2, 128, 2048, 65, ((128, 1), (128, 1), (128, 8))), (512, 4, 2, 128, 2048, 130, ((128, 1), (128, 1), (128, 8))),
+    (512, 4, 2, 128, 2048, 200, ((128, 1), (128, 1), (128, 8))), (512, 4, 2, 128, 2048, 390, ((128, 1), (128, 1), (128, 8))),
+    (1088, 17, 1, 64, 1472, 65, ((128, 4), (128, 4), (128, 5))), (1088, 17, 1, 64, 1472, 130, ((128, 4), (128, 4), (128, 5))),
+    (1088, 17, 1, 64, 1472, 200, ((128, 4), (128, 4), (128, 5))), (1088, 17, 1, 64, 1472, 390, ((128, 3), (128, 3), (128, 4))),
+    (1024, 8, 2, 128, 4096, 65, ((128, 4), (128, 4), (128, 16))), (1024, 8, 2, 128, 4096, 257, ((128, 4), (128, 4), (128, 11))),
+    (4096, 32, 8, 128, 14336, 257, ((192, 4), (128, 5), (192, 8))), (4096, 32, 8, 128, 14336, 333, ((128, 3), (128, 5), (192, 8))),
+    (4096, 32, 8, 128, 14336, 700, ((256, 3), (192, 4), (256, 5))), (8192, 64, 8, 128, 14336, 130, ((192, 6), (192, 8), (192, 8))),
+    (8192, 64, 8, 128, 14336, 400, ((256, 3), (256, 4), (256, 4)))])
+def test_layers_with_split_projections(B, d, Hq, Hkv, dh, F, rows, plans):
     from tests import gpu_util as G
+    assert tuple(B.dsk_gemm_plan(rows, n, k)[:2] for n, k in (((Hq + 2 * Hkv) * dh, d), (d, Hq * dh), (d, F))) == plans
     shape = synth.ModelShape(2, d, Hq, Hkv, dh, F, 10000.0, 1e-5, "bf16")
     x = G.to_dev(synth.hidden_states(shape, rows), shape)
     with G.GpuModel(shape, rows) as m:
@@ -56,6 +81,24 @@ def test_layers_with_split_projections(B, rows, d, Hq, Hkv, dh, F):
     # both are bf16 evaluations of the same layers, each within 1e-2 of the exact ones at this weight scale
     for a, b in ((kv, kv_ref), (h, h_ref)):
         assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2e-2
+
+
+# O and down in two launches (residual bf16 and fp32, result fp32 and bf16, two layers): the rows of a call are those of a call
+# over fewer of the sequences, which has no second launch, bit for bit
+def test_layers_with_projections_in_two_launches(B):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(2, 2048, 32, 4, 128, 4096, 10000.0, 1e-5, "bf16")
+    n, few = 12400, 6000
+    assert B.dsk_gemm_plan(n, 2048, 4096)[2:] == (8192, 192) and B.dsk_gemm_plan(few, 2048, 4096)[1:3] == (1, 0)
+    assert B.dsk_gemm_plan(few, 5120, 2048)[1] == 1   # and QKV is not split either
+    x = G.to_dev(synth.hidden_states(shape, n), shape)
+    with G.GpuModel(shape, n) as m:
+        m.init_random(17)
+        kv, h = m.partial(x, 0, 2, None, [100] * (n // 100))
+        for r0 in (0, n - few):   # rows of the first launch, and of both
+            kv_few, h_few = m.partial(x[r0:r0 + few].contiguous(), 0, 2, None, [100] * (few // 100))
+            torch.cuda.synchronize()
+            assert torch.equal(h[r0:r0 + few], h_few) and torch.equal(kv[:, :, r0:r0 + few], kv_few)
 
 
 # how a contraction is split, and with it the order of its sums, is a matter of the call's sizes alone: the same rows on a
@@ -116,12 +159,16 @@ def test_router_on_the_matrix_cores(B, n, d, E, k):
 
 
 # RoPE + KV write in the epilogue of an unsplit QKV projection (heads of 128): every tile height, a last column tile that is
-# half full, rows that end inside a tile, whole rounds and a rest in two launches (22000 rows); against the same model with
+# half full, rows that end inside a tile, whole rounds and a rest in two launches; against the same model with
 # the tiling forced, where the rotation is a pass of its own over the rounded projection
-@pytest.mark.parametrize("lens", [[65], [150, 1], [300], [500, 140], [1000] * 22])
-def test_rope_in_the_projection(B, lens):
+@pytest.mark.parametrize("d,Hq,lens,plan", [
+    (128, 3, [65], (128, 1, 0, 0)), (128, 3, [150, 1], (128, 1, 0, 0)), (128, 3, [500, 140], (128, 1, 0, 0)),
+    (128, 3, [1000] * 11, (192, 1, 0, 0)), (128, 3, [1000] * 17 + [30], (256, 1, 0, 0)),
+    (2048, 25, [200] * 55 + [30], (256, 1, 9216, 128)), (4096, 25, [200] * 35 + [30], (256, 1, 4608, 192))])
+def test_rope_in_the_projection(B, d, Hq, lens, plan):
+    assert B.dsk_gemm_plan(sum(lens), (Hq + 2) * 128, d) == plan
     from tests import gpu_util as G
-    shape = synth.ModelShape(1, 128, 3, 1, 128, 128, 10000.0, 1e-5, "bf16")
+    shape = synth.ModelShape(1, d, Hq, 1, 128, 128, 10000.0, 1e-5, "bf16")
     x = G.to_dev(synth.hidden_states(shape, sum(lens)), shape)
     with G.GpuModel(shape, sum(lens)) as m:
         m.init_random(9)
