@@ -37,7 +37,7 @@ constexpr int BKV = 64;  // keys per tile
 struct AttnParams {
   const bf16_t* q; int64_t ldq;
   const bf16_t* k; const bf16_t* vt; int64_t ldvt;
-  bf16_t* out; int out_blocks;  // rows of Hq*dh, or blocks (block_at)
+  bf16_t* out;
   float* part_o; float* part_ml;  // split mode: [n_q][Hq][splits][dh] and [n_q][Hq][splits][2]
   const int32_t* q_cu; const int32_t* p_cu;
   int n_seqs; int own_row0; int Hq, Hkv; int total_tiles; int splits;
@@ -429,9 +429,7 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
           bf16x4 v;
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = (bf16_t)(o[dt][4 * g + e] * inv);
-          const int at = 32 * dt + 8 * g + 4 * hh;
-          if (p.out_blocks) *(bf16x4*)(p.out + block_at(qrow, h * DH + at, p.Hq * DH)) = v;
-          else *(bf16x4*)(op + at) = v;
+          *(bf16x4*)(op + 32 * dt + 8 * g + 4 * hh) = v;
         }
     }
   }
@@ -607,14 +605,15 @@ hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s) {
     }
     return e;
   }
-  if ((a.dh != 128 && a.dh != 64) || !a.vt || (a.ldq & 7) || a.own_row0 + a.n_q >= ((int64_t)1 << 31))
+  // (few rows, whose result goes out in blocks, are all with the kernel above)
+  if (a.out_blocks || (a.dh != 128 && a.dh != 64) || !a.vt || (a.ldq & 7) || a.own_row0 + a.n_q >= ((int64_t)1 << 31))
     return hipErrorNotSupported;
   // per-lane tile offsets are 32-bit byte offsets
   if ((int64_t)a.dh * a.ldvt * 2 >= ((int64_t)1 << 32) || (int64_t)BKV * a.Hkv * a.dh * 2 >= ((int64_t)1 << 32))
     return hipErrorNotSupported;
   AttnParams p;
   p.q = (const bf16_t*)a.q; p.ldq = a.ldq; p.k = (const bf16_t*)a.k_rows; p.vt = (const bf16_t*)a.vt; p.ldvt = a.ldvt;
-  p.out = (bf16_t*)a.out; p.out_blocks = a.out_blocks; p.q_cu = a.q_cu; p.p_cu = a.p_cu; p.n_seqs = a.n_seqs; p.own_row0 = (int)a.own_row0;
+  p.out = (bf16_t*)a.out; p.q_cu = a.q_cu; p.p_cu = a.p_cu; p.n_seqs = a.n_seqs; p.own_row0 = (int)a.own_row0;
   p.Hq = a.Hq; p.Hkv = a.Hkv;
   // 4-wave workgroups (128 queries).  8-wave workgroups halve the tile loads a wave issues per key tile and are
   // faster when the kernel is timed alone (+14 % at 8k tokens) but slower inside the layer, behind the projections
@@ -658,7 +657,7 @@ hipError_t launch_attn_mfma_bf16(const AttnArgs& a, hipStream_t s) {
     ++g_split_launches;
     hipError_t e = a.dh == 128 ? launch_attn<128, true, 4>(p, grid, s) : launch_attn<64, true, 4>(p, grid, s);
     if (e != hipSuccess) return e;
-    return launch_attn_combine(p.part_o, p.part_ml, p.out, a.out_blocks, a.n_q, a.Hq, a.dh, splits, p.c, s);
+    return launch_attn_combine(p.part_o, p.part_ml, p.out, 0, a.n_q, a.Hq, a.dh, splits, p.c, s);
   }
   dim3 grid((unsigned)total * a.Hq);
   return a.dh == 128 ? launch_attn<128, false, 4>(p, grid, s) : launch_attn<64, false, 4>(p, grid, s);

@@ -76,9 +76,9 @@ __device__ __forceinline__ void store_quad(void* C, int64_t ldc, const void* R, 
 }
 
 // PARTIAL: write the fp32 accumulators of this K split to P[split][M][N] instead of the bf16 result.
-// EPI_SWIGLU (run-time flag; wave tiles with an even number of 32-column MFMA tiles): W holds gate and up
+// EPI_SWIGLU (run-time flag; wave tiles of two 32-column MFMA tiles): W holds gate and up
 // rows interleaved in blocks of 32 (packed rows 64b..64b+31 = gate rows 32b.., the next 32 = the same up
-// rows), so MFMA tiles j (even) and j+1 of a wave are gate and up of the same 32 FFN indices at the same
+// rows), so the two MFMA tiles of a wave are gate and up of the same 32 FFN indices at the same
 // lane/register; the epilogue writes silu(gate)*up to C[M, N/2].
 // SCHED: software-pipeline schedule of the k loop, see the top of the file.
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool PARTIAL, int SCHED, bool WB>
@@ -394,30 +394,6 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
         }
       }
       __builtin_amdgcn_wave_barrier();
-    }
-    return;
-  }
-  if constexpr (TN % 2 == 0 && !PARTIAL) if (epi & EPI_SWIGLU) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int m = m0 + wm * WTM + i * 32 + frag_row;
-      if (m >= M) continue;
-#pragma unroll
-      for (int j = 0; j < TN; j += 2) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int f = (n0 + wn * WTN + j * 32) / 2 + 8 * q + 4 * frag_hi;
-          if (f >= N / 2) continue;
-          bf16x4 o;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float g = acc[j][i][4 * q + e], u = acc[j + 1][i][4 * q + e];
-            const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
-            o[e] = (bf16_t)(g * sig * u);
-          }
-          *(bf16x4*)((bf16_t*)C + (int64_t)m * ldc + f) = o;
-        }
-      }
     }
     return;
   }
@@ -906,7 +882,8 @@ hipError_t launch_form(const void* A, int64_t lda, const void* W, int64_t ldw, v
   return hipGetLastError();
 }
 
-// W in rows or in blocks, as the caller has it
+// W in rows or in blocks, as the caller has it.  (The 64-row tiles meet blocks only in a model that was created under
+// "force_generic" with a head_dim the attention kernels do not take and runs without it.)
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool PARTIAL, int SCHED = 0>
 hipError_t launch(const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc, const void* R, int64_t ldr,
                   float* P, int M, int N, int K, int epi, int splits, int kt_per_split, hipStream_t s) {
