@@ -410,7 +410,7 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
   const bool can_split = c.dtype == DSK_BF16 && !g_force_generic && m->split_ws;
   auto splits = [&](int N, int K) { return can_split && gemm_mfma_splits(n, N, K); };
   const bool norm_here = !fp32_rope && !ready;
-  if (rope && norm_here && !h_in_f32 && norm_takes_rope(c.dtype, n, d)) {
+  if (rope && norm_here && !h_in_f32 && norm_takes_rope(c.dtype, d)) {
     HIP_TRY(launch_rmsnorm_rope(h_in, w.g1, m->xn, n, d, (float)c.rms_eps, *rope, s));
   } else {
     if (rope) HIP_TRY(launch_rope_table(*rope, s));

@@ -39,7 +39,7 @@ struct LayerWeights {
 constexpr int DSK_MAX_E_CHUNKS = 16;
 
 // The rotary table of a call: cs[t][j] = (cos, sin) of pos[t] * theta[j], angle and sincos in fp64, stored as fp32.  The
-// first norm of a call over few rows fills it as well (one launch of some 5 us less in front of the first projection).
+// first norm of a bf16 call fills it as well (one launch of some 5 us less in front of the first projection).
 struct RopeJob { const int32_t* pos; const double* theta; float2* cs; int T, half; };
 __device__ __forceinline__ void rope_entry(const RopeJob& j, int64_t i) {
   if (i >= (int64_t)j.T * j.half) return;
@@ -192,8 +192,8 @@ hipError_t launch_splice(const void* src, int64_t src_stride, int64_t src_v, voi
 hipError_t launch_pace_start(unsigned long long* t0, hipStream_t s);
 hipError_t launch_pace_wait(const unsigned long long* t0, unsigned long long ticks, hipStream_t s);
 hipError_t launch_rope_table(const RopeJob& rope, hipStream_t s);
-// RMSNorm of the first layer and the rotary table in one launch, where norm_takes_rope says so (bf16, up to 512 rows)
-bool norm_takes_rope(int dtype, int T, int d);
+// RMSNorm of the first layer and the rotary table in one launch, where norm_takes_rope says so (bf16)
+bool norm_takes_rope(int dtype, int d);
 hipError_t launch_rmsnorm_rope(const void* x, const void* g, void* y, int T, int d, float eps, const RopeJob& rope, hipStream_t s);
 // rotates q (in place) and k of qkv [T, n_qkv]; writes rotated k and v to the cache rows row0..row0+T-1
 hipError_t launch_rope_kv_write(int dtype, void* qkv, const float2* cs, void* k_rows, void* v_rows, int T, int Hq,

@@ -226,13 +226,13 @@ hipError_t launch_rope_table(const RopeJob& rope, hipStream_t s) {
   return hipGetLastError();
 }
 
-// One launch less: 246 -> 241 us for an 8B layer over 333 rows.  But the fp64 sincos takes the norm to where fewer waves fit a
-// compute unit: from about a thousand rows it loses (1145 -> 1152 us, two layers over 1024), where the norm is
-// bound by memory.
-bool norm_takes_rope(int dtype, int T, int d) { return dtype == DSK_BF16 && T <= 512 && d % 4 == 0 && d <= 8192; }
+// One launch less at any number of rows (both ways in turn, medians of 20): an 8B layer over 65 rows 169.1 -> 164.8 us, 512
+// rows 282.6 -> 277.6, 1024 rows 448.1 -> 442.3, 4096 rows 1449 -> 1445, 16384 rows 7110 -> 7097; from there on inside the
+// noise.  The widths are those of the norm that keeps its row in registers.
+bool norm_takes_rope(int dtype, int d) { return dtype == DSK_BF16 && d % 4 == 0 && d <= 8192; }
 
 hipError_t launch_rmsnorm_rope(const void* x, const void* g, void* y, int T, int d, float eps, const RopeJob& rope, hipStream_t s) {
-  if (rope.T != T || !norm_takes_rope(DSK_BF16, T, d)) return hipErrorNotSupported;
+  if (rope.T != T || !norm_takes_rope(DSK_BF16, d)) return hipErrorNotSupported;
   auto kern = d <= 4096 ? rmsnorm_vec_kernel<bf16_t, 4, true> : rmsnorm_vec_kernel<bf16_t, 8, true>;
   hipLaunchKernelGGL(kern, dim3(T + rope_blocks(rope)), dim3(256), 0, s, (const bf16_t*)x, (const bf16_t*)g, (bf16_t*)y, d, eps, rope);
   return hipGetLastError();

@@ -31,8 +31,10 @@ __global__ void __launch_bounds__(256) splice_kernel(const char* __restrict__ sr
 
 // Layers first .. first + n - 1, `bytes` (a multiple of 16) of K and of V each; all addresses and strides 16-byte aligned.
 // About 2048 workgroups in all, fewer when there is less than 16 KB for each: 32 layers of 8192 8B rows in 489 us, 4.4 TB/s
-// (copied layer by layer: 767 us).  Next to a recomputation (`background`) 128: at full rate the copy holds up the projections
-// it runs beside (29.93 against 29.86 ms for an 8B pass over 8192 rows), and it has milliseconds to finish.
+// (copied layer by layer: 767 us).  Next to a recomputation (`background`) 128: at full rate the copy holds up the kernels it
+// runs beside, and it has the recomputation's time to finish.  8192 rows, 32 8B layers of which one is recomputed, both ways
+// in turn: 7837 us (quartiles 7828-7857) against 7915 (7905-7928); eight recomputed: 29672 (29633-29701) and 29712
+// (29669-29800); over 1024 rows and at the 70B width no difference.
 hipError_t launch_splice(const void* src, int64_t src_stride, int64_t src_v, void* dst, int64_t dst_stride, int64_t dst_v, int first,
                          int n, int64_t bytes, int background, hipStream_t s) {
   if (n <= 0 || bytes <= 0) return hipSuccess;
