@@ -415,7 +415,7 @@ def main():
     else:
         out["roofline_load"] = {"bound": "hbm", "achieved": round(2 * moved / (t_splice * 1e-3) / 1e9, 1), "peak": 8000.0,
                                 "unit": "GB/s", "frac": round(2 * moved / (t_splice * 1e-3) / 8e12, 4), "traffic": None,
-                                "kernel": "hipMemcpyAsync device to device, all layers, nothing else running",
+                                "kernel": "splice_kernel, all layers in one launch, nothing else running",
                                 "algorithmic_bytes": int(2 * moved), "ms": round(t_splice, 3),
                                 "bytes_are": "every spliced byte read once and written once"}
     out.update(extra)

@@ -340,8 +340,8 @@ DSK_API int dsk_moe_route(int dtype, const void* x, const void* wr, int n, int d
  *                they arrive: 0 (default) = 4096-row chunks where that keeps every result bit-identical to the
  *                unchunked run (one sequence, bf16, chunks that still fill the chip), -1 = never, n > 0 (a multiple
  *                of 256) = n-row chunks on any single-sequence bf16 call (results then agree within tolerance only)
- *   "time_gemm": 1 = bracket every tensor-core GEMM launch that runs on the 256 x 256 prefill tiling (at least
- *                192 such tiles), and every tensor-core attention launch of the prefix pass (at least 1024 query rows, no
+ *   "time_gemm": 1 = bracket every tensor-core GEMM of the prefill (a projection of at least 192 tiles of 256 x 256;
+ *                dsk_gemm_plan says in which tiles it runs), and every tensor-core attention launch of the prefix pass (at least 1024 query rows, no
  *                earlier rows), by a pair of HIP events attached to the kernel's own dispatch (they receive its start and
  *                stop times, nothing else is put into the stream; read back through dsk_get_stat); a projection that runs as
  *                whole rounds of 256-row tiles and a rest in lower tiles is one such pair over both launches

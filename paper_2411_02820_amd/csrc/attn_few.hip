@@ -11,11 +11,12 @@
 // 16-key tile.  The contraction index of O^T += V^T P^T is numbered so that the two key tiles of a 32-key step are the
 // lane's eight values as they stand: index 8g + e is key 16*(e/4) + 4g + e%4, and the V operand follows with two transposing
 // reads of four keys each.
-// 8B shape, per layer, against a transposed copy and 32x32x16 tiles before: 64 queries and 8192 keys 22.5 us (28), one query and
+// 8B shape, per layer, against a transposed copy and 32x32x16 tiles before: 64 queries and 8192 keys 22.5 us (31), one query and
 // 4096 keys 7.8 us (17), and the merge of the key ranges 6 us in both.  Of the 22.5 us the loads alone take 10, the partial
 // outputs 4; runs of 64 keys per wave and stage (two independent steps to schedule) instead of 32 took 25 -> 22.5 us, four column
 // tiles per wave with one wave per SIMD take 35.
-// 128 queries for each of eight sequences of 1k to 8k keys: 189 us (transposed copy 35, attention 150, merge 15).
+// 128 queries for each of eight sequences of 1k to 8k keys: 190 us, one key range per workgroup (before: transposed copy 35,
+// attention 153, merge 15).
 #include <math.h>
 
 #include <type_traits>

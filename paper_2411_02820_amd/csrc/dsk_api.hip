@@ -471,8 +471,8 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
 // first chunk's transfer hides under compute (Sec. 4.3, Fig. 13(c): recomputation starts when the E cache is there).
 // Returns the number of chunks (0 or 1: not chunked) and their row boundaries in bounds[0..n].
 // By itself the library chunks only where every row's result keeps its bits: one sequence, a bf16 model, chunks of
-// 4096 rows (a multiple of every tile) that each still fill the chip, i.e. run the same GEMM tiling and the same
-// unsplit attention as the whole prefix would.
+// 4096 rows that each still fill the chip, i.e. run unsplit projections (in one or two launches: every tile height adds
+// in the same order) and the same unsplit attention as the whole prefix would.
 int plan_e_chunks(const dsk_model* m, int T, int n_seqs, int* bounds) {
   const dsk_config_t& c = m->cfg;
   if (g_e_chunk_rows < 0 || n_seqs != 1 || c.dtype != DSK_BF16 || g_force_generic || !m->vt) return 0;

@@ -1057,7 +1057,8 @@ void gemm_mfma_plan(int M, int N, int K, int may_split, int32_t* plan) {
   plan[0] = p.bm; plan[1] = p.splits; plan[2] = p.head_rows; plan[3] = p.rest_bm;
 }
 
-// Whether a projection of this size runs on the 256 x 256 prefill tiling (the kernel the roofline figure is about).
+// Whether a projection makes at least 192 tiles of 256 x 256: it fills the chip with them or with lower tiles of the same
+// kernel, and its contraction is not split (what the timing hook and the roofline figure are about).
 bool gemm_mfma_uses_prefill_tile(int M, int N) {
   return M > 64 && (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 192;
 }
