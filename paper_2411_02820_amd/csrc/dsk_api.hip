@@ -1183,7 +1183,7 @@ int dsk_set_option(const char* name, int value) {
 }
 
 int dsk_gemm_plan(int M, int N, int K, int may_split, int32_t* plan) {
-  if (!plan || M <= 64 || N < 1 || K < 64 || K % 64) return DSK_EINVAL;
+  if (!plan || M <= 64 || M > 1 << 30 || N < 1 || N > 1 << 30 || K < 64 || K % 64) return DSK_EINVAL;
   gemm_mfma_plan(M, N, K, may_split, plan);
   return DSK_OK;
 }

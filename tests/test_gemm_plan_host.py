@@ -28,6 +28,6 @@ def test_plans_keep_their_bounds():
 def test_sizes_that_have_no_plan():
     import ctypes as C
     plan = (C.c_int32 * 4)()
-    for M, N, K in ((64, 256, 256), (100, 0, 256), (100, 256, 0), (100, 256, 100)):
+    for M, N, K in ((64, 256, 256), (100, 0, 256), (100, 256, 0), (100, 256, 100), (2 ** 31 - 1, 256, 256), (100, 2 ** 31 - 1, 256)):
         assert B.lib.dsk_gemm_plan(M, N, K, 1, plan) == B.DSK_EINVAL
     assert B.lib.dsk_gemm_plan(100, 256, 256, 1, None) == B.DSK_EINVAL
