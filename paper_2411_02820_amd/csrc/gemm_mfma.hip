@@ -443,13 +443,22 @@ struct RopeOut {
   bf16_t *k, *v;     // [M][Hkv * 128]
   int Hq, Hkv;
 };
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false, bool ROPE = false>
+// DIRECT (unsplit 256-row tiles, weights in blocks): a wave loads its fragments of W straight to registers, 1.5 k-tiles ahead,
+// and only A goes through LDS, in a ring of four stages.  What bounds the large projections is power: the chip runs them
+// at 1.75 GHz with the matrix pipes busy 0.81 of the time, and with all operands zero the other form is the faster
+// one (8192 x 28672 x 4096 1912 against 1800 TFLOP/s).  On data this form is, because it moves less: 128 KB of LDS reads and
+// 32 KB of writes per k-tile instead of 192 and 64 (a fragment of W comes twice from L1, not twice through LDS; requests to
+// L2 the same within 4 %), and because an MFMA shares an operand with the one before it.  8192 rows, both forms in turn:
+// down 691 -> 666 us, QKV 303 -> 291, O 226 -> 222, gate/up 1300 -> 1285; 70B shapes 1.5 to 3 %; same sums, same order.
+// Measured without gain: 2, 3 or 6 fragments of A ahead, and the lines of W touched 4 to 8 k-tiles early (faster on zeros).
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false, bool ROPE = false, bool DIRECT = false>
 __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     gemm16_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W_all, int64_t ldw,
                        void* C, int64_t ldc, const void* __restrict__ R, int64_t ldr, int M_all, int N, int K,
                        int epi, int tiles_m, int tiles_n, int kt_per_split, const int4* __restrict__ tile_tab,
                        int64_t w_group_stride, const int32_t* __restrict__ a_row, int a_rows, RopeOut ro) {
   static_assert(!ROPE || (WB && !GROUPED && BN % 128 == 0 && BN / WAVES_N == 64), "two waves a head");
+  static_assert(!DIRECT || (WB && BM == 256 && BN / WAVES_N == 64), "W straight to registers: from blocks, four column tiles a wave");
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
   constexpr int TM = WTM / 16, TN = WTN / 16;  // 16x16 MFMA tiles per wave
@@ -457,6 +466,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   constexpr int PER_TILE = A_INST + W_INST;
   constexpr int NM = TM * TN;                  // MFMAs per k-step
   constexpr int NF = TM + TN;                  // fragment reads per k-step
+  constexpr int A_STAGES = 4;                  // DIRECT: stages of A alone
   static_assert(WTN == 64 && BK == 64 && TM % 2 == 0 && BM % (RPI * NW) == 0, "written for 64-column wave tiles, two k-steps");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t* sA = (bf16_t*)smem_raw;
@@ -495,35 +505,6 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     W = W_all + (int64_t)te.x * w_group_stride;
   }
 
-  const int lr = lane / CH, lp = lane % CH;
-  uint32_t a_off[A_INST], w_off[W_INST];
-#pragma unroll
-  for (int i = 0; i < A_INST; ++i) {
-    int row = RPI * (wave * A_INST + i) + lr;
-    int ar = min(m0 + row, M - 1);
-    if (GROUPED && a_row) ar = min(max(a_row[ar], 0), a_rows - 1);  // always inside A, whatever the table holds
-    a_off[i] = (uint32_t)(((int64_t)ar * lda + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
-  }
-#pragma unroll
-  for (int i = 0; i < W_INST; ++i) {
-    const int row = RPI * (wave * W_INST + i) + lr, blk = wave * W_INST + i;  // WB: block blk % 2 of rows 16 * (blk / 2) ..
-    w_off[i] = WB ? (uint32_t)(min(n0 / 16 + blk / 2, N / 16 - 1) * (int)(ldw / 32) + blk % 2) * (BLK * 2u) + lane * 16u
-                  : (uint32_t)(((int64_t)min(n0 + row, N - 1) * ldw + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
-  }
-  const uint32_t sA_lds = (uint32_t)(uintptr_t)sA, sW_lds = (uint32_t)(uintptr_t)sW;
-  auto issue_load = [&](int stage, int k0, int idx) {
-    const bool is_a = idx < A_INST;
-    const int li = is_a ? idx : idx - A_INST;
-    const char* base = is_a ? (const char*)A + (int64_t)k0 * 2 : (const char*)W + (int64_t)k0 * w_step<WB>();
-    const uint32_t voff = is_a ? a_off[li] : w_off[li];
-    const uint32_t dst = is_a ? sA_lds + (uint32_t)(stage * BM * BK + RPI * (wave * A_INST + li) * BK) * 2
-                              : sW_lds + (uint32_t)(stage * BN * BK + RPI * (wave * W_INST + li) * BK) * 2;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(dst), "v"(voff), "s"(base)
-                 : "memory", "m0");
-  };
-
   f32x4 acc[TN][TM];
 #pragma unroll
   for (int j = 0; j < TN; ++j)
@@ -531,95 +512,225 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[j][i][r] = 0.f;
-
-  // fragment f of a k-step, in the order the MFMAs (j outer, i inner) first need them: W 0, X 0..TM-1, W 1..TN-1
   const int frow = lane & 15, fq = lane >> 4;
-  bf16x8 xs[2][TM], ws[2][TN];
-  auto read_frag = [&](const bf16_t* a_s, const bf16_t* w_s, int ks, int f) {
-    const int ch = ks * 4 + fq;
-    const int j = f == 0 ? 0 : f - TM;
-    if (f >= 1 && f <= TM) xs[ks][f - 1] = *(const bf16x8*)(a_s + slot(wm * WTM + (f - 1) * 16 + frow, ch));
-    else {
-      const int cb = ROPE ? wn / 2 * 8 + wn % 2 * 2 + j / 2 * 4 + j % 2 : wn * WTN / 16 + j;  // 16-column block of the tile
-      ws[ks][j] = *(const bf16x8*)(w_s + (WB ? (cb * 2 + ks) * BLK + lane * 8 : slot(wn * WTN + j * 16 + frow, ch)));
-    }
-  };
-
+  // 16-column block of the tile that feeds the wave's column tile j
+  auto col_block = [&](int j) { return ROPE ? wn / 2 * 8 + wn % 2 * 2 + j / 2 * 4 + j % 2 : wn * WTN / 16 + j; };
   // k-tiles of this workgroup: all of them, or share blockIdx.y of a contraction split over workgroups (C then holds
   // one fp32 plane of M x N partial sums per share)
   const int kt0 = (int)blockIdx.y * kt_per_split, n_kt = min(K / BK - kt0, kt_per_split);
   if (!GROUPED) C = (char*)C + (int64_t)blockIdx.y * M_all * ldc * ((epi & EPI_C_F32) ? 4 : 2);
-#pragma unroll
-  for (int i = 0; i < PER_TILE; ++i) issue_load(0, kt0 * BK, i);
-  if (n_kt > 1) {
-#pragma unroll
-    for (int i = 0; i < PER_TILE; ++i) issue_load(1, (kt0 + 1) * BK, i);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_TILE) : "memory");
-  } else {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
-  __syncthreads();
-#pragma unroll
-  for (int f = 0; f < NF; ++f) read_frag(sA, sW, 0, f);
 
-  constexpr int LD = PER_TILE / 2;  // loads per wave in each half of k-step 1
-  auto tile_step = [&](int t, auto has_next, auto has_next2) {
-    const int stage = t & 1;
-    const bf16_t* a_s = sA + stage * BM * BK;
-    const bf16_t* w_s = sW + stage * BN * BK;
-    const bf16_t* a_n = sA + (stage ^ 1) * BM * BK;
-    const bf16_t* w_n = sW + (stage ^ 1) * BN * BK;
+  const int lr = lane / CH, lp = lane % CH;
+  uint32_t a_off[A_INST];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      if (ks == 1) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-      }
-      __builtin_amdgcn_sched_barrier(0);
+  for (int i = 0; i < A_INST; ++i) {
+    int row = RPI * (wave * A_INST + i) + lr;
+    int ar = min(m0 + row, M - 1);
+    if (GROUPED && a_row) ar = min(max(a_row[ar], 0), a_rows - 1);  // always inside A, whatever the table holds
+    a_off[i] = (uint32_t)(((int64_t)ar * lda + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
+  }
+  const uint32_t sA_lds = (uint32_t)(uintptr_t)sA;
+
+  if constexpr (DIRECT) {
+    // W frag of column tile j: 1 KB blocks, two per k-tile and 16 columns
+    uint32_t w_off[TN];
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j)
+      w_off[j] = (uint32_t)min(n0 / 16 + col_block(j), N / 16 - 1) * (uint32_t)(ldw / 32) * (BLK * 2u) + lane * 16u;
+    const auto w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, (uint32_t)((int64_t)N * ldw * 2), 0x00027000);
+    bf16x8 wf[2][2][TN], xf[2 * TM];
+    // tiles past the end repeat the last one: no branch splits the loop, and nothing uses what they bring
+    auto load_w = [&](int buf, int t, int ks, int j) {
+      const int at = (kt0 + min(t, n_kt - 1)) * (BK * 32) + ks * (BLK * 2);
+      wf[buf][ks][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, w_off[j], at, 0));
+    };
+    auto load_a = [&](int t, int i) {
+      const char* base = (const char*)A + (int64_t)(kt0 + min(t, n_kt - 1)) * (BK * 2);
+      const uint32_t dst = sA_lds + (uint32_t)(t % A_STAGES * BM * BK + RPI * (wave * A_INST + i) * BK) * 2;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :
+                   : "s"(dst), "v"(a_off[i]), "s"(base)
+                   : "memory", "m0");
+    };
+    constexpr int NX = 2 * TM, AHEAD = 4;  // activation fragments of a k-tile; read AHEAD of their MFMAs
+    const bf16_t* x_at[2] = {sA + slot(wm * WTM + frow, fq), sA + slot(wm * WTM + frow, 4 + fq)};
+    auto read_x = [&](int stage, int f) { xf[f] = *(const bf16x8*)(x_at[f / TM] + stage * BM * BK + f % TM * 16 * BK); };
+
+    // Loads return in the order in which they were issued.  The compiler counts those of W, not the direct ones of A, and
+    // may move the former: so no wait counts on its order.  Whatever of W is requested behind pin() follows the loads of A in
+    // front of it, and landed() lets the compiler wait for such loads of W, hence for that A too.
+    auto pin = [&] { asm volatile("" : "+v"(w_off[0]), "+v"(w_off[1]), "+v"(w_off[2]), "+v"(w_off[3]) : : "memory"); };
+    auto landed = [&](bf16x8* w) { asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]) : : "memory"); };
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int m = j * TM + i;
-          if (ks == 1 && m == NM / 2) {
-            if (has_next2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LD) : "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-          }
-          // fragment reads between the MFMAs: k-step 1's during k-step 0 (done a quarter before its end), the
-          // next tile's first ones during the second half of k-step 1
-          if (ks == 0 && m >= 1) {
-            constexpr int D = NM * 3 / 4 - 1;
-            __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < 2 * A_INST; ++i) load_a(i / A_INST, i % A_INST);
+    pin();
 #pragma unroll
-            for (int f = min(NF, (m - 1) * NF / D); f < min(NF, m * NF / D); ++f) read_frag(a_s, w_s, 1, f);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-          if (ks == 1 && has_next && m > NM / 2) {
-            constexpr int D = NM / 2 - 2;
-            const int mm = m - NM / 2;
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int f = min(NF, (mm - 1) * NF / D); f < min(NF, mm * NF / D); ++f) read_frag(a_n, w_n, 0, f);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-          acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ws[ks][j], xs[ks][i], acc[j][i], 0, 0, 0);
-          if (ks == 1 && has_next2) {
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int q = m * PER_TILE / NM; q < (m + 1) * PER_TILE / NM; ++q) issue_load(stage, (kt0 + t + 2) * BK, q);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      __builtin_amdgcn_sched_barrier(0);
+    for (int f = 0; f < 3 * TN; ++f) {
+      load_w(f / (2 * TN), f / (2 * TN), f / TN % 2, f % TN);
+      if (f == TN - 1) pin();
     }
-  };
-  int t = 0;
-  for (; t + 2 < n_kt; ++t) tile_step(t, std::true_type{}, std::true_type{});
-  if (t + 1 < n_kt) { tile_step(t, std::true_type{}, std::false_type{}); ++t; }
-  if (t < n_kt) tile_step(t, std::false_type{}, std::false_type{});
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < A_INST; ++i) load_a(2, i);
+    pin();
+    landed(wf[0][0]);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int f = 0; f < AHEAD; ++f) read_x(0, f);
+
+    auto tile_step = [&](auto buf_, int t) {
+      constexpr int buf = buf_();
+      const int stage = t % A_STAGES, next = (t + 1) % A_STAGES;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int f = 0; f < NX; ++f) {
+        if (f == NX - AHEAD) {
+          // A(t + 1) is older than this k-step's W, so it has landed for every wave; and every wave is past its reads of
+          // tile t - 1, whose stage takes A(t + 3)
+          landed(wf[buf][1]);
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        const int i = f % TM, ks = f / TM;
+#pragma unroll
+        for (int u = 0; u < TN; ++u) {
+          const int j = f & 1 ? TN - 1 - u : u;  // there and back: one operand changes from each MFMA to the next
+          acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[buf][ks][j], xf[f], acc[j][i], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (u == 0) {
+            if (f + AHEAD < NX) read_x(stage, f + AHEAD);
+            else read_x(next, f + AHEAD - NX);
+          }
+          if (u == 2 && i < TN) {
+            if (ks == 0) load_w(buf ^ 1, t + 1, 1, i);
+            else load_w(buf, t + 2, 0, i);
+          }
+          if (u == 3 && f >= NX - AHEAD) {
+            constexpr int per = A_INST / AHEAD;
+#pragma unroll
+            for (int q = 0; q < per; ++q) load_a(t + 3, (f - (NX - AHEAD)) * per + q);
+            if (f == NX - 1) pin();
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    int t = 0;
+    do {  // at least two k-tiles
+      tile_step(std::integral_constant<int, 0>{}, t);
+      tile_step(std::integral_constant<int, 1>{}, t + 1);
+      t += 2;
+    } while (t + 1 < n_kt);
+    if (t < n_kt) tile_step(std::integral_constant<int, 0>{}, t);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the epilogue's staging takes the ring
+    __syncthreads();
+  } else {
+    uint32_t w_off[W_INST];
+#pragma unroll
+    for (int i = 0; i < W_INST; ++i) {
+      const int row = RPI * (wave * W_INST + i) + lr, blk = wave * W_INST + i;  // WB: block blk % 2 of rows 16 * (blk / 2) ..
+      w_off[i] = WB ? (uint32_t)(min(n0 / 16 + blk / 2, N / 16 - 1) * (int)(ldw / 32) + blk % 2) * (BLK * 2u) + lane * 16u
+                    : (uint32_t)(((int64_t)min(n0 + row, N - 1) * ldw + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
+    }
+    const uint32_t sW_lds = (uint32_t)(uintptr_t)sW;
+    auto issue_load = [&](int stage, int k0, int idx) {
+      const bool is_a = idx < A_INST;
+      const int li = is_a ? idx : idx - A_INST;
+      const char* base = is_a ? (const char*)A + (int64_t)k0 * 2 : (const char*)W + (int64_t)k0 * w_step<WB>();
+      const uint32_t voff = is_a ? a_off[li] : w_off[li];
+      const uint32_t dst = is_a ? sA_lds + (uint32_t)(stage * BM * BK + RPI * (wave * A_INST + li) * BK) * 2
+                                : sW_lds + (uint32_t)(stage * BN * BK + RPI * (wave * W_INST + li) * BK) * 2;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :
+                   : "s"(dst), "v"(voff), "s"(base)
+                   : "memory", "m0");
+    };
+
+    // fragment f of a k-step, in the order the MFMAs (j outer, i inner) first need them: W 0, X 0..TM-1, W 1..TN-1
+    bf16x8 xs[2][TM], ws[2][TN];
+    auto read_frag = [&](const bf16_t* a_s, const bf16_t* w_s, int ks, int f) {
+      const int ch = ks * 4 + fq;
+      const int j = f == 0 ? 0 : f - TM;
+      if (f >= 1 && f <= TM) xs[ks][f - 1] = *(const bf16x8*)(a_s + slot(wm * WTM + (f - 1) * 16 + frow, ch));
+      else {
+        ws[ks][j] = *(const bf16x8*)(w_s + (WB ? (col_block(j) * 2 + ks) * BLK + lane * 8 : slot(wn * WTN + j * 16 + frow, ch)));
+      }
+    };
+
+#pragma unroll
+    for (int i = 0; i < PER_TILE; ++i) issue_load(0, kt0 * BK, i);
+    if (n_kt > 1) {
+#pragma unroll
+      for (int i = 0; i < PER_TILE; ++i) issue_load(1, (kt0 + 1) * BK, i);
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_TILE) : "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    __syncthreads();
+#pragma unroll
+    for (int f = 0; f < NF; ++f) read_frag(sA, sW, 0, f);
+
+    constexpr int LD = PER_TILE / 2;  // loads per wave in each half of k-step 1
+    auto tile_step = [&](int t, auto has_next, auto has_next2) {
+      const int stage = t & 1;
+      const bf16_t* a_s = sA + stage * BM * BK;
+      const bf16_t* w_s = sW + stage * BN * BK;
+      const bf16_t* a_n = sA + (stage ^ 1) * BM * BK;
+      const bf16_t* w_n = sW + (stage ^ 1) * BN * BK;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        if (ks == 1) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int i = 0; i < TM; ++i) {
+            const int m = j * TM + i;
+            if (ks == 1 && m == NM / 2) {
+              if (has_next2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LD) : "memory");
+              else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+              __builtin_amdgcn_s_barrier();
+              asm volatile("" ::: "memory");
+            }
+            // fragment reads between the MFMAs: k-step 1's during k-step 0 (done a quarter before its end), the
+            // next tile's first ones during the second half of k-step 1
+            if (ks == 0 && m >= 1) {
+              constexpr int D = NM * 3 / 4 - 1;
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int f = min(NF, (m - 1) * NF / D); f < min(NF, m * NF / D); ++f) read_frag(a_s, w_s, 1, f);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            if (ks == 1 && has_next && m > NM / 2) {
+              constexpr int D = NM / 2 - 2;
+              const int mm = m - NM / 2;
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int f = min(NF, (mm - 1) * NF / D); f < min(NF, mm * NF / D); ++f) read_frag(a_n, w_n, 0, f);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ws[ks][j], xs[ks][i], acc[j][i], 0, 0, 0);
+            if (ks == 1 && has_next2) {
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int q = m * PER_TILE / NM; q < (m + 1) * PER_TILE / NM; ++q) issue_load(stage, (kt0 + t + 2) * BK, q);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    int t = 0;
+    for (; t + 2 < n_kt; ++t) tile_step(t, std::true_type{}, std::true_type{});
+    if (t + 1 < n_kt) { tile_step(t, std::true_type{}, std::false_type{}); ++t; }
+    if (t < n_kt) tile_step(t, std::false_type{}, std::false_type{});
+  }
 
   // ---- epilogue through the wave's own LDS region, 32 rows at a time (as in the 32x32 kernel) ----
   constexpr int ROW_F = 64 + 4;
@@ -891,10 +1002,15 @@ hipError_t launch(const void* A, int64_t lda, const void* W, int64_t ldw, int w_
                   : launch_form<BM, BN, WAVES_M, WAVES_N, PARTIAL, SCHED, false>(A, lda, W, ldw, C, ldc, R, ldr, P, M, N, K, epi, splits, kt_per_split, s);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB>
+// Unsplit 256-row tiles take W in blocks straight to registers (DIRECT), from two k-tiles on (its loop runs in pairs).
+// Lower tiles and split contractions do not: half as many MFMAs share a fragment of W, or few k-tiles share the start (O over
+// 1536 rows, 128-row tiles, 62.7 -> 64.9 us; down over 333 rows, 192-row tiles in eight splits, 54.4 -> 55.1 us).
+bool w_direct(int K) { return K >= 2 * BK; }
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool DIRECT = false>
 hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R, int64_t ldr,
                          int M, int N, int K, int epi, int splits, int kt_per_split, hipStream_t s) {
-  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, WB>;
+  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, WB, false, false, DIRECT>;
   constexpr int lds = NSTAGE * (BM + BN) * BK * 2;
   static bool configured = false;
   if (!configured) {
@@ -909,9 +1025,9 @@ hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw,
   return hipGetLastError();
 }
 
-template <int BM>
+template <int BM, bool DIRECT>
 hipError_t launch16_rope(const void* A, const void* W, void* qkv, const RopeOut& ro, int M, int K, hipStream_t s) {
-  auto kern = gemm16_bf16_kernel<BM, 256, 2, 4, true, false, true>;
+  auto kern = gemm16_bf16_kernel<BM, 256, 2, 4, true, false, true, DIRECT>;
   constexpr int lds = NSTAGE * (BM + 256) * BK * 2;
   static bool configured = false;
   if (!configured) {
@@ -932,15 +1048,17 @@ hipError_t launch16(int bm, const void* A, int64_t lda, const void* W, int64_t l
 #define DSK_FORM(BM)                                                                                                      \
   (w_blocks ? launch16_form<BM, 256, 2, 4, true>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, splits, kt_per_split, s)   \
             : launch16_form<BM, 256, 2, 4, false>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, splits, kt_per_split, s))
+  if (bm == 256 && w_blocks && splits == 1 && w_direct(K))
+    return launch16_form<256, 256, 2, 4, true, true>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, 1, kt_per_split, s);
   return bm == 128 ? DSK_FORM(128) : bm == 192 ? DSK_FORM(192) : DSK_FORM(256);
 #undef DSK_FORM
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool DIRECT>
 hipError_t launch16_grouped(const void* A, int64_t lda, const int32_t* a_row, int a_rows, const void* W, int64_t ldw,
                             int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi, const int4* tile_tab, int tile_rows,
                             hipStream_t s) {
-  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, true, true>;
+  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, true, true, false, DIRECT>;
   constexpr int lds = NSTAGE * (BM + BN) * BK * 2;
   static bool configured = false;
   if (!configured) {
@@ -1143,7 +1261,10 @@ hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, 
   // (a model the tensor-core path takes has its weights in blocks)
   if (!w_blocks || K < BK || K % BK || N % 64 || (lda & 7) || (ldw & 7) || (ldc & 3) || (epi & EPI_RESIDUAL)) return hipErrorNotSupported;
   if (a_rows * lda * 2 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 2 >= ((int64_t)1 << 32)) return hipErrorNotSupported;
-  auto f = tile_m == 128 ? launch16_grouped<128, 256, 2, 4> : tile_m == 192 ? launch16_grouped<192, 256, 2, 4> : launch16_grouped<256, 256, 2, 4>;
+  auto f = tile_m == 128   ? launch16_grouped<128, 256, 2, 4, false>
+           : tile_m == 192 ? launch16_grouped<192, 256, 2, 4, false>
+           : w_direct(K)   ? launch16_grouped<256, 256, 2, 4, true>
+                           : launch16_grouped<256, 256, 2, 4, false>;
   return f(A, lda, a_row, (int)a_rows, W, ldw, w_group_stride, C, ldc, N, K, epi, (const int4*)tile_tab, tile_rows, s);
 }
 
@@ -1181,7 +1302,7 @@ hipError_t launch_gemm_rope(const void* A, const void* W, void* qkv, const float
   const GemmPlan p = gemm_plan(M, N, K, false);
   auto run = [&](int bm, int64_t r0, int64_t rows) {
     const RopeOut ro = {cs + r0 * 64, (bf16_t*)k_rows + r0 * Hkv * 128, (bf16_t*)v_rows + r0 * Hkv * 128, Hq, Hkv};
-    auto f = bm == 128 ? launch16_rope<128> : bm == 192 ? launch16_rope<192> : launch16_rope<256>;
+    auto f = bm == 128 ? launch16_rope<128, false> : bm == 192 ? launch16_rope<192, false> : w_direct(K) ? launch16_rope<256, true> : launch16_rope<256, false>;
     return f((const bf16_t*)A + r0 * K, W, (bf16_t*)qkv + r0 * N, ro, (int)rows, K, s);
   };
   if (p.head_rows == 0) return run(p.bm, 0, M);

@@ -182,3 +182,53 @@ def test_rope_in_the_projection(B, d, Hq, lens, plan):
     # k: one rounding here, up to two of each of the pair's elements there (2^-9 each); v and the state: one each
     for a, b in ((kv, kv_ref), (h, h_ref)):
         assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2 ** -7
+
+
+# unsplit 256-row tiles with W straight to registers: one to five and 17 k-tiles (one keeps the other form), an odd and an even
+# number of them, last column tiles that end early, rows that end inside a tile; QKV with the rotation, O with residual,
+# gate/up with SwiGLU, down.  Against the 128-row tiles of the other kernel.
+@pytest.mark.parametrize("d,Hq,F,n", [(64, 3, 128, 18030), (128, 3, 320, 18030), (192, 5, 192, 13001), (320, 3, 1088, 18030)])
+def test_weights_straight_to_registers(B, d, Hq, F, n):
+    from tests import gpu_util as G
+    assert B.dsk_gemm_plan(n, (Hq + 2) * 128, d)[:2] == (256, 1) and B.dsk_gemm_plan(n, 2 * F, d, False)[1] == 1
+    shape = synth.ModelShape(1, d, Hq, 1, 128, F, 10000.0, 1e-5, "bf16")
+    lens = [250] * (n // 250) + [n % 250]
+    x = G.to_dev(synth.hidden_states(shape, n), shape)
+    with G.GpuModel(shape, n) as m:
+        m.init_random(19)
+        B.dsk_set_option("gemm_tiling", 1)   # 256-row tiles for every projection; the rotation is a pass of its own
+        try:
+            forced = m.partial(x, 0, 1, None, lens)
+            B.dsk_set_option("gemm_tiling", 2)
+            ref = m.partial(x, 0, 1, None, lens)
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("gemm_tiling", 0)
+        planned = m.partial(x, 0, 1, None, lens)
+        torch.cuda.synchronize()
+    # as above: up to two roundings of 2^-9 for each of a pair's elements, one for v and the state
+    for got in (forced, planned):
+        for a, b in zip(got, ref):
+            assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2 ** -7
+
+
+# ... over experts (every token chooses both, so no choice hangs on a rounding), one, three and five k-tiles, against the
+# plain kernels
+@pytest.mark.parametrize("d,F", [(64, 192), (320, 128), (192, 320)])
+def test_expert_weights_straight_to_registers(B, d, F):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(1, d, 2, 1, 64, F, 10000.0, 1e-5, "bf16", 2, 2)
+    n = 601
+    x = G.to_dev(synth.hidden_states(shape, n), shape)
+    with G.GpuModel(shape, n) as m:
+        m.init_random(23, 0.05)
+        kv, h = m.partial(x, 0, 1, None, [n])
+        B.dsk_set_option("force_generic", 1)
+        try:
+            kv_ref, h_ref = m.partial(x, 0, 1, None, [n])
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("force_generic", 0)
+    # two bf16 evaluations of one layer
+    for a, b in ((kv, kv_ref), (h, h_ref)):
+        assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 1e-2
