@@ -410,15 +410,16 @@ int run_layer(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_out, 
   const bool can_split = c.dtype == DSK_BF16 && !g_force_generic && m->split_ws;
   auto splits = [&](int N, int K) { return can_split && gemm_mfma_splits(n, N, K); };
   const bool norm_here = !fp32_rope && !ready;
+  const bool rope_in_qkv = fp32_rope && gemm_fp32_takes_rope(n, c.n_q_heads, c.n_kv_heads, c.head_dim);
   if (rope && norm_here && !h_in_f32 && norm_takes_rope(c.dtype, d)) {
     HIP_TRY(launch_rmsnorm_rope(h_in, w.g1, m->xn, n, d, (float)c.rms_eps, *rope, s));
   } else {
-    if (rope) HIP_TRY(launch_rope_table(*rope, s));
+    if (rope && !rope_in_qkv) HIP_TRY(launch_rope_table(*rope, s));
     if (norm_here) HIP_TRY(launch_rmsnorm(c.dtype, h_in, h_in_f32 || all_f32, w.g1, m->xn, n, d, (float)c.rms_eps, s));
   }
   if (fp32_rope) {
     HIP_TRY(launch_gemm_fp32_norm_rope((const float*)h_in, w.g1, (float)c.rms_eps, w.wqkv, m->qkv, cs, k_own, v_own, n, d,
-                                       c.n_q_heads, c.n_kv_heads, c.head_dim, s));
+                                       c.n_q_heads, c.n_kv_heads, c.head_dim, rope_in_qkv ? rope : nullptr, s));
     ++g_stats.gemm_generic;
   } else if (splits(m->n_qkv, d)) {
     HIP_TRY(launch_gemm_split_rope(m->xn, w.wqkv, m->w_blocks, m->qkv, cs, k_own, v_own, n, d, c.n_q_heads, c.n_kv_heads, c.head_dim,

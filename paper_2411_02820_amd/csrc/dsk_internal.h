@@ -39,14 +39,17 @@ struct LayerWeights {
 constexpr int DSK_MAX_E_CHUNKS = 16;
 
 // The rotary table of a call: cs[t][j] = (cos, sin) of pos[t] * theta[j], angle and sincos in fp64, stored as fp32.  The
-// first norm of a bf16 call fills it as well (one launch of some 5 us less in front of the first projection).
+// first norm of a bf16 call, and the first QKV projection of an fp32 one, fills it as well (a launch less in front of them).
 struct RopeJob { const int32_t* pos; const double* theta; float2* cs; int T, half; };
-__device__ __forceinline__ void rope_entry(const RopeJob& j, int64_t i) {
-  if (i >= (int64_t)j.T * j.half) return;
-  const int t = (int)(i / j.half), k = (int)(i - (int64_t)t * j.half);
+__device__ __forceinline__ float2 rope_pair(const RopeJob& j, int t, int k) {  // of token t, pair k
   double s, c;
   sincos((double)j.pos[t] * j.theta[k], &s, &c);
-  j.cs[i] = make_float2((float)c, (float)s);
+  return make_float2((float)c, (float)s);
+}
+__device__ __forceinline__ void rope_entry(const RopeJob& j, int64_t i) {
+  if (i >= (int64_t)j.T * j.half) return;
+  const int t = (int)(i / j.half);
+  j.cs[i] = rope_pair(j, t, (int)(i - (int64_t)t * j.half));
 }
 inline unsigned rope_blocks(const RopeJob& j) { return (unsigned)(((int64_t)j.T * j.half + 255) / 256); }
 
@@ -121,7 +124,8 @@ bool gemm_fp32_supported(const void* A, int64_t lda, const void* W, int64_t ldw,
 hipError_t launch_gemm_fp32(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R,
                             int64_t ldr, int M, int N, int K, hipStream_t s);
 hipError_t launch_gemm_fp32_norm_rope(const float* h, const void* gain, float eps, const void* wqkv, void* qkv, const float2* cs,
-                                      void* k_rows, void* v_rows, int M, int d, int Hq, int Hkv, int dh, hipStream_t s);
+                                      void* k_rows, void* v_rows, int M, int d, int Hq, int Hkv, int dh, const RopeJob* job, hipStream_t s);
+bool gemm_fp32_takes_rope(int M, int Hq, int Hkv, int dh);
 hipError_t launch_gemm_fp32_norm_swiglu(const float* h, const void* gain, float eps, const void* wgu, void* act, int M, int d,
                                         int F, int gu_block, hipStream_t s);
 // bf16 MFMA GEMM; returns hipErrorNotSupported when the shape is outside what it handles.

@@ -5,9 +5,11 @@
 // What bounds these: the fp32 workload is small (128 tokens, width 256), every launch is a few microseconds of latency
 // and next to no arithmetic.  So a layer is five launches, every workgroup's loads go straight to registers (nothing to
 // share that the caches do not hold), and the contraction is split over the waves of a workgroup so that a
-// chain of loads is two to six long instead of forty.  The whole fp32 workload (2 layers over 128 tokens, 4 over 16)
-// takes 0.216 ms; on the plain-ALU kernels with separate norm, RoPE and SwiGLU launches it took 1.43 ms (projections 41 us,
-// attention 44 us a launch).  Error against 64 bits 1.4e-7 (2-norm; plain kernels 3.0e-7).
+// chain of loads is two to six long instead of forty; and since one matrix instruction is 32 cycles for 2048 flops, the chains
+// of those count as well: narrow tiles, eight waves for the keys.  The whole fp32 workload (2 layers over 128 tokens, 4 over
+// 16) takes 0.190 ms; with wide tiles, four waves for the keys and the rotary table in a launch of its own 0.220 ms; on the
+// plain-ALU kernels with separate norm, RoPE and SwiGLU launches 1.43 ms (projections 41 us, attention 44 us a launch).
+// Error against 64 bits 1.4e-7 (2-norm; plain kernels 3.0e-7).  More chunks in flight (six instead of three): no gain.
 #include "dsk_internal.h"
 
 namespace {
@@ -25,43 +27,48 @@ struct Fp32Gemm {
   int gu_block;                                     // EP_SWIGLU
   const float2* cs; float* k_rows; float* v_rows;   // EP_ROPE
   int Hq, Hkv, dh;
+  RopeJob job;                                      // EP_ROPE, job.cs set: the table is still to be filled (and cs is job.cs)
 };
 
 enum { EP_PLAIN = 0, EP_SWIGLU = 1, EP_ROPE = 2 };
 
-// Columns of W come in units of two 16-column tiles (c0, c1), paired so that a lane holds what its epilogue combines:
-// neighbours; gate and up of the same FFN index; or the two halves of rotary pairs.
-template <int EP>
+// Columns of W come in units of two sides c0 and c1 of 8 * CT columns, paired so that a lane holds what its epilogue
+// combines: neighbours; gate and up of the same FFN index; or the two halves of rotary pairs.  CT = 2: a 16-column tile for
+// either side; CT = 1: one tile for both.
+template <int EP, int CT>
 __device__ __forceinline__ void unit_cols(const Fp32Gemm& p, int u, int* c0, int* c1) {
+  constexpr int UP = 8 * CT;
   if (EP == EP_SWIGLU) {
-    const int f = 16 * u, gb = p.gu_block;
+    const int f = UP * u, gb = p.gu_block;
     *c0 = f / gb * 2 * gb + f % gb;
     *c1 = *c0 + gb;
   } else if (EP == EP_ROPE) {
-    const int half = p.dh >> 1, per = half >> 4, n_rot = (p.Hq + p.Hkv) * per;
+    const int half = p.dh >> 1, per = half / UP, n_rot = (p.Hq + p.Hkv) * per;
     if (u < n_rot) {
-      *c0 = u / per * p.dh + u % per * 16;
+      *c0 = u / per * p.dh + u % per * UP;
       *c1 = *c0 + half;
     } else {
-      *c0 = (p.Hq + p.Hkv) * p.dh + 32 * (u - n_rot);
-      *c1 = *c0 + 16;
+      *c0 = (p.Hq + p.Hkv) * p.dh + 2 * UP * (u - n_rot);
+      *c1 = *c0 + UP;
     }
   } else {
-    *c0 = 32 * u;
-    *c1 = *c0 + 16;
+    *c0 = 2 * UP * u;
+    *c1 = *c0 + UP;
   }
 }
 
-// One lane's share of unit u: x0, x1 = four consecutive columns of row m in tiles c0 and c1, at column offset q4.
-template <int EP>
-__device__ __forceinline__ void unit_store(const Fp32Gemm& p, int m, int u, int q4, f32x4 x0, f32x4 x1) {
+// One lane's share of unit u: x0, x1 = four consecutive columns of row m behind c0 and c1, at column offset q4; cs: the
+// (cos, sin) of the four pairs of a rotated unit.
+template <int EP, int CT>
+__device__ __forceinline__ void unit_store(const Fp32Gemm& p, int m, int u, int q4, f32x4 x0, f32x4 x1, const float2* cs) {
+  constexpr int UP = 8 * CT;
   int c0, c1;
-  unit_cols<EP>(p, u, &c0, &c1);
+  unit_cols<EP, CT>(p, u, &c0, &c1);
   if (EP == EP_SWIGLU) {
     f32x4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = x0[e] / (1.0f + __expf(-x0[e])) * x1[e];
-    *(f32x4*)(p.C + (int64_t)m * p.ldc + 16 * u + q4) = o;
+    *(f32x4*)(p.C + (int64_t)m * p.ldc + UP * u + q4) = o;
   } else if (EP == EP_ROPE) {
     const int half = p.dh >> 1, rot_cols = (p.Hq + p.Hkv) * p.dh, kvw = p.Hkv * p.dh;
     if (c0 < rot_cols) {
@@ -69,7 +76,7 @@ __device__ __forceinline__ void unit_store(const Fp32Gemm& p, int m, int u, int 
       f32x4 y0, y1;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float2 c = p.cs[(int64_t)m * half + i0 + e];
+        const float2 c = cs[e];
         y0[e] = x0[e] * c.x - x1[e] * c.y;
         y1[e] = x1[e] * c.x + x0[e] * c.y;
       }
@@ -79,11 +86,11 @@ __device__ __forceinline__ void unit_store(const Fp32Gemm& p, int m, int u, int 
     } else {
       float* dst = p.v_rows + (int64_t)m * kvw + (c0 - rot_cols) + q4;
       *(f32x4*)dst = x0;
-      *(f32x4*)(dst + 16) = x1;
+      *(f32x4*)(dst + UP) = x1;
     }
   } else {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < CT; ++t) {  // CT = 1: the unit's 16 columns are the lanes' four by four
       const int n = (t ? c1 : c0) + q4;
       if (n >= p.N) continue;  // N is a multiple of 4
       f32x4 v = t ? x1 : x0;
@@ -100,30 +107,33 @@ __device__ __forceinline__ void unit_store(const Fp32Gemm& p, int m, int u, int 
 // a lane is column 4*(lane/16) + r of row lane%16.
 // NORM: the rows are scaled by rsqrt(mean(a^2) + eps) behind the contraction and by the gain in front of it; the sum of
 // squares falls out of the loads, every wave (with its KW peers) reads its rows whole.
-template <int TM, int U, int WM, int WN, int KW, int PF, bool NORM, int EP>
+template <int TM, int U, int WM, int WN, int KW, int PF, bool NORM, int EP, int CT>
 __global__ void __launch_bounds__(64 * WM * WN * KW) gemm_fp32_kernel(Fp32Gemm p) {
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kw = wave % KW, wt = wave / KW, wm = wt % WM, wn = wt / WM;
   const int m0 = (blockIdx.y * WM + wm) * 16 * TM, u0 = (blockIdx.x * WN + wn) * U;
   const float* ap[TM];
-  const float* wp[2 * U];
+  static_assert(CT == 2 || (U == 1 && KW > 1), "the halves of a narrow unit meet in LDS");
+  constexpr int NT = CT * U;  // column tiles
+  const float* wp[NT];
 #pragma unroll
   for (int i = 0; i < TM; ++i) ap[i] = p.A + (int64_t)min(m0 + 16 * i + r16, p.M - 1) * p.lda + 4 * g;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     int c0, c1;
-    unit_cols<EP>(p, min(u0 + u, p.units - 1), &c0, &c1);
-    wp[2 * u] = p.W + (int64_t)min(c0 + r16, p.N - 1) * p.ldw + 4 * g;
-    wp[2 * u + 1] = p.W + (int64_t)min(c1 + r16, p.N - 1) * p.ldw + 4 * g;
+    unit_cols<EP, CT>(p, min(u0 + u, p.units - 1), &c0, &c1);
+    if (CT == 1 && r16 >= 8) c0 = c1 - 8;  // row r16 of the tile is column c1 + r16 - 8
+    wp[CT * u] = p.W + (int64_t)min(c0 + r16, p.N - 1) * p.ldw + 4 * g;
+    if (CT == 2) wp[CT * u + 1] = p.W + (int64_t)min(c1 + r16, p.N - 1) * p.ldw + 4 * g;
   }
-  f32x4 acc[TM][2 * U];
+  f32x4 acc[TM][NT];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 2 * U; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   float ss[TM] = {};
-  f32x4 fa[PF][TM], fw[PF][2 * U], fg[PF];
+  f32x4 fa[PF][TM], fw[PF][NT], fg[PF];
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   const int n_chunks = (p.K + 15) / 16;
   auto load = [&](int s, int c) {
@@ -132,11 +142,29 @@ __global__ void __launch_bounds__(64 * WM * WN * KW) gemm_fp32_kernel(Fp32Gemm p
 #pragma unroll
     for (int i = 0; i < TM; ++i) fa[s][i] = in ? *(const f32x4*)(ap[i] + 16 * c) : zero;
 #pragma unroll
-    for (int j = 0; j < 2 * U; ++j) fw[s][j] = in ? *(const f32x4*)(wp[j] + 16 * c) : zero;
+    for (int j = 0; j < NT; ++j) fw[s][j] = in ? *(const f32x4*)(wp[j] + 16 * c) : zero;
     if (NORM) fg[s] = in ? *(const f32x4*)(p.gain + 16 * c + 4 * g) : zero;
   };
 #pragma unroll
   for (int s = 0; s < PF; ++s) load(s, kw + s * KW);
+  constexpr int UP = 8 * CT;  // columns of a unit on either side
+  __shared__ float2 pairs[EP == EP_ROPE && KW > 1 ? WM * WN : 1][TM][U][16][UP];
+  if (EP == EP_ROPE && KW > 1) {
+    // The rotary pairs of the tile, while the operands arrive: read behind the reduction they cost a round trip to memory,
+    // and the table in a launch of its own 3.5 us a call.  The workgroups of head 0 write it for the layers that follow.
+    const int half = p.dh >> 1, per = half / UP, n_rot = (p.Hq + p.Hkv) * per;
+    for (int q = kw * 64 + lane; q < TM * U * 16 * UP; q += KW * 64) {
+      const int i = q / (U * 16 * UP), u = q / (16 * UP) % U, row = q / UP % 16, m = m0 + 16 * i + row, k = (u0 + u) % per * UP + q % UP;
+      if (m >= p.M || u0 + u >= n_rot) continue;
+      if (p.job.cs) {
+        const float2 c = rope_pair(p.job, m, k);
+        if (u0 + u < per) p.job.cs[(int64_t)m * half + k] = c;
+        pairs[wt][i][u][row][q % UP] = c;
+      } else {
+        pairs[wt][i][u][row][q % UP] = p.cs[(int64_t)m * half + k];
+      }
+    }
+  }
   for (int c = kw; c < n_chunks; c += PF * KW) {
 #pragma unroll
     for (int s = 0; s < PF; ++s) {
@@ -154,7 +182,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KW) gemm_fp32_kernel(Fp32Gemm p
 #pragma unroll
           for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < 2 * U; ++j)
+            for (int j = 0; j < NT; ++j)
               acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[s][j][k], fa[s][i][k], acc[i][j], 0, 0, 0);
         load(s, c + (s + PF) * KW);
       }
@@ -176,66 +204,88 @@ __global__ void __launch_bounds__(64 * WM * WN * KW) gemm_fp32_kernel(Fp32Gemm p
       const float rs = NORM ? 1.0f / sqrtf(ss[i] * inv_k + p.eps) : 1.0f;
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (u0 + u < p.units) unit_store<EP>(p, m, u0 + u, 4 * g, acc[i][2 * u] * rs, acc[i][2 * u + 1] * rs);
+        if (u0 + u < p.units) {
+          const int half = p.dh >> 1;
+          const float2* cs = EP == EP_ROPE ? p.cs + (int64_t)m * half + (u0 + u) * 16 % half + 4 * g : nullptr;
+          unit_store<EP, 2>(p, m, u0 + u, 4 * g, acc[i][2 * u] * rs, acc[i][2 * u + 1] * rs, cs);
+        }
     }
   } else {
     // partial sums of the KW waves meet in LDS and are added in wave order
-    __shared__ f32x4 red[WM * WN][KW][TM * 2 * U][64];
+    __shared__ f32x4 red[WM * WN][KW][TM * NT][64];
     __shared__ float red_ss[WM * WN][KW][TM * 16];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
-      for (int j = 0; j < 2 * U; ++j) red[wt][kw][i * 2 * U + j][lane] = acc[i][j];
+      for (int j = 0; j < NT; ++j) red[wt][kw][i * NT + j][lane] = acc[i][j];
       if (NORM && g == 0) red_ss[wt][kw][i * 16 + r16] = ss[i];
     }
     __syncthreads();
     for (int it = kw; it < TM * U; it += KW) {  // (row block, unit) pairs go round the KW waves
       const int i = it / U, u = it % U, m = m0 + 16 * i + r16;
       if (m >= p.M || u0 + u >= p.units) continue;
-      f32x4 x0 = red[wt][0][i * 2 * U + 2 * u][lane], x1 = red[wt][0][i * 2 * U + 2 * u + 1][lane];
+      constexpr bool MEET = CT == 1 && EP != EP_PLAIN;  // two lanes' sums are one lane's unit
+      if (MEET && g >= 2) continue;
+      const int j0 = i * NT + CT * u, j1 = CT == 2 ? j0 + 1 : j0, l1 = MEET ? lane + 32 : lane;
+      f32x4 x0 = red[wt][0][j0][lane], x1 = red[wt][0][j1][l1];
       float s = NORM ? red_ss[wt][0][i * 16 + r16] : 0.f;
 #pragma unroll
       for (int k = 1; k < KW; ++k) {
-        x0 += red[wt][k][i * 2 * U + 2 * u][lane];
-        x1 += red[wt][k][i * 2 * U + 2 * u + 1][lane];
+        x0 += red[wt][k][j0][lane];
+        if (CT == 2 || MEET) x1 += red[wt][k][j1][l1];
         if (NORM) s += red_ss[wt][k][i * 16 + r16];
       }
       const float rs = NORM ? 1.0f / sqrtf(s * inv_k + p.eps) : 1.0f;
-      unit_store<EP>(p, m, u0 + u, 4 * g, x0 * rs, x1 * rs);
+      unit_store<EP, CT>(p, m, u0 + u, 4 * g, x0 * rs, x1 * rs, EP == EP_ROPE ? &pairs[wt][i][u][r16][4 * g] : nullptr);
     }
   }
 }
 
-template <int TM, int U, int WM, int WN, int KW, int PF, bool NORM, int EP>
+template <int TM, int U, int WM, int WN, int KW, int PF, bool NORM, int EP, int CT = 2>
 hipError_t launch_tiled(const Fp32Gemm& p, hipStream_t s) {
   const dim3 grid((p.units + U * WN - 1) / (U * WN), (p.M + 16 * TM * WM - 1) / (16 * TM * WM));
-  hipLaunchKernelGGL((gemm_fp32_kernel<TM, U, WM, WN, KW, PF, NORM, EP>), grid, dim3(64 * WM * WN * KW), 0, s, p);
+  hipLaunchKernelGGL((gemm_fp32_kernel<TM, U, WM, WN, KW, PF, NORM, EP, CT>), grid, dim3(64 * WM * WN * KW), 0, s, p);
   return hipGetLastError();
 }
 
 // Three tilings, by how many workgroups a problem has: 128 x 128 per workgroup (64 x 64 wave tiles, the matrix pipe
 // is the bound) once that makes 256 of them, one per compute unit; 16 x 32 with the contraction split over eight waves
 // while that stays within 1024, four per compute unit (latency is the bound); 32 x 64 over four waves in between.
+enum { FP32_LARGE, FP32_MEDIUM, FP32_SMALL };
+int fp32_tiling(const Fp32Gemm& p) {
+  auto groups = [&](int rows, int units) { return (int64_t)((p.M + rows - 1) / rows) * ((p.units + units - 1) / units); };
+  return groups(128, 4) >= 256 ? FP32_LARGE : groups(16, 1) <= 1024 ? FP32_SMALL : FP32_MEDIUM;
+}
 template <bool NORM, int EP>
 hipError_t launch_fp32(const Fp32Gemm& p, hipStream_t s) {
-  auto groups = [&](int rows, int units) { return (int64_t)((p.M + rows - 1) / rows) * ((p.units + units - 1) / units); };
-  if (groups(128, 4) >= 256) return launch_tiled<4, 2, 2, 2, 1, 2, NORM, EP>(p, s);
-  if (groups(16, 1) <= 1024) return launch_tiled<1, 1, 1, 1, 8, 3, NORM, EP>(p, s);
-  return launch_tiled<2, 2, 1, 1, 4, 2, NORM, EP>(p, s);
+  switch (fp32_tiling(p)) {
+    case FP32_LARGE: return launch_tiled<4, 2, 2, 2, 1, 2, NORM, EP>(p, s);
+    case FP32_SMALL:
+      // One column tile a workgroup while that leaves no compute unit a second one: half the matrix instructions behind one
+      // another, which is what a wave of these takes longest for (16 rows of the fp32 workload, us: down 5.7 -> 4.5, O 3.9 ->
+      // 3.7, QKV 4.9 -> 4.5, gate/up 4.9 -> 4.4).
+      if ((int64_t)((p.M + 15) / 16) * p.units * 2 <= 256) {
+        Fp32Gemm q = p;
+        q.units *= 2;
+        return launch_tiled<1, 1, 1, 1, 8, 3, NORM, EP, 1>(q, s);
+      }
+      return launch_tiled<1, 1, 1, 1, 8, 3, NORM, EP>(p, s);
+    default: return launch_tiled<2, 2, 1, 1, 4, 2, NORM, EP>(p, s);
+  }
 }
 
-// Causal attention, one workgroup per 16 queries of one (sequence, q head); its four waves take every fourth chunk of
+// Causal attention, one workgroup per 16 queries of one (sequence, q head); its NW waves take every NW-th chunk of
 // 32 keys with a running softmax of their own and merge through LDS in wave order.  Scores are computed transposed
 // (keys are the MFMA rows), so a lane owns one query (lane%16) and four keys of a 16-key tile (4*(lane/16) + r), which is
 // the operand layout of P^T in O^T += V^T P^T: register r feeds MFMA r, with V read as rows 4*(lane/16) + r.
-template <int DH>
-__global__ void __launch_bounds__(256) attn_fp32_kernel(const float* __restrict__ q, int64_t ldq, const float* __restrict__ k_rows,
+template <int DH, int NW>
+__global__ void __launch_bounds__(64 * NW) attn_fp32_kernel(const float* __restrict__ q, int64_t ldq, const float* __restrict__ k_rows,
                                                         const float* __restrict__ v_rows, float* __restrict__ out,
                                                         const int32_t* __restrict__ q_cu, const int32_t* __restrict__ p_cu,
                                                         int n_seqs, int64_t own_row0, int Hq, int Hkv) {
   constexpr int NC = DH / 16;
-  __shared__ f32x4 red_o[4][NC][64];
-  __shared__ float red_m[4][16], red_l[4][16];
+  extern __shared__ f32x4 red_o[];  // [NW][NC][64]
+  __shared__ float red_m[NW][16], red_l[NW][16];
   const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int head = blockIdx.y, kvh = head / (Hq / Hkv);
@@ -266,7 +316,7 @@ __global__ void __launch_bounds__(256) attn_fp32_kernel(const float* __restrict_
 #pragma unroll
   for (int c = 0; c < NC; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;
-  for (int j0 = 32 * wave; j0 < n_keys; j0 += 128) {
+  for (int j0 = 32 * wave; j0 < n_keys; j0 += 32 * NW) {
     f32x4 kf[2][NC];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -287,6 +337,7 @@ __global__ void __launch_bounds__(256) attn_fp32_kernel(const float* __restrict_
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (t == 1 && j0 + 16 >= n_keys) break;  // (masked below)
 #pragma unroll
       for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -334,11 +385,13 @@ __global__ void __launch_bounds__(256) attn_fp32_kernel(const float* __restrict_
     }
     if (!by_key) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c)
+      for (int t = 0; t < 2; ++t) {
+        if (t == 1 && j0 + 16 >= n_keys) break;
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int c = 0; c < NC; ++c)
 #pragma unroll
           for (int r = 0; r < 4; ++r) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][r][c], s[t][r], o[c], 0, 0, 0);
+      }
     } else {
 #pragma unroll
       for (int t = 0; t < 2; ++t)
@@ -356,7 +409,7 @@ __global__ void __launch_bounds__(256) attn_fp32_kernel(const float* __restrict_
     }
   }
 #pragma unroll
-  for (int c = 0; c < NC; ++c) red_o[wave][c][lane] = o[c];
+  for (int c = 0; c < NC; ++c) red_o[(wave * NC + c) * 64 + lane] = o[c];
   if (g == 0) {
     red_m[wave][r16] = m;
     red_l[wave][r16] = l;
@@ -365,19 +418,18 @@ __global__ void __launch_bounds__(256) attn_fp32_kernel(const float* __restrict_
   if (q0 + r16 >= q_end) return;
   float M = red_m[0][r16];
 #pragma unroll
-  for (int w = 1; w < 4; ++w) M = fmaxf(M, red_m[w][r16]);  // finite: wave 0 holds key 0, which every query sees
-  float wgt[4], den = 0.f;
+  for (int w = 1; w < NW; ++w) M = fmaxf(M, red_m[w][r16]);  // finite: wave 0 holds key 0, which every query sees
+  float wgt[NW], den = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < NW; ++w) {
     wgt[w] = expf(red_m[w][r16] - M);
     den += red_l[w][r16] * wgt[w];
   }
   const float inv = 1.0f / den;
+  for (int c = wave; c < NC; c += NW) {
+    f32x4 x = red_o[c * 64 + lane] * wgt[0];
 #pragma unroll
-  for (int c = wave; c < NC; c += 4) {
-    f32x4 x = red_o[0][c][lane] * wgt[0];
-#pragma unroll
-    for (int w = 1; w < 4; ++w) x += red_o[w][c][lane] * wgt[w];
+    for (int w = 1; w < NW; ++w) x += red_o[(w * NC + c) * 64 + lane] * wgt[w];
     *(f32x4*)(out + (int64_t)qi * Hq * DH + head * DH + 16 * c + 4 * g) = x * inv;
   }
 }
@@ -409,12 +461,21 @@ hipError_t launch_gemm_fp32(const void* A, int64_t lda, const void* W, int64_t l
   return launch_fp32<false, EP_PLAIN>(p, s);
 }
 
+// Whether QKV over M rows runs on a tiling that can fill the rotary table as well.
+bool gemm_fp32_takes_rope(int M, int Hq, int Hkv, int dh) {
+  Fp32Gemm p = {};
+  p.M = M; p.units = ((Hq + 2 * Hkv) * dh + 31) / 32;
+  return fp32_tiling(p) != FP32_LARGE;
+}
+
+// job (gemm_fp32_takes_rope): fill the rotary table cs on the way
 hipError_t launch_gemm_fp32_norm_rope(const float* h, const void* gain, float eps, const void* wqkv, void* qkv, const float2* cs,
-                                      void* k_rows, void* v_rows, int M, int d, int Hq, int Hkv, int dh, hipStream_t s) {
+                                      void* k_rows, void* v_rows, int M, int d, int Hq, int Hkv, int dh, const RopeJob* job, hipStream_t s) {
   const int N = (Hq + 2 * Hkv) * dh;
   Fp32Gemm p = plain_args(h, d, wqkv, d, qkv, N, M, N, d);
   p.gain = (const float*)gain; p.eps = eps;
   p.cs = cs; p.k_rows = (float*)k_rows; p.v_rows = (float*)v_rows; p.Hq = Hq; p.Hkv = Hkv; p.dh = dh;
+  if (job) p.job = *job;
   return launch_fp32<true, EP_ROPE>(p, s);
 }
 
@@ -432,10 +493,23 @@ bool attn_fp32_supported(const AttnArgs& a) {
 hipError_t launch_attn_fp32(const AttnArgs& a, hipStream_t s) {
   if (a.n_q <= 0) return hipSuccess;
   int64_t tiles = 0;
-  for (int b = 0; b < a.n_seqs; ++b) tiles += (a.q_cu_host[b + 1] - a.q_cu_host[b] + 15) / 16;
-  const dim3 grid((unsigned)tiles, a.Hq);
-  auto kern = a.dh == 64 ? attn_fp32_kernel<64> : attn_fp32_kernel<128>;
-  hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, (const float*)a.q, a.ldq, (const float*)a.k_rows, (const float*)a.v_rows,
-                     (float*)a.out, a.q_cu, a.p_cu, a.n_seqs, a.own_row0, a.Hq, a.Hkv);
-  return hipGetLastError();
+  int max_keys = 0;
+  for (int b = 0; b < a.n_seqs; ++b) {
+    const int len = a.q_cu_host[b + 1] - a.q_cu_host[b], keys = len + (a.p_cu_host ? a.p_cu_host[b + 1] - a.p_cu_host[b] : 0);
+    tiles += (len + 15) / 16;
+    if (keys > max_keys) max_keys = keys;
+  }
+  // waves of a workgroup: a chunk of 32 keys each, four while that takes them one chunk (144 keys: 8.1 us with four, 6.8 with eight)
+  auto launch = [&](auto kern, int nw) -> hipError_t {
+    const int lds = nw * a.dh / 16 * 1024;
+    if (lds > 48 << 10) {
+      const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles, a.Hq), dim3(64 * nw), lds, s, (const float*)a.q, a.ldq, (const float*)a.k_rows,
+                       (const float*)a.v_rows, (float*)a.out, a.q_cu, a.p_cu, a.n_seqs, a.own_row0, a.Hq, a.Hkv);
+    return hipGetLastError();
+  };
+  if (max_keys > 128) return a.dh == 64 ? launch(attn_fp32_kernel<64, 8>, 8) : launch(attn_fp32_kernel<128, 8>, 8);
+  return a.dh == 64 ? launch(attn_fp32_kernel<64, 4>, 4) : launch(attn_fp32_kernel<128, 4>, 4);
 }

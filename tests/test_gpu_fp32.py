@@ -92,3 +92,25 @@ def test_layer_fp32_fused_steps_match_the_plain_kernels(B, rows, d, Hq, Hkv, dh,
     # two evaluations in fp32 of the same layers: a few sums of at most 2048 terms each
     for a, b in ((kv, kv_ref), (h, h_ref)):
         assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2e-5
+
+
+# where the tile narrows to eight columns of either side (256 workgroups; QKV, then gate/up, on both sides of it), and 32-row
+# tiles, each with the rotary table filled by the first layer's projection and read by the second's
+@pytest.mark.parametrize("rows,d,Hq,Hkv,dh,F", [(128, 64, 4, 2, 64, 688), (129, 64, 4, 2, 64, 96), (256, 64, 1, 1, 32, 128),
+                                                (257, 64, 1, 1, 32, 128), (600, 128, 16, 8, 128, 128)])
+def test_layer_fp32_narrow_tiles(B, rows, d, Hq, Hkv, dh, F):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(2, d, Hq, Hkv, dh, F, 10000.0, 1e-5, "f32")
+    x = G.to_dev(synth.hidden_states(shape, rows), shape)
+    with G.GpuModel(shape, rows) as m:
+        m.init_random(3, std=0.05)
+        kv, h = m.partial(x, 0, 2, None, [rows - 4, 4])
+        B.dsk_set_option("force_generic", 1)
+        try:
+            kv_ref, h_ref = m.partial(x, 0, 2, None, [rows - 4, 4])
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("force_generic", 0)
+    # two evaluations in fp32 of the same layers: a few sums of at most 688 terms each
+    for a, b in ((kv, kv_ref), (h, h_ref)):
+        assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2e-5
