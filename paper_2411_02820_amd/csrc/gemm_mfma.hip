@@ -429,7 +429,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 // between the k-steps frees the stage; the loads of tile t+2 go out one per four MFMAs of k-step 1; a barrier in
 // the middle of k-step 1 publishes tile t+1, whose first fragments are read during the rest of it.
 // GROUPED (the expert projections of a mixture-of-experts layer): the token rows are sorted by expert, and row tile
-// tm of the grid is described by tile_tab[tm] = {expert, first row, end of the expert's rows, -} (built on the
+// tm of the grid is described by tile_tab[tm] = {expert, first row, end of the expert's rows, scheduling group} (built on the
 // device; tile_tab[tiles_m].x = number of tiles that exist; expert < 0: no such tile, the workgroup leaves); the
 // expert's matrix is W + expert * w_group_stride.  a_row (optional): sorted row r is row a_row[r] of A's a_rows rows, so
 // that the rows are read where they are (gathered into a buffer first they cost 38 us more at 8192 tokens).
@@ -489,11 +489,21 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     const int xcd = pid % N_XCD, loc = pid / N_XCD;
     pid = (xcd < rem) ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
   }
-  const int per_group = GROUP_M * tiles_n;
-  const int group = pid / per_group;
-  const int first_m = group * GROUP_M;
-  const int gsz = min(GROUP_M, n_tiles_m - first_m);
-  const int in_group = pid - group * per_group;
+  int first_m, gsz, in_group;
+  if constexpr (GROUPED) {
+    // A scheduling group is of one expert, and a balanced expert is one group: a die then streams that expert's W once.  In
+    // groups of four, which straddle experts, gate/up over 16384 rows of eight experts (8B widths) took 2949 us (2833), down
+    // 1687 (1650).  The workgroups of a group are one range of ids, whatever its size.
+    const int packed = tile_tab[pid / tiles_n].w;
+    first_m = packed & ((1 << MOE_GROUP_SHIFT) - 1);
+    gsz = packed >> MOE_GROUP_SHIFT;
+    in_group = pid - first_m * tiles_n;
+  } else {
+    const int per_group = GROUP_M * tiles_n, group = pid / per_group;
+    first_m = group * GROUP_M;
+    gsz = min(GROUP_M, n_tiles_m - first_m);
+    in_group = pid - group * per_group;
+  }
   int m0 = (first_m + in_group % gsz) * BM, M = M_all;
   const int n0 = (in_group / gsz) * BN;
   const bf16_t* W = W_all;

@@ -174,7 +174,8 @@ __global__ void __launch_bounds__(256) moe_route_mfma_kernel(const bf16_t* __res
 // depend on timing).  One workgroup per expert e: it counts the entries of every expert (LDS histogram), derives the
 // first slot of its own rows and the first row tile of its own tiles, then walks the entries in order and gives the
 // j-th entry of expert e the slot first + j.  slot_of[entry] = slot, src_token[slot] = token.  tile_tab[r], r <
-// tile_rows_max: {expert, first slot of the tile, end of the expert's slots, 0}, the tiles of all experts back to back,
+// tile_rows_max: {expert, first slot of the tile, end of the expert's slots, first tile of its scheduling group | tiles of
+// that << MOE_GROUP_SHIFT}, the tiles of all experts back to back,
 // expert -1 past the last tile; tile_tab[tile_rows_max].x = number of tiles (the GEMM spreads exactly those over the
 // chip: a grid sized for the worst case would leave the dies that get its empty end idle).
 constexpr int PLACE_T = 1024;  // threads: the walk is a chain of rounds, wider ones make it shorter (256: 23 us at 8192 tokens)
@@ -202,8 +203,16 @@ __global__ void __launch_bounds__(PLACE_T) moe_place_kernel(const int32_t* __res
   }
   const int mine = hist[e];
   const int my_tiles = (mine + tile_m - 1) / tile_m;
-  for (int r = tid; r < my_tiles; r += PLACE_T)
-    if (first_tile + r < tile_rows_max) tile_tab[first_tile + r] = make_int4(e, first + r * tile_m, first + mine, 0);
+  // scheduling groups: an expert's tiles in as few equal ones as the most allows
+  const int n_groups = (my_tiles + MOE_GROUP_MOST - 1) / MOE_GROUP_MOST;
+  auto group_begin = [&](int g) { return (int)((int64_t)g * my_tiles / n_groups); };
+  for (int r = tid; r < my_tiles; r += PLACE_T) {
+    int g = (int)((int64_t)r * n_groups / my_tiles);
+    if (r >= group_begin(g + 1)) ++g;
+    const int g0 = group_begin(g), size = group_begin(g + 1) - g0;
+    if (first_tile + r < tile_rows_max)
+      tile_tab[first_tile + r] = make_int4(e, first + r * tile_m, first + mine, (first_tile + g0) | size << MOE_GROUP_SHIFT);
+  }
   if (e == E - 1) {
     for (int r = first_tile + my_tiles + tid; r < tile_rows_max; r += PLACE_T) tile_tab[r] = make_int4(-1, 0, 0, 0);
     if (tid == 0) tile_tab[tile_rows_max] = make_int4(min(first_tile + my_tiles, tile_rows_max), 0, 0, 0);

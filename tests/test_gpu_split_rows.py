@@ -212,13 +212,12 @@ def test_weights_straight_to_registers(B, d, Hq, F, n):
             assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2 ** -7
 
 
-# ... over experts (every token chooses both, so no choice hangs on a rounding), one, three and five k-tiles, against the
-# plain kernels
-@pytest.mark.parametrize("d,F", [(64, 192), (320, 128), (192, 320)])
-def test_expert_weights_straight_to_registers(B, d, F):
+# ... over experts (every token chooses both, so no choice hangs on a rounding), one, three and five k-tiles, an expert's tiles
+# in one scheduling group and in three, against the plain kernels
+@pytest.mark.parametrize("d,F,n", [(64, 192, 601), (320, 128, 601), (192, 320, 601), (128, 128, 7001)])
+def test_expert_weights_straight_to_registers(B, d, F, n):
     from tests import gpu_util as G
     shape = synth.ModelShape(1, d, 2, 1, 64, F, 10000.0, 1e-5, "bf16", 2, 2)
-    n = 601
     x = G.to_dev(synth.hidden_states(shape, n), shape)
     with G.GpuModel(shape, n) as m:
         m.init_random(23, 0.05)
