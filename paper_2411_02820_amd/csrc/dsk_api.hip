@@ -359,7 +359,8 @@ int run_layer_few(dsk_model* m, int l, const void* h_in, int h_in_f32, void* h_o
   if (!ready) HIP_TRY(launch_few_norm(h_in, h_in_f32, w.g1, m->xn, m->ssq, n, d, rope, s));
   HIP_TRY(launch_few_qkv(m->xn, m->ssq, eps, w.wqkv, m->qkv, m->n_qkv, m->rope_cs, k_layer + own, v_layer + own, n, d, c.n_q_heads,
                          c.n_kv_heads, c.head_dim, s));
-  int rc = layer_attention(m, k_layer, v_layer, own_row0, q_cu, q_cu_host, p_cu, p_cu_host, n_pre_rows, n_seqs, n, -1, 1, s);
+  int rc = layer_attention(m, k_layer, v_layer, own_row0, q_cu, q_cu_host, p_cu, p_cu_host, n_pre_rows, n_seqs, n, -1,
+                           !few_rows_row_major(n), s);
   if (rc) return rc;
   g_stats.gemm_mfma += 2;
   HIP_TRY(launch_few_residual(m->attn, w.wo, h_in, h_in_f32, m->h, 1, w.g2, m->xn, m->ssq, n, d, nq, m->gemm_ws, m->gemm_ws_bytes, s));

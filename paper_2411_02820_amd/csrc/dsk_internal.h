@@ -151,6 +151,7 @@ hipError_t launch_gemm_split_norm(const void* A, const void* W, int w_blocks, fl
 // Few token rows (M <= 64, bf16, few_rows.hip): weights and activations in blocks, the step that follows a projection (and
 // the RMSNorm in front of it) done by the projection.  a = bf16(h * gain) in blocks, ssq [d/16][64] its sums of squares.
 bool few_rows_supported(int M, int d, int F, int Hq, int Hkv, int dh);
+bool few_rows_row_major(int M);  // whether its activations stand in rows instead of blocks
 int64_t few_rows_workspace_bytes(int d, int K_max);
 // rope: also fills the rotary table (may be null)
 hipError_t launch_few_norm(const void* h, int h_f32, const void* gain, void* a, float* ssq, int M, int d, const RopeJob* rope,

@@ -6,7 +6,8 @@
 // 77 us with only the operands' layout changed).  So both operands are kept in blocks of 16 rows x 32 columns, each
 // block the 1 KB that a wave loads for one MFMA operand in lane order: block (r/16, k/32) of a matrix with K columns is at
 // ((r/16) * K/32 + k/32) * 512 elements, element ((k%32)/8 * 16 + r%16) * 8 + k%8 inside it.  Weights are packed that way
-// when they are set; activations are written that way by the step in front (they live in the workspace only).
+// when they are set; activations are written that way by the step in front (they live in the workspace only), up to eight
+// rows as rows (few_rows_row_major).
 //
 // No LDS ring: a wave streams both operands straight to registers, PF steps ahead; the waves of a workgroup split
 // the contraction (neighbouring chunks, so that a workgroup reads 512 contiguous bytes and more per row block) and
@@ -24,10 +25,13 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 enum { EP_ROPE = 0, EP_SWIGLU = 1, EP_RES = 2, EP_PART = 3 };
 
+// Activations of few_rows_row_major(M) rows stand in rows instead of blocks.
+__device__ __forceinline__ int64_t act_at(int64_t m, int64_t k, int64_t K, int rows) { return rows ? m * K + k : block_at(m, k, K); }
+
 struct StreamArgs {
-  const bf16_t* X;  // blocks, rows up to a multiple of 16
+  const bf16_t* X;  // blocks, rows up to a multiple of 16; or rows (x_rows)
   const bf16_t* W;  // blocks
-  int M, N, K;
+  int M, N, K, x_rows;
   const float* ssq; float eps;  // EP_ROPE, EP_SWIGLU: row factor of the RMSNorm in front, from [K/16][64] sums of squares
   bf16_t* out;                  // EP_ROPE: q rows, stride ldq; EP_SWIGLU: blocks [M, N/2]; EP_RES: blocks a = h * gain
   int64_t ldq;
@@ -49,7 +53,7 @@ __device__ __forceinline__ bf16x4 to_bf16x4(f32x4 v) {
 // v[n..n+3] of row m: + R, C, and the next norm's share; the four lanes of a 16-column group are at lane ^ X1, lane ^ X2
 template <int X1, int X2>
 __device__ __forceinline__ void residual_quad(f32x4 v, int m, int n, int N, bool in, const void* R, int r_f32, void* C,
-                                              int c_f32, const bf16_t* gain, bf16_t* a, float* ssq_out) {
+                                              int c_f32, const bf16_t* gain, bf16_t* a, int a_rows, float* ssq_out) {
   const int64_t at = (int64_t)m * N + n;
   if (in) {
     if (r_f32) {
@@ -71,7 +75,7 @@ __device__ __forceinline__ void residual_quad(f32x4 v, int m, int n, int N, bool
     const bf16x4 g = *(const bf16x4*)(gain + n);
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] *= (float)g[e];
-    *(bf16x4*)(a + block_at(m, n, N)) = to_bf16x4(v);
+    *(bf16x4*)(a + act_at(m, n, N, a_rows)) = to_bf16x4(v);
     if (n % 16 == 0) ssq_out[(n / 16) * 64 + m] = ss;
   }
 }
@@ -115,6 +119,10 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
   for (int j = 0; j < NT; ++j) wo[j] = ((uint32_t)(col0(j) >> 4) * kb * 64 + lane) * 16;
 #pragma unroll
   for (int i = 0; i < MT; ++i) xo[i] = ((uint32_t)i * kb * 64 + lane) * 16;
+  // rows: a lane's eight values of its row (the last one for those past it), 64 bytes a block
+  const bool x_rows = MT == 1 && p.x_rows;
+  if (x_rows) xo[0] = ((uint32_t)min(r16, p.M - 1) * p.K + 8 * g) * 2;
+  const int x_step = x_rows ? 64 : 1024;
   f32x4 acc[NT][MT];
 #pragma unroll
   for (int j = 0; j < NT; ++j)
@@ -130,7 +138,7 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
     for (int q = 0; q < KS; ++q) {
       const int b = c * KS + q;
       const char* wb = (const char*)p.W + (int64_t)b * 1024;
-      const char* xb = (const char*)p.X + (int64_t)b * 1024;
+      const char* xb = (const char*)p.X + (int64_t)b * x_step;
 #pragma unroll
       for (int j = 0; j < NT; ++j) fw[s][q][j] = __builtin_nontemporal_load((const bf16x8*)(wb + wo[j]));
 #pragma unroll
@@ -196,7 +204,7 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
       if (EP == EP_PART) {
         if (in) *(f32x4*)(p.P + ((int64_t)blockIdx.y * p.M + m) * p.N + n) = v;
       } else {
-        residual_quad<16, 32>(v, m, n, p.N, in, p.R, p.r_f32, p.C, p.c_f32, p.gain, p.out, p.ssq_out);
+        residual_quad<16, 32>(v, m, n, p.N, in, p.R, p.r_f32, p.C, p.c_f32, p.gain, p.out, p.x_rows, p.ssq_out);
       }
       continue;
     }
@@ -215,7 +223,7 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
         const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x0[e]));
         o[e] = x0[e] * sig * x1[e];
       }
-      *(bf16x4*)(p.out + block_at(m, 16 * (unit0 + jj) + 4 * g, p.N >> 1)) = to_bf16x4(o);
+      *(bf16x4*)(p.out + act_at(m, 16 * (unit0 + jj) + 4 * g, p.N >> 1, p.x_rows)) = to_bf16x4(o);
     } else {
       const int c0 = col0(2 * jj), rot_cols = (p.Hq + p.Hkv) * p.dh, kvw = p.Hkv * p.dh;
       if (c0 < rot_cols) {
@@ -244,7 +252,7 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
 // thread per 4 columns of a row.
 __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restrict__ P, int splits, const void* R, int r_f32,
                                                            void* C, int c_f32, const bf16_t* __restrict__ gain,
-                                                           bf16_t* __restrict__ a, float* __restrict__ ssq_out, int M, int N) {
+                                                           bf16_t* __restrict__ a, int a_rows, float* __restrict__ ssq_out, int M, int N) {
   const int i = blockIdx.x * 256 + threadIdx.x, quads = N / 4;
   const bool in = i < M * quads;
   const int m = in ? i / quads : 0, n = in ? (i - m * quads) * 4 : 0;
@@ -262,7 +270,7 @@ __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restri
         if (k + u < splits) v += b[u];
     }
   }
-  residual_quad<1, 2>(v, m, n, N, in, R, r_f32, C, c_f32, gain, a, ssq_out);
+  residual_quad<1, 2>(v, m, n, N, in, R, r_f32, C, c_f32, gain, a, a_rows, ssq_out);
 }
 
 // Router of an expert layer on the prepared rows a (blocks; the RMSNorm factor is applied to the logits), one workgroup per
@@ -270,7 +278,7 @@ __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restri
 // rules as the router over rows (moe.hip): fp32 logits, equal ones to the lower expert, NaN last.
 __global__ void __launch_bounds__(256) few_route_kernel(const bf16_t* __restrict__ a, const float* __restrict__ ssq, float eps,
                                                         const bf16_t* __restrict__ wr, int32_t* __restrict__ experts,
-                                                        float* __restrict__ gates, int d, int E, int top_k) {
+                                                        float* __restrict__ gates, int a_rows, int d, int E, int top_k) {
   __shared__ float part[4][9];
   __shared__ float logit[DSK_MOE_MAX_EXPERTS];
   const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -279,7 +287,7 @@ __global__ void __launch_bounds__(256) few_route_kernel(const bf16_t* __restrict
   for (int e0 = 0; e0 < E; e0 += 8) {
     float acc[9] = {};
     for (int c = tid; c < d / 8; c += 256) {
-      const bf16x8 x = *(const bf16x8*)(a + block_at(t, 8 * c, d));
+      const bf16x8 x = *(const bf16x8*)(a + act_at(t, 8 * c, d, a_rows));
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const bf16x8 w = *(const bf16x8*)(wr + (int64_t)min(e0 + e, E - 1) * d + 8 * c);
@@ -321,7 +329,7 @@ __global__ void __launch_bounds__(256) few_route_kernel(const bf16_t* __restrict
 // C = h + sum_j gates[t][j] * y[experts[t][j]][t], and the next norm's share, as few_residual_kernel
 __global__ void __launch_bounds__(256) few_combine_kernel(const float* __restrict__ y, const int32_t* __restrict__ experts,
                                                           const float* __restrict__ gates, int top_k, int E, const void* R, void* C,
-                                                          int c_f32, const bf16_t* __restrict__ gain, bf16_t* __restrict__ a,
+                                                          int c_f32, const bf16_t* __restrict__ gain, bf16_t* __restrict__ a, int a_rows,
                                                           float* __restrict__ ssq_out, int M, int N) {
   const int i = blockIdx.x * 256 + threadIdx.x, quads = N / 4;
   const bool in = i < M * quads;
@@ -333,13 +341,13 @@ __global__ void __launch_bounds__(256) few_combine_kernel(const float* __restric
       v += *(const f32x4*)(y + ((int64_t)e * M + m) * N + n) * gates[m * top_k + j];
     }
   }
-  residual_quad<1, 2>(v, m, n, N, in, R, 1, C, c_f32, gain, a, ssq_out);
+  residual_quad<1, 2>(v, m, n, N, in, R, 1, C, c_f32, gain, a, a_rows, ssq_out);
 }
 
 // The input norm of a call's first layer and the call's rotary table: workgroups 0 .. n_norm-1, and those behind them.
 __global__ void __launch_bounds__(256) few_norm_rope_kernel(const void* h, int h_f32, const bf16_t* __restrict__ gain,
-                                                            bf16_t* __restrict__ a, float* __restrict__ ssq_out, int M, int N,
-                                                            int n_norm, RopeJob rope) {
+                                                            bf16_t* __restrict__ a, int a_rows, float* __restrict__ ssq_out, int M,
+                                                            int N, int n_norm, RopeJob rope) {
   if ((int)blockIdx.x >= n_norm) {
     rope_entry(rope, (int64_t)((int)blockIdx.x - n_norm) * 256 + threadIdx.x);
     return;
@@ -347,7 +355,7 @@ __global__ void __launch_bounds__(256) few_norm_rope_kernel(const void* h, int h
   const int i = blockIdx.x * 256 + threadIdx.x, quads = N / 4;
   const bool in = i < M * quads;
   const int m = in ? i / quads : 0, n = in ? (i - m * quads) * 4 : 0;
-  residual_quad<1, 2>(f32x4{0.f, 0.f, 0.f, 0.f}, m, n, N, in, h, h_f32, nullptr, 0, gain, a, ssq_out);
+  residual_quad<1, 2>(f32x4{0.f, 0.f, 0.f, 0.f}, m, n, N, in, h, h_f32, nullptr, 0, gain, a, a_rows, ssq_out);
 }
 
 template <int MT, int NT, int KW, int PF, int KS, int EP>
@@ -384,6 +392,12 @@ bool few_rows_supported(int M, int d, int F, int Hq, int Hkv, int dh) {
   return M >= 1 && M <= 64 && d % 64 == 0 && F % 64 == 0 && dh % 32 == 0 && Hq * dh % 64 == 0;
 }
 
+// A block holds 16 rows whatever M is, and what an unfilled one costs is its cache lines: eight a load, against one a row where
+// the activations stand in rows.  8B shape, us a launch, blocks against rows: one row QKV 12.2 -> 11.2, O 8.8 -> 8.2, gate/up
+// 40.5 -> 38.4, down 22.8 -> 20.0; eight rows 12.2 -> 12.1, 8.7 -> 8.2, 40.4 -> 40.3, 22.6 -> 20.9; twelve rows 12.4 -> 12.8,
+// 8.9 -> 9.0, 40.5 -> 41.7, 23.1 -> 22.9.
+bool few_rows_row_major(int M) { return M <= 8; }
+
 int64_t few_rows_workspace_bytes(int d, int K_max) {
   const int s = residual_splits(64, d, K_max);
   return (int64_t)(s > 0 ? s : 1) * 64 * d * 4;
@@ -394,14 +408,14 @@ hipError_t launch_few_norm(const void* h, int h_f32, const void* gain, void* a, 
   const int n_norm = (M * (d / 4) + 255) / 256;
   const RopeJob job = rope ? *rope : RopeJob{};
   hipLaunchKernelGGL(few_norm_rope_kernel, dim3(n_norm + rope_blocks(job)), dim3(256), 0, s, h, h_f32, (const bf16_t*)gain, (bf16_t*)a,
-                     ssq, M, d, n_norm, job);
+                     (int)few_rows_row_major(M), ssq, M, d, n_norm, job);
   return hipGetLastError();
 }
 
 hipError_t launch_few_qkv(const void* a, const float* ssq, float eps, const void* W, void* qkv, int64_t ldq, const float2* cs,
                           void* k_rows, void* v_rows, int M, int d, int Hq, int Hkv, int dh, hipStream_t s) {
   StreamArgs p = {};
-  p.X = (const bf16_t*)a; p.W = (const bf16_t*)W; p.M = M; p.N = (Hq + 2 * Hkv) * dh; p.K = d; p.ssq = ssq; p.eps = eps;
+  p.X = (const bf16_t*)a; p.W = (const bf16_t*)W; p.M = M; p.x_rows = few_rows_row_major(M); p.N = (Hq + 2 * Hkv) * dh; p.K = d; p.ssq = ssq; p.eps = eps;
   p.out = (bf16_t*)qkv; p.ldq = ldq; p.cs = cs; p.k_rows = (bf16_t*)k_rows; p.v_rows = (bf16_t*)v_rows;
   p.Hq = Hq; p.Hkv = Hkv; p.dh = dh;
   const int tiles = p.N / 32;
@@ -418,7 +432,7 @@ hipError_t launch_few_qkv(const void* a, const float* ssq, float eps, const void
 hipError_t launch_few_swiglu(const void* a, const float* ssq, float eps, const void* W, void* act, int M, int N, int K,
                              hipStream_t s) {
   StreamArgs p = {};
-  p.X = (const bf16_t*)a; p.W = (const bf16_t*)W; p.M = M; p.N = N; p.K = K; p.ssq = ssq; p.eps = eps; p.out = (bf16_t*)act;
+  p.X = (const bf16_t*)a; p.W = (const bf16_t*)W; p.M = M; p.x_rows = few_rows_row_major(M); p.N = N; p.K = K; p.ssq = ssq; p.eps = eps; p.out = (bf16_t*)act;
   switch ((M + 15) / 16) {
     case 1: return launch_stream<1, 2, 8, 2, 2, EP_SWIGLU>(p, N / 32, 1, s);
     case 2: return launch_stream<2, 2, 8, 2, 2, EP_SWIGLU>(p, N / 32, 1, s);
@@ -430,7 +444,7 @@ hipError_t launch_few_swiglu(const void* a, const float* ssq, float eps, const v
 hipError_t launch_few_residual(const void* x, const void* W, const void* R, int r_f32, void* C, int c_f32, const void* gain,
                                void* a, float* ssq, int M, int N, int K, void* ws, int64_t ws_bytes, hipStream_t s) {
   StreamArgs p = {};
-  p.X = (const bf16_t*)x; p.W = (const bf16_t*)W; p.M = M; p.N = N; p.K = K;
+  p.X = (const bf16_t*)x; p.W = (const bf16_t*)W; p.M = M; p.x_rows = few_rows_row_major(M); p.N = N; p.K = K;
   p.R = R; p.r_f32 = r_f32; p.C = C; p.c_f32 = c_f32; p.gain = (const bf16_t*)gain; p.out = (bf16_t*)a; p.ssq_out = ssq;
   p.P = (float*)ws;
   const int mt = (M + 15) / 16, splits = residual_splits(M, N, K);
@@ -440,7 +454,7 @@ hipError_t launch_few_residual(const void* x, const void* W, const void* R, int 
                            : launch_stream<4, 4, 8, 2, 1, EP_PART>(p, N / 64, splits, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(few_residual_kernel, dim3((M * (N / 4) + 255) / 256), dim3(256), 0, s, (const float*)ws, splits, R, r_f32,
-                       C, c_f32, (const bf16_t*)gain, (bf16_t*)a, ssq, M, N);
+                       C, c_f32, (const bf16_t*)gain, (bf16_t*)a, p.x_rows, ssq, M, N);
     return hipGetLastError();
   }
   switch (mt) {
@@ -454,8 +468,8 @@ hipError_t launch_few_residual(const void* x, const void* W, const void* R, int 
 hipError_t launch_few_route(const void* a, const float* ssq, float eps, const void* wr, int32_t* experts, float* gates, int n,
                             int d, int E, int top_k, hipStream_t s) {
   if (E < 1 || E > DSK_MOE_MAX_EXPERTS || top_k < 1 || top_k > DSK_MOE_MAX_TOP_K || top_k > E) return hipErrorNotSupported;
-  hipLaunchKernelGGL(few_route_kernel, dim3(n), dim3(256), 0, s, (const bf16_t*)a, ssq, eps, (const bf16_t*)wr, experts, gates, d,
-                     E, top_k);
+  hipLaunchKernelGGL(few_route_kernel, dim3(n), dim3(256), 0, s, (const bf16_t*)a, ssq, eps, (const bf16_t*)wr, experts, gates,
+                     (int)few_rows_row_major(n), d, E, top_k);
   return hipGetLastError();
 }
 
@@ -466,7 +480,7 @@ hipError_t launch_few_route(const void* a, const float* ssq, float eps, const vo
 hipError_t launch_few_experts(const void* a, const float* ssq, float eps, const void* wgu, const void* wd, void* act, float* y,
                               const int32_t* experts, int M, int d, int F, int E, int top_k, hipStream_t s) {
   StreamArgs p = {};
-  p.X = (const bf16_t*)a; p.W = (const bf16_t*)wgu; p.M = M; p.N = 2 * F; p.K = d; p.ssq = ssq; p.eps = eps; p.out = (bf16_t*)act;
+  p.X = (const bf16_t*)a; p.W = (const bf16_t*)wgu; p.M = M; p.x_rows = few_rows_row_major(M); p.N = 2 * F; p.K = d; p.ssq = ssq; p.eps = eps; p.out = (bf16_t*)act;
   p.experts = experts; p.n_entries = M * top_k;
   p.w_expert = 2 * (int64_t)F * d; p.out_expert = (int64_t)(M + 15) / 16 * 16 * F;
   hipError_t e;
@@ -491,6 +505,6 @@ hipError_t launch_few_experts(const void* a, const float* ssq, float eps, const 
 hipError_t launch_few_combine(const float* y, const int32_t* experts, const float* gates, int top_k, int E, const float* h, void* C,
                               int c_f32, const void* gain, void* a, float* ssq, int M, int d, hipStream_t s) {
   hipLaunchKernelGGL(few_combine_kernel, dim3((M * (d / 4) + 255) / 256), dim3(256), 0, s, y, experts, gates, top_k, E,
-                     (const void*)h, C, c_f32, (const bf16_t*)gain, (bf16_t*)a, ssq, M, d);
+                     (const void*)h, C, c_f32, (const bf16_t*)gain, (bf16_t*)a, (int)few_rows_row_major(M), ssq, M, d);
   return hipGetLastError();
 }

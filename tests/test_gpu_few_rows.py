@@ -84,3 +84,19 @@ def test_expert_layers_match_the_plain_kernels(B, rows, E, k):
     # two bf16 evaluations of one layer: each within 1e-2 of the exact one at this weight scale
     assert O.max_rel_err(G.to_np(h), G.to_np(h_ref).astype(np.float64)) <= 2e-2
     assert O.max_rel_err(G.to_np(kv[0]), G.to_np(kv_ref[0]).astype(np.float64)) <= 2e-2
+
+
+# activations of up to eight rows stand in rows, of more in blocks: the same sums in the same order, bit for bit; a single
+# row, the most rows, dense and expert layers, an odd number of 32-column blocks
+@pytest.mark.parametrize("d,Hq,Hkv,dh,F,E", [(448, 7, 1, 64, 832, 0), (512, 6, 2, 128, 320, 0), (320, 5, 1, 64, 192, 5)])
+def test_activations_in_rows_and_in_blocks_agree(B, d, Hq, Hkv, dh, F, E):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(2, d, Hq, Hkv, dh, F, 10000.0, 1e-5, "bf16", E, 2 if E else 0)
+    x = G.to_dev(synth.hidden_states(shape, 9), shape)
+    with G.GpuModel(shape, 9) as m:
+        m.init_random(5, std=0.05)
+        kv, h = m.partial(x, 0, 2, None, [1] * 9)
+        for r0, n in ((0, 8), (8, 1), (3, 5)):
+            kv_n, h_n = m.partial(x[r0:r0 + n].contiguous(), 0, 2, None, [1] * n)
+            torch.cuda.synchronize()
+            assert torch.equal(h[r0:r0 + n], h_n) and torch.equal(kv[:, :, r0:r0 + n], kv_n)
