@@ -25,8 +25,10 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 enum { EP_ROPE = 0, EP_SWIGLU = 1, EP_RES = 2, EP_PART = 3 };
 
-// Activations of few_rows_row_major(M) rows stand in rows instead of blocks.
+// Activations of few_rows_row_major(M) rows stand in rows instead of blocks, and so do their sums of squares ([M][K/16]
+// instead of [K/16][64]).
 __device__ __forceinline__ int64_t act_at(int64_t m, int64_t k, int64_t K, int rows) { return rows ? m * K + k : block_at(m, k, K); }
+__device__ __forceinline__ int ssq_at(int m, int part, int K, int rows) { return rows ? m * (K >> 4) + part : part * 64 + m; }
 
 struct StreamArgs {
   const bf16_t* X;  // blocks, rows up to a multiple of 16; or rows (x_rows)
@@ -76,7 +78,7 @@ __device__ __forceinline__ void residual_quad(f32x4 v, int m, int n, int N, bool
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] *= (float)g[e];
     *(bf16x4*)(a + act_at(m, n, N, a_rows)) = to_bf16x4(v);
-    if (n % 16 == 0) ssq_out[(n / 16) * 64 + m] = ss;
+    if (n % 16 == 0) ssq_out[ssq_at(m, n / 16, N, a_rows)] = ss;
   }
 }
 
@@ -147,7 +149,25 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
   };
 #pragma unroll
   for (int s = 0; s < PF; ++s) load(s, begin + kw + s * KW);
-  if (PAIRS) {
+  if (PAIRS && x_rows) {
+    // Sums of squares in rows: a wave per row, 32 lanes each every 32nd part, added up as below.  (As columns of 64 a row's parts
+    // lie in a cache line each.)
+    static_assert(MT > 1 || KW == 8, "a wave per row, 32 lanes as the groups of 16 lanes below");
+    const int parts = p.K >> 4;
+    float s = 0.f;
+    if (kw < p.M && lane < 32) {
+      for (int q = lane; q < parts; q += 8 * 32) {
+        float b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) b[u] = q + u * 32 < parts ? p.ssq[kw * parts + q + u * 32] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += b[u];
+      }
+    }
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    if (lane < 32 && lane % 4 == 0) ((float*)red_ss)[lane / 4 * 64 + kw] = s;
+  } else if (PAIRS) {
     // Sums of squares: four rows a lane, eight loads in flight.  One load at a time took longer than the matrix (25 us instead
     // of 18.6 us for QKV over 64 rows, 58 us instead of 43.7 us for gate/up); requested in front of the operands: 49 us.
     const float* src = p.ssq + 4 * r16;
@@ -204,7 +224,7 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
       if (EP == EP_PART) {
         if (in) *(f32x4*)(p.P + ((int64_t)blockIdx.y * p.M + m) * p.N + n) = v;
       } else {
-        residual_quad<16, 32>(v, m, n, p.N, in, p.R, p.r_f32, p.C, p.c_f32, p.gain, p.out, p.x_rows, p.ssq_out);
+        residual_quad<16, 32>(v, m, n, p.N, in, p.R, p.r_f32, p.C, p.c_f32, p.gain, p.out, x_rows, p.ssq_out);
       }
       continue;
     }
@@ -223,7 +243,7 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
         const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x0[e]));
         o[e] = x0[e] * sig * x1[e];
       }
-      *(bf16x4*)(p.out + act_at(m, 16 * (unit0 + jj) + 4 * g, p.N >> 1, p.x_rows)) = to_bf16x4(o);
+      *(bf16x4*)(p.out + act_at(m, 16 * (unit0 + jj) + 4 * g, p.N >> 1, x_rows)) = to_bf16x4(o);
     } else {
       const int c0 = col0(2 * jj), rot_cols = (p.Hq + p.Hkv) * p.dh, kvw = p.Hkv * p.dh;
       if (c0 < rot_cols) {
@@ -252,7 +272,7 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
 // thread per 4 columns of a row.
 __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restrict__ P, int splits, const void* R, int r_f32,
                                                            void* C, int c_f32, const bf16_t* __restrict__ gain,
-                                                           bf16_t* __restrict__ a, int a_rows, float* __restrict__ ssq_out, int M, int N) {
+                                                           bf16_t* __restrict__ a, float* __restrict__ ssq_out, int M, int N) {
   const int i = blockIdx.x * 256 + threadIdx.x, quads = N / 4;
   const bool in = i < M * quads;
   const int m = in ? i / quads : 0, n = in ? (i - m * quads) * 4 : 0;
@@ -270,7 +290,7 @@ __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restri
         if (k + u < splits) v += b[u];
     }
   }
-  residual_quad<1, 2>(v, m, n, N, in, R, r_f32, C, c_f32, gain, a, a_rows, ssq_out);
+  residual_quad<1, 2>(v, m, n, N, in, R, r_f32, C, c_f32, gain, a, 0, ssq_out);
 }
 
 // Router of an expert layer on the prepared rows a (blocks; the RMSNorm factor is applied to the logits), one workgroup per
@@ -283,7 +303,7 @@ __global__ void __launch_bounds__(256) few_route_kernel(const bf16_t* __restrict
   __shared__ float logit[DSK_MOE_MAX_EXPERTS];
   const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float ss = 0.f;
-  for (int q = tid; q < d / 16; q += 256) ss += ssq[q * 64 + t];
+  for (int q = tid; q < d / 16; q += 256) ss += ssq[ssq_at(t, q, d, a_rows)];
   for (int e0 = 0; e0 < E; e0 += 8) {
     float acc[9] = {};
     for (int c = tid; c < d / 8; c += 256) {
@@ -393,9 +413,9 @@ bool few_rows_supported(int M, int d, int F, int Hq, int Hkv, int dh) {
 }
 
 // A block holds 16 rows whatever M is, and what an unfilled one costs is its cache lines: eight a load, against one a row where
-// the activations stand in rows.  8B shape, us a launch, blocks against rows: one row QKV 12.2 -> 11.2, O 8.8 -> 8.2, gate/up
-// 40.5 -> 38.4, down 22.8 -> 20.0; eight rows 12.2 -> 12.1, 8.7 -> 8.2, 40.4 -> 40.3, 22.6 -> 20.9; twelve rows 12.4 -> 12.8,
-// 8.9 -> 9.0, 40.5 -> 41.7, 23.1 -> 22.9.
+// the activations stand in rows; a row's sums of squares likewise.  8B shape, us a launch, blocks against rows: one row QKV
+// 12.2 -> 10.8, O 8.8 -> 7.9, gate/up 40.5 -> 37.8, down 22.8 -> 19.9; eight rows 12.2 -> 11.6, 8.7 -> 8.1, 40.4 -> 39.4, 22.6 ->
+// 20.7; twelve rows (activations alone) 12.4 -> 12.8, 8.9 -> 9.0, 40.5 -> 41.7, 23.1 -> 22.9.
 bool few_rows_row_major(int M) { return M <= 8; }
 
 int64_t few_rows_workspace_bytes(int d, int K_max) {
@@ -454,7 +474,7 @@ hipError_t launch_few_residual(const void* x, const void* W, const void* R, int 
                            : launch_stream<4, 4, 8, 2, 1, EP_PART>(p, N / 64, splits, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(few_residual_kernel, dim3((M * (N / 4) + 255) / 256), dim3(256), 0, s, (const float*)ws, splits, R, r_f32,
-                       C, c_f32, (const bf16_t*)gain, (bf16_t*)a, p.x_rows, ssq, M, N);
+                       C, c_f32, (const bf16_t*)gain, (bf16_t*)a, ssq, M, N);
     return hipGetLastError();
   }
   switch (mt) {
