@@ -22,6 +22,8 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 enum { EP_ROPE = 0, EP_SWIGLU = 1, EP_RES = 2, EP_PART = 3 };
 
@@ -52,16 +54,35 @@ __device__ __forceinline__ bf16x4 to_bf16x4(f32x4 v) {
   return o;
 }
 
-// v[n..n+3] of row m: + R, C, and the next norm's share; the four lanes of a 16-column group are at lane ^ X1, lane ^ X2
-template <int X1, int X2>
-__device__ __forceinline__ void residual_quad(f32x4 v, int m, int n, int N, bool in, const void* R, int r_f32, void* C,
-                                              int c_f32, const bf16_t* gain, bf16_t* a, int a_rows, float* ssq_out) {
+// What a quad of the residual stream (row m, columns n .. n+3) reads besides its sum, requested before the sum is there: behind
+// it these were two round trips to memory one after the other, at the end of every launch (one row through four 8B layers 359.8 ->
+// 357.6 us, with the rotary pairs of QKV).
+struct ResidualIn { u32x4 r; bf16x4 g; };  // r: as it lies, four fp32 or (in the lower half) four bf16
+__device__ __forceinline__ ResidualIn residual_in(int m, int n, int N, bool in, const void* R, int r_f32, const bf16_t* gain) {
+  ResidualIn q = {};
   const int64_t at = (int64_t)m * N + n;
   if (in) {
     if (r_f32) {
-      v += *(const f32x4*)((const float*)R + at);
+      q.r = *(const u32x4*)((const float*)R + at);
     } else {
-      const bf16x4 r = *(const bf16x4*)((const bf16_t*)R + at);
+      const u32x2 r = *(const u32x2*)((const bf16_t*)R + at);
+      q.r[0] = r[0]; q.r[1] = r[1];
+    }
+    if (gain) q.g = *(const bf16x4*)(gain + n);
+  }
+  return q;
+}
+
+// v[n..n+3] of row m: + R, C, and the next norm's share; the four lanes of a 16-column group are at lane ^ X1, lane ^ X2
+template <int X1, int X2>
+__device__ __forceinline__ void residual_quad(f32x4 v, const ResidualIn& q, int m, int n, int N, bool in, int r_f32, void* C,
+                                              int c_f32, bool norm, bf16_t* a, int a_rows, float* ssq_out) {
+  const int64_t at = (int64_t)m * N + n;
+  if (in) {
+    if (r_f32) {
+      v += __builtin_bit_cast(f32x4, q.r);
+    } else {
+      const bf16x4 r = __builtin_bit_cast(bf16x4, u32x2{q.r[0], q.r[1]});
       v[0] += (float)r[0]; v[1] += (float)r[1]; v[2] += (float)r[2]; v[3] += (float)r[3];
     }
     if (C) {
@@ -69,14 +90,13 @@ __device__ __forceinline__ void residual_quad(f32x4 v, int m, int n, int N, bool
       else *(bf16x4*)((bf16_t*)C + at) = to_bf16x4(v);
     }
   }
-  if (!gain) return;
+  if (!norm) return;
   float ss = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
   ss += __shfl_xor(ss, X1, 64);
   ss += __shfl_xor(ss, X2, 64);
   if (in) {
-    const bf16x4 g = *(const bf16x4*)(gain + n);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] *= (float)g[e];
+    for (int e = 0; e < 4; ++e) v[e] *= (float)q.g[e];
     *(bf16x4*)(a + act_at(m, n, N, a_rows)) = to_bf16x4(v);
     if (n % 16 == 0) ssq_out[ssq_at(m, n / 16, N, a_rows)] = ss;
   }
@@ -147,6 +167,19 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
       for (int i = 0; i < MT; ++i) fx[s][q][i] = *(const bf16x8*)(xb + xo[i]);
     }
   };
+  // What the epilogue of the wave's item (one at most) reads: in flight under the contraction
+  static_assert((EP != EP_RES && EP != EP_ROPE) || MT * (PAIRS ? NT / 2 : NT) <= KW, "one item a wave");
+  ResidualIn res;
+  f32x4 cs[2];  // four (cos, sin)
+  if ((EP == EP_RES || EP == EP_ROPE) && kw < MT * (PAIRS ? NT / 2 : NT)) {
+    const int m = 16 * (kw % MT) + r16, c0 = col0(PAIRS ? kw / MT * 2 : kw / MT);
+    if (EP == EP_RES) res = residual_in(m, c0 + 4 * g, p.N, m < p.M, p.R, p.r_f32, p.gain);
+    if (EP == EP_ROPE && m < p.M && c0 < (p.Hq + p.Hkv) * p.dh) {
+      const f32x4* src = (const f32x4*)(p.cs + (int64_t)m * half + c0 % p.dh + 4 * g);
+      cs[0] = src[0];
+      cs[1] = src[1];
+    }
+  }
 #pragma unroll
   for (int s = 0; s < PF; ++s) load(s, begin + kw + s * KW);
   if (PAIRS && x_rows) {
@@ -224,7 +257,7 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
       if (EP == EP_PART) {
         if (in) *(f32x4*)(p.P + ((int64_t)blockIdx.y * p.M + m) * p.N + n) = v;
       } else {
-        residual_quad<16, 32>(v, m, n, p.N, in, p.R, p.r_f32, p.C, p.c_f32, p.gain, p.out, x_rows, p.ssq_out);
+        residual_quad<16, 32>(v, res, m, n, p.N, in, p.r_f32, p.C, p.c_f32, p.gain, p.out, x_rows, p.ssq_out);
       }
       continue;
     }
@@ -251,9 +284,9 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
         f32x4 y0, y1;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float2 c = p.cs[(int64_t)m * half + i0 + e];
-          y0[e] = x0[e] * c.x - x1[e] * c.y;
-          y1[e] = x1[e] * c.x + x0[e] * c.y;
+          const float co = cs[e / 2][e % 2 * 2], si = cs[e / 2][e % 2 * 2 + 1];
+          y0[e] = x0[e] * co - x1[e] * si;
+          y1[e] = x1[e] * co + x0[e] * si;
         }
         bf16_t* dst = head < p.Hq ? p.out + (int64_t)m * p.ldq + head * p.dh + i0
                                   : p.k_rows + (int64_t)m * kvw + (head - p.Hq) * p.dh + i0;
@@ -276,6 +309,7 @@ __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restri
   const int i = blockIdx.x * 256 + threadIdx.x, quads = N / 4;
   const bool in = i < M * quads;
   const int m = in ? i / quads : 0, n = in ? (i - m * quads) * 4 : 0;
+  const ResidualIn q = residual_in(m, n, N, in, R, r_f32, gain);
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
   if (in) {
     f32x4 b[4];
@@ -290,7 +324,7 @@ __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restri
         if (k + u < splits) v += b[u];
     }
   }
-  residual_quad<1, 2>(v, m, n, N, in, R, r_f32, C, c_f32, gain, a, 0, ssq_out);
+  residual_quad<1, 2>(v, q, m, n, N, in, r_f32, C, c_f32, gain, a, 0, ssq_out);
 }
 
 // Router of an expert layer on the prepared rows a (blocks; the RMSNorm factor is applied to the logits), one workgroup per
@@ -354,6 +388,7 @@ __global__ void __launch_bounds__(256) few_combine_kernel(const float* __restric
   const int i = blockIdx.x * 256 + threadIdx.x, quads = N / 4;
   const bool in = i < M * quads;
   const int m = in ? i / quads : 0, n = in ? (i - m * quads) * 4 : 0;
+  const ResidualIn q = residual_in(m, n, N, in, R, 1, gain);
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
   if (in) {
     for (int j = 0; j < top_k; ++j) {
@@ -361,7 +396,7 @@ __global__ void __launch_bounds__(256) few_combine_kernel(const float* __restric
       v += *(const f32x4*)(y + ((int64_t)e * M + m) * N + n) * gates[m * top_k + j];
     }
   }
-  residual_quad<1, 2>(v, m, n, N, in, R, 1, C, c_f32, gain, a, a_rows, ssq_out);
+  residual_quad<1, 2>(v, q, m, n, N, in, 1, C, c_f32, gain, a, a_rows, ssq_out);
 }
 
 // The input norm of a call's first layer and the call's rotary table: workgroups 0 .. n_norm-1, and those behind them.
@@ -375,7 +410,7 @@ __global__ void __launch_bounds__(256) few_norm_rope_kernel(const void* h, int h
   const int i = blockIdx.x * 256 + threadIdx.x, quads = N / 4;
   const bool in = i < M * quads;
   const int m = in ? i / quads : 0, n = in ? (i - m * quads) * 4 : 0;
-  residual_quad<1, 2>(f32x4{0.f, 0.f, 0.f, 0.f}, m, n, N, in, h, h_f32, nullptr, 0, gain, a, a_rows, ssq_out);
+  residual_quad<1, 2>(f32x4{0.f, 0.f, 0.f, 0.f}, residual_in(m, n, N, in, h, h_f32, gain), m, n, N, in, h_f32, nullptr, 0, gain, a, a_rows, ssq_out);
 }
 
 template <int MT, int NT, int KW, int PF, int KS, int EP>
