@@ -100,3 +100,25 @@ def test_activations_in_rows_and_in_blocks_agree(B, d, Hq, Hkv, dh, F, E):
             kv_n, h_n = m.partial(x[r0:r0 + n].contiguous(), 0, 2, None, [1] * n)
             torch.cuda.synchronize()
             assert torch.equal(h[r0:r0 + n], h_n) and torch.equal(kv[:, :, r0:r0 + n], kv_n)
+
+
+# three to seven steps a wave, waves that differ by one: the loop and the steps behind it, one to four row tiles, against the
+# plain kernels
+@pytest.mark.parametrize("rows", [1, 9, 30, 46, 64])
+@pytest.mark.parametrize("d,F", [(1536, 1984), (2048, 2112), (2624, 3136)])
+def test_steps_behind_the_loop(B, rows, d, F):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(1, d, d // 64, 1, 64, F, 10000.0, 1e-5, "bf16")
+    x = G.to_dev(synth.hidden_states(shape, rows), shape)
+    with G.GpuModel(shape, rows) as m:
+        m.init_random(11)
+        kv, h = m.partial(x, 0, 1, None, [rows])
+        B.dsk_set_option("force_generic", 1)
+        try:
+            kv_ref, h_ref = m.partial(x, 0, 1, None, [rows])
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("force_generic", 0)
+    # two bf16 evaluations of one layer, each within 1e-2 of the exact one at this weight scale
+    assert O.max_rel_err(G.to_np(h), G.to_np(h_ref).astype(np.float64)) <= 2e-2
+    assert O.max_rel_err(G.to_np(kv[0]), G.to_np(kv_ref[0]).astype(np.float64)) <= 2e-2
