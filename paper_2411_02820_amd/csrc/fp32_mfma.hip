@@ -333,11 +333,12 @@ __global__ void __launch_bounds__(64 * NW) attn_fp32_kernel(const float* __restr
 #pragma unroll
         for (int c = 0; c < NC; ++c) vf[t][r][c] = vp[16 * c];
       }
+    // (All 32 keys, also where the chunk has 16 or fewer: with a branch around the second 16, 1024 keys took 37.8 us instead of
+    // 34.9 and 128 keys 6.3 instead of 5.9, heads of 64; 144 keys 6.4 instead of 6.8.)
     f32x4 s[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (t == 1 && j0 + 16 >= n_keys) break;  // (masked below)
 #pragma unroll
       for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -385,13 +386,11 @@ __global__ void __launch_bounds__(64 * NW) attn_fp32_kernel(const float* __restr
     }
     if (!by_key) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        if (t == 1 && j0 + 16 >= n_keys) break;
+      for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
           for (int r = 0; r < 4; ++r) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][r][c], s[t][r], o[c], 0, 0, 0);
-      }
     } else {
 #pragma unroll
       for (int t = 0; t < 2; ++t)
