@@ -498,7 +498,14 @@ hipError_t launch_attn_fp32(const AttnArgs& a, hipStream_t s) {
     tiles += (len + 15) / 16;
     if (keys > max_keys) max_keys = keys;
   }
-  // waves of a workgroup: a chunk of 32 keys each, four while that takes them one chunk (144 keys: 8.1 us with four, 6.8 with eight)
+  // Waves of a workgroup, a chunk of 32 keys each: four while that takes them one chunk.  Past that eight shorten the chain of
+  // chunks, which pays where it is what a launch takes: with heads of 128 always (four waves' registers leave one workgroup a
+  // compute unit, so eight are twice as many in flight), with heads of 64 while no compute unit gets a second workgroup
+  // (three of four waves fit there, one of eight).  Four -> eight waves, us:
+  //   heads of 64: 144 keys, 36 workgroups 7.9 -> 6.8, 252 8.7 -> 7.7, 288 9.7 -> 10.7, 2304 34.0 -> 57.9;  512 keys, 256 workgroups
+  //   13.8 -> 12.4;  1024 keys, 256 workgroups 22.9 -> 20.3, 512 34.9 -> 37.0
+  //   heads of 128: 144 keys, 36 workgroups 12.6 -> 10.9, 2304 94.9 -> 91.1;  1024 keys, 512 workgroups 78.0 -> 66.8
+  const bool eight = max_keys > 128 && (a.dh == 128 || tiles * a.Hq <= 256);
   auto launch = [&](auto kern, int nw) -> hipError_t {
     const int lds = nw * a.dh / 16 * 1024;
     if (lds > 48 << 10) {
@@ -509,6 +516,6 @@ hipError_t launch_attn_fp32(const AttnArgs& a, hipStream_t s) {
                        (const float*)a.v_rows, (float*)a.out, a.q_cu, a.p_cu, a.n_seqs, a.own_row0, a.Hq, a.Hkv);
     return hipGetLastError();
   };
-  if (max_keys > 128) return a.dh == 64 ? launch(attn_fp32_kernel<64, 8>, 8) : launch(attn_fp32_kernel<128, 8>, 8);
+  if (eight) return a.dh == 64 ? launch(attn_fp32_kernel<64, 8>, 8) : launch(attn_fp32_kernel<128, 8>, 8);
   return a.dh == 64 ? launch(attn_fp32_kernel<64, 4>, 4) : launch(attn_fp32_kernel<128, 4>, 4);
 }

@@ -47,6 +47,18 @@ def _attention(B, q, k, v, lens, plens, own_row0, Hq, Hkv, dh):
 @pytest.mark.parametrize("dh", [64, 128, 96])
 @pytest.mark.parametrize("lens,plens", [([1], None), ([17, 1, 40], None), ([200], None), ([5, 18], [33, 150])])
 def test_attention_fp32(B, lens, plens, dh):
+    _attention_against_float64(B, lens, plens, dh)
+
+
+# on both sides of the lines between four and eight waves: 128 keys; 256 workgroups (heads of 64), 4 heads a tile of 16 queries
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("lens,plens", [([128], None), ([129], None), ([16] * 64, [113] * 64), ([16] * 64 + [1], [113] * 65),
+                                        ([3, 20], [300, 1])])
+def test_attention_fp32_four_and_eight_waves(B, lens, plens, dh):
+    _attention_against_float64(B, lens, plens, dh)
+
+
+def _attention_against_float64(B, lens, plens, dh):
     Hq, Hkv = 4, 2
     n, n_pre = sum(lens), sum(plens or [])
     own0 = n_pre + 3 if plens else 0
@@ -62,7 +74,15 @@ def test_attention_fp32(B, lens, plens, dh):
 
 
 def test_attention_fp32_rows_that_are_not_finite_reach_later_queries_only(B):
-    Hq, Hkv, dh, n, bad = 4, 2, 64, 50, 37
+    _rows_that_are_not_finite(B, 50, 37)
+
+
+def test_attention_fp32_rows_that_are_not_finite_eight_waves(B):
+    _rows_that_are_not_finite(B, 150, 133)
+
+
+def _rows_that_are_not_finite(B, n, bad):
+    Hq, Hkv, dh = 4, 2, 64
     q = synth.normal(n * Hq * dh, 33, 0, 1.0).reshape(n, Hq, dh)
     k, v = (synth.normal(n * Hkv * dh, 33, j, 1.0).reshape(n, Hkv, dh) for j in (1, 2))
     clean = _attention(B, q, k, v, [n], None, 0, Hq, Hkv, dh)
