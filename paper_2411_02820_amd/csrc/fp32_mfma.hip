@@ -148,10 +148,13 @@ __global__ void __launch_bounds__(64 * WM * WN * KW) gemm_fp32_kernel(Fp32Gemm p
 #pragma unroll
   for (int s = 0; s < PF; ++s) load(s, kw + s * KW);
   constexpr int UP = 8 * CT;  // columns of a unit on either side
-  __shared__ float2 pairs[EP == EP_ROPE && KW > 1 ? WM * WN : 1][TM][U][16][UP];
-  if (EP == EP_ROPE && KW > 1) {
-    // The rotary pairs of the tile, while the operands arrive: read behind the reduction they cost a round trip to memory,
-    // and the table in a launch of its own 3.5 us a call.  The workgroups of head 0 write it for the layers that follow.
+  // The rotary pairs of a small tile, while the operands arrive: read behind the reduction they cost a round trip to memory,
+  // and the table in a launch of its own 3.5 us a call.  The workgroups of head 0 write it for the layers that follow.  Not on
+  // the larger tiles: there the LDS for the pairs and the registers of the angles take one workgroup in four from a compute
+  // unit, in every layer (QKV over 1024 rows, 1536 columns of 512: 50.5 us, with both 60.5; 500 rows 18.2 and 20.4).
+  constexpr bool PAIRS = EP == EP_ROPE && TM * U == 1;
+  __shared__ float2 pairs[PAIRS ? WM * WN : 1][TM][U][16][UP];
+  if (PAIRS) {
     const int half = p.dh >> 1, per = half / UP, n_rot = (p.Hq + p.Hkv) * per;
     for (int q = kw * 64 + lane; q < TM * U * 16 * UP; q += KW * 64) {
       const int i = q / (U * 16 * UP), u = q / (16 * UP) % U, row = q / UP % 16, m = m0 + 16 * i + row, k = (u0 + u) % per * UP + q % UP;
@@ -236,7 +239,10 @@ __global__ void __launch_bounds__(64 * WM * WN * KW) gemm_fp32_kernel(Fp32Gemm p
         if (NORM) s += red_ss[wt][k][i * 16 + r16];
       }
       const float rs = NORM ? 1.0f / sqrtf(s * inv_k + p.eps) : 1.0f;
-      unit_store<EP, CT>(p, m, u0 + u, 4 * g, x0 * rs, x1 * rs, EP == EP_ROPE ? &pairs[wt][i][u][r16][4 * g] : nullptr);
+      const float2* cs = PAIRS           ? &pairs[wt][i][u][r16][4 * g]
+                         : EP == EP_ROPE ? p.cs + (int64_t)m * (p.dh >> 1) + (u0 + u) * UP % (p.dh >> 1) + 4 * g
+                                         : nullptr;
+      unit_store<EP, CT>(p, m, u0 + u, 4 * g, x0 * rs, x1 * rs, cs);
     }
   }
 }
@@ -460,11 +466,11 @@ hipError_t launch_gemm_fp32(const void* A, int64_t lda, const void* W, int64_t l
   return launch_fp32<false, EP_PLAIN>(p, s);
 }
 
-// Whether QKV over M rows runs on a tiling that can fill the rotary table as well.
+// Whether QKV over M rows runs on the tiling that can fill the rotary table as well.
 bool gemm_fp32_takes_rope(int M, int Hq, int Hkv, int dh) {
   Fp32Gemm p = {};
   p.M = M; p.units = ((Hq + 2 * Hkv) * dh + 31) / 32;
-  return fp32_tiling(p) != FP32_LARGE;
+  return fp32_tiling(p) == FP32_SMALL;
 }
 
 // job (gemm_fp32_takes_rope): fill the rotary table cs on the way
