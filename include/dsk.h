@@ -357,7 +357,8 @@ DSK_API int dsk_gemm_plan(int M, int N, int K, int may_split, int32_t* plan);
 
 /* Counters since the last reset: "e_cache_chunks" (row chunks of host-resident E caches that a first recomputed
  * layer followed as they arrived), "splice_launches" (launches that copied reused layers from a device-resident cache, a run
- * of layers each), "gemm_mfma_launches", "gemm_generic_launches", "attn_mfma_launches",
+ * of layers each), "gemm_mfma_launches", "gemm_direct_launches" (launches of 256-row tiles that take the weights straight to
+ * registers), "gemm_generic_launches", "attn_mfma_launches",
  * "attn_generic_launches" (the two "generic" ones count fp32 work, on whichever kernel), "attn_few_query_launches"
  * (tensor-core attention launches on the kernel for few queries, whose workgroups take the q heads of a kv group together),
  * "attn_key_split_launches" (tensor-core attention launches that split the keys over workgroups) and, of those,

@@ -289,7 +289,7 @@ int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, 
         HIP_TRY(g_stats.gemm.begin(s, &timed));
       }
       const hipError_t e = launch_gemm_mfma_grouped(A, lda, a_rows, a_row, W, ldw, m->w_blocks, w_stride, C, ldc, N, K, epi, m->moe_tab,
-                                                    tile_m, tile_rows, s);
+                                                    tile_m, tile_rows, (int64_t)n * k / E, s);
       if (e != hipSuccess && timed) g_stats.gemm.abandon();
       HIP_TRY(e);
       ++g_stats.gemm_mfma;
@@ -1180,6 +1180,7 @@ int dsk_set_option(const char* name, int value) {
     g_stats.gemm.n = g_stats.attn.n = 0;
     g_stats.gemm.flops = g_stats.attn.flops = 0.0;
     attn_mfma_counts(nullptr, nullptr, nullptr, 1);
+    gemm_mfma_direct_launches(1);
   } else return DSK_EINVAL;
   return DSK_OK;
 }
@@ -1193,6 +1194,7 @@ int dsk_gemm_plan(int M, int N, int K, int may_split, int32_t* plan) {
 int dsk_get_stat(const char* name, double* value) {
   if (!name || !value) return DSK_EINVAL;
   if (!strcmp(name, "gemm_mfma_launches")) *value = (double)g_stats.gemm_mfma.load();
+  else if (!strcmp(name, "gemm_direct_launches")) *value = (double)gemm_mfma_direct_launches(0);
   else if (!strcmp(name, "gemm_generic_launches")) *value = (double)g_stats.gemm_generic.load();
   else if (!strcmp(name, "attn_mfma_launches")) *value = (double)g_stats.attn_mfma.load();
   else if (!strcmp(name, "attn_generic_launches")) *value = (double)g_stats.attn_generic.load();

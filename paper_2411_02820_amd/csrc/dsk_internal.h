@@ -263,10 +263,11 @@ hipError_t launch_moe_combine(const float* y, const float* h_mid, const float* g
                               hipStream_t s);
 hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw,
                                     int w_blocks, int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
-                                    const void* tile_tab, int tile_m, int tile_rows, hipStream_t s);
+                                    const void* tile_tab, int tile_m, int tile_rows, int64_t rows_per_expert, hipStream_t s);
 
 // tuning knobs (dsk_set_option)
 void gemm_mfma_set_variant(int v);
+int64_t gemm_mfma_direct_launches(int reset);
 void attn_mfma_counts(int64_t* split, int64_t* split_64, int64_t* few, int reset);
 bool gemm_mfma_uses_prefill_tile(int M, int N);
 void gemm_mfma_plan(int M, int N, int K, int may_split, int32_t* plan);  // dsk_gemm_plan

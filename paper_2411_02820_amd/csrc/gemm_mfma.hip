@@ -28,6 +28,7 @@
 // order (deterministic), applies the residual and rounds.
 #include <math.h>
 
+#include <atomic>
 #include <type_traits>
 
 #include "dsk_internal.h"
@@ -1012,10 +1013,24 @@ hipError_t launch(const void* A, int64_t lda, const void* W, int64_t ldw, int w_
                   : launch_form<BM, BN, WAVES_M, WAVES_N, PARTIAL, SCHED, false>(A, lda, W, ldw, C, ldc, R, ldr, P, M, N, K, epi, splits, kt_per_split, s);
 }
 
-// Unsplit 256-row tiles take W in blocks straight to registers (DIRECT), from two k-tiles on (its loop runs in pairs).
-// Lower tiles and split contractions do not: half as many MFMAs share a fragment of W, or few k-tiles share the start (O over
-// 1536 rows, 128-row tiles, 62.7 -> 64.9 us; down over 333 rows, 192-row tiles in eight splits, 54.4 -> 55.1 us).
-bool w_direct(int K) { return K >= 2 * BK; }
+// Whether a launch of unsplit 256-row tiles takes W in blocks straight to registers (DIRECT); rows: those that share W, of an
+// expert the average.  Some 180 launches, widths of 1024 to 8192 and 512 to 16384 rows, both forms in turn; time of DIRECT over
+// that of the other form:
+//   QKV, O and down: contractions of 4096 and longer 0.95 to 1.00 (2048 rows, QKV 4096 wide 93.3 -> 90.9 us; 8192 rows, down 14336
+//   long 662 -> 638), of 3584 0.98 to 1.00, of 3072 and 2048 0.97 to 1.01 (layers 3072 wide over 4096 and 8192 rows 1.01), of 1024 1.00
+//   to 1.01.
+//   gate/up, whose W is the longest stream for its rows: 4096 wide 1.02 at 1536 rows, 1.01 at 4096, 0.99 at 8192, 0.985 at 16384;
+//   5120 wide 1.02 at 1024, 1.00 at 6144, 0.986 at 7000; 8192 wide 1.01 at 1024, 0.99 at 2048, 0.97 at 8192; 2048 wide 1.01 to 1.03.
+//   Experts: one row tile each 1.02 to 1.06 (W comes once, from HBM, and wants the longer lead); more than one: down 0.96 to 1.02,
+//   mean 0.98, gate/up 0.97 to 1.02, mean 1.00.
+// Lower tiles and split contractions keep the other form: half as many MFMAs share a fragment of W, or few k-tiles share the start (O
+// over 1536 rows, 128-row tiles, 62.7 -> 64.9 us; down over 333 rows, 192-row tiles in eight splits, 54.4 -> 55.1 us; unsplit
+// 192-row tiles were not measured).  (The loop of DIRECT wants two k-tiles at least.)
+std::atomic<int64_t> g_direct_launches{0};
+bool w_direct(int64_t rows, int K, bool gate_up) {
+  if (gate_up) return K >= 8192 ? rows >= 1536 : K >= 3584 && rows * K >= (int64_t)1 << 25;
+  return K >= 3584 && rows > 256;
+}
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool DIRECT = false>
 hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R, int64_t ldr,
@@ -1032,6 +1047,7 @@ hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw,
   DSK_LAUNCH_TIMED(kern, dim3(tiles_m * tiles_n, splits), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
                    (const bf16_t*)W, ldw, C, ldc, R, ldr, M, N, K, epi, tiles_m, tiles_n, kt_per_split, (const int4*)nullptr,
                    (int64_t)0, (const int32_t*)nullptr, 0, RopeOut{});
+  g_direct_launches += DIRECT;
   return hipGetLastError();
 }
 
@@ -1049,6 +1065,7 @@ hipError_t launch16_rope(const void* A, const void* W, void* qkv, const RopeOut&
   DSK_LAUNCH_TIMED(kern, dim3(tiles_m * tiles_n), dim3(512), lds, s, (const bf16_t*)A, (int64_t)K, (const bf16_t*)W, (int64_t)K, qkv,
                    (int64_t)N, (const void*)nullptr, (int64_t)0, M, N, K, (int)EPI_STORE, tiles_m, tiles_n, K / BK,
                    (const int4*)nullptr, (int64_t)0, (const int32_t*)nullptr, 0, ro);
+  g_direct_launches += DIRECT;
   return hipGetLastError();
 }
 
@@ -1058,7 +1075,7 @@ hipError_t launch16(int bm, const void* A, int64_t lda, const void* W, int64_t l
 #define DSK_FORM(BM)                                                                                                      \
   (w_blocks ? launch16_form<BM, 256, 2, 4, true>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, splits, kt_per_split, s)   \
             : launch16_form<BM, 256, 2, 4, false>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, splits, kt_per_split, s))
-  if (bm == 256 && w_blocks && splits == 1 && w_direct(K))
+  if (bm == 256 && w_blocks && splits == 1 && w_direct(M, K, epi & EPI_SWIGLU))
     return launch16_form<256, 256, 2, 4, true, true>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, 1, kt_per_split, s);
   return bm == 128 ? DSK_FORM(128) : bm == 192 ? DSK_FORM(192) : DSK_FORM(256);
 #undef DSK_FORM
@@ -1080,6 +1097,7 @@ hipError_t launch16_grouped(const void* A, int64_t lda, const int32_t* a_row, in
   DSK_LAUNCH_TIMED(kern, dim3(tile_rows * tiles_n), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
                    (const bf16_t*)W, ldw, C, ldc, (const void*)nullptr, (int64_t)0, 0, N, K, epi, tile_rows, tiles_n,
                    K / BK, tile_tab, w_group_stride, a_row, a_rows, RopeOut{});
+  g_direct_launches += DIRECT;
   return hipGetLastError();
 }
 
@@ -1148,6 +1166,7 @@ GemmPlan gemm_plan(int M, int N, int K, bool may_split) {
 }  // namespace
 
 void gemm_mfma_set_variant(int v) { g_variant = v; }
+int64_t gemm_mfma_direct_launches(int reset) { return reset ? g_direct_launches.exchange(0) : g_direct_launches.load(); }
 
 // How a projection over few token rows (M <= 64) is split: 64x64 tiles and about 768 workgroups; a very wide N
 // (the gate/up projection) has enough 64x128 tiles to fill the chip with few splits, which halves the share of the
@@ -1266,15 +1285,15 @@ int moe_tile_rows_for(int64_t n_rows, int E) {
 // epi: EPI_SWIGLU (C bf16 [slots, N/2]) or EPI_C_F32 / EPI_STORE (C [slots, N]); no residual.
 hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw,
                                     int w_blocks, int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
-                                    const void* tile_tab, int tile_m, int tile_rows, hipStream_t s) {
+                                    const void* tile_tab, int tile_m, int tile_rows, int64_t rows_per_expert, hipStream_t s) {
   if (tile_rows <= 0) return hipSuccess;
   // (a model the tensor-core path takes has its weights in blocks)
   if (!w_blocks || K < BK || K % BK || N % 64 || (lda & 7) || (ldw & 7) || (ldc & 3) || (epi & EPI_RESIDUAL)) return hipErrorNotSupported;
   if (a_rows * lda * 2 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 2 >= ((int64_t)1 << 32)) return hipErrorNotSupported;
   auto f = tile_m == 128   ? launch16_grouped<128, 256, 2, 4, false>
            : tile_m == 192 ? launch16_grouped<192, 256, 2, 4, false>
-           : w_direct(K)   ? launch16_grouped<256, 256, 2, 4, true>
-                           : launch16_grouped<256, 256, 2, 4, false>;
+           : w_direct(rows_per_expert, K, false) ? launch16_grouped<256, 256, 2, 4, true>
+                                               : launch16_grouped<256, 256, 2, 4, false>;
   return f(A, lda, a_row, (int)a_rows, W, ldw, w_group_stride, C, ldc, N, K, epi, (const int4*)tile_tab, tile_rows, s);
 }
 
@@ -1312,7 +1331,10 @@ hipError_t launch_gemm_rope(const void* A, const void* W, void* qkv, const float
   const GemmPlan p = gemm_plan(M, N, K, false);
   auto run = [&](int bm, int64_t r0, int64_t rows) {
     const RopeOut ro = {cs + r0 * 64, (bf16_t*)k_rows + r0 * Hkv * 128, (bf16_t*)v_rows + r0 * Hkv * 128, Hq, Hkv};
-    auto f = bm == 128 ? launch16_rope<128, false> : bm == 192 ? launch16_rope<192, false> : w_direct(K) ? launch16_rope<256, true> : launch16_rope<256, false>;
+    auto f = bm == 128   ? launch16_rope<128, false>
+             : bm == 192 ? launch16_rope<192, false>
+             : w_direct(rows, K, false) ? launch16_rope<256, true>
+                                            : launch16_rope<256, false>;
     return f((const bf16_t*)A + r0 * K, W, (bf16_t*)qkv + r0 * N, ro, (int)rows, K, s);
   };
   if (p.head_rows == 0) return run(p.bm, 0, M);

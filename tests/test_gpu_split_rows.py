@@ -184,18 +184,21 @@ def test_rope_in_the_projection(B, d, Hq, lens, plan):
         assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2 ** -7
 
 
-# unsplit 256-row tiles with W straight to registers: one to five and 17 k-tiles (one keeps the other form), an odd and an even
-# number of them, last column tiles that end early, rows that end inside a tile; QKV with the rotation, O with residual,
-# gate/up with SwiGLU, down.  Against the 128-row tiles of the other kernel.
+# unsplit 256-row tiles of short contractions: one to five and 17 k-tiles, last column tiles that end early, rows that end inside a
+# tile; QKV with the rotation, O with residual, gate/up with SwiGLU, down, with weights with which a k-tile left out of any
+# of them shows in the state (a tenth of it and more).  Against the 128-row tiles of the other kernel.
 @pytest.mark.parametrize("d,Hq,F,n", [(64, 3, 128, 18030), (128, 3, 320, 18030), (192, 5, 192, 13001), (320, 3, 1088, 18030)])
-def test_weights_straight_to_registers(B, d, Hq, F, n):
+def test_unsplit_256_row_tiles(B, d, Hq, F, n):
     from tests import gpu_util as G
-    assert B.dsk_gemm_plan(n, (Hq + 2) * 128, d)[:2] == (256, 1) and B.dsk_gemm_plan(n, 2 * F, d, False)[1] == 1
+    assert B.dsk_gemm_plan(n, (Hq + 2) * 128, d)[:2] == (256, 1)
     shape = synth.ModelShape(1, d, Hq, 1, 128, F, 10000.0, 1e-5, "bf16")
     lens = [250] * (n // 250) + [n % 250]
     x = G.to_dev(synth.hidden_states(shape, n), shape)
     with G.GpuModel(shape, n) as m:
-        m.init_random(19)
+        m.init_random(19, std=0.1)
+        for t, rows in ((B.DSK_WQ, Hq * 128), (B.DSK_WK, 128)):
+            w = synth.normal(rows * d, 19, t, 0.02).reshape(rows, d)
+            B.dsk_model_set_tensor(m.handle, 0, t, G.to_dev(w, shape))
         B.dsk_set_option("gemm_tiling", 1)   # 256-row tiles for every projection; the rotation is a pass of its own
         try:
             forced = m.partial(x, 0, 1, None, lens)
@@ -206,16 +209,91 @@ def test_weights_straight_to_registers(B, d, Hq, F, n):
             B.dsk_set_option("gemm_tiling", 0)
         planned = m.partial(x, 0, 1, None, lens)
         torch.cuda.synchronize()
-    # as above: up to two roundings of 2^-9 for each of a pair's elements, one for v and the state
+    # as above: up to two roundings of 2^-9 for each of a pair's elements, one for v and the state.  The roundings of q and k reach the
+    # state as changes of a score: with wq and wk at 0.02 a score is the mean of 128 products of at most 0.36 x 0.36 in the mean
+    # square, times sqrt(128), so 1.5 in the mean square at most and its error 1.5 * 2^-8 / sqrt(128), a tenth of a rounding (at 0.1
+    # scores are 25 times that); those in front of down as a mean over F columns.
     for got in (forced, planned):
         for a, b in zip(got, ref):
             assert O.max_rel_err(G.to_np(a), G.to_np(b).astype(np.float64)) <= 2 ** -7
 
 
-# ... over experts (every token chooses both, so no choice hangs on a rounding), one, three and five k-tiles, an expert's tiles
-# in one scheduling group and in three, against the plain kernels
-@pytest.mark.parametrize("d,F,n", [(64, 192, 601), (320, 128, 601), (192, 320, 601), (128, 128, 7001)])
+def _count_direct(B, m, x, lens):
+    B.dsk_set_option("reset_stats", 0)
+    out = m.partial(x[:sum(lens)].contiguous(), 0, 1, None, lens)
+    torch.cuda.synchronize()
+    return (*out, B.dsk_get_stat("gemm_direct_launches"))
+
+
+# Unsplit 256-row tiles with W straight to registers add in the order of every other tile of that kernel: the rows of a call that
+# takes them are those of a call over fewer sequences that does not, bit for bit, with weights that make the MLP the larger part
+# of the state.  On both sides of the rule's lines: QKV, O and down past 256 rows (contractions of 57, 58 and 59 k-tiles, of 64,
+# 56 and 56), gate/up from 1536 rows on at 8192 and from 2^25 elements on below (128, 129, 65 k-tiles, a last column tile that
+# ends early); no launch at a contraction of 3520, nor for gate/up over the 512 rows of an 8B layer.
+@pytest.mark.parametrize("d,Hq,F,n,few,unit,launches", [
+    (3648, 29, 3776, 300, 256, 64, (3, 0)), (4096, 28, 3584, 300, 256, 64, (3, 0)), (3520, 5, 64, 300, 256, 64, (0, 0)),
+    (8192, 3, 192, 1536, 1500, 100, (2, 1)), (8256, 3, 320, 1536, 1500, 100, (2, 1)), (4160, 3, 192, 8100, 8000, 100, (2, 1)),
+    (4096, 3, 64, 512, 500, 100, (1, 1))])
+def test_weights_straight_to_registers(B, d, Hq, F, n, few, unit, launches):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(1, d, Hq, 1, 128, F, 10000.0, 1e-5, "bf16")
+    lens = [unit] * (n // unit) + [n % unit] * (n % unit > 0)
+    assert few % unit == 0
+    x = torch.randn((n, d), generator=torch.Generator(device="cuda").manual_seed(19), device="cuda").to(torch.bfloat16)
+    with G.GpuModel(shape, n) as m:
+        m.init_random(19, std=0.1)
+        B.dsk_set_option("gemm_tiling", 1)   # 256-row tiles for every projection; the rotation is a pass of its own
+        try:
+            kv, h, got = _count_direct(B, m, x, lens)
+            kv_few, h_few, got_few = _count_direct(B, m, x, [unit] * (few // unit))
+        finally:
+            B.dsk_set_option("gemm_tiling", 0)
+    assert (got, got_few) == launches and torch.isfinite(h).all()
+    assert torch.equal(h[:few], h_few) and torch.equal(kv[:, :, :few], kv_few)
+
+
+# ... and QKV with the rotation, as planned: 57 and 64 k-tiles of 256-row tiles, against 192-row tiles of the other form
+@pytest.mark.parametrize("d,n,few,launches", [(3648, 4000, 2500, (2, 0)), (4096, 4000, 2500, (2, 0))])
+def test_rotation_with_weights_straight_to_registers(B, d, n, few, launches):
+    from tests import gpu_util as G
+    Hq, F = 28, 128
+    assert B.dsk_gemm_plan(n, (Hq + 2) * 128, d, False) == (256, 1, 0, 0) and B.dsk_gemm_plan(few, (Hq + 2) * 128, d, False)[0] == 192
+    assert B.dsk_gemm_plan(n, d, Hq * 128)[1] == B.dsk_gemm_plan(few, d, Hq * 128)[1] == 1   # nor is O split
+    shape = synth.ModelShape(1, d, Hq, 1, 128, F, 10000.0, 1e-5, "bf16")
+    x = torch.randn((n, d), generator=torch.Generator(device="cuda").manual_seed(20), device="cuda").to(torch.bfloat16)
+    with G.GpuModel(shape, n) as m:
+        m.init_random(20, std=0.1)
+        kv, h, got = _count_direct(B, m, x, [100] * (n // 100))
+        kv_few, h_few, got_few = _count_direct(B, m, x, [100] * (few // 100))
+    assert (got, got_few) == launches and torch.isfinite(h).all()
+    assert torch.equal(h[:few], h_few) and torch.equal(kv[:, :, :few], kv_few)
+
+
+# ... and over experts (every token chooses both) of more than 256 rows in the mean: gate/up of 56 and 65 k-tiles, down of 65 and
+# 56, rows of another expert behind the last tile of the first, one scheduling group an expert and three
+@pytest.mark.parametrize("d,F,n", [(3584, 4160, 300), (4160, 3584, 300), (3584, 3584, 7040)])
 def test_expert_weights_straight_to_registers(B, d, F, n):
+    from tests import gpu_util as G
+    few = 256
+    shape = synth.ModelShape(1, d, 2, 1, 64, F, 10000.0, 1e-5, "bf16", 2, 2)
+    lens = [64] * (n // 64) + [n % 64] * (n % 64 > 0)
+    x = torch.randn((n, d), generator=torch.Generator(device="cuda").manual_seed(23), device="cuda").to(torch.bfloat16)
+    with G.GpuModel(shape, n) as m:
+        m.init_random(23, std=0.1)
+        B.dsk_set_option("gemm_tiling", 1)   # (of the other projections)
+        try:
+            kv, h, got = _count_direct(B, m, x, lens)
+            kv_few, h_few, got_few = _count_direct(B, m, x, [64] * (few // 64))
+        finally:
+            B.dsk_set_option("gemm_tiling", 0)
+    assert (got, got_few) == (3, 0) and torch.isfinite(h).all()
+    assert torch.equal(h[:few], h_few) and torch.equal(kv[:, :, :few], kv_few)
+
+
+# experts in tiles of 256 rows with W through LDS: one, three and five k-tiles, an expert's tiles in one scheduling group and in
+# three, against the plain kernels
+@pytest.mark.parametrize("d,F,n", [(64, 192, 601), (320, 128, 601), (192, 320, 601), (128, 128, 7001)])
+def test_expert_tiles_of_256_rows(B, d, F, n):
     from tests import gpu_util as G
     shape = synth.ModelShape(1, d, 2, 1, 64, F, 10000.0, 1e-5, "bf16", 2, 2)
     x = G.to_dev(synth.hidden_states(shape, n), shape)
