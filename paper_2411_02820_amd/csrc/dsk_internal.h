@@ -255,7 +255,9 @@ hipError_t launch_moe_place(const int32_t* experts, int32_t* slot_of, int32_t* s
                             int E, int tile_m, int tile_rows_max, hipStream_t s);
 // rows of the grouped projections' tile table for n_rows rows over E experts in tiles of tile_m (every expert may end in a
 // partial tile)
-constexpr int MOE_GROUP_MOST = 12, MOE_GROUP_SHIFT = 20;  // tiles of a scheduling group; place of their number in the tile table
+// Tiles of a scheduling group, at most (a Mixtral layer over 4096, 6000, 8192 tokens, us: four 3055, 4095, 5988; eight 3015, 3987, 5897;
+// twelve 3007, 3974, 5915; twenty-four 3004, 3987, 5906: from eight on it does not matter), and the place of their number in the table.
+constexpr int MOE_GROUP_MOST = 12, MOE_GROUP_SHIFT = 20;
 int moe_tile_rows_for(int64_t n_rows, int E);
 inline int moe_tile_table_rows(int64_t n_rows, int E, int tile_m) { return (int)((n_rows + tile_m - 1) / tile_m) + E; }
 hipError_t launch_moe_combine(const float* y, const float* h_mid, const float* gates, const int32_t* experts,

@@ -203,13 +203,11 @@ __global__ void __launch_bounds__(PLACE_T) moe_place_kernel(const int32_t* __res
   }
   const int mine = hist[e];
   const int my_tiles = (mine + tile_m - 1) / tile_m;
-  // scheduling groups: an expert's tiles in as few equal ones as the most allows
-  const int n_groups = (my_tiles + MOE_GROUP_MOST - 1) / MOE_GROUP_MOST;
-  auto group_begin = [&](int g) { return (int)((int64_t)g * my_tiles / n_groups); };
+  // scheduling groups: an expert's tiles in as few as the most allows, the first ones longer by a tile where they are not equal
+  const int n_groups = max((my_tiles + MOE_GROUP_MOST - 1) / MOE_GROUP_MOST, 1), least = my_tiles / n_groups;
+  const int longer = (my_tiles - n_groups * least) * (least + 1);  // tiles of the longer ones
   for (int r = tid; r < my_tiles; r += PLACE_T) {
-    int g = (int)((int64_t)r * n_groups / my_tiles);
-    if (r >= group_begin(g + 1)) ++g;
-    const int g0 = group_begin(g), size = group_begin(g + 1) - g0;
+    const int size = r < longer ? least + 1 : least, from = r < longer ? 0 : longer, g0 = from + (r - from) / size * size;
     if (first_tile + r < tile_rows_max)
       tile_tab[first_tile + r] = make_int4(e, first + r * tile_m, first + mine, (first_tile + g0) | size << MOE_GROUP_SHIFT);
   }
