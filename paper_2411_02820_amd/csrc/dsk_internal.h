@@ -75,7 +75,7 @@ struct dsk_model {
   double* theta;    // [dh/2]         rope_base^(-2i/dh)
   void* vt;         // [Hkv*dh, ldvt] transposed V of the layer in flight (bf16 MFMA attention)
   int64_t ldvt;     // max_kv_rows rounded up to 64
-  float* ssq;       // [d/16, 64] sums of squares of the few-row pass (RMSNorm split in two)
+  float* ssq;       // sums of squares of the few-row pass (RMSNorm split in two): [d/16][64], up to eight rows [rows][d/16]
   void* gemm_ws;    // fp32 partial tiles of the K-split small-M GEMM
   int64_t gemm_ws_bytes;
   void* split_ws;   // the same for more than 64 rows: gu where nothing else uses it there, else gemm_ws; large enough for
@@ -149,16 +149,17 @@ hipError_t launch_gemm_rope(const void* A, const void* W, void* qkv, const float
 hipError_t launch_gemm_split_norm(const void* A, const void* W, int w_blocks, float* h, const void* R, int r_f32, const void* g, void* xn,
                                   float eps, int M, int d, int K, void* ws, int64_t ws_bytes, hipStream_t s);
 // Few token rows (M <= 64, bf16, few_rows.hip): weights and activations in blocks, the step that follows a projection (and
-// the RMSNorm in front of it) done by the projection.  a = bf16(h * gain) in blocks, ssq [d/16][64] its sums of squares.
+// the RMSNorm in front of it) done by the projection.  a = bf16(h * gain) and ssq [d/16][64] its sums of squares; up to
+// eight rows (few_rows_row_major) every activation in rows instead of blocks, and ssq [M][d/16].
 bool few_rows_supported(int M, int d, int F, int Hq, int Hkv, int dh);
-bool few_rows_row_major(int M);  // whether its activations stand in rows instead of blocks
+bool few_rows_row_major(int M);
 int64_t few_rows_workspace_bytes(int d, int K_max);
 // rope: also fills the rotary table (may be null)
 hipError_t launch_few_norm(const void* h, int h_f32, const void* gain, void* a, float* ssq, int M, int d, const RopeJob* rope,
                            hipStream_t s);
 hipError_t launch_few_qkv(const void* a, const float* ssq, float eps, const void* W, void* qkv, int64_t ldq, const float2* cs,
                           void* k_rows, void* v_rows, int M, int d, int Hq, int Hkv, int dh, hipStream_t s);
-// act (blocks, [M, N/2]) = silu(gate) * up
+// act [M, N/2] (laid out as a) = silu(gate) * up
 hipError_t launch_few_swiglu(const void* a, const float* ssq, float eps, const void* W, void* act, int M, int N, int K,
                              hipStream_t s);
 // C (row-major) = x W^T + R; with gain: a and ssq for the next projection

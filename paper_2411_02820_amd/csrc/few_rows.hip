@@ -36,8 +36,8 @@ struct StreamArgs {
   const bf16_t* X;  // blocks, rows up to a multiple of 16; or rows (x_rows)
   const bf16_t* W;  // blocks
   int M, N, K, x_rows;
-  const float* ssq; float eps;  // EP_ROPE, EP_SWIGLU: row factor of the RMSNorm in front, from [K/16][64] sums of squares
-  bf16_t* out;                  // EP_ROPE: q rows, stride ldq; EP_SWIGLU: blocks [M, N/2]; EP_RES: blocks a = h * gain
+  const float* ssq; float eps;  // EP_ROPE, EP_SWIGLU: row factor of the RMSNorm in front, from sums of squares (ssq_at)
+  bf16_t* out;                  // EP_ROPE: q rows, stride ldq; EP_SWIGLU: [M, N/2], EP_RES: a = h * gain, both in blocks or rows as X
   int64_t ldq;
   const float2* cs; bf16_t* k_rows; bf16_t* v_rows; int Hq, Hkv, dh;
   const void* R; int r_f32; void* C; int c_f32;         // EP_RES: C = sum + R, row-major
@@ -226,7 +226,7 @@ __global__ void __launch_bounds__(64 * KW, 1) stream_kernel(StreamArgs p) {
   }
   // Where a load is under a condition the compiler counts on the path without it, and waits at a step's first operands for
   // nearly all that is in flight; the same where it mixes the loads of two steps.  So the loop has no conditions, the last
-  // 2 * PF - 1 steps come behind it, and no load crosses into another step's.
+  // steps, 2 * PF - 1 at most, come behind it, and no load crosses into another step's.
   // (Four 8B layers, 64 rows 545 -> 536 us, one row 357.6 -> 355.6; a Mixtral layer over 64 rows 582 -> 575.)
   auto step = [&](int s) {
 #pragma unroll
@@ -342,7 +342,7 @@ __global__ void __launch_bounds__(256) few_residual_kernel(const float* __restri
   residual_quad<1, 2>(v, q, m, n, N, in, r_f32, C, c_f32, gain, a, 0, ssq_out);
 }
 
-// Router of an expert layer on the prepared rows a (blocks; the RMSNorm factor is applied to the logits), one workgroup per
+// Router of an expert layer on the prepared rows a (blocks or rows; the RMSNorm factor is applied to the logits), one workgroup per
 // token: eight experts at a time, every thread eight columns of each, sums over the workgroup in a fixed order.  Same
 // rules as the router over rows (moe.hip): fp32 logits, equal ones to the lower expert, NaN last.
 __global__ void __launch_bounds__(256) few_route_kernel(const bf16_t* __restrict__ a, const float* __restrict__ ssq, float eps,
@@ -545,8 +545,8 @@ hipError_t launch_few_route(const void* a, const float* ssq, float eps, const vo
 
 // The expert MLPs over all rows (a few rows hit most experts, and what it costs is the weights): one launch per projection
 // over every expert that some token has chosen (Mixtral width, 64 rows: 407 + 176 us for 2.8 GB; expert by expert with a
-// reduction behind each, 32 launches, 730 us; one row streams two experts of the eight).  act: [E][rows up to 16][F] in
-// blocks; y: [E][M][d].
+// reduction behind each, 32 launches, 730 us; one row streams two experts of the eight).  act: [E][rows up to 16][F],
+// blocks or rows (few_rows_row_major); y: [E][M][d].
 hipError_t launch_few_experts(const void* a, const float* ssq, float eps, const void* wgu, const void* wd, void* act, float* y,
                               const int32_t* experts, int M, int d, int F, int E, int top_k, hipStream_t s) {
   StreamArgs p = {};

@@ -6,9 +6,10 @@
 // and next to no arithmetic.  So a layer is five launches, every workgroup's loads go straight to registers (nothing to
 // share that the caches do not hold), and the contraction is split over the waves of a workgroup so that a
 // chain of loads is two to six long instead of forty; and since one matrix instruction is 32 cycles for 2048 flops, the chains
-// of those count as well: narrow tiles, eight waves for the keys.  The whole fp32 workload (2 layers over 128 tokens, 4 over
-// 16) takes 0.190 ms; with wide tiles, four waves for the keys and the rotary table in a launch of its own 0.220 ms; on the
-// plain-ALU kernels with separate norm, RoPE and SwiGLU launches 1.43 ms (projections 41 us, attention 44 us a launch).
+// of those count as well: narrow tiles, eight waves for the keys of a launch that few workgroups make.  The whole fp32 workload
+// (2 layers over 128 tokens, 4 over 16) takes 0.190 ms; with wide tiles, four waves for the keys and the rotary table in a launch
+// of its own 0.220 ms; on the plain-ALU kernels with separate norm, RoPE and SwiGLU launches 1.43 ms (projections 41 us, attention
+// 44 us a launch).
 // Error against 64 bits 1.4e-7 (2-norm; plain kernels 3.0e-7).  More chunks in flight (six instead of three): no gain.
 #include "dsk_internal.h"
 
@@ -22,7 +23,7 @@ struct Fp32Gemm {
   float* C; int64_t ldc;
   const float* R; int64_t ldr;
   int M, N, K;
-  int units;  // pairs of 16-column tiles
+  int units;  // of 32 columns of W (unit_cols), of 16 on narrow tiles
   const float* gain; float eps;                     // RMSNorm in front (NORM)
   int gu_block;                                     // EP_SWIGLU
   const float2* cs; float* k_rows; float* v_rows;   // EP_ROPE
@@ -150,8 +151,9 @@ __global__ void __launch_bounds__(64 * WM * WN * KW) gemm_fp32_kernel(Fp32Gemm p
   constexpr int UP = 8 * CT;  // columns of a unit on either side
   // The rotary pairs of a small tile, while the operands arrive: read behind the reduction they cost a round trip to memory,
   // and the table in a launch of its own 3.5 us a call.  The workgroups of head 0 write it for the layers that follow.  Not on
-  // the larger tiles: there the LDS for the pairs and the registers of the angles take one workgroup in four from a compute
-  // unit, in every layer (QKV over 1024 rows, 1536 columns of 512: 50.5 us, with both 60.5; 500 rows 18.2 and 20.4).
+  // the larger tiles: there the registers of the angles leave a compute unit two workgroups instead of three (and the LDS of the
+  // pairs three instead of four), in every layer (QKV over 1024 rows, 1536 columns of 512: 50.5 us, with both 60.5; 500 rows 18.2
+  // and 20.4).
   constexpr bool PAIRS = EP == EP_ROPE && TM * U == 1;
   __shared__ float2 pairs[PAIRS ? WM * WN : 1][TM][U][16][UP];
   if (PAIRS) {

@@ -438,19 +438,21 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 // p0 .. p0 + 31 and their partners 64 further on: tiles j and j + 2, the same lane and register), so that the epilogue
 // rotates the fp32 sums and writes q to C and k and v straight to their cache rows.  The separate pass read and wrote
 // every row once more (33 us for 8192 rows of the 8B shape); a layer over 4096 rows 1432 -> 1421 us, over eight ragged
-// contexts (39892 rows) 18.60 -> 18.42 ms, a Mixtral layer over 8192 rows 5958 -> 5925 us, a 70B one 10489 -> 10461 us.
+// contexts (49523 rows) 18.60 -> 18.42 ms, a Mixtral layer over 8192 rows 5958 -> 5925 us, a 70B one 10489 -> 10461 us.
 struct RopeOut {
   const float2* cs;  // [M][64] (cos, sin)
   bf16_t *k, *v;     // [M][Hkv * 128]
   int Hq, Hkv;
 };
-// DIRECT (unsplit 256-row tiles, weights in blocks): a wave loads its fragments of W straight to registers, 1.5 k-tiles ahead,
-// and only A goes through LDS, in a ring of four stages.  What bounds the large projections is power: the chip runs them
-// at 1.75 GHz with the matrix pipes busy 0.81 of the time, and with all operands zero the other form is the faster
+// DIRECT (unsplit 256-row tiles, weights in blocks, w_direct): a wave loads its fragments of W straight to registers, and only A
+// goes through LDS, in a ring of four stages.  W is requested 1.5 k-tiles ahead; the compiler's waits, which count these loads
+// but not those of A between them, leave some 0.8 of a k-tile of that (vmcnt 6 to 11 where 13 to 19 newer loads are in flight).
+// What bounds the large projections is power, and with all operands zero the other form is the faster
 // one (8192 x 28672 x 4096 1912 against 1800 TFLOP/s).  On data this form is, because it moves less: 128 KB of LDS reads and
 // 32 KB of writes per k-tile instead of 192 and 64 (a fragment of W comes twice from L1, not twice through LDS; requests to
 // L2 the same within 4 %), and because an MFMA shares an operand with the one before it.  8192 rows, both forms in turn:
-// down 691 -> 666 us, QKV 303 -> 291, O 226 -> 222, gate/up 1300 -> 1285; 70B shapes 1.5 to 3 %; same sums, same order.
+// down 662 -> 638 us, QKV 297 -> 292, O 246.5 -> 245, gate/up 1262 -> 1250; 70B QKV, down and gate/up 1005 -> 988, 2635 -> 2624 and
+// 5160 -> 4996; same sums, same order.
 // Measured without gain: 2, 3 or 6 fragments of A ahead, and the lines of W touched 4 to 8 k-tiles early (faster on zeros).
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false, bool ROPE = false, bool DIRECT = false>
 __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
@@ -1110,6 +1112,8 @@ int g_variant = 0;
 // to 3000 rows with cold weights (in brackets the 128 x 128 tiles with split contraction this replaces):
 //   QKV 333 rows 32.8 [43.0], 1500 rows 71.7 [91.7], 3000 rows 140 [165];  O 333 rows 27.8 [35.8], 3000 rows 85 [96];
 //   down 333 rows 55 [81], 700 rows 85 [135], 1500 rows 149 [207].
+// The times of 256-row tiles are those of the form that brings W through LDS; where w_direct takes the other one they are 0 to 5 %
+// too long, which the choices do not reflect.
 struct GemmPlan { int bm, splits, per, head_rows, rest_bm; };
 
 // the best single launch and its time (a matter of the sizes alone: the scratch holds every split, gemm_mfma_split_bytes)

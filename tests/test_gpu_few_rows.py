@@ -87,7 +87,7 @@ def test_expert_layers_match_the_plain_kernels(B, rows, E, k):
 
 
 # activations of up to eight rows stand in rows, of more in blocks: the same sums in the same order, bit for bit; a single
-# row, the most rows, dense and expert layers, an odd number of 32-column blocks
+# row, the most rows, dense and expert layers, an odd number of 64-column steps
 @pytest.mark.parametrize("d,Hq,Hkv,dh,F,E", [(448, 7, 1, 64, 832, 0), (512, 6, 2, 128, 320, 0), (320, 5, 1, 64, 192, 5)])
 def test_activations_in_rows_and_in_blocks_agree(B, d, Hq, Hkv, dh, F, E):
     from tests import gpu_util as G
