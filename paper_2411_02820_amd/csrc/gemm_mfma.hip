@@ -1016,7 +1016,7 @@ hipError_t launch(const void* A, int64_t lda, const void* W, int64_t ldw, int w_
 }
 
 // Whether a launch of unsplit 256-row tiles takes W in blocks straight to registers (DIRECT); rows: those that share W, of an
-// expert the average.  Some 180 launches, widths of 1024 to 8192 and 512 to 16384 rows, both forms in turn; time of DIRECT over
+// expert the average.  Some 220 launches, widths of 1024 to 8192 and 512 to 16384 rows, both forms in turn; time of DIRECT over
 // that of the other form:
 //   QKV, O and down: contractions of 4096 and longer 0.95 to 1.00 (2048 rows, QKV 4096 wide 93.3 -> 90.9 us; 8192 rows, down 14336
 //   long 662 -> 638), of 3584 0.98 to 1.00, of 3072 and 2048 0.97 to 1.01 (layers 3072 wide over 4096 and 8192 rows 1.01), of 1024 1.00
