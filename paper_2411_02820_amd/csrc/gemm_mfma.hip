@@ -6,7 +6,7 @@
 // v_mfma_f32_32x32x16_bf16 for 64 rows and fewer of row-major weights (K-split tiles) and for gate/up over up to 256 rows.
 // (Few rows of a model's own weights: few_rows.hip.)  A workgroup owns a BM x BN tile of C and walks K in steps of 64
 // through a two-stage
-// LDS ring filled by direct global->LDS loads (global_load_lds_dwordx4: no staging registers, no
+// LDS ring (W up to four: w_stages) filled by direct global->LDS loads (global_load_lds_dwordx4: no staging registers, no
 // ds_write).  The loads of k-tile kt+2 go out, between MFMAs, as soon as a barrier shows that every wave
 // has read k-tile kt out of the stage they overwrite; fragments are read from LDS one or two k-steps ahead
 // of the MFMAs that use them.  Two schedules of the 32x32x16 kernel (SCHED): 0 frees the stage before the last k-step
@@ -427,7 +427,8 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 // W rows are the MFMA "A" operand again: lane l holds row l%16 and the eight k values 8*(l/16)..+7 of a 32-wide
 // k-step; accumulator register r of tile (j,i) is C[m][n + r], m = 16i + l%16, n = 16j + 4*(l/16).
 // Schedule per k-tile (two k-steps of 32 MFMAs): the fragments of k-step 1 are read during k-step 0; a barrier
-// between the k-steps frees the stage; the loads of tile t+2 go out one per four MFMAs of k-step 1; a barrier in
+// between the k-steps frees the stage; the loads of A of tile t+2 and of W of the tile that takes this one's stage (w_stages) are
+// spread over the MFMAs of k-step 1; a barrier in
 // the middle of k-step 1 publishes tile t+1, whose first fragments are read during the rest of it.
 // GROUPED (the expert projections of a mixture-of-experts layer): the token rows are sorted by expert, and row tile
 // tm of the grid is described by tile_tab[tm] = {expert, first row, end of the expert's rows, scheduling group} (built on the
@@ -454,6 +455,14 @@ struct RopeOut {
 // down 662 -> 638 us, QKV 297 -> 292, O 246.5 -> 245, gate/up 1262 -> 1250; 70B QKV, down and gate/up 1005 -> 988, 2635 -> 2624 and
 // 5160 -> 4996; same sums, same order.
 // Measured without gain: 2, 3 or 6 fragments of A ahead, and the lines of W touched 4 to 8 k-tiles early (faster on zeros).
+//
+// Stages of W in LDS (not DIRECT; A has two).  Lower tiles have less to compute on a k-tile of W, which is the same 32 KB for every
+// height, so with two stages they wait for it: W runs further ahead, as far as LDS goes (128 rows 160 KB, 192 rows 144 KB).  us a
+// launch, two stages -> these: 128 rows QKV over 1024 rows 64.4 -> 60.3, O over 1500 rows 73.0 -> 68.3; 192 rows gate/up over 333 rows 81.5
+// -> 77.8 (70B 307.7 -> 296.0), QKV over 1500 rows 73.9 -> 72.7.  256 rows with three stages: 0.5 to 1 % slower (gate/up over 4096 rows
+// 628.8 -> 632.9), so they keep two.  Shares of eight k-tiles lose up to 0.8 us of 17 (O over 96 rows), a layer over 96 rows 0.2 %.
+template <int BM> constexpr int w_stages() { return BM == 128 ? 4 : BM == 192 ? 3 : 2; }
+template <int BM, int BN, bool DIRECT> constexpr int lds16() { return (DIRECT ? 4 * BM : NSTAGE * BM + w_stages<BM>() * BN) * BK * 2; }
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false, bool ROPE = false, bool DIRECT = false>
 __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     gemm16_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W_all, int64_t ldw,
@@ -473,7 +482,8 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   static_assert(WTN == 64 && BK == 64 && TM % 2 == 0 && BM % (RPI * NW) == 0, "written for 64-column wave tiles, two k-steps");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t* sA = (bf16_t*)smem_raw;
-  bf16_t* sW = sA + NSTAGE * BM * BK;
+  bf16_t* sW = sA + NSTAGE * BM * BK;  // [WS][BN][BK], not DIRECT
+  constexpr int WS = w_stages<BM>();
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -648,13 +658,14 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
                     : (uint32_t)(((int64_t)min(n0 + row, N - 1) * ldw + (lp ^ ((row >> 1) & (CH - 1))) * 8) * 2);
     }
     const uint32_t sW_lds = (uint32_t)(uintptr_t)sW;
-    auto issue_load = [&](int stage, int k0, int idx) {
+    // load idx of a k-tile step: A of k-tile ta to stage sa, then W of k-tile tw to stage sw
+    auto issue_load = [&](int sa, int ta, int sw, int tw, int idx) {
       const bool is_a = idx < A_INST;
       const int li = is_a ? idx : idx - A_INST;
-      const char* base = is_a ? (const char*)A + (int64_t)k0 * 2 : (const char*)W + (int64_t)k0 * w_step<WB>();
+      const char* base = is_a ? (const char*)A + (int64_t)(kt0 + ta) * (BK * 2) : (const char*)W + (int64_t)(kt0 + tw) * (BK * w_step<WB>());
       const uint32_t voff = is_a ? a_off[li] : w_off[li];
-      const uint32_t dst = is_a ? sA_lds + (uint32_t)(stage * BM * BK + RPI * (wave * A_INST + li) * BK) * 2
-                                : sW_lds + (uint32_t)(stage * BN * BK + RPI * (wave * W_INST + li) * BK) * 2;
+      const uint32_t dst = is_a ? sA_lds + (uint32_t)(sa * BM * BK + RPI * (wave * A_INST + li) * BK) * 2
+                                : sW_lds + (uint32_t)(sw * BN * BK + RPI * (wave * W_INST + li) * BK) * 2;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                    :
                    : "s"(dst), "v"(voff), "s"(base)
@@ -672,26 +683,42 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
       }
     };
 
+    // Loads return in order.  In front of the loop: tile 0, tile 1, then W alone of the tiles up to WS - 1.
 #pragma unroll
-    for (int i = 0; i < PER_TILE; ++i) issue_load(0, kt0 * BK, i);
-    if (n_kt > 1) {
+    for (int i = 0; i < PER_TILE; ++i) issue_load(0, 0, 0, 0, i);
+    if (n_kt > WS) {
 #pragma unroll
-      for (int i = 0; i < PER_TILE; ++i) issue_load(1, (kt0 + 1) * BK, i);
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_TILE) : "memory");
+      for (int i = 0; i < PER_TILE; ++i) issue_load(1, 1, 1, 1, i);
+#pragma unroll
+      for (int u = 2; u < WS; ++u)
+#pragma unroll
+        for (int i = A_INST; i < PER_TILE; ++i) issue_load(0, 0, u, u, i);
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_TILE + (WS - 2) * W_INST) : "memory");
     } else {
+      if (n_kt > 1) {
+#pragma unroll
+        for (int i = 0; i < PER_TILE; ++i) issue_load(1, 1, 1, 1, i);
+      }
+      for (int u = 2; u < n_kt; ++u)
+#pragma unroll
+        for (int i = A_INST; i < PER_TILE; ++i) issue_load(0, 0, u, u, i);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
 #pragma unroll
     for (int f = 0; f < NF; ++f) read_frag(sA, sW, 0, f);
 
-    constexpr int LD = PER_TILE / 2;  // loads per wave in each half of k-step 1
-    auto tile_step = [&](int t, auto has_next, auto has_next2) {
-      const int stage = t & 1;
+    // k-tile t (stage w_at of W) brings A of t + 2 (n_ld = A_INST loads) and W of t + WS (n_ld = PER_TILE).  Behind A(t + 1), which the
+    // wait in the middle of k-step 1 is for, come W(t + WS - 1) and the loads issued since; W(t + 1) is older (for t = 0 it is followed
+    // by W of the tiles 2 to WS - 1, no fewer loads).
+    int w_at = 0;
+    auto tile_step = [&](int t, auto has_next, auto n_ld_) {
+      constexpr int n_ld = n_ld_(), newer = NM / 2 * n_ld / NM + (n_ld == PER_TILE && WS > 2 ? W_INST : 0);
+      const int stage = t & 1, w_next = w_at + 1 == WS ? 0 : w_at + 1;
       const bf16_t* a_s = sA + stage * BM * BK;
-      const bf16_t* w_s = sW + stage * BN * BK;
+      const bf16_t* w_s = sW + w_at * BN * BK;
       const bf16_t* a_n = sA + (stage ^ 1) * BM * BK;
-      const bf16_t* w_n = sW + (stage ^ 1) * BN * BK;
+      const bf16_t* w_n = sW + w_next * BN * BK;
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         if (ks == 1) {
@@ -706,8 +733,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
           for (int i = 0; i < TM; ++i) {
             const int m = j * TM + i;
             if (ks == 1 && m == NM / 2) {
-              if (has_next2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LD) : "memory");
-              else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+              asm volatile("s_waitcnt vmcnt(%0)" ::"n"(newer) : "memory");
               __builtin_amdgcn_s_barrier();
               asm volatile("" ::: "memory");
             }
@@ -729,20 +755,22 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
               __builtin_amdgcn_sched_barrier(0);
             }
             acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ws[ks][j], xs[ks][i], acc[j][i], 0, 0, 0);
-            if (ks == 1 && has_next2) {
+            if (ks == 1 && n_ld > 0) {
               __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-              for (int q = m * PER_TILE / NM; q < (m + 1) * PER_TILE / NM; ++q) issue_load(stage, (kt0 + t + 2) * BK, q);
+              for (int q = m * n_ld / NM; q < (m + 1) * n_ld / NM; ++q) issue_load(stage, t + 2, w_at, t + WS, q);
               __builtin_amdgcn_sched_barrier(0);
             }
           }
         __builtin_amdgcn_sched_barrier(0);
       }
+      w_at = w_next;
     };
     int t = 0;
-    for (; t + 2 < n_kt; ++t) tile_step(t, std::true_type{}, std::true_type{});
-    if (t + 1 < n_kt) { tile_step(t, std::true_type{}, std::false_type{}); ++t; }
-    if (t < n_kt) tile_step(t, std::false_type{}, std::false_type{});
+    for (; t + WS < n_kt; ++t) tile_step(t, std::true_type{}, std::integral_constant<int, PER_TILE>{});
+    for (; t + 2 < n_kt; ++t) tile_step(t, std::true_type{}, std::integral_constant<int, A_INST>{});
+    if (t + 1 < n_kt) { tile_step(t, std::true_type{}, std::integral_constant<int, 0>{}); ++t; }
+    if (t < n_kt) tile_step(t, std::false_type{}, std::integral_constant<int, 0>{});
   }
 
   // ---- epilogue through the wave's own LDS region, 32 rows at a time (as in the 32x32 kernel) ----
@@ -1038,7 +1066,7 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool DIRECT = false
 hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R, int64_t ldr,
                          int M, int N, int K, int epi, int splits, int kt_per_split, hipStream_t s) {
   auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, WB, false, false, DIRECT>;
-  constexpr int lds = NSTAGE * (BM + BN) * BK * 2;
+  constexpr int lds = lds16<BM, BN, DIRECT>();
   static bool configured = false;
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1056,7 +1084,7 @@ hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw,
 template <int BM, bool DIRECT>
 hipError_t launch16_rope(const void* A, const void* W, void* qkv, const RopeOut& ro, int M, int K, hipStream_t s) {
   auto kern = gemm16_bf16_kernel<BM, 256, 2, 4, true, false, true, DIRECT>;
-  constexpr int lds = NSTAGE * (BM + 256) * BK * 2;
+  constexpr int lds = lds16<BM, 256, DIRECT>();
   static bool configured = false;
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1088,7 +1116,7 @@ hipError_t launch16_grouped(const void* A, int64_t lda, const int32_t* a_row, in
                             int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi, const int4* tile_tab, int tile_rows,
                             hipStream_t s) {
   auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, true, true, false, DIRECT>;
-  constexpr int lds = NSTAGE * (BM + BN) * BK * 2;
+  constexpr int lds = lds16<BM, BN, DIRECT>();
   static bool configured = false;
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);

@@ -52,6 +52,26 @@ def test_linear_bf16_medium_rows(B, M, N, K, residual, plan):
         assert torch.equal(y, y256)
 
 
+# contractions of one k-tile up to more than the stages of W that a lower tile has (four and three): the bits of the 256-row tiles,
+# whose sums have the same order
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 320, 384, 512])
+@pytest.mark.parametrize("M,N,bm", [(65, 64, 128), (200, 516, 128), (4200, 4612, 192)])
+def test_lower_tiles_run_ahead_on_w(B, M, N, bm, K):
+    assert B.dsk_gemm_plan(M, N, K, False) == (bm, 1, 0, 0)
+    x, w = torch.randn(M, K, device="cuda").bfloat16(), torch.randn(N, K, device="cuda").bfloat16()
+    y, y256 = (torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    for tiling, out in ((0, y), (1, y256)):
+        B.dsk_set_option("gemm_tiling", tiling)
+        try:
+            B.dsk_linear(B.DSK_BF16, x, w, out, None, M, N, K)
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("gemm_tiling", 0)
+    # one bf16 rounding of the result
+    assert O.max_rel_err(y.float().cpu().numpy(), x.double().cpu().numpy() @ w.double().cpu().numpy().T) <= 2 ** -8
+    assert torch.equal(y, y256)
+
+
 # two layers, so that the split down projection also leaves the next layer's norm input; against the same model with the
 # tiling forced (which neither splits nor fuses).  plans: (tile rows, splits) of QKV, O and down: RoPE + KV write with heads
 # of 64 and 128 and RMSNorm at widths up to 4096 and beyond in the reduction, every tile height, QKV unsplit
