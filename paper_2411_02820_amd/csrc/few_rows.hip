@@ -445,12 +445,13 @@ hipError_t launch_stream(const StreamArgs& p, int tiles, int splits, hipStream_t
 }
 
 // A projection with residual runs unsplit on 16-column tiles (every compute unit gets one at the 8B width) as long as
-// that many tiles re-reading the activations stay cheap; beyond 256 MB of such reads the contraction is split over about 256
-// workgroups of 64 columns, and a reduction launch adds up.  64 rows, 8B shape: O (134 MB of reads) 13.6 us against
-// 10.6 us + 4.9 us split; down (470 MB) 40 us against 24.6 us + 4.9 us.
+// that many tiles re-reading the activations stay cheap; beyond 180 MB of such reads the contraction is split over about 256
+// workgroups of 64 columns, and a reduction launch adds up.  8B shape: O over 64 rows (134 MB of reads) 13.6 us against
+// 10.6 us + 4.9 us split; down over 64 rows (470 MB) 40 us against 24.6 us + 4.9 us, over 32 (235 MB) 31.8 against 21.6 + 4.8,
+// over 16 (117 MB) 24.0 unsplit.
 int residual_splits(int M, int N, int K) {
   const int rows = (M + 15) / 16 * 16;
-  if (rows <= 32 || (int64_t)(N / 16) * rows * K * 2 <= (int64_t)256 << 20) return 0;
+  if (rows <= 16 || (int64_t)(N / 16) * rows * K * 2 <= (int64_t)180 << 20) return 0;
   const int tiles = N / 64, splits = (256 + tiles - 1) / tiles;
   return splits > K / 512 ? (K / 512 > 0 ? K / 512 : 1) : splits;
 }
@@ -497,15 +498,17 @@ hipError_t launch_few_qkv(const void* a, const float* ssq, float eps, const void
   }
 }
 
-// 32 rows and fewer: 32-column tiles; more: 128-column tiles (224 workgroups at the 8B width), which read the activations
-// a quarter as often (64 rows, 8B shape: 45 us against 57 us; with one step in flight instead of two 50 us)
+// Up to 16 rows: 32-column tiles; more: 128-column tiles (224 workgroups at the 8B width), which read the activations
+// a quarter as often (8B shape, 64 rows 45 us against 57 us; with one step in flight instead of two 50 us; 32 rows 42.0 against 47.3;
+// 12 rows 43.2 against 42.2).  With 17 to 32 rows only where there are enough of them for the chip.
 hipError_t launch_few_swiglu(const void* a, const float* ssq, float eps, const void* W, void* act, int M, int N, int K,
                              hipStream_t s) {
   StreamArgs p = {};
   p.X = (const bf16_t*)a; p.W = (const bf16_t*)W; p.M = M; p.x_rows = few_rows_row_major(M); p.N = N; p.K = K; p.ssq = ssq; p.eps = eps; p.out = (bf16_t*)act;
   switch ((M + 15) / 16) {
     case 1: return launch_stream<1, 2, 8, 2, 2, EP_SWIGLU>(p, N / 32, 1, s);
-    case 2: return launch_stream<2, 2, 8, 2, 2, EP_SWIGLU>(p, N / 32, 1, s);
+    case 2: return N / 128 >= 192 ? launch_stream<2, 8, 4, 2, 1, EP_SWIGLU>(p, N / 128, 1, s)
+                                  : launch_stream<2, 2, 8, 2, 2, EP_SWIGLU>(p, N / 32, 1, s);
     case 3: return launch_stream<3, 8, 4, 2, 1, EP_SWIGLU>(p, N / 128, 1, s);
     default: return launch_stream<4, 8, 4, 2, 1, EP_SWIGLU>(p, N / 128, 1, s);
   }
@@ -520,7 +523,8 @@ hipError_t launch_few_residual(const void* x, const void* W, const void* R, int 
   const int mt = (M + 15) / 16, splits = residual_splits(M, N, K);
   if (splits > 0) {
     if (!ws || (int64_t)splits * M * N * 4 > ws_bytes) return hipErrorNotSupported;
-    hipError_t e = mt == 3 ? launch_stream<3, 4, 8, 2, 1, EP_PART>(p, N / 64, splits, s)
+    hipError_t e = mt == 2 ? launch_stream<2, 4, 8, 2, 1, EP_PART>(p, N / 64, splits, s)
+                   : mt == 3 ? launch_stream<3, 4, 8, 2, 1, EP_PART>(p, N / 64, splits, s)
                            : launch_stream<4, 4, 8, 2, 1, EP_PART>(p, N / 64, splits, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(few_residual_kernel, dim3((M * (N / 4) + 255) / 256), dim3(256), 0, s, (const float*)ws, splits, R, r_f32,
@@ -544,8 +548,11 @@ hipError_t launch_few_route(const void* a, const float* ssq, float eps, const vo
 }
 
 // The expert MLPs over all rows (a few rows hit most experts, and what it costs is the weights): one launch per projection
-// over every expert that some token has chosen (Mixtral width, 64 rows: 407 + 176 us for 2.8 GB; expert by expert with a
-// reduction behind each, 32 launches, 730 us; one row streams two experts of the eight).  act: [E][rows up to 16][F],
+// over every expert that some token has chosen (Mixtral width, 64 rows: 332 + 150 us for 2.8 GB; expert by expert with a
+// reduction behind each, 32 launches, 730 us; one row streams two experts of the eight).  Tiles as wide as still give the chip 256
+// workgroups read the activations (of down 1.8 MB a workgroup at 64 rows) less often: down in 128- instead of 64-column tiles over 64
+// rows 166.5 -> 149.7 us, over 40 161 -> 150, over 24 (32-column tiles before) 169 -> 146; gate/up over 24 rows 321 -> 304; down over 12
+// rows in 64- instead of 16-column tiles 145.7 -> 129.8 (over 4 rows, five experts or six, 98 against 82: up to eight rows 16 columns).  act: [E][rows up to 16][F],
 // blocks or rows (few_rows_row_major); y: [E][M][d].
 hipError_t launch_few_experts(const void* a, const float* ssq, float eps, const void* wgu, const void* wd, void* act, float* y,
                               const int32_t* experts, int M, int d, int F, int E, int top_k, hipStream_t s) {
@@ -554,9 +561,13 @@ hipError_t launch_few_experts(const void* a, const float* ssq, float eps, const 
   p.experts = experts; p.n_entries = M * top_k;
   p.w_expert = 2 * (int64_t)F * d; p.out_expert = (int64_t)(M + 15) / 16 * 16 * F;
   hipError_t e;
+  const int chosen = M * top_k < E ? M * top_k : E;  // experts that run, at most
   switch ((M + 15) / 16) {
     case 1: e = launch_stream<1, 2, 8, 2, 2, EP_SWIGLU>(p, p.N / 32, 1, s, E); break;
-    case 2: e = launch_stream<2, 2, 8, 2, 2, EP_SWIGLU>(p, p.N / 32, 1, s, E); break;
+    case 2:
+      e = (int64_t)p.N / 128 * chosen >= 192 ? launch_stream<2, 8, 4, 2, 1, EP_SWIGLU>(p, p.N / 128, 1, s, E)
+                                             : launch_stream<2, 2, 8, 2, 2, EP_SWIGLU>(p, p.N / 32, 1, s, E);
+      break;
     case 3: e = launch_stream<3, 8, 4, 2, 1, EP_SWIGLU>(p, p.N / 128, 1, s, E); break;
     default: e = launch_stream<4, 8, 4, 2, 1, EP_SWIGLU>(p, p.N / 128, 1, s, E); break;
   }
@@ -564,11 +575,17 @@ hipError_t launch_few_experts(const void* a, const float* ssq, float eps, const 
   p.X = (const bf16_t*)act; p.x_expert = p.out_expert;
   p.W = (const bf16_t*)wd; p.w_expert = (int64_t)d * F;
   p.N = d; p.K = F; p.P = y; p.out_expert = (int64_t)M * d;
+  const bool wide = d % 128 == 0 && (int64_t)d / 128 * chosen >= 256;
   switch ((M + 15) / 16) {
-    case 1: return launch_stream<1, 1, 8, 2, 2, EP_PART>(p, d / 16, 1, s, E);
-    case 2: return launch_stream<2, 2, 8, 2, 2, EP_PART>(p, d / 32, 1, s, E);
-    case 3: return launch_stream<3, 4, 8, 2, 1, EP_PART>(p, d / 64, 1, s, E);
-    default: return launch_stream<4, 4, 8, 2, 1, EP_PART>(p, d / 64, 1, s, E);
+    case 1:
+      return M > 8 && (int64_t)d / 64 * chosen >= 256 ? launch_stream<1, 4, 8, 2, 1, EP_PART>(p, d / 64, 1, s, E)
+                                                      : launch_stream<1, 1, 8, 2, 2, EP_PART>(p, d / 16, 1, s, E);
+    case 2:
+      return wide ? launch_stream<2, 8, 4, 2, 1, EP_PART>(p, d / 128, 1, s, E) : launch_stream<2, 2, 8, 2, 2, EP_PART>(p, d / 32, 1, s, E);
+    case 3:
+      return wide ? launch_stream<3, 8, 4, 2, 1, EP_PART>(p, d / 128, 1, s, E) : launch_stream<3, 4, 8, 2, 1, EP_PART>(p, d / 64, 1, s, E);
+    default:
+      return wide ? launch_stream<4, 8, 4, 2, 1, EP_PART>(p, d / 128, 1, s, E) : launch_stream<4, 4, 8, 2, 1, EP_PART>(p, d / 64, 1, s, E);
   }
 }
 

@@ -122,3 +122,29 @@ def test_steps_behind_the_loop(B, rows, d, F):
     # two bf16 evaluations of one layer, each within 1e-2 of the exact one at this weight scale
     assert O.max_rel_err(G.to_np(h), G.to_np(h_ref).astype(np.float64)) <= 2e-2
     assert O.max_rel_err(G.to_np(kv[0]), G.to_np(kv_ref[0]).astype(np.float64)) <= 2e-2
+
+
+# the wider tiles of 9 to 64 rows: experts enough for 256 workgroups of 64 and 128 columns (one to four row tiles), a dense gate/up of
+# 192 tiles and down split over workgroups at 17 to 32 rows; against the plain kernels
+@pytest.mark.parametrize("rows", [9, 16, 17, 32, 33, 64])
+@pytest.mark.parametrize("d,F,E", [(2048, 1600, 16), (256, 12352, 0), (2048, 28736, 0)])
+def test_wide_tiles_of_few_rows(B, rows, d, F, E):
+    from tests import gpu_util as G
+    shape = synth.ModelShape(1, d, d // 128, 1, 128, F, 10000.0, 1e-5, "bf16", E, 1 if E else 0)
+    with G.GpuModel(shape, rows) as m:
+        m.init_random(11)
+        x = synth.hidden_states(shape, rows)
+        if E:  # a part along one router row per token, so that the choice of experts does not hang on rounding
+            wr = G.to_np(m.get_tensor(0, synth.WR))
+            x += 9.0 * wr[np.arange(rows) * 3 % E] / np.linalg.norm(wr, axis=1).mean()
+        x = G.to_dev(x, shape)
+        kv, h = m.partial(x, 0, 1, None, [rows])
+        B.dsk_set_option("force_generic", 1)
+        try:
+            kv_ref, h_ref = m.partial(x, 0, 1, None, [rows])
+            torch.cuda.synchronize()
+        finally:
+            B.dsk_set_option("force_generic", 0)
+    # two bf16 evaluations of one layer, each within 1e-2 of the exact one at this weight scale
+    assert O.max_rel_err(G.to_np(h), G.to_np(h_ref).astype(np.float64)) <= 2e-2
+    assert O.max_rel_err(G.to_np(kv[0]), G.to_np(kv_ref[0]).astype(np.float64)) <= 2e-2
