@@ -15,7 +15,7 @@
 // 4096 keys 7.8 us (17), and the merge of the key ranges 6 us in both.  Of the 22.5 us the loads alone take 10, the partial
 // outputs 4; runs of 64 keys per wave and stage (two independent steps to schedule) instead of 32 took 25 -> 22.5 us, four column
 // tiles per wave with one wave per SIMD take 35.
-// 128 queries for each of eight sequences of 1k to 8k keys: 190 us, one key range per workgroup (before: transposed copy 35,
+// 128 queries for each of eight sequences of 1k to 8k keys: 153 us, one key range per workgroup (before: transposed copy 35,
 // attention 153, merge 15).
 #include <math.h>
 
@@ -95,16 +95,43 @@ __global__ void __launch_bounds__(64 * QG * KH) attn_few_kernel(FewParams p) {
   auto load_to = [](uint32_t dst, const void* src) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
   };
-  auto issue = [&](int st) {
-    const int stage = (st - st0) % NST;
+  // A stage inside the prefix: the lanes' byte offsets from its first row are those of every stage, so its loads take a scalar base and
+  // no arithmetic per lane.  (The swizzles repeat after KP and VP loads of RPI rows.)
+  constexpr int KP = INST < 16 / RPI ? INST : 16 / RPI, VP = INST < 8 / RPI ? INST : 8 / RPI;
+  uint32_t k_off[KP], v_off[VP];
 #pragma unroll
-    for (int i = 0; i < INST; ++i) {
-      const int r0 = RPI * (wave * INST + i), r = r0 + lane / SLOTS, s = lane % SLOTS;
-      const int j = min(st * KEYS + r, n_keys - 1);  // rows past the end repeat the last one and are masked
-      const int64_t row = j < n_pre ? pre_begin + j : own_begin + (j - n_pre);
-      const uint32_t at = (uint32_t)((stage * KEYS + r0) * DH) * 2u;
-      load_to(sK_lds + at, kb + row * ldkv + (s ^ kswz(r)) * 8);
-      load_to(sV_lds + at, vb + row * ldkv + (s ^ vswz(r)) * 8);
+  for (int i = 0; i < KP; ++i) {
+    const int r = RPI * (wave * INST + i) + lane / SLOTS;
+    k_off[i] = (uint32_t)(r * ldkv + (lane % SLOTS ^ kswz(r)) * 8) * 2u;
+  }
+#pragma unroll
+  for (int i = 0; i < VP; ++i) {
+    const int r = RPI * (wave * INST + i) + lane / SLOTS;
+    v_off[i] = (uint32_t)(r * ldkv + (lane % SLOTS ^ vswz(r)) * 8) * 2u;
+  }
+  auto load_off = [](uint32_t dst, uint32_t off, const void* base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(off), "s"(base) : "memory", "m0");
+  };
+  auto issue = [&](int st) {
+    const uint32_t at = (uint32_t)(((st - st0) % NST * KEYS + RPI * wave * INST) * DH) * 2u;
+    if ((st + 1) * KEYS <= n_pre) {
+      const int64_t row0 = (int64_t)(pre_begin + st * KEYS) * ldkv;
+#pragma unroll
+      for (int i = 0; i < INST; ++i) {
+        load_off(sK_lds + at + i * 1024, k_off[i % KP], kb + row0 + (int64_t)(i / KP * KP) * RPI * ldkv);
+        load_off(sV_lds + at + i * 1024, v_off[i % VP], vb + row0 + (int64_t)(i / VP * VP) * RPI * ldkv);
+      }
+    } else {
+      int lane_s = lane;
+      asm volatile("" : "+v"(lane_s));  // nothing of this path is kept in registers over the loop
+#pragma unroll
+      for (int i = 0; i < INST; ++i) {
+        const int r = RPI * (wave * INST + i) + lane_s / SLOTS, s = lane_s % SLOTS;
+        const int j = min(st * KEYS + r, n_keys - 1);  // rows past the end repeat the last one and are masked
+        const int64_t row = j < n_pre ? pre_begin + j : own_begin + (j - n_pre);
+        load_to(sK_lds + at + i * 1024, kb + row * ldkv + (s ^ kswz(r)) * 8);
+        load_to(sV_lds + at + i * 1024, vb + row * ldkv + (s ^ vswz(r)) * 8);
+      }
     }
   };
 
@@ -143,7 +170,7 @@ __global__ void __launch_bounds__(64 * QG * KH) attn_few_kernel(FewParams p) {
   constexpr int PER = 2 * INST;  // loads per wave and stage
   for (int st = st0; st < st1; ++st) {
     // the stages behind this one may still be in flight
-    const int behind = min(NST - 1, st1 - 1 - st);
+    const int behind = min(st == st0 ? NST - 1 : NST - 2, st1 - 1 - st);
     if (behind >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * PER) : "memory");
     else if (behind == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
     else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER) : "memory");
@@ -175,8 +202,16 @@ __global__ void __launch_bounds__(64 * QG * KH) attn_few_kernel(FewParams p) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       }
     }
+    // The one barrier of a stage: the stage is there for every wave, and every wave is past the one in front (its reads have
+    // returned), which takes the next loads.  With a second barrier behind the MFMAs, and addresses worked out per lane: 8 x 128
+    // queries (49523 keys in all) 174 us instead of 153, 4 x 100 queries and 4096 keys each 51.6 instead of 46.0, 64 queries and
+    // 8192 keys 21.8 instead of 21.2.  What bounds it now, one thing left out at a time (timing only): no tile loads 0.83 of the time,
+    // no reads of K 0.87, no exponentials 0.95, no reads of V 1.0.  Measured without gain: the scores of the next stage beside the
+    // exponentials of this one (153 us, and 3 us more at the start), fragments read four or six ahead of their MFMAs.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    if (st > st0 && st + NST - 1 < st1) issue(st + NST - 1);
     if (active && key0 < n_keys) {
       const bf16_t* kt = sK + (stage * KEYS + KW * kh) * DH;
       const bf16_t* vt = sV + (stage * KEYS + KW * kh) * DH;
@@ -263,13 +298,6 @@ __global__ void __launch_bounds__(64 * QG * KH) attn_few_kernel(FewParams p) {
 #pragma unroll
           for (int t = 0; t < QT; ++t) o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfrag, pf[t][k], o[t][dt], 0, 0, 0);
         }
-    }
-    if (st + NST < st1) {
-      // every wave has read this stage (its reads have returned: they fed its MFMAs); it takes the next loads
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      issue(st + NST);
     }
   }
 

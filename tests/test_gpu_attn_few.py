@@ -64,6 +64,29 @@ def test_attention_few_queries_component_call(B):
     assert O.max_rel_err(out.float().cpu().numpy().reshape(n, Hq, dh), ref) <= 1e-2
 
 
+# prefixes that end on both sides of a stage of 128 keys, from one stage to more than the ring holds: stages wholly inside the prefix
+# are loaded another way than those that reach past it; every column form, a second sequence whose rows start elsewhere
+@pytest.mark.parametrize("pre", [1, 127, 128, 129, 255, 256, 257, 511, 512, 640])
+@pytest.mark.parametrize("n", [2, 9, 40])
+@pytest.mark.parametrize("Hkv,dh", [(1, 128), (3, 64)])
+def test_attention_prefix_ends_at_a_stage(B, pre, n, Hkv, dh):
+    Hq, lens, plens = 4 * Hkv, [n, n], [pre, pre + 128]
+    torch.manual_seed(pre)
+    q, k, v = (torch.randn(r, h, dh, device="cuda").bfloat16() for r, h in ((2 * n, Hq), (sum(plens) + 2 * n, Hkv), (sum(plens) + 2 * n, Hkv)))
+    out = torch.empty((2 * n, Hq * dh), dtype=torch.bfloat16, device="cuda")
+    scratch = torch.empty(Hkv * dh * ((k.shape[0] + 63) // 64 * 64), dtype=torch.bfloat16, device="cuda")
+    qb, pb = B.Batch(synth.cu_seqlens(lens)), B.Batch(synth.cu_seqlens(plens))
+    B.dsk_attention(B.DSK_BF16, q, k, v, out, qb.desc, pb.desc, sum(plens), Hq, Hkv, dh, scratch)
+    torch.cuda.synchronize()
+    qd, kd, vd = (t.double().cpu().numpy() for t in (q, k, v))
+    got = out.float().cpu().numpy().reshape(2 * n, Hq, dh)
+    for b, p0 in ((0, 0), (1, plens[0])):
+        for i in range(n):
+            rows = np.r_[p0:p0 + plens[b], sum(plens) + b * n:sum(plens) + b * n + i + 1]
+            # rounding of the probabilities and of the result: 2^-9 each
+            assert O.max_rel_err(got[b * n + i], O.attend_row(qd[b * n + i], kd[rows], vd[rows])) <= 1e-2
+
+
 # more than 128 queries over short key ranges: the first and the last sizes of the rule and one past it, without and with
 # keys in front, ragged
 @pytest.mark.parametrize("lens,plens", [([129], None), ([333, 130, 1], None), ([500, 161], [524, 17]), ([1024], None),
