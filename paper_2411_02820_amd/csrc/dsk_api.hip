@@ -278,18 +278,19 @@ int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, 
     const int tile_m = moe_tile_rows_for((int64_t)n * k, E);
     int tile_rows = moe_tile_table_rows((int64_t)n * k, E, tile_m);
     if (tile_rows > m->moe_tile_rows) tile_rows = m->moe_tile_rows;
-    HIP_TRY(launch_moe_place(m->moe_experts, m->moe_slot, m->moe_src, m->moe_tab, n, k, E, tile_m, tile_rows, s));
+    HIP_TRY(launch_moe_place(m->moe_experts, m->moe_slot, m->moe_src, m->moe_tab, n, k, E, tile_m, (d + 255) / 256, tile_rows, s));
     // under "time_gemm" the two grouped launches are bracketed like the other prefill projections (n*k rows each)
     auto grouped = [&](const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw, int64_t w_stride, void* C, int64_t ldc, int N,
-                       int K, int epi) -> int {
+                       int K, int epi, int table) -> int {
       std::unique_lock<std::mutex> timed_lock(g_stats.timed_mu, std::defer_lock);
       bool timed = false;
       if (g_time_gemm && gemm_mfma_uses_prefill_tile(n * k, N)) {
         timed_lock.lock();
         HIP_TRY(g_stats.gemm.begin(s, &timed));
       }
-      const hipError_t e = launch_gemm_mfma_grouped(A, lda, a_rows, a_row, W, ldw, m->w_blocks, w_stride, C, ldc, N, K, epi, m->moe_tab,
-                                                    tile_m, tile_rows, (int64_t)n * k / E, s);
+      const hipError_t e = launch_gemm_mfma_grouped(A, lda, a_rows, a_row, W, ldw, m->w_blocks, w_stride, C, ldc, N, K, epi,
+                                                    (const char*)m->moe_tab + (int64_t)table * (tile_rows + 1) * 16, tile_m, tile_rows,
+                                                    table ? E : 0, (int64_t)n * k / E, s);
       if (e != hipSuccess && timed) g_stats.gemm.abandon();
       HIP_TRY(e);
       ++g_stats.gemm_mfma;
@@ -297,8 +298,8 @@ int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, 
       return DSK_OK;
     };
     // gate/up reads the token rows where they are; its result, and what follows, is in sorted order
-    int rc = grouped(m->xn, d, n, m->moe_src, w.wgu, d, wgu_stride, m->act, F, 2 * F, d, EPI_SWIGLU);
-    if (rc == DSK_OK) rc = grouped(m->act, F, (int64_t)n * k, nullptr, w.wd, F, wd_stride, m->moe_y, d, d, F, EPI_C_F32);
+    int rc = grouped(m->xn, d, n, m->moe_src, w.wgu, d, wgu_stride, m->act, F, 2 * F, d, EPI_SWIGLU, 0);
+    if (rc == DSK_OK) rc = grouped(m->act, F, (int64_t)n * k, nullptr, w.wd, F, wd_stride, m->moe_y, d, d, F, EPI_C_F32, 1);
     if (rc) return rc;
     HIP_TRY(launch_moe_combine(m->moe_y, h_mid, m->moe_gates, m->moe_experts, m->moe_slot, h_out, out_f32, n, d, k,
                                (int64_t)n * k, s));
@@ -630,7 +631,7 @@ int dsk_model_create(const dsk_config_t* cfg, int64_t max_tokens, int64_t max_kv
     if (rc == DSK_OK) rc = alloc_dev((void**)&m->moe_gates, T * top_k * 4, &m->workspace_bytes);
     if (rc == DSK_OK) rc = alloc_dev((void**)&m->moe_slot, T * top_k * 4, &m->workspace_bytes);
     if (rc == DSK_OK) rc = alloc_dev((void**)&m->moe_src, T * top_k * 4, &m->workspace_bytes);
-    if (rc == DSK_OK) rc = alloc_dev(&m->moe_tab, ((int64_t)m->moe_tile_rows + 1) * 16, &m->workspace_bytes);
+    if (rc == DSK_OK) rc = alloc_dev(&m->moe_tab, 2 * ((int64_t)m->moe_tile_rows + 1) * 16, &m->workspace_bytes);
     if (rc == DSK_OK) rc = alloc_dev((void**)&m->moe_y, m->moe_y_rows * d * 4, &m->workspace_bytes);
   }
   if (rc == DSK_OK) rc = alloc_dev((void**)&m->h, T * d * 4, &m->workspace_bytes);

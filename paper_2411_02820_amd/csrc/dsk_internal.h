@@ -251,22 +251,25 @@ hipError_t launch_fill_weight(int dtype, void* packed, int64_t rows, int64_t col
 // mixture-of-experts MLP: router, grouping by expert, grouped projections, gate-weighted sum (moe.hip, gemm_mfma.hip)
 hipError_t launch_moe_route(int dtype, const void* xn, const void* wr, int32_t* experts, float* gates, int n, int d, int E,
                             int top_k, hipStream_t s);
-// tile_tab: int4 [tile_rows_max + 1] (the last entry receives the number of tiles)
+// tile_tab: two tables of int4 [tile_rows_max + 1], gate/up's and down's (the last entry of each receives its numbers of tiles)
 hipError_t launch_moe_place(const int32_t* experts, int32_t* slot_of, int32_t* src_token, void* tile_tab, int n, int top_k,
-                            int E, int tile_m, int tile_rows_max, hipStream_t s);
-// rows of the grouped projections' tile table for n_rows rows over E experts in tiles of tile_m (every expert may end in a
-// partial tile)
+                            int E, int tile_m, int down_tiles_n, int tile_rows_max, hipStream_t s);
 // Tiles of a scheduling group, at most (a Mixtral layer over 4096, 6000, 8192 tokens, us: four 3055, 4095, 5988; eight 3015, 3987, 5897;
 // twelve 3007, 3974, 5915; twenty-four 3004, 3987, 5906: from eight on it does not matter), and the place of their number in the table.
 constexpr int MOE_GROUP_MOST = 12, MOE_GROUP_SHIFT = 20;
 int moe_tile_rows_for(int64_t n_rows, int E);
+// Low tiles: an expert's last rows where they are no more than MOE_LOW_ROWS and its other tiles have MOE_HIGH_ROWS.
+constexpr int MOE_HIGH_ROWS = 256, MOE_LOW_ROWS = 128, MOE_LOW_COLS = 128;
+// rows of the grouped projections' tile table for n_rows rows over E experts in tiles of tile_m (every expert may end in a
+// partial tile)
 inline int moe_tile_table_rows(int64_t n_rows, int E, int tile_m) { return (int)((n_rows + tile_m - 1) / tile_m) + E; }
 hipError_t launch_moe_combine(const float* y, const float* h_mid, const float* gates, const int32_t* experts,
                               const int32_t* slot_of, void* out, int out_f32, int n, int d, int top_k, int64_t y_rows,
                               hipStream_t s);
 hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw,
                                     int w_blocks, int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
-                                    const void* tile_tab, int tile_m, int tile_rows, int64_t rows_per_expert, hipStream_t s);
+                                    const void* tile_tab, int tile_m, int tile_rows, int low_rows, int64_t rows_per_expert,
+                                    hipStream_t s);
 
 // tuning knobs (dsk_set_option)
 void gemm_mfma_set_variant(int v);

@@ -432,7 +432,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 // the middle of k-step 1 publishes tile t+1, whose first fragments are read during the rest of it.
 // GROUPED (the expert projections of a mixture-of-experts layer): the token rows are sorted by expert, and row tile
 // tm of the grid is described by tile_tab[tm] = {expert, first row, end of the expert's rows, scheduling group} (built on the
-// device; tile_tab[tiles_m].x = number of tiles that exist; expert < 0: no such tile, the workgroup leaves); the
+// device; tile_tab[tiles_m] = numbers of tiles that exist, and of low ones behind them; expert < 0: no such tile, the workgroup leaves); the
 // expert's matrix is W + expert * w_group_stride.  a_row (optional): sorted row r is row a_row[r] of A's a_rows rows, so
 // that the rows are read where they are (gathered into a buffer first they cost 38 us more at 8192 tokens).
 // ROPE (the QKV projection, heads of 128, weights in blocks): a wave's 64 columns are 32 rotary pairs of one head (elements
@@ -463,12 +463,12 @@ struct RopeOut {
 // 628.8 -> 632.9), so they keep two.  Shares of eight k-tiles lose up to 0.8 us of 17 (O over 96 rows), a layer over 96 rows 0.2 %.
 template <int BM> constexpr int w_stages() { return BM == 128 ? 4 : BM == 192 ? 3 : 2; }
 template <int BM, int BN, bool DIRECT> constexpr int lds16() { return (DIRECT ? 4 * BM : NSTAGE * BM + w_stages<BM>() * BN) * BK * 2; }
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false, bool ROPE = false, bool DIRECT = false>
-__global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
-    gemm16_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W_all, int64_t ldw,
-                       void* C, int64_t ldc, const void* __restrict__ R, int64_t ldr, int M_all, int N, int K,
-                       int epi, int tiles_m, int tiles_n, int kt_per_split, const int4* __restrict__ tile_tab,
-                       int64_t w_group_stride, const int32_t* __restrict__ a_row, int a_rows, RopeOut ro) {
+// One tile: rows m0 .. of A up to row M, columns n0 .. of the product with W.
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED, bool ROPE, bool DIRECT>
+__device__ __forceinline__ void gemm16_tile(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W, int64_t ldw, void* C,
+                                            int64_t ldc, const void* __restrict__ R, int64_t ldr, int m0, int n0, int M, int M_all, int N,
+                                            int K, int epi, int kt_per_split, const int32_t* __restrict__ a_row, int a_rows,
+                                            const RopeOut& ro) {
   static_assert(!ROPE || (WB && !GROUPED && BN % 128 == 0 && BN / WAVES_N == 64), "two waves a head");
   static_assert(!DIRECT || (WB && BM == 256 && BN / WAVES_N == 64), "W straight to registers: from blocks, four column tiles a wave");
   constexpr int NW = WAVES_M * WAVES_N;
@@ -488,45 +488,6 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WAVES_M, wn = wave / WAVES_M;
-  int pid = blockIdx.x;
-  int nb = gridDim.x, n_tiles_m = tiles_m;
-  if constexpr (GROUPED) {
-    // the grid is sized for the worst case; the tiles that exist are the first tile_tab[tiles_m].x of the table, and
-    // only their workgroups are spread over the dies (the rest, the highest block ids, leave at once)
-    n_tiles_m = min(tile_tab[tiles_m].x, tiles_m);
-    nb = n_tiles_m * tiles_n;
-    if (pid >= nb) return;
-  }
-  {
-    const int q = nb / N_XCD, rem = nb % N_XCD;
-    const int xcd = pid % N_XCD, loc = pid / N_XCD;
-    pid = (xcd < rem) ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
-  }
-  int first_m, gsz, in_group;
-  if constexpr (GROUPED) {
-    // A scheduling group is of one expert, and a balanced expert is one group: a die then streams that expert's W once.  In
-    // groups of four, which straddle experts, gate/up over 16384 rows of eight experts (8B widths) took 2949 us (2833), down
-    // 1687 (1650).  The workgroups of a group are one range of ids, whatever its size.
-    const int packed = tile_tab[pid / tiles_n].w;
-    first_m = packed & ((1 << MOE_GROUP_SHIFT) - 1);
-    gsz = packed >> MOE_GROUP_SHIFT;
-    in_group = pid - first_m * tiles_n;
-  } else {
-    const int per_group = GROUP_M * tiles_n, group = pid / per_group;
-    first_m = group * GROUP_M;
-    gsz = min(GROUP_M, n_tiles_m - first_m);
-    in_group = pid - group * per_group;
-  }
-  int m0 = (first_m + in_group % gsz) * BM, M = M_all;
-  const int n0 = (in_group / gsz) * BN;
-  const bf16_t* W = W_all;
-  if constexpr (GROUPED) {
-    const int4 te = tile_tab[first_m + in_group % gsz];
-    if (te.x < 0) return;  // uniform over the workgroup, before any barrier
-    m0 = te.y;
-    M = te.z;
-    W = W_all + (int64_t)te.x * w_group_stride;
-  }
 
   f32x4 acc[TN][TM];
 #pragma unroll
@@ -776,7 +737,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   // ---- epilogue through the wave's own LDS region, 32 rows at a time (as in the 32x32 kernel) ----
   constexpr int ROW_F = 64 + 4;
   float* stage_f = (float*)smem_raw + wave * (32 * ROW_F);
-  static_assert(NW * 32 * ROW_F * 4 <= NSTAGE * (BM + BN) * BK * 2, "staging region fits the tile ring");
+  static_assert(NW * 32 * ROW_F * 4 <= lds16<BM, BN, DIRECT>(), "staging region fits the tile ring");
   const bool swiglu = (epi & EPI_SWIGLU) != 0;
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));  // indices derived after the k loop: not kept in registers across it
@@ -898,6 +859,69 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
       }
     }
     __builtin_amdgcn_wave_barrier();
+  }
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false, bool ROPE = false, bool DIRECT = false, bool LOW = false>
+__global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
+    gemm16_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W_all, int64_t ldw,
+                       void* C, int64_t ldc, const void* __restrict__ R, int64_t ldr, int M_all, int N, int K,
+                       int epi, int tiles_m, int tiles_n, int kt_per_split, const int4* __restrict__ tile_tab,
+                       int64_t w_group_stride, const int32_t* __restrict__ a_row, int a_rows, RopeOut ro) {
+  int pid = blockIdx.x;
+  int nb = gridDim.x;
+  bool behind = false;
+  if constexpr (GROUPED) {
+    // the grid is sized for the worst case; the tiles that exist are the first ones of the table, and only their
+    // workgroups are spread over the dies (the rest, the highest block ids, leave at once).  Low tiles that stand behind all
+    // others are spread by themselves.
+    const int4 counts = tile_tab[tiles_m];
+    nb = min(counts.x, tiles_m) * tiles_n;
+    if (LOW && pid >= nb) {
+      behind = true;
+      pid -= nb;
+      nb = min(counts.y, tiles_m - min(counts.x, tiles_m)) * ((N + MOE_LOW_COLS - 1) / MOE_LOW_COLS);
+    }
+    if (pid >= nb) return;
+  }
+  {
+    const int q = nb / N_XCD, rem = nb % N_XCD;
+    const int xcd = pid % N_XCD, loc = pid / N_XCD;
+    pid = (xcd < rem) ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
+  }
+  if constexpr (GROUPED) {
+    int4 te;
+    int n0;
+    if (behind) {
+      const int cols = (N + MOE_LOW_COLS - 1) / MOE_LOW_COLS;
+      te = tile_tab[min(tile_tab[tiles_m].x, tiles_m) + pid / cols];
+      n0 = pid % cols * MOE_LOW_COLS;
+    } else {
+      // A scheduling group is of one expert, and a balanced expert is one group: a die then streams that expert's W once.  In
+      // groups of four, which straddle experts, gate/up over 16384 rows of eight experts (8B widths) took 2949 us (2833), down
+      // 1687 (1650).  The workgroups of a group are one range of ids, whatever its size.
+      const int packed = tile_tab[pid / tiles_n].w;
+      const int first_m = packed & ((1 << MOE_GROUP_SHIFT) - 1), gsz = packed >> MOE_GROUP_SHIFT, in_group = pid - first_m * tiles_n;
+      te = tile_tab[first_m + in_group % gsz];
+      n0 = in_group / gsz * BN;
+    }
+    if (te.x < 0) return;  // uniform over the workgroup, before any barrier
+    const bf16_t* W = W_all + (int64_t)te.x * w_group_stride;
+    if constexpr (LOW) {
+      if (behind) {
+        gemm16_tile<MOE_LOW_ROWS, MOE_LOW_COLS, 4, 2, WB, GROUPED, ROPE, false>(A, lda, W, ldw, C, ldc, R, ldr, te.y, n0, te.z, M_all, N, K, epi,
+                                                                               kt_per_split, a_row, a_rows, ro);
+        return;
+      }
+    }
+    gemm16_tile<BM, BN, WAVES_M, WAVES_N, WB, GROUPED, ROPE, DIRECT>(A, lda, W, ldw, C, ldc, R, ldr, te.y, n0, te.z, M_all, N, K, epi,
+                                                                    kt_per_split, a_row, a_rows, ro);
+  } else {
+    const int per_group = GROUP_M * tiles_n, group = pid / per_group, first_m = group * GROUP_M;
+    const int gsz = min(GROUP_M, tiles_m - first_m), in_group = pid - group * per_group;
+    gemm16_tile<BM, BN, WAVES_M, WAVES_N, WB, GROUPED, ROPE, DIRECT>(A, lda, W_all, ldw, C, ldc, R, ldr, (first_m + in_group % gsz) * BM,
+                                                                    in_group / gsz * BN, M_all, M_all, N, K, epi, kt_per_split, a_row,
+                                                                    a_rows, ro);
   }
 }
 
@@ -1111,12 +1135,12 @@ hipError_t launch16(int bm, const void* A, int64_t lda, const void* W, int64_t l
 #undef DSK_FORM
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool DIRECT>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool DIRECT, bool LOW = false>
 hipError_t launch16_grouped(const void* A, int64_t lda, const int32_t* a_row, int a_rows, const void* W, int64_t ldw,
                             int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi, const int4* tile_tab, int tile_rows,
-                            hipStream_t s) {
-  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, true, true, false, DIRECT>;
-  constexpr int lds = lds16<BM, BN, DIRECT>();
+                            int low_rows, hipStream_t s) {
+  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, true, true, false, DIRECT, LOW>;
+  constexpr int own = lds16<BM, BN, DIRECT>(), of_low = lds16<MOE_LOW_ROWS, MOE_LOW_COLS, false>(), lds = LOW && of_low > own ? of_low : own;
   static bool configured = false;
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1124,7 +1148,8 @@ hipError_t launch16_grouped(const void* A, int64_t lda, const int32_t* a_row, in
     configured = true;
   }
   const int tiles_n = (N + BN - 1) / BN;
-  DSK_LAUNCH_TIMED(kern, dim3(tile_rows * tiles_n), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
+  const int low_n = (N + MOE_LOW_COLS - 1) / MOE_LOW_COLS;
+  DSK_LAUNCH_TIMED(kern, dim3(tile_rows * tiles_n + low_rows * (low_n - tiles_n)), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
                    (const bf16_t*)W, ldw, C, ldc, (const void*)nullptr, (int64_t)0, 0, N, K, epi, tile_rows, tiles_n,
                    K / BK, tile_tab, w_group_stride, a_row, a_rows, RopeOut{});
   g_direct_launches += DIRECT;
@@ -1317,16 +1342,18 @@ int moe_tile_rows_for(int64_t n_rows, int E) {
 // epi: EPI_SWIGLU (C bf16 [slots, N/2]) or EPI_C_F32 / EPI_STORE (C [slots, N]); no residual.
 hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw,
                                     int w_blocks, int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
-                                    const void* tile_tab, int tile_m, int tile_rows, int64_t rows_per_expert, hipStream_t s) {
+                                    const void* tile_tab, int tile_m, int tile_rows, int low_rows, int64_t rows_per_expert, hipStream_t s) {
   if (tile_rows <= 0) return hipSuccess;
   // (a model the tensor-core path takes has its weights in blocks)
   if (!w_blocks || K < BK || K % BK || N % 64 || (lda & 7) || (ldw & 7) || (ldc & 3) || (epi & EPI_RESIDUAL)) return hipErrorNotSupported;
   if (a_rows * lda * 2 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 2 >= ((int64_t)1 << 32)) return hipErrorNotSupported;
+  const bool direct = w_direct(rows_per_expert, K, false);
   auto f = tile_m == 128   ? launch16_grouped<128, 256, 2, 4, false>
            : tile_m == 192 ? launch16_grouped<192, 256, 2, 4, false>
-           : w_direct(rows_per_expert, K, false) ? launch16_grouped<256, 256, 2, 4, true>
-                                               : launch16_grouped<256, 256, 2, 4, false>;
-  return f(A, lda, a_row, (int)a_rows, W, ldw, w_group_stride, C, ldc, N, K, epi, (const int4*)tile_tab, tile_rows, s);
+           : low_rows      ? (direct ? launch16_grouped<256, 256, 2, 4, true, true> : launch16_grouped<256, 256, 2, 4, false, true>)
+           : direct        ? launch16_grouped<256, 256, 2, 4, true>
+                           : launch16_grouped<256, 256, 2, 4, false>;
+  return f(A, lda, a_row, (int)a_rows, W, ldw, w_group_stride, C, ldc, N, K, epi, (const int4*)tile_tab, tile_rows, low_rows, s);
 }
 
 // More than 64 rows, dense operands: whether the contraction is split, i.e. a reduction runs behind the projection, which

@@ -7,6 +7,7 @@
 
 namespace {
 
+
 constexpr int MAX_K = DSK_MOE_MAX_TOP_K;
 
 template <typename T> struct Vec8;
@@ -175,13 +176,31 @@ __global__ void __launch_bounds__(256) moe_route_mfma_kernel(const bf16_t* __res
 // first slot of its own rows and the first row tile of its own tiles, then walks the entries in order and gives the
 // j-th entry of expert e the slot first + j.  slot_of[entry] = slot, src_token[slot] = token.  tile_tab[r], r <
 // tile_rows_max: {expert, first slot of the tile, end of the expert's slots, first tile of its scheduling group | tiles of
-// that << MOE_GROUP_SHIFT}, the tiles of all experts back to back,
-// expert -1 past the last tile; tile_tab[tile_rows_max].x = number of tiles (the GEMM spreads exactly those over the
-// chip: a grid sized for the worst case would leave the dies that get its empty end idle).
+// that << MOE_GROUP_SHIFT}, the tiles of all experts back to back, behind them low ones,
+// expert -1 past the last tile; tile_tab[tile_rows_max] = {number of tiles, number of low ones} (the GEMM spreads exactly those over the
+// chip: a grid sized for the worst case would leave the dies that get its empty end idle).  A second table behind the first is
+// the down projection's, tiles_n column tiles wide.
+//
+// Low tiles (128 x 128): down has few column tiles, so an expert's partly filled last tiles decide how many rounds of workgroups it
+// takes; balanced experts with whole tiles to the row fill whole rounds, and the few rows that some have beyond them cost one more.
+// Where an expert's last rows fit a low tile, and the rounds are fewer so (a low tile taken for half a high one), they run as low
+// tiles behind all others.  The rule is on the counts, i.e. on the device.  us, eight experts of the 8B widths, down over 2048, 4096, 6300,
+// 8192 tokens: 614 -> 467, 938 -> 812, 1327 -> 1181, 1681 -> 1515; 1100, 2400 and 3200 tokens, where the rounds are as many, keep the
+// high ones (low ones as 128 x 256 tiles whatever the rounds: 2400 tokens 635 -> 696).  Half as wide as the others because what a
+// low tile takes is its stream of W, and one compute unit draws only so much: 128 x 256 tiles took 526, 862, 1288, 1559.
+// Gate/up has seven times the column tiles and streams an expert's W once for all its row tiles: low tiles behind the others stream
+// it again (2400 tokens 1069 -> 1077), low tiles in the expert's group 1069 -> 1024 there, but 843 -> 890 over 2048 tokens.
+__host__ __device__ inline bool moe_low_tiles(int n_plain, int n_high, int n_low, int tiles_n) {
+  constexpr int CUS = 256;
+  if (n_low == 0) return false;
+  const int64_t plain = ((int64_t)n_plain * tiles_n + CUS - 1) / CUS, high = (int64_t)n_high * tiles_n;
+  const int64_t rounds = (high + CUS - 1) / CUS, left = (int64_t)n_low * tiles_n - (rounds * CUS - high);  // what the last round has no room for
+  return 2 * rounds + (left > 0 ? (2 * left + CUS - 1) / CUS : 0) < 2 * plain;
+}
 constexpr int PLACE_T = 1024;  // threads: the walk is a chain of rounds, wider ones make it shorter (256: 23 us at 8192 tokens)
 __global__ void __launch_bounds__(PLACE_T) moe_place_kernel(const int32_t* __restrict__ experts, int32_t* __restrict__ slot_of,
                                                         int32_t* __restrict__ src_token, int4* __restrict__ tile_tab,
-                                                        int n_entries, int top_k, int E, int tile_m, int tile_rows_max) {
+                                                        int n_entries, int top_k, int E, int tile_m, int tiles_n, int tile_rows_max) {
   __shared__ int hist[DSK_MOE_MAX_EXPERTS];
   __shared__ int wave_cnt[2][4][PLACE_T / 64];
   const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -196,25 +215,48 @@ __global__ void __launch_bounds__(PLACE_T) moe_place_kernel(const int32_t* __res
       if ((unsigned)x[q] < (unsigned)E) atomicAdd(&hist[x[q]], 1);  // the router only writes experts below E
   }
   __syncthreads();
-  int first = 0, first_tile = 0;
-  for (int x = 0; x < e; ++x) {
-    first += hist[x];
-    first_tile += (hist[x] + tile_m - 1) / tile_m;
+  // an expert's tiles, and whether its last one may be low
+  __shared__ int tiles_of[DSK_MOE_MAX_EXPERTS];
+  if (tid < E) {
+    const int plain = (hist[tid] + tile_m - 1) / tile_m;
+    const bool low = tile_m == MOE_HIGH_ROWS && plain > 0 && hist[tid] - (plain - 1) * tile_m <= MOE_LOW_ROWS;
+    tiles_of[tid] = 2 * plain + low;
   }
-  const int mine = hist[e];
-  const int my_tiles = (mine + tile_m - 1) / tile_m;
-  // scheduling groups: an expert's tiles in as few as the most allows, the first ones longer by a tile where they are not equal
-  const int n_groups = max((my_tiles + MOE_GROUP_MOST - 1) / MOE_GROUP_MOST, 1), least = my_tiles / n_groups;
-  const int longer = (my_tiles - n_groups * least) * (least + 1);  // tiles of the longer ones
-  for (int r = tid; r < my_tiles; r += PLACE_T) {
-    const int size = r < longer ? least + 1 : least, from = r < longer ? 0 : longer, g0 = from + (r - from) / size * size;
-    if (first_tile + r < tile_rows_max)
-      tile_tab[first_tile + r] = make_int4(e, first + r * tile_m, first + mine, (first_tile + g0) | size << MOE_GROUP_SHIFT);
+  __syncthreads();
+  // [0]: without low tiles; [1]: with them
+  int first = 0, n_high[2] = {0, 0}, high0[2] = {0, 0}, n_low = 0, low0 = 0;
+  for (int x = 0; x < E; ++x) {
+    const int plain = tiles_of[x] >> 1, low = tiles_of[x] & 1;
+    if (x == e) {
+      high0[0] = n_high[0];
+      high0[1] = n_high[1];
+      low0 = n_low;
+    }
+    if (x < e) first += hist[x];
+    n_high[0] += plain;
+    n_high[1] += plain - low;
+    n_low += low;
   }
-  if (e == E - 1) {
-    for (int r = first_tile + my_tiles + tid; r < tile_rows_max; r += PLACE_T) tile_tab[r] = make_int4(-1, 0, 0, 0);
-    if (tid == 0) tile_tab[tile_rows_max] = make_int4(min(first_tile + my_tiles, tile_rows_max), 0, 0, 0);
-  }
+  const int mine = hist[e], my_low = tiles_of[e] & 1, my_high[2] = {tiles_of[e] >> 1, (tiles_of[e] >> 1) - my_low};
+  // One table: the expert's `high` tiles from entry at0 on, and its low one at low_at (< 0: none); n_at, n_behind: all experts' tiles of
+  // either kind.  Scheduling groups: an expert's tiles in as few as the most allows, the first ones longer by a tile where they are
+  // not equal.
+  auto write_table = [&](int4* tab, int at0, int high, int low_at, int n_at, int n_behind) {
+    const int n_groups = max((high + MOE_GROUP_MOST - 1) / MOE_GROUP_MOST, 1), least = high / n_groups;
+    const int longer = (high - n_groups * least) * (least + 1);  // tiles of the longer ones
+    for (int r = tid; r < high; r += PLACE_T) {
+      const int size = r < longer ? least + 1 : least, from = r < longer ? 0 : longer, g0 = from + (r - from) / size * size;
+      if (at0 + r < tile_rows_max) tab[at0 + r] = make_int4(e, first + r * tile_m, first + mine, (at0 + g0) | size << MOE_GROUP_SHIFT);
+    }
+    if (tid == 0 && low_at >= 0 && low_at < tile_rows_max) tab[low_at] = make_int4(e, first + high * tile_m, first + mine, 0);
+    if (e == E - 1) {
+      for (int r = n_at + n_behind + tid; r < tile_rows_max; r += PLACE_T) tab[r] = make_int4(-1, 0, 0, 0);
+      if (tid == 0) tab[tile_rows_max] = make_int4(min(n_at, tile_rows_max), min(n_behind, max(tile_rows_max - n_at, 0)), 0, 0);
+    }
+  };
+  write_table(tile_tab, high0[0], my_high[0], -1, n_high[0], 0);
+  const bool low = moe_low_tiles(n_high[0], n_high[1], n_low, tiles_n);
+  write_table(tile_tab + tile_rows_max + 1, high0[low], my_high[low], low && my_low ? n_high[1] + low0 : -1, n_high[low], low ? n_low : 0);
   // rounds of 4 * PLACE_T entries, four groups of PLACE_T in entry order; a thread's four entries are requested together (the
   // walk is a chain of short rounds: what it takes is the round trips to memory)
   int running = 0;
@@ -302,10 +344,10 @@ hipError_t launch_moe_route(int dtype, const void* xn, const void* wr, int32_t* 
 }
 
 hipError_t launch_moe_place(const int32_t* experts, int32_t* slot_of, int32_t* src_token, void* tile_tab, int n, int top_k,
-                            int E, int tile_m, int tile_rows_max, hipStream_t s) {
+                            int E, int tile_m, int tiles_n, int tile_rows_max, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(moe_place_kernel, dim3(E), dim3(PLACE_T), 0, s, experts, slot_of, src_token, (int4*)tile_tab, n * top_k,
-                     top_k, E, tile_m, tile_rows_max);
+                     top_k, E, tile_m, tiles_n, tile_rows_max);
   return hipGetLastError();
 }
 

@@ -262,6 +262,30 @@ def host_moe_layer(shape, seed, layer):
             for k, v in w.items()}
 
 
+# 4096 tokens on four experts of 2049, 2176, 2048 and 1919 rows: whole tiles, and last tiles of 1, 128 and 127 rows, which leave the down
+# projection (eight column tiles) one round of workgroups instead of two; a width below and one of that form of the
+# tiles that takes its weights straight to registers.  Inputs decide the routing, so every sampled row counts.
+@pytest.mark.parametrize("ffn", [192, 3584])
+def test_last_rows_of_experts_in_low_tiles(G, monkeypatch, ffn):
+    shape = synth.ModelShape(1, 2048, 16, 4, 128, ffn, 500000.0, 1e-5, "bf16", 4, 2)
+    T, counts, lens = 4096, [2049, 2176, 2048, 1919], [256] * 16
+    slots = np.repeat(np.arange(4), counts)
+    pick = np.stack([slots[:T], slots[T:]], axis=1)[np.random.default_rng(1).permutation(T)]   # no expert twice
+    w = host_moe_layer(shape, synth.SEED_RECEIVER, 0)
+    r = w["router"] / np.linalg.norm(w["router"], axis=1, keepdims=True)
+    x = synth.hidden_states(shape, T).astype(np.float32) + (16.0 * r[pick[:, 0]] + 12.0 * r[pick[:, 1]]).astype(np.float32)
+    x = torch.from_numpy(x).to(torch.bfloat16)
+    rows = sorted({0, 1, T // 2, *range(T - 24, T), *(int(np.flatnonzero((pick == e).any(1))[i]) for e in range(4) for i in (0, -129, -128, -1))})
+    rec = RouteRecorder(monkeypatch, shape.top_k, MARGIN["bf16"])
+    h_ref, _, _ = O.prefix_layer(oracle_config(shape), w, x.double().numpy(), synth.packed_positions(lens), synth.cu_seqlens(lens), rows=rows)
+    assert not rec.calls[0].any()
+    with G.GpuModel(shape, T) as m:
+        m.init_random(synth.SEED_RECEIVER)
+        _, h = m.partial(x.cuda(), 0, 1, None, lens)
+        torch.cuda.synchronize()
+        assert O.max_rel_err(G.to_np(h)[rows], h_ref) <= TOL["bf16"]
+
+
 def test_mixtral_width_layer_over_4096_tokens_and_suffix_pass(G, monkeypatch):
     # Two layers of the Mixtral 8x7B layer shape (d 4096, 32/8 heads, 8 experts of width 14336, top 2), weights from the
     # device generator (bit-identical to the host's).  (a) Layer 0 over 4096 tokens: 8192 expert rows grouped on the
