@@ -493,8 +493,14 @@ int plan_e_chunks(const dsk_model* m, int T, int n_seqs, int* bounds) {
     };
     for (int n = 2048; n < first; n += 256)
       if (whole(n)) first = n;
+    // Less than two chunks of 4096 rows: the first one and the rest.  us, selective prefill and suffix pass over eight layers, two recomputed:
+    // 4608 rows 5497 -> 5126, 6000 rows 6844 -> 6249, 8191 rows 8812 -> 7997.
+    if (T < 2 * rows) {
+      if (T < 2 * first || !whole(T - first) || !whole(T)) return 0;
+      rows = T - first;
+    }
   }
-  if (rows % 256 || T < 2 * rows) return 0;
+  if (first % 256 || T < first + rows) return 0;
   int n = 1 + (T - first) / rows;
   if (n > DSK_MAX_E_CHUNKS) {
     first = rows = ((T + DSK_MAX_E_CHUNKS - 1) / DSK_MAX_E_CHUNKS + 255) / 256 * 256;

@@ -120,3 +120,23 @@ def test_cache_that_is_not_this_devices_memory_is_copied():
         torch.cuda.synchronize()
         assert B.dsk_get_stat("splice_launches") == 0
     assert torch.equal(out.cpu(), kv)
+
+
+# an 8B layer behind a host-resident E cache: the shortest contexts that are chunked, a rest that is not a multiple of a tile, and
+# whole chunks of 4096 rows behind the first; against the layer in one piece, bit for bit
+@pytest.mark.parametrize("T,chunks", [(4607, 0), (4608, 2), (5001, 2), (8191, 2), (9001, 2), (12288, 3)])
+def test_chunked_first_layer_keeps_its_bits(T, chunks):
+    from paper_2411_02820_amd import binding as B
+    from tests import gpu_util as G
+    s = synth.LLAMA_8B
+    shape = synth.ModelShape(1, s.hidden, s.n_q_heads, s.n_kv_heads, s.head_dim, s.ffn, s.rope_base, s.rms_eps, "bf16")
+    x = torch.randn((T, s.hidden), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16).pin_memory()
+    with G.GpuModel(shape, T) as m:
+        m.init_random(synth.SEED_RECEIVER)
+        B.dsk_set_option("reset_stats", 0)
+        kv_c, h_c = m.partial(x, 0, 1, None, [T])
+        torch.cuda.synchronize()
+        assert B.dsk_get_stat("e_cache_chunks") == chunks
+        kv_1, h_1 = m.partial(x.cuda(), 0, 1, None, [T])
+        torch.cuda.synchronize()
+        assert torch.equal(kv_c, kv_1) and torch.equal(h_c, h_1)
