@@ -5,17 +5,21 @@
 // A workgroup of NW waves (4 are used) owns 32*NW query rows of one (sequence, q head); each wave 32 of them.
 // Keys are walked in tiles of 64 cache rows (aligned to multiples of 64), staged in two-stage LDS rings
 // by direct global->LDS loads (global_load_lds_dwordx4):
-//   K tile  [64 keys][dh]   - rows permuted (bits 2 and 3 of the key offset swapped), see below
+//   K tile  [64 keys][dh]   - rows permuted (perm_key), see below
 //   Vt tile [dh][64 keys]   - from a transposed copy of V kept in the model's workspace
 // Both the row permutation and the 16-byte slot swizzle are applied on the global side (which address a
 // lane fetches), since the LDS destination of such a load is fixed by the lane id.
-// Scores are computed transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16 (K rows as the MFMA A
-// operand, Q rows as B): a lane then owns ONE query (column lane%32) and 16 keys per 32-key tile in its
-// accumulator registers, so the softmax row maximum/sum are in-lane reductions plus a single exchange
-// with lane^32.  With the K-row permutation the 8 registers [8t, 8t+8) of a lane are 8 consecutive keys
-// (16t + 8*(lane/32) + 0..7), i.e. exactly the B-operand layout of P^T for O^T += Vt P^T, and the
+// Scores are computed transposed, S^T = K Q^T, with v_mfma_f32_16x16x32_bf16 (K rows as the MFMA A
+// operand, Q rows as B): a lane then owns TWO queries (lane%16 of the wave's two 16-query tiles) and 16 keys of each
+// 64-key tile; a row sum stays in the lane until the end, and a row maximum is exchanged between the four lanes of a query only when
+// one of them is far above the reference.  With the K-row permutation a lane's scores of two neighbouring 16-row tiles are 8
+// consecutive keys (32*half + 8*(lane/16) + 0..7), i.e. exactly the B-operand layout of P^T for O^T += Vt P^T, and the
 // matching Vt fragment is one 16-byte LDS read.  The output accumulator O^T[d][q] keeps the query in the
 // lane as well, so rescaling by the running maximum is a per-lane scalar multiply.
+// Bound: LDS reads (a 1 KB fragment feeds 32 cycles of MFMA, which is what LDS delivers to four SIMDs) and, in a layer, the power
+// limit.  The 16x16x32 instruction sustains some 10 % more flops than the 32x32x16 one there: us a launch, before -> after, one 8B
+// context of 2048 rows 58.2 -> 55.9, 4096 161 -> 153, 8192 545 -> 515 (1067 TFLOP/s causal), 16384 2100 -> 2004; a layer over 16384 rows
+// 7205 -> 7124.  Fragments read three or four ahead instead of two, and a higher wave priority in phase 2: no gain.
 //
 // Few queries against many keys (the suffix pass) would leave most CUs idle, so the key tiles of a
 // workgroup can be split over blockIdx.z; each split writes its unnormalised fp32 output with its running
@@ -29,7 +33,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int BKV = 64;  // keys per tile
@@ -45,8 +48,8 @@ struct AttnParams {
   int k_row_max;   // last cache row that may be read
 };
 
-// MFMA row of key offset u inside a 64-key tile: bits 2 and 3 swapped (an involution)
-__device__ __forceinline__ int perm_key(int u) { return (u & ~0xC) | ((u & 4) << 1) | ((u & 8) >> 1); }
+// key offset inside a 64-key tile that stands in LDS row rho: bits 4, 3, 2 of the row are bits 2, 4, 3 of the key
+__device__ __forceinline__ int perm_key(int rho) { return (rho & 0x23) | ((rho & 0xC) << 1) | ((rho & 0x10) >> 2); }
 
 template <int DH, bool SPLIT, int NW>
 __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p) {
@@ -55,14 +58,14 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
   constexpr int K_RPI = 64 / KCH;         // K rows per wave load instruction
   constexpr int K_INST = BKV / K_RPI / NW; // per wave
   constexpr int V_INST = DH / 8 / NW;     // Vt rows are 64 keys = 8 slots -> 8 rows per instruction
-  constexpr int NKS = DH / 16, NDT = DH / 32;
+  constexpr int NKS = DH / 32, NDT = DH / 16;  // steps of 32 along the head, output tiles of 16
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t* sK = (bf16_t*)smem_raw;        // [2][BKV * DH]  K ring
   bf16_t* sV = sK + 2 * BKV * DH;        // [2][DH * BKV]  Vt ring
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lq = lane & 31, hh = lane >> 5;
+  const int lq = lane & 15, g = lane >> 4;
   // ---- which (head, sequence, query tile).  Workgroups are handed out in blockIdx.x order, round-robin over
   //      the 8 XCDs (each with its own L2).  Late query tiles carry the most key tiles, so they come first for
   //      every head (a heavy workgroup started late would run on alone at the end), and with a head count
@@ -97,10 +100,9 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
   if (q0 >= seq_end) return;              // cannot happen for a well-formed grid
   const int qw0 = q0 + 32 * wave;  // first query row of this wave
   const bool wave_active = qw0 < seq_end;
-  const int qi = min(qw0 + lq, seq_end - 1);  // this lane's query (clamped for the padding rows)
+  const int qi[2] = {min(qw0 + lq, seq_end - 1), min(qw0 + 16 + lq, seq_end - 1)};  // this lane's queries (clamped for the padding rows)
 
   const int own_begin = p.own_row0 + seq_begin;
-  const int lim = p.own_row0 + qi;                                   // last own row this lane's query sees
   const int wave_lim_min = p.own_row0 + min(qw0, seq_end - 1);       // smallest limit in the wave
   const int wave_lim_max = p.own_row0 + min(qw0 + 31, seq_end - 1);  // largest limit in the wave
   const int blk_lim = p.own_row0 + min(q0 + BQ, seq_end) - 1;
@@ -116,12 +118,13 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
     it_end = min(n_tiles, it_begin + per);
   }
 
-  // ---- Q fragments (B operand): query = lane%32, d = 16*ks + 8*(lane/32) .. +7 ----
-  bf16x8 qf[NKS];
-  {
-    const bf16_t* qp = p.q + (int64_t)qi * p.ldq + h * DH + 8 * hh;
+  // ---- Q fragments (B operand): query = 16*qt + lane%16, d = 32*ks + 8*(lane/16) .. +7 ----
+  bf16x8 qf[2][NKS];
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const bf16x8*)(qp + 16 * ks);
+  for (int qt = 0; qt < 2; ++qt) {
+    const bf16_t* qp = p.q + (int64_t)qi[qt] * p.ldq + h * DH + 8 * g;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) qf[qt][ks] = *(const bf16x8*)(qp + 32 * ks);
   }
 
   // ---- tile loads, direct to LDS.  K: LDS row rho (MFMA row) holds key offset perm_key(rho); slot s of a
@@ -195,60 +198,72 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
   int act_end = it_begin;
   if (wave_active) act_end = max(it_begin, min(it_end, nA + wave_lim_max / BKV - tb0 + 1));
 
-  f32x16 o[NDT];
+  f32x4 o[NDT][2];
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
-  // running state: m = row maximum over the tiles scored so far, mc = m * c (0 while no key was visible),
-  // alpha = factor that brings sums and outputs accumulated under the previous maximum to m
-  float m = -INFINITY, mc = 0.f, alpha = 1.f, l = 0.f;
+    for (int qt = 0; qt < 2; ++qt) o[dt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // running state of the lane's two queries: m = reference maximum, mc = m * c (0 while no key was visible), l = sum over this
+  // lane's keys
+  float m[2] = {-INFINITY, -INFINITY}, mc[2] = {0.f, 0.f}, l[2] = {0.f, 0.f};
 
-  constexpr int NQK = 2 * NKS;   // MFMAs of one score tile
-  constexpr int NPV = 4 * NDT;   // MFMAs of one output update
-  // MFMA j of a score tile works on key half j % 2 and head-dim step j / 2, MFMA j of an output update on
-  // d-tile j % NDT and key chunk j / NDT: consecutive MFMAs go to different accumulators
+  constexpr int NF = 4 * NKS;    // K fragments of a tile, each the operand of two MFMAs (one per 16 queries)
+  constexpr int NV = 2 * NDT;    // Vt fragments
+  // fragment j of K: LDS rows 16 * (j % 4) .., head-dim step j / 4; of Vt: d-tile j % NDT, key half j / NDT: consecutive MFMAs go to
+  // different accumulators
   auto k_frag = [&](const bf16_t* kt_s, int j) {
-    const int kt = j % 2, ks = j / 2, row = 32 * kt + lq;
-    return *(const bf16x8*)(kt_s + row * DH + (((2 * ks + hh) ^ kswz(row)) * 8));
+    const int row = 16 * (j % 4) + lq;
+    return *(const bf16x8*)(kt_s + row * DH + (((4 * (j / 4) + g) ^ kswz(row)) * 8));
   };
   auto v_frag = [&](const bf16_t* vt_s, int j) {
-    const int dt = j % NDT, kt = j / NDT / 2, t = (j / NDT) % 2, d = 32 * dt + lq;
-    return *(const bf16x8*)(vt_s + d * BKV + (((4 * kt + 2 * t + hh) ^ vswz(d)) * 8));
+    const int d = 16 * (j % NDT) + lq;
+    return *(const bf16x8*)(vt_s + d * BKV + (((4 * (j / NDT) + g) ^ vswz(d)) * 8));
   };
-  // masks the scores of tile `it` where a key is outside this lane's visible range;
-  // register r of half kt is key r0 + 32*kt + 16*(r/8) + 8*(lane/32) + r%8
-  auto mask = [&](int it, f32x16* s) {
+  // masks the scores of tile `it` where a key is outside the visible range of the lane's query;
+  // register r of row tile kt is key r0 + 32*(kt/2) + 8*(lane/16) + 4*(kt%2) + r
+  auto mask = [&](int it, f32x4 (*s)[2]) {
     const int r0 = tile_row0(it);
     const bool segA = it < nA;
     const int lo = segA ? pre_begin : own_begin;
-    const int hi = segA ? pre_end - 1 : lim;
     const bool full = r0 >= lo && r0 + BKV - 1 <= (segA ? pre_end - 1 : wave_lim_min);
     if (!full) {
-      const int kb = r0 + 8 * hh;
+      const int kb = r0 + 8 * g;
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int qt = 0; qt < 2; ++qt) {
+        const int hi = segA ? pre_end - 1 : p.own_row0 + qi[qt];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = kb + 32 * kt + 16 * (r >> 3) + (r & 7);
-          s[kt][r] = (key >= lo && key <= hi) ? s[kt][r] : -INFINITY;
-        }
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int key = kb + 32 * (kt >> 1) + 4 * (kt & 1) + r;
+            s[kt][qt][r] = (key >= lo && key <= hi) ? s[kt][qt][r] : -INFINITY;
+          }
+      }
     }
   };
-  // the lane's query has its 64 scores of a tile in this lane and in lane^32
+  // A query has its 64 scores of a tile in four lanes (lane%16 alike).
   // The exponentials are taken relative to a reference maximum m that follows the true running maximum
   // lazily: it moves only when the true maximum exceeds it by more than 2^8 in the exponent, so that
   // probabilities stay below 2^8 and the accumulated sums and outputs rarely need rescaling.  The
-  // normalised result does not depend on the reference.
-  auto new_max = [&](float mx) {
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_true = fmaxf(m, mx);
-    const bool keep = (m_true - m) * p.c <= 8.0f;  // false for m = -inf (first visible key)
-    const float m_new = keep ? m : m_true;
-    const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-    alpha = keep ? 1.0f : __builtin_amdgcn_exp2f((m - m_safe) * p.c);
-    mc = m_safe * p.c;
-    m = m_new;
+  // normalised result does not depend on the reference.  While no lane's own maximum is that far above, nothing is exchanged.
+  auto new_max = [&](const float* mx) {
+    const bool far = (mx[0] - m[0]) * p.c > 8.0f || (mx[1] - m[1]) * p.c > 8.0f;  // true for m = -inf and a visible key
+    if (__builtin_amdgcn_ballot_w64(far) == 0) return;
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+      float x = fmaxf(mx[qt], __shfl_xor(mx[qt], 16, 64));
+      x = fmaxf(x, __shfl_xor(x, 32, 64));
+      const float m_true = fmaxf(m[qt], x);
+      const bool keep = (m_true - m[qt]) * p.c <= 8.0f;  // false for m = -inf (first visible key)
+      const float m_new = keep ? m[qt] : m_true;
+      const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+      const float alpha = keep ? 1.0f : __builtin_amdgcn_exp2f((m[qt] - m_safe) * p.c);
+      mc[qt] = m_safe * p.c;
+      m[qt] = m_new;
+      l[qt] *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) o[dt][qt] *= alpha;
+    }
   };
 
   // One key tile.  The matrix pipe and the vector ALU of a SIMD run side by side only when their
@@ -256,77 +271,70 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
   // MFMA by MFMA, with the vector work of the neighbouring tile:
   //   phase 1:  S(it+1) = K(it+1) Q^T      with   P(it) = exp2(S(it) c - m c), row sums, bf16 packing
   //   phase 2:  O^T += Vt(it) P(it)^T       with   row maximum of S(it+1)
-  // s_i holds the masked scores of tile `it` (m, mc, alpha already include it), s_n receives tile it+1.
-  // Fragments are read from LDS two MFMAs ahead.
-  auto tile_step = [&](auto has_next_c, int it, f32x16* s_i, f32x16* s_n) {
+  // s_i holds the masked scores of tile `it` (m, mc already include it), s_n receives tile it+1.
+  // Fragments are read from LDS two ahead.
+  auto tile_step = [&](auto has_next_c, int it, f32x4 (*s_i)[2], f32x4 (*s_n)[2]) {
     constexpr bool HN = decltype(has_next_c)::value;
-    // outputs and sums accumulated so far move to the current maximum (rare after the first tiles of a row)
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
-    }
-    float psum = 0.f;
-    u32x4 pf[2][2];
+    float psum[2] = {0.f, 0.f};
+    u32x4 pf[2][2];  // [key half][query tile]
     {
       const bf16_t* kt_s = sK + ((it + 1 - it_begin) & 1) * BKV * DH;
-      constexpr int EPM = 32 / NQK;
-      bf16x8 kf[NQK];
+      constexpr int PPF = 16 / NF;  // pairs of scores per fragment
+      bf16x8 kf[NF];
       if (HN) {
         kf[0] = k_frag(kt_s, 0);
         kf[1] = k_frag(kt_s, 1);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < NQK; ++j) {
-        if (HN) {
-          if (j + 2 < NQK) kf[j + 2] = k_frag(kt_s, j + 2);
-          const int kt = j % 2, ks = j / 2;
-          if (ks == 0) {
-            const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            s_n[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j], qf[ks], z, 0, 0, 0);
-          } else {
-            s_n[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j], qf[ks], s_n[kt], 0, 0, 0);
-          }
-        }
+      for (int j = 0; j < NF; ++j) {
+        if (HN && j + 2 < NF) kf[j + 2] = k_frag(kt_s, j + 2);
 #pragma unroll
-        for (int e = 0; e < EPM; e += 2) {
-          const int idx = j * EPM + e, kt = idx / 16, r = idx % 16;
-          const float e0 = __builtin_amdgcn_exp2f(s_i[kt][r] * p.c - mc);
-          const float e1 = __builtin_amdgcn_exp2f(s_i[kt][r + 1] * p.c - mc);
-          psum += e0;
-          psum += e1;
+        for (int qt = 0; qt < 2; ++qt)
+          if (HN) {
+            const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+            s_n[j % 4][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[j], qf[qt][j / 4], j < 4 ? z : s_n[j % 4][qt], 0, 0, 0);
+          }
+#pragma unroll
+        for (int e = 0; e < PPF; ++e) {
+          const int idx = j * PPF + e, kt = idx / 4, qt = idx / 2 % 2, r = idx % 2 * 2;
+          const float e0 = __builtin_amdgcn_exp2f(s_i[kt][qt][r] * p.c - mc[qt]);
+          const float e1 = __builtin_amdgcn_exp2f(s_i[kt][qt][r + 1] * p.c - mc[qt]);
+          psum[qt] += e0;
+          psum[qt] += e1;
           bf16x2 pk = {(bf16_t)e0, (bf16_t)e1};
           uint32_t pku = __builtin_bit_cast(uint32_t, pk);
           // keeps this arithmetic between the neighbouring MFMAs (its results are first used in phase 2, and
           // the optimiser would otherwise move it there)
-          asm volatile("" : "+v"(pku), "+v"(psum));
-          pf[kt][r >> 3][(r & 7) >> 1] = pku;
+          asm volatile("" : "+v"(pku), "+v"(psum[qt]));
+          pf[kt >> 1][qt][(kt & 1) * 2 + (r >> 1)] = pku;
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    l = l * alpha + psum;
+    l[0] += psum[0];
+    l[1] += psum[1];
     if (HN) mask(it + 1, s_n);
     {
       const bf16_t* vt_s = sV + ((it - it_begin) & 1) * DH * BKV;
-      constexpr int EPM = 32 / NPV;
-      bf16x8 vf[NPV];
+      constexpr int EPF = 32 / NV;  // scores per fragment
+      bf16x8 vf[NV];
       vf[0] = v_frag(vt_s, 0);
       vf[1] = v_frag(vt_s, 1);
-      float mx = -INFINITY;
+      float mx[2] = {-INFINITY, -INFINITY};
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < NPV; ++j) {
-        if (j + 2 < NPV) vf[j + 2] = v_frag(vt_s, j + 2);
-        const int dt = j % NDT, kt = j / NDT / 2, t = (j / NDT) % 2;
-        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[j], __builtin_bit_cast(bf16x8, pf[kt][t]), o[dt], 0, 0, 0);
+      for (int j = 0; j < NV; ++j) {
+        if (j + 2 < NV) vf[j + 2] = v_frag(vt_s, j + 2);
+        const int dt = j % NDT, hf = j / NDT;
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt)
+          o[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[j], __builtin_bit_cast(bf16x8, pf[hf][qt]), o[dt][qt], 0, 0, 0);
         if (HN) {
 #pragma unroll
-          for (int e = 0; e < EPM; ++e) {
-            const int idx = j * EPM + e;
-            mx = fmaxf(mx, s_n[idx / 16][idx % 16]);
+          for (int e = 0; e < EPF; ++e) {
+            const int idx = j * EPF + e;
+            mx[idx / 16] = fmaxf(mx[idx / 16], s_n[idx % 16 / 4][idx / 16][idx % 4]);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -346,11 +354,11 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
     if (it + 1 < it_end) issue_v(it + 1);
   };
 
-  f32x16 s_a[2], s_b[2];
+  f32x4 s_a[4][2], s_b[4][2];
 #pragma unroll
-  for (int kt = 0; kt < 2; ++kt)
+  for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s_a[kt][r] = s_b[kt][r] = 0.f;
+    for (int qt = 0; qt < 2; ++qt) s_a[kt][qt] = s_b[kt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (it_begin < it_end) {
     // the first two K tiles and the first Vt tile are requested together, behind the Q fragments, and waited for
     // once: one round trip to memory at the start of a workgroup instead of two (the wait is for everything: the
@@ -363,18 +371,21 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
     __syncthreads();
     if (it_begin < act_end) {
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int j = 0; j < NF; ++j) {
+        const bf16x8 kf = k_frag(sK, j);
+        if (j % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // not all fragments at once: registers
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
-          s_a[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(sK, 2 * ks + kt), qf[ks], s_a[kt], 0, 0, 0);
+        for (int qt = 0; qt < 2; ++qt) s_a[j % 4][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[qt][j / 4], s_a[j % 4][qt], 0, 0, 0);
+      }
       mask(it_begin, s_a);
-      float mx = -INFINITY;
+      float mx[2] = {-INFINITY, -INFINITY};
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s_a[kt][r]);
+        for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mx[qt] = fmaxf(mx[qt], s_a[kt][qt][r]);
       new_max(mx);
-      alpha = 1.f;  // nothing accumulated yet
     }
   }
   {
@@ -401,36 +412,32 @@ __global__ void __launch_bounds__(64 * NW, 8 / NW) attn_bf16_kernel(AttnParams p
     for (; it < it_end; ++it) tile_sync(it);
   }
 
-  // ---- store: register 4g+e of d-tile dt is out[q][32dt + 8g + 4*(lane/32) + e] ----
-  const float l_tot = l + __shfl_xor(l, 32, 64);
-  if (wave_active && qw0 + lq < seq_end) {
-    const int64_t qrow = qw0 + lq;
+  // ---- store: register e of d-tile dt is out[q][16*dt + 4*(lane/16) + e] ----
+#pragma unroll
+  for (int qt = 0; qt < 2; ++qt) {
+    float l_tot = l[qt] + __shfl_xor(l[qt], 16, 64);
+    l_tot += __shfl_xor(l_tot, 32, 64);
+    const int64_t qrow = qw0 + 16 * qt + lq;
+    if (!wave_active || qrow >= seq_end) continue;
     if (SPLIT) {
       float* po = p.part_o + ((qrow * p.Hq + h) * p.splits + blockIdx.z) * DH;
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          f32x4 v = {o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
-          *(f32x4*)(po + 32 * dt + 8 * g + 4 * hh) = v;
-        }
-      if (hh == 0) {
+      for (int dt = 0; dt < NDT; ++dt) *(f32x4*)(po + 16 * dt + 4 * g) = o[dt][qt];
+      if (g == 0) {
         float* pm = p.part_ml + ((qrow * p.Hq + h) * p.splits + blockIdx.z) * 2;
-        pm[0] = m;
+        pm[0] = m[qt];
         pm[1] = l_tot;
       }
     } else {
       const float inv = 1.0f / l_tot;
       bf16_t* op = p.out + qrow * p.Hq * DH + h * DH;
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
+      for (int dt = 0; dt < NDT; ++dt) {
+        bf16x4 v;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          bf16x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = (bf16_t)(o[dt][4 * g + e] * inv);
-          *(bf16x4*)(op + 32 * dt + 8 * g + 4 * hh) = v;
-        }
+        for (int e = 0; e < 4; ++e) v[e] = (bf16_t)(o[dt][qt][e] * inv);
+        *(bf16x4*)(op + 16 * dt + 4 * g) = v;
+      }
     }
   }
 }
