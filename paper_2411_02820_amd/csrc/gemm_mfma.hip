@@ -435,6 +435,7 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
 // device; tile_tab[tiles_m] = numbers of tiles that exist, and of low ones behind them; expert < 0: no such tile, the workgroup leaves); the
 // expert's matrix is W + expert * w_group_stride.  a_row (optional): sorted row r is row a_row[r] of A's a_rows rows, so
 // that the rows are read where they are (gathered into a buffer first they cost 38 us more at 8192 tokens).
+// LOW (down): the table may end in low tiles, 128 x 128, for experts' last rows (moe_low_tiles has the rule and its figures).
 // ROPE (the QKV projection, heads of 128, weights in blocks): a wave's 64 columns are 32 rotary pairs of one head (elements
 // p0 .. p0 + 31 and their partners 64 further on: tiles j and j + 2, the same lane and register), so that the epilogue
 // rotates the fp32 sums and writes q to C and k and v straight to their cache rows.  The separate pass read and wrote

@@ -442,7 +442,7 @@ def test_config4_8b_prefix16384_kv_in_pinned_host_memory(G, B):
         e_host = G.to_dev(hidden_host, shape, pinned=True)
         B.dsk_set_option("reset_stats", 0)
         kv_out, h_out = m.partial(e_host, lo, hi, kv_r, [T], n_rows=T + S, flags=B.DSK_DEFER_JOIN)
-        assert B.dsk_get_stat("e_cache_chunks") == 4, "layer 4 follows the E cache in four 4096-row chunks"
+        assert B.dsk_get_stat("e_cache_chunks") == 4, "layer 4 follows the E cache in four chunks"
         xs = device_normal(B, (S, shape.hidden), synth.SEED_SUFFIX, 0)
         hs = m.suffix(xs, kv_out, [T], [S])
         torch.cuda.synchronize()
