@@ -482,6 +482,7 @@ int plan_e_chunks(const dsk_model* m, int T, int n_seqs, int* bounds) {
   if (g_e_chunk_rows < 0 || n_seqs != 1 || c.dtype != DSK_BF16 || g_force_generic || !m->vt) return 0;
   int rows = g_e_chunk_rows, first = rows;
   if (rows == 0) {
+    if (T < 2 * 2048) return 0;  // two of the shortest first chunks below
     first = rows = 4096;
     const int widths[4] = {m->n_qkv, c.hidden, 2 * c.ffn, c.hidden};
     for (int i = 0; i < 4; ++i)
