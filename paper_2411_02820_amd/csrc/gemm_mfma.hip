@@ -461,7 +461,8 @@ struct RopeOut {
 // height, so with two stages they wait for it: W runs further ahead, as far as LDS goes (128 rows 160 KB, 192 rows 144 KB).  us a
 // launch, two stages -> these: 128 rows QKV over 1024 rows 64.4 -> 60.3, O over 1500 rows 73.0 -> 68.3; 192 rows gate/up over 333 rows 81.5
 // -> 77.8 (70B 307.7 -> 296.0), QKV over 1500 rows 73.9 -> 72.7.  256 rows with three stages: 0.5 to 1 % slower (gate/up over 4096 rows
-// 628.8 -> 632.9), so they keep two.  Shares of eight k-tiles lose up to 0.8 us of 17 (O over 96 rows), a layer over 96 rows 0.2 %.
+// 628.8 -> 632.9), so they keep two.  Shares of eight k-tiles gain nothing (O over 96 rows 16.4 and 16.5) or lose (QKV 19.2 and 20.0: the
+// ring is filled at once in front of the loop, and the first k-tile comes with all of it).
 template <int BM> constexpr int w_stages() { return BM == 128 ? 4 : BM == 192 ? 3 : 2; }
 template <int BM, int BN, bool DIRECT> constexpr int lds16() { return (DIRECT ? 4 * BM : NSTAGE * BM + w_stages<BM>() * BN) * BK * 2; }
 // One tile: rows m0 .. of A up to row M, columns n0 .. of the product with W.
@@ -645,10 +646,10 @@ __device__ __forceinline__ void gemm16_tile(const bf16_t* __restrict__ A, int64_
       }
     };
 
-    // Loads return in order.  In front of the loop: tile 0, tile 1, then W alone of the tiles up to WS - 1.
+    // Loads return in order.  In front of the loop: tile 0, tile 1, then W alone of the tiles up to WS - 1; only tile 0 is waited for.
 #pragma unroll
     for (int i = 0; i < PER_TILE; ++i) issue_load(0, 0, 0, 0, i);
-    if (n_kt > WS) {
+    if (n_kt >= WS) {
 #pragma unroll
       for (int i = 0; i < PER_TILE; ++i) issue_load(1, 1, 1, 1, i);
 #pragma unroll
@@ -656,26 +657,31 @@ __device__ __forceinline__ void gemm16_tile(const bf16_t* __restrict__ A, int64_
 #pragma unroll
         for (int i = A_INST; i < PER_TILE; ++i) issue_load(0, 0, u, u, i);
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_TILE + (WS - 2) * W_INST) : "memory");
-    } else {
-      if (n_kt > 1) {
+    } else if (WS > 2 && n_kt > 1) {
 #pragma unroll
-        for (int i = 0; i < PER_TILE; ++i) issue_load(1, 1, 1, 1, i);
+      for (int i = 0; i < PER_TILE; ++i) issue_load(1, 1, 1, 1, i);
+      if (n_kt > 2) {
+#pragma unroll
+        for (int i = A_INST; i < PER_TILE; ++i) issue_load(0, 0, 2, 2, i);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_TILE + W_INST) : "memory");
+      } else {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_TILE) : "memory");
       }
-      for (int u = 2; u < n_kt; ++u)
-#pragma unroll
-        for (int i = A_INST; i < PER_TILE; ++i) issue_load(0, 0, u, u, i);
+    } else {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
+    static_assert(WS >= 2 && WS <= 4, "a contraction shorter than the ring: three k-tiles at most");
     __syncthreads();
 #pragma unroll
     for (int f = 0; f < NF; ++f) read_frag(sA, sW, 0, f);
 
-    // k-tile t (stage w_at of W) brings A of t + 2 (n_ld = A_INST loads) and W of t + WS (n_ld = PER_TILE).  Behind A(t + 1), which the
-    // wait in the middle of k-step 1 is for, come W(t + WS - 1) and the loads issued since; W(t + 1) is older (for t = 0 it is followed
-    // by W of the tiles 2 to WS - 1, no fewer loads).
+    // k-tile t (stage w_at of W) brings A of t + 2 (n_ld = A_INST loads) and W of t + WS (n_ld = PER_TILE).  The wait in the middle of
+    // k-step 1 is for A(t + 1) and W(t + 1).  Behind A(t + 1) come the loads of W that its step issued after it (w_behind: W(t + WS - 1),
+    // or nothing more where W had ended) and the loads issued since; W(t + 1) is older where WS > 2 (for t = 0, where tile 1 ends with it, it is
+    // followed by W of the tiles from 2 on, no fewer loads), and is W(t + WS - 1) itself where WS = 2.
     int w_at = 0;
-    auto tile_step = [&](int t, auto has_next, auto n_ld_) {
-      constexpr int n_ld = n_ld_(), newer = NM / 2 * n_ld / NM + (n_ld == PER_TILE && WS > 2 ? W_INST : 0);
+    auto tile_step = [&](int t, auto has_next, auto n_ld_, auto w_behind) {
+      constexpr int n_ld = n_ld_(), newer = NM / 2 * n_ld / NM + w_behind();
       const int stage = t & 1, w_next = w_at + 1 == WS ? 0 : w_at + 1;
       const bf16_t* a_s = sA + stage * BM * BK;
       const bf16_t* w_s = sW + w_at * BN * BK;
@@ -729,10 +735,15 @@ __device__ __forceinline__ void gemm16_tile(const bf16_t* __restrict__ A, int64_
       w_at = w_next;
     };
     int t = 0;
-    for (; t + WS < n_kt; ++t) tile_step(t, std::true_type{}, std::integral_constant<int, PER_TILE>{});
-    for (; t + 2 < n_kt; ++t) tile_step(t, std::true_type{}, std::integral_constant<int, A_INST>{});
-    if (t + 1 < n_kt) { tile_step(t, std::true_type{}, std::integral_constant<int, 0>{}); ++t; }
-    if (t < n_kt) tile_step(t, std::false_type{}, std::integral_constant<int, 0>{});
+    constexpr std::integral_constant<int, 0> none{};
+    constexpr std::integral_constant<int, A_INST> a_only{};
+    constexpr std::integral_constant<int, PER_TILE> a_and_w{};
+    constexpr std::integral_constant<int, (WS > 2 ? W_INST : 0)> w_last{};
+    for (; t + WS < n_kt; ++t) tile_step(t, std::true_type{}, a_and_w, w_last);
+    if (WS > 2 && t + 2 < n_kt) { tile_step(t, std::true_type{}, a_only, w_last); ++t; }
+    if (WS > 3 && t + 2 < n_kt) { tile_step(t, std::true_type{}, a_only, none); ++t; }
+    if (t + 1 < n_kt) { tile_step(t, std::true_type{}, none, none); ++t; }
+    if (t < n_kt) tile_step(t, std::false_type{}, none, none);
   }
 
   // ---- epilogue through the wave's own LDS region, 32 rows at a time (as in the 32x32 kernel) ----

@@ -54,7 +54,7 @@ def test_linear_bf16_medium_rows(B, M, N, K, residual, plan):
 
 # contractions of one k-tile up to more than the stages of W that a lower tile has (four and three): the bits of the 256-row tiles,
 # whose sums have the same order
-@pytest.mark.parametrize("K", [64, 128, 192, 256, 320, 384, 512])
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 320, 384, 448, 512, 576])
 @pytest.mark.parametrize("M,N,bm", [(65, 64, 128), (200, 516, 128), (4200, 4612, 192)])
 def test_lower_tiles_run_ahead_on_w(B, M, N, bm, K):
     assert B.dsk_gemm_plan(M, N, K, False) == (bm, 1, 0, 0)
