@@ -461,12 +461,15 @@ struct RopeOut {
 // height, so with two stages they wait for it: W runs further ahead, as far as LDS goes (128 rows 160 KB, 192 rows 144 KB).  us a
 // launch, two stages -> these: 128 rows QKV over 1024 rows 64.4 -> 60.3, O over 1500 rows 73.0 -> 68.3; 192 rows gate/up over 333 rows 81.5
 // -> 77.8 (70B 307.7 -> 296.0), QKV over 1500 rows 73.9 -> 72.7.  256 rows with three stages: 0.5 to 1 % slower (gate/up over 4096 rows
-// 628.8 -> 632.9), so they keep two.  Shares of eight k-tiles gain nothing (O over 96 rows 16.4 and 16.5) or lose (QKV 19.2 and 20.0: the
-// ring is filled at once in front of the loop, and the first k-tile comes with all of it).
+// 628.8 -> 632.9), so they keep two.  Up to 128 rows of a dense projection keep two as well: one row tile streams W once, from HBM,
+// and what fills a longer ring in front of the loop holds up the first k-tile.  us, four stages -> two: 96 rows QKV 19.9 -> 19.0, O 17.0 ->
+// 16.3, down 32.3 -> 31.9, 70B O 37.4 -> 34.4, a 2048-wide shape's down 16.0 -> 14.8; over 128 rows O 17.7 -> 17.0, 70B O 39.2 -> 36.0,
+// QKV 20.8 and 70B QKV 41.9 -> 42.4.  From 129 rows on four: over 160 rows QKV 22.6 -> 22.2, O 17.6 -> 18.2, a layer the same; 230 rows
+// 208.5 -> 205.6.
 template <int BM> constexpr int w_stages() { return BM == 128 ? 4 : BM == 192 ? 3 : 2; }
-template <int BM, int BN, bool DIRECT> constexpr int lds16() { return (DIRECT ? 4 * BM : NSTAGE * BM + w_stages<BM>() * BN) * BK * 2; }
+template <int BM, int BN, bool DIRECT, int WS = w_stages<BM>()> constexpr int lds16() { return (DIRECT ? 4 * BM : NSTAGE * BM + WS * BN) * BK * 2; }
 // One tile: rows m0 .. of A up to row M, columns n0 .. of the product with W.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED, bool ROPE, bool DIRECT>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED, bool ROPE, bool DIRECT, int WS = w_stages<BM>()>
 __device__ __forceinline__ void gemm16_tile(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W, int64_t ldw, void* C,
                                             int64_t ldc, const void* __restrict__ R, int64_t ldr, int m0, int n0, int M, int M_all, int N,
                                             int K, int epi, int kt_per_split, const int32_t* __restrict__ a_row, int a_rows,
@@ -485,7 +488,6 @@ __device__ __forceinline__ void gemm16_tile(const bf16_t* __restrict__ A, int64_
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t* sA = (bf16_t*)smem_raw;
   bf16_t* sW = sA + NSTAGE * BM * BK;  // [WS][BN][BK], not DIRECT
-  constexpr int WS = w_stages<BM>();
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -749,7 +751,7 @@ __device__ __forceinline__ void gemm16_tile(const bf16_t* __restrict__ A, int64_
   // ---- epilogue through the wave's own LDS region, 32 rows at a time (as in the 32x32 kernel) ----
   constexpr int ROW_F = 64 + 4;
   float* stage_f = (float*)smem_raw + wave * (32 * ROW_F);
-  static_assert(NW * 32 * ROW_F * 4 <= lds16<BM, BN, DIRECT>(), "staging region fits the tile ring");
+  static_assert(NW * 32 * ROW_F * 4 <= lds16<BM, BN, DIRECT, WS>(), "staging region fits the tile ring");
   const bool swiglu = (epi & EPI_SWIGLU) != 0;
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));  // indices derived after the k loop: not kept in registers across it
@@ -874,7 +876,8 @@ __device__ __forceinline__ void gemm16_tile(const bf16_t* __restrict__ A, int64_
   }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false, bool ROPE = false, bool DIRECT = false, bool LOW = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool GROUPED = false, bool ROPE = false, bool DIRECT = false, bool LOW = false,
+          int WS = w_stages<BM>()>
 __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
     gemm16_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W_all, int64_t ldw,
                        void* C, int64_t ldc, const void* __restrict__ R, int64_t ldr, int M_all, int N, int K,
@@ -931,9 +934,9 @@ __global__ void __launch_bounds__(WAVES_M* WAVES_N * 64)
   } else {
     const int per_group = GROUP_M * tiles_n, group = pid / per_group, first_m = group * GROUP_M;
     const int gsz = min(GROUP_M, tiles_m - first_m), in_group = pid - group * per_group;
-    gemm16_tile<BM, BN, WAVES_M, WAVES_N, WB, GROUPED, ROPE, DIRECT>(A, lda, W_all, ldw, C, ldc, R, ldr, (first_m + in_group % gsz) * BM,
-                                                                    in_group / gsz * BN, M_all, M_all, N, K, epi, kt_per_split, a_row,
-                                                                    a_rows, ro);
+    gemm16_tile<BM, BN, WAVES_M, WAVES_N, WB, GROUPED, ROPE, DIRECT, WS>(A, lda, W_all, ldw, C, ldc, R, ldr, (first_m + in_group % gsz) * BM,
+                                                                        in_group / gsz * BN, M_all, M_all, N, K, epi, kt_per_split, a_row,
+                                                                        a_rows, ro);
   }
 }
 
@@ -1098,11 +1101,11 @@ bool w_direct(int64_t rows, int K, bool gate_up) {
   return K >= 3584 && rows > 256;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool DIRECT = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool WB, bool DIRECT = false, int WS = w_stages<BM>()>
 hipError_t launch16_form(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc, const void* R, int64_t ldr,
                          int M, int N, int K, int epi, int splits, int kt_per_split, hipStream_t s) {
-  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, WB, false, false, DIRECT>;
-  constexpr int lds = lds16<BM, BN, DIRECT>();
+  auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, WB, false, false, DIRECT, false, WS>;
+  constexpr int lds = lds16<BM, BN, DIRECT, WS>();
   static bool configured = false;
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1138,12 +1141,12 @@ hipError_t launch16_rope(const void* A, const void* W, void* qkv, const RopeOut&
 // bm: rows of the tile (128, 192 or 256; 256 columns).  splits > 1: fp32 partial planes in C, epi = EPI_C_F32.
 hipError_t launch16(int bm, const void* A, int64_t lda, const void* W, int64_t ldw, int w_blocks, void* C, int64_t ldc, const void* R,
                     int64_t ldr, int M, int N, int K, int epi, int splits, int kt_per_split, hipStream_t s) {
-#define DSK_FORM(BM)                                                                                                      \
-  (w_blocks ? launch16_form<BM, 256, 2, 4, true>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, splits, kt_per_split, s)   \
-            : launch16_form<BM, 256, 2, 4, false>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, splits, kt_per_split, s))
+#define DSK_FORM(BM, WS)                                                                                                             \
+  (w_blocks ? launch16_form<BM, 256, 2, 4, true, false, WS>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, splits, kt_per_split, s)   \
+            : launch16_form<BM, 256, 2, 4, false, false, WS>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, splits, kt_per_split, s))
   if (bm == 256 && w_blocks && splits == 1 && w_direct(M, K, epi & EPI_SWIGLU))
     return launch16_form<256, 256, 2, 4, true, true>(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, epi, 1, kt_per_split, s);
-  return bm == 128 ? DSK_FORM(128) : bm == 192 ? DSK_FORM(192) : DSK_FORM(256);
+  return bm == 128 ? (M <= 128 ? DSK_FORM(128, 2) : DSK_FORM(128, 4)) : bm == 192 ? DSK_FORM(192, 3) : DSK_FORM(256, 2);
 #undef DSK_FORM
 }
 

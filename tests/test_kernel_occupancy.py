@@ -23,7 +23,7 @@ def test_fp32_qkv_on_medium_tiles_is_no_heavier_than_the_plain_projection():
 
 
 def test_lower_tiles_do_not_wait_for_w_that_is_not_due(tmp_path):
-    # GEMM tiles of 128 and 192 rows, W through LDS with stages ahead (four and three).  Loads return in order, so a wait names how many
+    # GEMM tiles of 128 and 192 rows, W through LDS with stages ahead (four and three; none, i.e. two, up to 128 rows).  Loads return in order, so a wait names how many
     # may be outstanding.  In the middle of a k-tile half of the loads of A (a k-tile is a loads of A and w of W to a wave) have gone
     # out behind A of the next one, and, until W has ended for a whole k-tile, w loads of W that are not due yet.  In front of the loop
     # only the first k-tile is due, with fewer k-tiles than stages too.
@@ -31,15 +31,15 @@ def test_lower_tiles_do_not_wait_for_w_that_is_not_due(tmp_path):
     r = subprocess.run([build.HIPCC, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "gemm_mfma.hip"), "-o", str(asm)],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
-    seen = 0
+    seen = []
     for name, body in re.findall(r"^(\S*gemm16_bf16_kernelI\S+):(.*?)^\.Lfunc_end", asm.read_text(), re.S | re.M):
-        bm, bn, wm, wn = (int(v) for v in re.findall(r"Li(\d+)E", name)[:4])
+        bm, bn, wm, wn, stages = (int(v) for v in re.findall(r"Li(\d+)E", name))
         if bm == 256:
             continue
         waits = [int(v) for v in re.findall(r"ASMSTART\s+s_waitcnt vmcnt\((\d+)\)", body)]
-        a, w, ahead = bm // (8 * wm * wn), bn // (8 * wm * wn), {128: 4, 192: 3}[bm] - 2
-        loop = {a // 2 + w, a // 2} if ahead == 2 else {a // 2 + w}            # the k-tiles that bring A alone
+        a, w, ahead = bm // (8 * wm * wn), bn // (8 * wm * wn), stages - 2
+        loop = [set(), {a // 2 + w}, {a // 2 + w, a // 2}][ahead]              # the k-tiles that bring A alone
         front = {a + w + u * w for u in range(ahead + 1)}
-        assert loop | front | {(a + w) // 2 + w, 0} == set(waits), (name, waits)
-        seen += 1
-    assert seen >= 6
+        assert loop | front | {(a + w) // 2 + (w if ahead else 0), 0} == set(waits), (name, waits)
+        seen.append((bm, stages))
+    assert set(seen) == {(128, 2), (128, 4), (192, 3)} and len(seen) >= 8
