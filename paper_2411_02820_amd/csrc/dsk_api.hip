@@ -290,7 +290,7 @@ int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, 
       }
       const hipError_t e = launch_gemm_mfma_grouped(A, lda, a_rows, a_row, W, ldw, m->w_blocks, w_stride, C, ldc, N, K, epi,
                                                     (const char*)m->moe_tab + (int64_t)table * (tile_rows + 1) * 16, tile_m, tile_rows,
-                                                    table ? E : 0, (int64_t)n * k / E, s);
+                                                    table ? E : 0, (int64_t)n * k / E, s);  // a low tile an expert at most
       if (e != hipSuccess && timed) g_stats.gemm.abandon();
       HIP_TRY(e);
       ++g_stats.gemm_mfma;
@@ -299,7 +299,8 @@ int run_moe_mlp(dsk_model* m, const LayerWeights& w, int n, const float* h_mid, 
     };
     // gate/up reads the token rows where they are; its result, and what follows, is in sorted order
     int rc = grouped(m->xn, d, n, m->moe_src, w.wgu, d, wgu_stride, m->act, F, 2 * F, d, EPI_SWIGLU, 0);
-    if (rc == DSK_OK) rc = grouped(m->act, F, (int64_t)n * k, nullptr, w.wd, F, wd_stride, m->moe_y, d, d, F, EPI_C_F32, 1);
+    if (rc == DSK_OK) rc = grouped(m->act, F, (int64_t)n * k, nullptr, w.wd, F, wd_stride, m->moe_y, d, d, F, EPI_C_F32,
+                                   tile_m == MOE_HIGH_ROWS);
     if (rc) return rc;
     HIP_TRY(launch_moe_combine(m->moe_y, h_mid, m->moe_gates, m->moe_experts, m->moe_slot, h_out, out_f32, n, d, k,
                                (int64_t)n * k, s));

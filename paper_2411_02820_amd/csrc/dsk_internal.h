@@ -88,7 +88,7 @@ struct dsk_model {
   float* moe_gates;      // [maxT, top_k] their gate weights
   int32_t* moe_slot;     // [maxT, top_k] row of the entry once the rows are grouped by expert
   int32_t* moe_src;      // [maxT*top_k]  token of every grouped row
-  void* moe_tab;         // int4 [moe_tile_rows] row tiles of the grouped projections
+  void* moe_tab;         // int4 [2][moe_tile_rows + 1] row tiles of the grouped projections and their numbers, gate/up's and down's
   int moe_tile_rows;
   float* moe_y;          // expert outputs, fp32: [maxT*top_k, d] grouped, or [E][n][d] when every expert runs over all rows
   int64_t moe_y_rows;
@@ -268,7 +268,7 @@ hipError_t launch_moe_combine(const float* y, const float* h_mid, const float* g
                               hipStream_t s);
 hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw,
                                     int w_blocks, int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
-                                    const void* tile_tab, int tile_m, int tile_rows, int low_rows, int64_t rows_per_expert,
+                                    const void* tile_tab, int tile_m, int tile_rows, int low_tiles, int64_t rows_per_expert,
                                     hipStream_t s);
 
 // tuning knobs (dsk_set_option)

@@ -1153,7 +1153,7 @@ hipError_t launch16(int bm, const void* A, int64_t lda, const void* W, int64_t l
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool DIRECT, bool LOW = false>
 hipError_t launch16_grouped(const void* A, int64_t lda, const int32_t* a_row, int a_rows, const void* W, int64_t ldw,
                             int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi, const int4* tile_tab, int tile_rows,
-                            int low_rows, hipStream_t s) {
+                            int low_tiles, hipStream_t s) {
   auto kern = gemm16_bf16_kernel<BM, BN, WAVES_M, WAVES_N, true, true, false, DIRECT, LOW>;
   constexpr int own = lds16<BM, BN, DIRECT>(), of_low = lds16<MOE_LOW_ROWS, MOE_LOW_COLS, false>(), lds = LOW && of_low > own ? of_low : own;
   static bool configured = false;
@@ -1164,7 +1164,7 @@ hipError_t launch16_grouped(const void* A, int64_t lda, const int32_t* a_row, in
   }
   const int tiles_n = (N + BN - 1) / BN;
   const int low_n = (N + MOE_LOW_COLS - 1) / MOE_LOW_COLS;
-  DSK_LAUNCH_TIMED(kern, dim3(tile_rows * tiles_n + low_rows * (low_n - tiles_n)), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
+  DSK_LAUNCH_TIMED(kern, dim3(tile_rows * tiles_n + low_tiles * (low_n - tiles_n)), dim3(WAVES_M * WAVES_N * 64), lds, s, (const bf16_t*)A, lda,
                    (const bf16_t*)W, ldw, C, ldc, (const void*)nullptr, (int64_t)0, 0, N, K, epi, tile_rows, tiles_n,
                    K / BK, tile_tab, w_group_stride, a_row, a_rows, RopeOut{});
   g_direct_launches += DIRECT;
@@ -1357,7 +1357,7 @@ int moe_tile_rows_for(int64_t n_rows, int E) {
 // epi: EPI_SWIGLU (C bf16 [slots, N/2]) or EPI_C_F32 / EPI_STORE (C [slots, N]); no residual.
 hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw,
                                     int w_blocks, int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
-                                    const void* tile_tab, int tile_m, int tile_rows, int low_rows, int64_t rows_per_expert, hipStream_t s) {
+                                    const void* tile_tab, int tile_m, int tile_rows, int low_tiles, int64_t rows_per_expert, hipStream_t s) {
   if (tile_rows <= 0) return hipSuccess;
   // (a model the tensor-core path takes has its weights in blocks)
   if (!w_blocks || K < BK || K % BK || N % 64 || (lda & 7) || (ldw & 7) || (ldc & 3) || (epi & EPI_RESIDUAL)) return hipErrorNotSupported;
@@ -1365,10 +1365,10 @@ hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, 
   const bool direct = w_direct(rows_per_expert, K, false);
   auto f = tile_m == 128   ? launch16_grouped<128, 256, 2, 4, false>
            : tile_m == 192 ? launch16_grouped<192, 256, 2, 4, false>
-           : low_rows      ? (direct ? launch16_grouped<256, 256, 2, 4, true, true> : launch16_grouped<256, 256, 2, 4, false, true>)
+           : low_tiles     ? (direct ? launch16_grouped<256, 256, 2, 4, true, true> : launch16_grouped<256, 256, 2, 4, false, true>)
            : direct        ? launch16_grouped<256, 256, 2, 4, true>
                            : launch16_grouped<256, 256, 2, 4, false>;
-  return f(A, lda, a_row, (int)a_rows, W, ldw, w_group_stride, C, ldc, N, K, epi, (const int4*)tile_tab, tile_rows, low_rows, s);
+  return f(A, lda, a_row, (int)a_rows, W, ldw, w_group_stride, C, ldc, N, K, epi, (const int4*)tile_tab, tile_rows, low_tiles, s);
 }
 
 // More than 64 rows, dense operands: whether the contraction is split, i.e. a reduction runs behind the projection, which

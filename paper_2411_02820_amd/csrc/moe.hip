@@ -7,7 +7,6 @@
 
 namespace {
 
-
 constexpr int MAX_K = DSK_MOE_MAX_TOP_K;
 
 template <typename T> struct Vec8;
@@ -178,8 +177,8 @@ __global__ void __launch_bounds__(256) moe_route_mfma_kernel(const bf16_t* __res
 // tile_rows_max: {expert, first slot of the tile, end of the expert's slots, first tile of its scheduling group | tiles of
 // that << MOE_GROUP_SHIFT}, the tiles of all experts back to back, behind them low ones,
 // expert -1 past the last tile; tile_tab[tile_rows_max] = {number of tiles, number of low ones} (the GEMM spreads exactly those over the
-// chip: a grid sized for the worst case would leave the dies that get its empty end idle).  A second table behind the first is
-// the down projection's, tiles_n column tiles wide.
+// chip: a grid sized for the worst case would leave the dies that get its empty end idle).  With tiles of MOE_HIGH_ROWS a second
+// table behind the first is the down projection's, tiles_n column tiles wide.
 //
 // Low tiles (128 x 128): down has few column tiles, so an expert's partly filled last tiles decide how many rounds of workgroups it
 // takes; balanced experts with whole tiles to the row fill whole rounds, and the few rows that some have beyond them cost one more.
@@ -190,7 +189,7 @@ __global__ void __launch_bounds__(256) moe_route_mfma_kernel(const bf16_t* __res
 // low tile takes is its stream of W, and one compute unit draws only so much: 128 x 256 tiles took 526, 862, 1288, 1559.
 // Gate/up has seven times the column tiles and streams an expert's W once for all its row tiles: low tiles behind the others stream
 // it again (2400 tokens 1069 -> 1077), low tiles in the expert's group 1069 -> 1024 there, but 843 -> 890 over 2048 tokens.
-__host__ __device__ inline bool moe_low_tiles(int n_plain, int n_high, int n_low, int tiles_n) {
+__device__ inline bool moe_low_tiles(int n_plain, int n_high, int n_low, int tiles_n) {
   constexpr int CUS = 256;
   if (n_low == 0) return false;
   const int64_t plain = ((int64_t)n_plain * tiles_n + CUS - 1) / CUS, high = (int64_t)n_high * tiles_n;
@@ -255,8 +254,10 @@ __global__ void __launch_bounds__(PLACE_T) moe_place_kernel(const int32_t* __res
     }
   };
   write_table(tile_tab, high0[0], my_high[0], -1, n_high[0], 0);
-  const bool low = moe_low_tiles(n_high[0], n_high[1], n_low, tiles_n);
-  write_table(tile_tab + tile_rows_max + 1, high0[low], my_high[low], low && my_low ? n_high[1] + low0 : -1, n_high[low], low ? n_low : 0);
+  if (tile_m == MOE_HIGH_ROWS) {
+    const bool low = moe_low_tiles(n_high[0], n_high[1], n_low, tiles_n);
+    write_table(tile_tab + tile_rows_max + 1, high0[low], my_high[low], low && my_low ? n_high[1] + low0 : -1, n_high[low], low ? n_low : 0);
+  }
   // rounds of 4 * PLACE_T entries, four groups of PLACE_T in entry order; a thread's four entries are requested together (the
   // walk is a chain of short rounds: what it takes is the round trips to memory)
   int running = 0;
