@@ -365,7 +365,8 @@ DSK_API int dsk_gemm_plan(int M, int N, int K, int may_split, int32_t* plan);
  * "attn_packed_head_launches" (calls with at most 64 queries per sequence, all on the kernel for few queries); and for the
  * launches bracketed under "time_gemm": "timed_gemm_launches", "timed_gemm_ms" (sum of their durations; waits for
  * them to finish), "timed_gemm_flops" (sum of 2*M*N*K), and the same three as "timed_attn_..." for the attention
- * launches (flops = 4*Hq*dh per (query, visible key) pair, i.e. causal). */
+ * launches (flops = 4*Hq*dh per (query, visible key) pair, i.e. causal).  "moe_low_tiles" is counted on the device, since the process
+ * began: how many experts' last rows ran as low tiles of the grouped down projection, as far as the device has got. */
 DSK_API int dsk_get_stat(const char* name, double* value);
 
 /* Sizes, for callers that budget memory. */

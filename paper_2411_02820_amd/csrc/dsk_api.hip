@@ -1215,6 +1215,11 @@ int dsk_get_stat(const char* name, double* value) {
   else if (!strcmp(name, "gemm_generic_launches")) *value = (double)g_stats.gemm_generic.load();
   else if (!strcmp(name, "attn_mfma_launches")) *value = (double)g_stats.attn_mfma.load();
   else if (!strcmp(name, "attn_generic_launches")) *value = (double)g_stats.attn_generic.load();
+  else if (!strcmp(name, "moe_low_tiles")) {
+    unsigned long long n = 0;
+    HIP_TRY(moe_low_tile_count(&n));
+    *value = (double)n;
+  }
   else if (!strcmp(name, "e_cache_chunks")) *value = (double)g_stats.e_chunks.load();
   else if (!strcmp(name, "splice_launches")) *value = (double)g_stats.splices.load();
   else if (!strcmp(name, "attn_key_split_launches") || !strcmp(name, "attn_packed_head_launches") || !strcmp(name, "attn_few_query_launches")) {

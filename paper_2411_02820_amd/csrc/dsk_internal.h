@@ -254,6 +254,7 @@ hipError_t launch_moe_route(int dtype, const void* xn, const void* wr, int32_t* 
 // tile_tab: two tables of int4 [tile_rows_max + 1], gate/up's and down's (the last entry of each receives its numbers of tiles)
 hipError_t launch_moe_place(const int32_t* experts, int32_t* slot_of, int32_t* src_token, void* tile_tab, int n, int top_k,
                             int E, int tile_m, int down_tiles_n, int tile_rows_max, hipStream_t s);
+hipError_t moe_low_tile_count(unsigned long long* count);  // low tiles that calls on this device have written to tables
 // Tiles of a scheduling group, at most (a Mixtral layer over 4096, 6000, 8192 tokens, us: four 3055, 4095, 5988; eight 3015, 3987, 5897;
 // twelve 3007, 3974, 5915; twenty-four 3004, 3987, 5906: from eight on it does not matter), and the place of their number in the table.
 constexpr int MOE_GROUP_MOST = 12, MOE_GROUP_SHIFT = 20;

@@ -196,6 +196,7 @@ __device__ inline bool moe_low_tiles(int n_plain, int n_high, int n_low, int til
   const int64_t rounds = (high + CUS - 1) / CUS, left = (int64_t)n_low * tiles_n - (rounds * CUS - high);  // what the last round has no room for
   return 2 * rounds + (left > 0 ? (2 * left + CUS - 1) / CUS : 0) < 2 * plain;
 }
+__device__ unsigned long long low_tiles_written;  // by all calls on this device
 constexpr int PLACE_T = 1024;  // threads: the walk is a chain of rounds, wider ones make it shorter (256: 23 us at 8192 tokens)
 __global__ void __launch_bounds__(PLACE_T) moe_place_kernel(const int32_t* __restrict__ experts, int32_t* __restrict__ slot_of,
                                                         int32_t* __restrict__ src_token, int4* __restrict__ tile_tab,
@@ -257,6 +258,7 @@ __global__ void __launch_bounds__(PLACE_T) moe_place_kernel(const int32_t* __res
   if (tile_m == MOE_HIGH_ROWS) {
     const bool low = moe_low_tiles(n_high[0], n_high[1], n_low, tiles_n);
     write_table(tile_tab + tile_rows_max + 1, high0[low], my_high[low], low && my_low ? n_high[1] + low0 : -1, n_high[low], low ? n_low : 0);
+    if (low && e == E - 1 && tid == 0) atomicAdd(&low_tiles_written, (unsigned long long)n_low);
   }
   // rounds of 4 * PLACE_T entries, four groups of PLACE_T in entry order; a thread's four entries are requested together (the
   // walk is a chain of short rounds: what it takes is the round trips to memory)
@@ -343,6 +345,8 @@ hipError_t launch_moe_route(int dtype, const void* xn, const void* wr, int32_t* 
                        d, E, top_k);
   return hipGetLastError();
 }
+
+hipError_t moe_low_tile_count(unsigned long long* count) { return hipMemcpyFromSymbol(count, HIP_SYMBOL(low_tiles_written), sizeof *count); }
 
 hipError_t launch_moe_place(const int32_t* experts, int32_t* slot_of, int32_t* src_token, void* tile_tab, int n, int top_k,
                             int E, int tile_m, int tiles_n, int tile_rows_max, hipStream_t s) {

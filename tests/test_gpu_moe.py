@@ -264,11 +264,17 @@ def host_moe_layer(shape, seed, layer):
 
 # 4096 tokens on four experts of 2049, 2176, 2048 and 1919 rows: whole tiles, and last tiles of 1, 128 and 127 rows, which leave the down
 # projection (eight column tiles) one round of workgroups instead of two; a width below and one of that form of the
-# tiles that takes its weights straight to registers.  Inputs decide the routing, so every sampled row counts.
-@pytest.mark.parametrize("ffn", [192, 3584])
-def test_last_rows_of_experts_in_low_tiles(G, monkeypatch, ffn):
-    shape = synth.ModelShape(1, 2048, 16, 4, 128, ffn, 500000.0, 1e-5, "bf16", 4, 2)
-    T, counts, lens = 4096, [2049, 2176, 2048, 1919], [256] * 16
+# tiles that takes its weights straight to registers.  Nine column tiles, the last of them, and the last low one, half as wide as the
+# projection goes: 28 tiles fill a round, and three low ones another half.  30 tiles of eight columns are one round either way, so
+# they stay high.  Inputs decide the routing, so every sampled row counts.
+@pytest.mark.parametrize("hidden,ffn,counts,low", [(2048, 192, [2049, 2176, 2048, 1919], 3), (2048, 3584, [2049, 2176, 2048, 1919], 3),
+                                                   (2112, 192, [1793, 1920, 1792, 1919], 3), (2112, 3584, [1793, 1920, 1792, 1919], 3),
+                                                   (2048, 192, [1793, 1920, 1536, 1919], 0)])
+def test_last_rows_of_experts_in_low_tiles(G, monkeypatch, hidden, ffn, counts, low):
+    from paper_2411_02820_amd import binding as B
+    shape = synth.ModelShape(1, hidden, 16, 4, 128, ffn, 500000.0, 1e-5, "bf16", 4, 2)
+    T = sum(counts) // 2
+    lens = [256] * (T // 256) + [T % 256] * (T % 256 > 0)
     slots = np.repeat(np.arange(4), counts)
     pick = np.stack([slots[:T], slots[T:]], axis=1)[np.random.default_rng(1).permutation(T)]   # no expert twice
     w = host_moe_layer(shape, synth.SEED_RECEIVER, 0)
@@ -281,8 +287,10 @@ def test_last_rows_of_experts_in_low_tiles(G, monkeypatch, ffn):
     assert not rec.calls[0].any()
     with G.GpuModel(shape, T) as m:
         m.init_random(synth.SEED_RECEIVER)
+        before = B.dsk_get_stat("moe_low_tiles")
         _, h = m.partial(x.cuda(), 0, 1, None, lens)
         torch.cuda.synchronize()
+        assert B.dsk_get_stat("moe_low_tiles") - before == low
         assert O.max_rel_err(G.to_np(h)[rows], h_ref) <= TOL["bf16"]
 
 
