@@ -122,15 +122,21 @@ def test_cache_that_is_not_this_devices_memory_is_copied():
     assert torch.equal(out.cpu(), kv)
 
 
-# an 8B layer behind a host-resident E cache: the shortest contexts that are chunked, a rest that is not a multiple of a tile, and
-# whole chunks of 4096 rows behind the first; against the layer in one piece, bit for bit
-@pytest.mark.parametrize("T,chunks", [(4607, 0), (4608, 2), (5001, 2), (8191, 2), (9001, 2), (12288, 3)])
-def test_chunked_first_layer_keeps_its_bits(T, chunks):
+# a layer behind a host-resident E cache: the shortest contexts that are chunked, a rest that is not a multiple of a tile, and
+# whole chunks of 4096 rows behind the first; against the layer in one piece, bit for bit.  The 8B shape; expert layers (a chunk
+# groups its own rows by expert); 64 heads of 64; a width whose first chunk is not the 8B one's
+WIDTHS = {"8b": (4096, 32, 8, 128, 14336), "experts": (4096, 32, 8, 128, 1536), "heads of 64": (4096, 64, 8, 64, 1536),
+          "3072": (3072, 24, 8, 128, 1536)}
+
+
+@pytest.mark.parametrize("width,T,chunks", [("8b", 4607, 0), ("8b", 4608, 2), ("8b", 5001, 2), ("8b", 8191, 2), ("8b", 9001, 2), ("8b", 12288, 3),
+                                            ("experts", 4095, 0), ("experts", 4096, 2), ("experts", 5001, 2), ("experts", 9001, 2),
+                                            ("heads of 64", 5001, 2), ("3072", 5631, 0), ("3072", 5632, 2), ("3072", 9001, 2)])
+def test_chunked_first_layer_keeps_its_bits(width, T, chunks):
     from paper_2411_02820_amd import binding as B
     from tests import gpu_util as G
-    s = synth.LLAMA_8B
-    shape = synth.ModelShape(1, s.hidden, s.n_q_heads, s.n_kv_heads, s.head_dim, s.ffn, s.rope_base, s.rms_eps, "bf16")
-    x = torch.randn((T, s.hidden), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16).pin_memory()
+    shape = synth.ModelShape(1, *WIDTHS[width], 500000.0, 1e-5, "bf16", *((8, 2) if width == "experts" else ()))
+    x = torch.randn((T, shape.hidden), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16).pin_memory()
     with G.GpuModel(shape, T) as m:
         m.init_random(synth.SEED_RECEIVER)
         B.dsk_set_option("reset_stats", 0)
