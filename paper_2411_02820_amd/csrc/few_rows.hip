@@ -448,7 +448,9 @@ hipError_t launch_stream(const StreamArgs& p, int tiles, int splits, hipStream_t
 // that many tiles re-reading the activations stay cheap; beyond 180 MB of such reads the contraction is split over about 256
 // workgroups of 64 columns, and a reduction launch adds up.  8B shape: O over 64 rows (134 MB of reads) 13.6 us against
 // 10.6 us + 4.9 us split; down over 64 rows (470 MB) 40 us against 24.6 us + 4.9 us, over 32 (235 MB) 31.8 against 21.6 + 4.8,
-// over 16 (117 MB) 24.0 unsplit.
+// over 16 (117 MB) 24.0 unsplit.  Other widths, us a layer unsplit -> split: down over 64 rows, 3072 wide (201 MB) 92.2 -> 92.1; O over
+// 64 rows, 5120 wide (210 MB) 160.8 -> 155.9; O over 40 rows, 6144 wide (226 MB) 190.0 -> 186.7; O over 32 rows, 8192 wide (268 MB)
+// 314.0 -> 308.3.
 int residual_splits(int M, int N, int K) {
   const int rows = (M + 15) / 16 * 16;
   if (rows <= 16 || (int64_t)(N / 16) * rows * K * 2 <= (int64_t)180 << 20) return 0;

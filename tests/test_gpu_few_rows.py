@@ -125,9 +125,10 @@ def test_steps_behind_the_loop(B, rows, d, F):
 
 
 # the wider tiles of 9 to 64 rows: experts enough for 256 workgroups of 64 and 128 columns (one to four row tiles), a dense gate/up of
-# 192 tiles and down split over workgroups at 17 to 32 rows; against the plain kernels
+# 192 tiles and down split over workgroups at 17 to 32 rows, O split from 17 rows on (8192 wide) and from 49 on (5120); against the plain
+# kernels
 @pytest.mark.parametrize("rows", [9, 16, 17, 32, 33, 64])
-@pytest.mark.parametrize("d,F,E", [(2048, 1600, 16), (256, 12352, 0), (2048, 28736, 0)])
+@pytest.mark.parametrize("d,F,E", [(2048, 1600, 16), (256, 12352, 0), (2048, 28736, 0), (8192, 64, 0), (5120, 64, 0)])
 def test_wide_tiles_of_few_rows(B, rows, d, F, E):
     from tests import gpu_util as G
     shape = synth.ModelShape(1, d, d // 128, 1, 128, F, 10000.0, 1e-5, "bf16", E, 1 if E else 0)
