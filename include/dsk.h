@@ -337,7 +337,9 @@ DSK_API int dsk_moe_route(int dtype, const void* x, const void* wr, int n, int d
  *                size, with 128- and 192-row tiles and split contractions among the choices): 1 = 256x256 tiles on the
  *                16x16x32 MFMA, 2 = 128x128 tiles on the 32x32x16 MFMA
  *   "e_chunk_rows": how a host-resident E cache is cut into row chunks that the first recomputed layer follows as
- *                they arrive: 0 (default) = 4096-row chunks where that keeps every result bit-identical to the
+ *                they arrive: 0 (default) = a first chunk of 2048 to 4096 rows (2304 of the 8B shape: as few as keep every
+ *                result's bits) and 4096-row ones behind it, or the rest in one where less than 8192 rows leave no two such, where
+ *                that keeps every result bit-identical to the
  *                unchunked run (one sequence, bf16, chunks that still fill the chip), -1 = never, n > 0 (a multiple
  *                of 256) = n-row chunks on any single-sequence bf16 call (results then agree within tolerance only)
  *   "time_gemm": 1 = bracket every tensor-core GEMM of the prefill (a projection of at least 192 tiles of 256 x 256;

@@ -4,19 +4,20 @@
 // Bound: the rate at which K and V arrive from HBM, and how soon the first of them do; then the softmax arithmetic of the
 // resident wave or two per SIMD.  So: the q heads of a kv group and their queries form one list of columns (query-major)
 // that is cut into 16-column MFMA tiles, and a workgroup reads K and V of its key range once for all of its columns; the key
-// ranges are cut so that about 256 workgroups run; K and V go to a ring of LDS stages by direct loads, up to 128 KB of them
-// in flight per compute unit; V is read from LDS through the transposing read, so no transposed copy of the prefix is
+// ranges are cut so that about 256 workgroups run; K and V go to a ring of LDS stages by direct loads (heads of 128: two stages of
+// 64 KB, both in flight at the start, one beside the stage in work from then on); V is read from LDS through the transposing read, so no transposed copy of the prefix is
 // made (it was a launch of its own over all prefix rows).
 // Scores are transposed, S^T = K Q^T on v_mfma_f32_16x16x32_bf16: a lane owns one column and keys 4*(lane/16) + r of a
 // 16-key tile.  The contraction index of O^T += V^T P^T is numbered so that the two key tiles of a 32-key step are the
 // lane's eight values as they stand: index 8g + e is key 16*(e/4) + 4g + e%4, and the V operand follows with two transposing
 // reads of four keys each.
-// 8B shape, per layer, against a transposed copy and 32x32x16 tiles before: 64 queries and 8192 keys 22.5 us (31), one query and
-// 4096 keys 7.8 us (17), and the merge of the key ranges 6 us in both.  Of the 22.5 us the loads alone take 10, the partial
+// 8B shape, per layer, against a transposed copy and 32x32x16 tiles before: 64 queries and 8192 keys 21.2 us (31), one query and
+// 4096 keys 7.2 us (17), and the merge of the key ranges 5 us in both.  Of the 21.2 us the loads alone take 10, the partial
 // outputs 4; runs of 64 keys per wave and stage (two independent steps to schedule) instead of 32 took 25 -> 22.5 us, four column
 // tiles per wave with one wave per SIMD take 35.
 // 128 queries for each of eight sequences of 1k to 8k keys: 153 us, one key range per workgroup (before: transposed copy 35,
-// attention 153, merge 15).
+// attention 153, merge 15).  The sequences have 26 to 63 stages and one key range each, so the launch lasts as long as the longest of
+// them: an even share would be 50 stages.
 #include <math.h>
 
 #include <type_traits>

@@ -496,7 +496,9 @@ int plan_e_chunks(const dsk_model* m, int T, int n_seqs, int* bounds) {
     for (int n = 2048; n < first; n += 256)
       if (whole(n)) first = n;
     // Less than two chunks of 4096 rows: the first one and the rest.  us, selective prefill and suffix pass over eight layers, two recomputed:
-    // 4608 rows 5497 -> 5126, 6000 rows 6844 -> 6249, 8191 rows 8812 -> 7997.
+    // 4608 rows 5497 -> 5126, 6000 rows 6844 -> 6249, 8191 rows 8812 -> 7997.  Four layers, one recomputed, of the Mixtral shape (first chunk
+    // 2048 rows; each chunk streams the experts' weights): 4096 rows 5520 -> 5591 (two recomputed 9243 -> 8991), 4160 rows 6262 -> 6008, 5000
+    // rows 7044 -> 6672, 8000 rows 10118 -> 8692; three of the 70B shape: 4096 rows 8683 -> 7548, 6000 rows 10993 -> 9528.
     if (T < 2 * rows) {
       if (T < 2 * first || !whole(T - first) || !whole(T)) return 0;
       rows = T - first;

@@ -1181,7 +1181,8 @@ int g_variant = 0;
 //   QKV 333 rows 32.8 [43.0], 1500 rows 71.7 [91.7], 3000 rows 140 [165];  O 333 rows 27.8 [35.8], 3000 rows 85 [96];
 //   down 333 rows 55 [81], 700 rows 85 [135], 1500 rows 149 [207].
 // The times of 256-row tiles are those of the form that brings W through LDS; where w_direct takes the other one they are 0 to 5 %
-// too long, which the choices do not reflect.
+// too long.  Those of 128- and 192-row tiles are of two stages of W; with the stages that these have now (w_stages) they are up to 6 %
+// too long.  The choices reflect neither.
 struct GemmPlan { int bm, splits, per, head_rows, rest_bm; };
 
 // the best single launch and its time (a matter of the sizes alone: the scratch holds every split, gemm_mfma_split_bytes)
@@ -1294,8 +1295,10 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
   int variant = g_variant;
   if (epi & EPI_SWIGLU) {
     if (!gemm_mfma_swiglu_supported(M, N, K)) return hipErrorNotSupported;
-    // up to 256 rows the 128 x 128 tiles fill the chip twice over (two workgroups per compute unit) and are faster: 61 us
-    // against 74 us for 96 rows, 71 against 76 us for 200, 8B gate/up
+    // up to 256 rows the 128 x 128 tiles, which fill the chip twice over (two workgroups per compute unit).  us, 8B gate/up, against
+    // the 128 x 256 tiles of the plan: 96 rows 59 against 69, 128 rows 60 against 71; since those have four stages of W they are the
+    // faster ones from 129 rows on (160 rows 69.5 against 65.2, 200 rows 70.4 against 67.4, 256 rows 77.0 against 70.6; 70B, 256 x 256
+    // tiles of the plan, 200 rows 273 against 213), which the line does not reflect
     if (variant == 2 || (variant == 0 && M <= 256))
       return launch<128, 128, 2, 2, false, 1>(A, lda, W, ldw, w_blocks, C, ldc, R, ldr, nullptr, M, N, K, epi, 1, KT, s);
     if (variant == 1) return launch16(256, A, lda, W, ldw, w_blocks, C, ldc, R, ldr, M, N, K, epi, 1, KT, s);
@@ -1345,7 +1348,7 @@ hipError_t launch_gemm_mfma_bf16(const void* A, int64_t lda, const void* W, int6
 }
 
 // Row tile of the grouped projections: 256 rows, lower where an expert has fewer (all its rows in one tile, with room for
-// the spread of a balanced router).
+// the spread of a balanced router).  The lines are from tiles with two stages of W.
 int moe_tile_rows_for(int64_t n_rows, int E) {
   const int64_t avg = n_rows / E;
   return avg <= 104 ? 128 : avg <= 168 ? 192 : 256;
@@ -1353,7 +1356,8 @@ int moe_tile_rows_for(int64_t n_rows, int E) {
 
 // Projections of a mixture-of-experts layer over token rows sorted by expert: one launch over all experts.
 // tile_tab[0..tile_rows) describes the tiles of tile_m rows and tile_tab[tile_rows] holds their number (see the kernel);
-// rows of C are the sorted slots, rows of A too unless a_row says where they are.  sorted_rows: number of slots.
+// rows of C are the sorted slots, rows of A too unless a_row says where they are.  low_tiles: how many low tiles the table may hold (0:
+// it holds none).
 // epi: EPI_SWIGLU (C bf16 [slots, N/2]) or EPI_C_F32 / EPI_STORE (C [slots, N]); no residual.
 hipError_t launch_gemm_mfma_grouped(const void* A, int64_t lda, int64_t a_rows, const int32_t* a_row, const void* W, int64_t ldw,
                                     int w_blocks, int64_t w_group_stride, void* C, int64_t ldc, int N, int K, int epi,
